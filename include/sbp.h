@@ -171,8 +171,8 @@ size_t sbp_backward_linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t 
 
 /*
  * Host only.  Which kernels sbp_backward_linear runs for these sizes (a report for logs and
- * benchmarks; the results do not depend on it): SBP_ENGINE_PLAIN (fp32, or channel counts that are
- * not multiples of 8), SBP_ENGINE_MFMA (128 x 128 tiles), SBP_ENGINE_MFMA_LARGE (256-wide tiles, one
+ * benchmarks; the results do not depend on it): SBP_ENGINE_PLAIN (fp32 matrix cores: fp32 tensors, or
+ * channel counts that are not multiples of 8), SBP_ENGINE_MFMA (128 x 128 tiles), SBP_ENGINE_MFMA_LARGE (256-wide tiles, one
  * workgroup per CU); -1 on invalid sizes.  If split_count is not NULL it receives the number of
  * fp32 partial sums of dW that the reduction adds.
  */
@@ -209,7 +209,7 @@ int32_t sbp_backward_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Co
  *   workspace    device, 256-byte aligned, at least sbp_backward_linear_workspace(...) bytes;
  *                contents on entry are irrelevant, contents on exit are unspecified
  * Channel counts that are multiples of 8 take the MFMA path for SBP_BF16; any other shape
- * and SBP_F32 take a plain (slower) kernel -- never an error.
+ * and SBP_F32 take the fp32 matrix-core kernel (SBP_ENGINE_PLAIN) -- never an error.
  */
 int32_t sbp_backward_linear(const void* dY, const int32_t* idx, const int32_t* inv, const void* X_k,
                             const void* W,

@@ -133,6 +133,19 @@ void timeline_target(unsigned long long** buf, int* capacity_records) {
   *capacity_records = g_timeline_cap;
 }
 
+void allow_dynamic_lds(const void* kernel, size_t lds) {
+  if (lds <= 64 * 1024) return;
+  static std::mutex m;
+  static std::vector<std::pair<const void*, size_t>> granted;      // a handful of kernels
+  std::lock_guard<std::mutex> lock(m);
+  for (auto& g : granted)
+    if (g.first == kernel) {
+      if (lds > g.second && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) g.second = lds;
+      return;
+    }
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) granted.emplace_back(kernel, lds);
+}
+
 static int32_t validate_desc(const sbp_sample_desc* d) {
   if (!d) return fail(SBP_ERR_NULL, "sample descriptor is NULL");
   if (d->B < 1 || d->P < 0 || d->H < 1 || d->W < 1)

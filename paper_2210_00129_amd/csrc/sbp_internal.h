@@ -28,6 +28,9 @@ struct ProfScope {
 // Measurement aid: where the kernels that support it write per-workgroup time stamps (NULL, 0: nowhere).
 void timeline_target(unsigned long long** buf, int* capacity_records);
 
+// Grants a kernel more than 64 KB of dynamic LDS; asked of the runtime once per kernel and size (one device per process).
+void allow_dynamic_lds(const void* kernel, size_t lds);
+
 #define SBP_LAUNCH(cls, stream, ...)             \
   do {                                            \
     ::sbp::ProfScope _prof_scope((cls), (stream)); \
@@ -75,7 +78,7 @@ int32_t launch_patches(bool scatter, const void* src, const int32_t* idx, const 
 
 // ---- linear backward ---------------------------------------------------------------------
 struct LinearPlan {
-  bool   mfma;          // bf16 MFMA path (else plain kernels)
+  bool   mfma;          // bf16 engines (else the fp32 engine)
   int    bm_w, bn_w;    // tile of both contractions (rows x columns)
   int    splits;        // split-K factor of the dW contraction
   int    rows_per_split;// kept rows per split (multiple of the k-step)
@@ -101,6 +104,12 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
                                const void* Xk, const void* W, int64_t M, int64_t K, int32_t Cin, int32_t Cout,
                                int32_t dtype, void* dW, float* db, void* dX, void* ws, uint32_t flags,
                                hipStream_t s);
+
+// fp32 tensors, odd channel counts, unaligned tensors (sbp_linear_f32.hip).  dbp: partials [splits][Cout] or NULL
+void plan_linear_f32(int64_t K, int32_t Cin, int32_t Cout, int* splits, int* rows_per_split);
+void launch_linear_f32(int splits, int rows_per_split, const void* dY, const int32_t* idx_in, const int32_t* idx_out,
+                       const int32_t* idx, const int32_t* inv, const void* Xk, const void* W, int64_t M, int64_t K, int32_t Cin,
+                       int32_t Cout, int32_t dtype, bool want_dw, float* part, float* dbp, void* dX, hipStream_t s);
 
 // several independent layers in one launch
 struct BatchLayer {

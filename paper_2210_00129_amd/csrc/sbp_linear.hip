@@ -9,7 +9,7 @@
 // sbp_mfma_big.h) where the layer is large enough to keep the CUs busy with them, linear_bwd_kernel
 // (128 x 128 tiles, sbp_mfma_gemm.h) otherwise.  dW is split along the kept rows into fp32 partial
 // sums that a second kernel adds in a fixed order (deterministic, no floating-point atomics).
-// fp32 and odd shapes take plain kernels.
+// fp32 tensors, odd channel counts and unaligned tensors take the fp32 matrix-core kernel of sbp_linear_f32.hip.
 #include <cstdio>
 #include <cstdlib>
 
@@ -498,83 +498,6 @@ __global__ void __launch_bounds__(NTHREADS) fill_zero_kernel(uint32_t* __restric
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plain kernels (fp32 storage, or bf16 with channel counts that are not multiples of 8).
-// ------------------------------------------------------------------------------------------------
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-  static __device__ __forceinline__ float ld(const float* p) { return *p; }
-  static __device__ __forceinline__ void st(float* p, float v) { *p = v; }
-};
-template <> struct Elem<uint16_t> {
-  static __device__ __forceinline__ float ld(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
-  static __device__ __forceinline__ void st(uint16_t* p, float v) { *p = (uint16_t)(bf16_pack(v, 0.f) & 0xffffu); }
-};
-
-// one thread per (kept row j, input channel i)
-template <typename T>
-__global__ void __launch_bounds__(NTHREADS) plain_dx_kernel(const T* __restrict__ dY, const int32_t* __restrict__ idx_in,
-                                                             const int32_t* __restrict__ idx_out,
-                                                             const T* __restrict__ W, long long K, int Cin, int Cout,
-                                                             T* __restrict__ dX) {
-  const long long total = K * Cin;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const long long j = e / Cin;
-    const int i = (int)(e - j * Cin);
-    const long long rin = idx_in ? (long long)idx_in[j] : j;
-    const long long rout = idx_out ? (long long)idx_out[j] : j;
-    const T* g = dY + rin * Cout;
-    float a = 0.f;
-    for (int o = 0; o < Cout; ++o) a = fmaf(Elem<T>::ld(g + o), Elem<T>::ld(W + (long long)o * Cin + i), a);
-    Elem<T>::st(dX + rout * Cin + i, a);
-  }
-}
-
-// one thread per (o, i) and row split; sums in chunks of 256 rows to keep fp32 rounding small
-template <typename T>
-__global__ void __launch_bounds__(NTHREADS) plain_dw_kernel(const T* __restrict__ dY, const int32_t* __restrict__ idx,
-                                                             const T* __restrict__ Xk, int K, int Cin, int Cout,
-                                                             int rows_per_split, float* __restrict__ partial) {
-  const long long nW = (long long)Cin * Cout;
-  const int j0 = blockIdx.y * rows_per_split, j1 = min(K, j0 + rows_per_split);
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < nW;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int o = (int)(e / Cin), i = (int)(e - (long long)o * Cin);
-    float total = 0.f;
-    for (int jc = j0; jc < j1; jc += 256) {
-      float a = 0.f;
-      const int je = min(j1, jc + 256);
-      for (int j = jc; j < je; ++j) {
-        const long long r = idx ? (long long)idx[j] : (long long)j;
-        a = fmaf(Elem<T>::ld(dY + r * Cout + o), Elem<T>::ld(Xk + (long long)j * Cin + i), a);
-      }
-      total += a;
-    }
-    partial[(long long)blockIdx.y * nW + e] = total;
-  }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(NTHREADS) plain_db_kernel(const T* __restrict__ dY, const int32_t* __restrict__ idx,
-                                                             int K, int Cout, int rows_per_split,
-                                                             float* __restrict__ dbp) {
-  const int j0 = blockIdx.y * rows_per_split, j1 = min(K, j0 + rows_per_split);
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= Cout) return;
-  float total = 0.f;
-  for (int jc = j0; jc < j1; jc += 256) {
-    float a = 0.f;
-    const int je = min(j1, jc + 256);
-    for (int j = jc; j < je; ++j) {
-      const long long r = idx ? (long long)idx[j] : (long long)j;
-      a += Elem<T>::ld(dY + r * Cout + o);
-    }
-    total += a;
-  }
-  dbp[(long long)blockIdx.y * Cout + o] = total;
-}
-
-// ------------------------------------------------------------------------------------------------
 // Host side: plan and launches.
 // ------------------------------------------------------------------------------------------------
 static constexpr int kNumCU = 256;
@@ -773,7 +696,10 @@ LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t 
       if (p.bm_w == 128 && p.kb == 64 && ceil_div(K, 128) * ceil_div(Cin, 128) + tiles * splits + 64 <= 700) p.dx_bm = 64;   // (measured: still ahead at 650 workgroups, behind at 770)
       if (opt.dxrows) p.dx_bm = opt.dxrows == 64 && p.bm_w == 128 && p.kb == 64 ? 64 : 128;
     } else {
-      splits = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(K, 512), 64));
+      int rps = 0;
+      plan_linear_f32(K, Cin, Cout, &splits, &rps);
+      p.rows_per_split = rps; p.n_big = splits;
+      two_sizes = true;
     }
   }
   if (!two_sizes) {
@@ -798,44 +724,6 @@ LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t 
   if (flags & SBP_FLAG_XK_KMAJOR) off += align_up((size_t)K * Cin * 2, 256);
   p.bytes = off;
   return p;
-}
-
-template <typename T>
-static int32_t launch_plain(const LinearPlan& p, const T* dY, const int32_t* idx_in, const int32_t* idx_out,
-                            const T* Xk, const T* W, int64_t K, int32_t Cin, int32_t Cout, float* part,
-                            float* dbp, bool want_dw, bool want_db, T* dX, hipStream_t s) {
-  if (want_dw) {
-    long long nW = (long long)Cin * Cout;
-    dim3 grid((unsigned)std::min<long long>(ceil_div(nW, NTHREADS), 8192), p.splits);
-    SBP_LAUNCH(SBP_PROF_DW_GEMM, s, (plain_dw_kernel<T>), grid, dim3(NTHREADS), 0, s, dY, idx_in, Xk, (int)K, Cin, Cout,
-                       p.rows_per_split, part);
-  }
-  if (want_db) {
-    dim3 grid((unsigned)ceil_div(Cout, NTHREADS), p.splits);
-    SBP_LAUNCH(SBP_PROF_COLSUM, s, (plain_db_kernel<T>), grid, dim3(NTHREADS), 0, s, dY, idx_in, (int)K, Cout,
-                       p.rows_per_split, dbp);
-  }
-  if (dX) {
-    long long total = (long long)K * Cin;
-    unsigned blocks = (unsigned)std::min<long long>(ceil_div(total, NTHREADS), 65535);
-    SBP_LAUNCH(SBP_PROF_DX_GEMM, s, (plain_dx_kernel<T>), dim3(blocks), dim3(NTHREADS), 0, s, dY, idx_in, idx_out, W,
-                       (long long)K, Cin, Cout, dX);
-  }
-  return SBP_OK;
-}
-
-// Dynamic LDS beyond 64 KB has to be granted per kernel; asked for once per kernel and size (one device per process).
-template <typename KernelT>
-static void allow_big_lds(KernelT kernel, size_t lds) {
-  static std::mutex m;                          // one instance of these per kernel type
-  static size_t granted = 0;
-  static KernelT granted_for = nullptr;
-  std::lock_guard<std::mutex> lock(m);
-  if (lds <= 64 * 1024 || (granted_for == kernel && lds <= granted)) return;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) {
-    granted = lds;
-    granted_for = kernel;
-  }
 }
 
 // fills in the segment sizes and their order; returns the number of workgroups, *lds_out the LDS bytes a workgroup needs
@@ -872,7 +760,7 @@ static void launch_linear_bwd(const LinearPlan& p, LinArgs a, bool want_dx, bool
   size_t lds = 0;
   const unsigned grid = prepare_linear_bwd<BM, BN, NW, KB, NSTAGE, BMX, NSX>(p, a, want_dx, want_dw, want_zero, &lds);
   if (grid == 0) return;
-  allow_big_lds(linear_bwd_kernel<BM, BN, NW, KB, NSTAGE, BMX, NSX>, lds);
+  allow_dynamic_lds(reinterpret_cast<const void*>(linear_bwd_kernel<BM, BN, NW, KB, NSTAGE, BMX, NSX>), lds);
   SBP_LAUNCH(SBP_PROF_DW_GEMM, s, (linear_bwd_kernel<BM, BN, NW, KB, NSTAGE, BMX, NSX>), dim3(grid), dim3(64 * NW), lds, s, a);
 }
 
@@ -906,7 +794,7 @@ void launch_zero_dropped_rows(const int32_t* idx, const int32_t* inv, int64_t K,
 static void launch_linear_big(const LinearPlan& p, LinArgs a, bool want_dx, bool want_dw, bool want_zero, hipStream_t s) {
   // behind the ring: the row ids of a dW split (read one stage ahead) or the 256 output rows of a dX tile
   const size_t lds = (size_t)big::RING + std::max<size_t>((size_t)(std::max(p.rows_per_split, p.rows_small) + 2 * big::KB), big::BT) * sizeof(int);
-  allow_big_lds(linear_big_kernel, lds);
+  allow_dynamic_lds(reinterpret_cast<const void*>(linear_big_kernel), lds);
   const long long tiles_n = ceil_div(a.Cin, big::BT);
   a.n_zero = want_zero ? big_zero_blocks(a.M) : 0;
   // with dW wanted, db comes out of the dW units (one slice per split and tile column); column-sum blocks
@@ -970,6 +858,8 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
   const bool aligned = ((uintptr_t)dY % 16 == 0) && ((uintptr_t)Xk % 16 == 0) && ((uintptr_t)W % 16 == 0) &&
                        ((uintptr_t)dX % 16 == 0);
   const bool use_mfma = p.mfma && aligned;
+  // the fp32 engine with one split writes dW and db itself
+  const bool direct = !use_mfma && p.splits == 1 && !accumulate && !dw_bf16;
   bool kmajor = (flags & SBP_FLAG_XK_KMAJOR) && dW && Xk;
   if (kmajor && !(use_mfma && p.big && p.rows_per_split % 8 == 0 && p.rows_small % 8 == 0)) {
     void* rows = static_cast<char*>(ws) + p.off_xrows;
@@ -1004,19 +894,16 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
       launch_linear_bwd<128, 128, 4, 64, 2, 64, 3>(p, a, want_dx, want_dw, scatter, s);
     else
       launch_linear_bwd<128, 128, 4, 64, 2>(p, a, want_dx, want_dw, scatter, s);
-  } else if (dtype == SBP_F32) {
-    launch_plain<float>(p, (const float*)dY, idx_in, idx_out, (const float*)Xk, (const float*)W, K, Cin, Cout, part,
-                        dbp, dW != nullptr, db != nullptr, (float*)dX, s);
   } else {
-    launch_plain<uint16_t>(p, (const uint16_t*)dY, idx_in, idx_out, (const uint16_t*)Xk, (const uint16_t*)W, K, Cin,
-                           Cout, part, dbp, dW != nullptr, db != nullptr, (uint16_t*)dX, s);
+    launch_linear_f32(p.splits, p.rows_per_split, dY, idx_in, idx_out, idx, inv, Xk, W, M, K, Cin, Cout, dtype,
+                      dW != nullptr, direct ? static_cast<float*>(dW) : part, direct ? db : (db ? dbp : nullptr), dX, s);
   }
 
-  if (dW || db) {
+  if ((dW || db) && !direct) {
     if (nW % 4 == 0) {
       const long long total = (dW ? nW / 4 : 0) + (db ? Cout : 0);
       // (large tiles with dW: db partials come from the dW units, one per split and tile column)
-      const int nsplit_b = use_mfma && !(p.big && dW) ? p.db_slices : (p.big ? p.splits * (int)ceil_div(Cin, big::BT) : p.splits);
+      const int nsplit_b = !use_mfma ? p.splits : (p.big && dW ? p.splits * (int)ceil_div(Cin, big::BT) : p.db_slices);
       const int deepest = std::max(dW ? p.splits : 0, db ? nsplit_b : 0);
       const int G = reduce_lanes(total, deepest);
       unsigned blocks = (unsigned)std::min<long long>(ceil_div(total * G, NTHREADS), 4096);
@@ -1036,8 +923,6 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
     }
   }
 
-  if (scatter && !use_mfma)   // the MFMA launch zero-fills by itself
-    launch_zero_dropped_rows(idx, inv, K, M, (int64_t)Cin * eb, dX, s);
   return check_launch("backward_linear");
 }
 
@@ -1457,7 +1342,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
   }
   m.start[p.n] = blk;
   if (blk > 0) {
-    allow_big_lds(linear_bwd_multi_kernel, lds);
+    allow_dynamic_lds(reinterpret_cast<const void*>(linear_bwd_multi_kernel), lds);
     SBP_LAUNCH(SBP_PROF_DW_GEMM, s, linear_bwd_multi_kernel, dim3((unsigned)blk), dim3(256), lds, s, m);
   }
   if (any_reduce) {
@@ -1581,7 +1466,7 @@ int32_t launch_backward_linear_batch(const BatchPlan& p, const sbp_linear_layer*
       grid = kNumXCD * (int)ceil_div((int64_t)total * 5, 4 * kNumXCD);
       SBP_LAUNCH(SBP_PROF_OTHER, s, fill_zero_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(a.counters), (long long)kNumXCD);
     }
-    allow_big_lds(linear_multi_kernel, lds);
+    allow_dynamic_lds(reinterpret_cast<const void*>(linear_multi_kernel), lds);
     SBP_LAUNCH(SBP_PROF_DW_GEMM, s, linear_multi_kernel, dim3((unsigned)grid), dim3(256), lds, s, a, dynamic);
   }
   if (any_reduce) {

@@ -1,0 +1,77 @@
+"""The fp32 matrix-core kernel of the linear backward (fp32 tensors, odd channel counts, unaligned tensors) at the edges of
+its tiles, stages (64 each) and splits, against the oracle.  Bounds: fp32 sums of at most 22000 exact or singly
+rounded products stay below 1e-5 of max |result|; dX of bf16 tensors is rounded once (gpu_util)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2210_00129_amd as sbp
+import synth_inputs as si
+from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, nerr
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(M, K, seed=3):
+    return np.random.default_rng(seed).permutation(M)[:K].astype(np.int32)
+
+
+# (K, Cin, Cout): one row; one short of, at and one past a stage and a tile; several splits; pieces of 4 and single elements
+SIZES = [(1, 4, 4), (1, 1, 1), (31, 64, 32), (32, 60, 64), (33, 68, 96), (64, 128, 65), (65, 63, 128), (257, 7, 130),
+         (700, 64, 260), (1500, 132, 36), (3000, 66, 190)]
+
+
+@pytest.mark.parametrize("K,Cin,Cout", SIZES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tile_stage_and_split_edges(K, Cin, Cout, dtype):
+    if dtype == "bf16" and Cin % 8 == 0 and Cout % 8 == 0:
+        Cin += 3                                             # (multiples of 8 go to the bf16 engines)
+    M = K + K // 2 + 5
+    X, W, dY = si.linear_case(M, Cin, Cout, 11, dtype)
+    idx = _rows(M, K)
+    check_linear(X, W, dY, idx, dtype)
+    check_linear(X, W, dY, idx, dtype, flags=sbp.FLAG_DY_COMPACT | sbp.FLAG_DX_COMPACT, check_cache=False)
+
+
+@pytest.mark.parametrize("K,Cin,Cout", [(21900, 260, 132), (21801, 259, 130)])
+def test_more_units_than_fit_at_once(K, Cin, Cout):
+    # several rounds of workgroups, in pieces of 4 and in single elements
+    M = K + 777
+    X, W, dY = si.linear_case(M, Cin, Cout, 12, "f32")
+    check_linear(X, W, dY, _rows(M, K), "f32", inv_mode="sampler")
+
+
+@pytest.mark.parametrize("want", [("db",), ("dX",), ("dW",), ("dW", "db"), ("db", "dX")])
+@pytest.mark.parametrize("K", [100, 2000])                   # one split (dW and db written directly) and several
+def test_single_outputs_and_accumulation(want, K):
+    M, Cin, Cout = K + 50, 72, 200
+    X, W, dY = si.linear_case(M, Cin, Cout, 13, "f32")
+    idx_np = _rows(M, K)
+    idx = torch.from_numpy(idx_np).cuda()
+    Xk = X[idx.cpu().long()].cuda()
+    ref = dict(zip(("dW", "db", "dX"), oracle.backward_linear(si.to_f64(dY), idx_np, si.to_f64(X)[idx_np], si.to_f64(W), M)))
+    for flags in (0, sbp.FLAG_ACCUMULATE_DW):
+        out = {}
+        if flags:
+            out = {n: torch.ones(s, device="cuda") for n, s in (("dW", (Cout, Cin)), ("db", (Cout,))) if n in want}
+        got = dict(zip(("dW", "db", "dX"), sbp.backward_linear(dY.cuda(), idx, Xk, W.cuda(), want=want, flags=flags, **out)))
+        torch.cuda.synchronize()
+        for n in ("dW", "db", "dX"):
+            assert (got[n] is not None) == (n in want)
+            if n in want:
+                assert nerr(f64(got[n]), ref[n] + (1 if flags and n != "dX" else 0)) <= TOL_F32, (n, flags)
+
+
+def test_unaligned_bf16_tensors_of_a_large_layer():
+    # sizes that plan the 256-wide bf16 engine, addresses that rule it out
+    M, K, Cin, Cout = 3000, 2100, 256, 512
+    X, W, dY = si.linear_case(M, Cin, Cout, 14, "bf16")
+    idx_np = _rows(M, K)
+    shift = lambda t: torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t)
+    idx = torch.from_numpy(idx_np).cuda()
+    dW, db, dX = sbp.backward_linear(shift(dY), idx, shift(X[torch.from_numpy(idx_np).long()]), shift(W))
+    torch.cuda.synchronize()
+    rW, rb, rX = oracle.backward_linear(si.to_f64(dY), idx_np, si.to_f64(X)[idx_np], si.to_f64(W), M)
+    assert nerr(f64(dW), rW) <= TOL_F32 and nerr(f64(db), rb) <= TOL_F32 and nerr(f64(dX), rX) <= TOL_BF16_TIGHT
+    assert np.all(bits(dX)[np.setdiff1d(np.arange(M), idx_np)] == 0)
