@@ -396,7 +396,7 @@ int32_t sbp_backward_layerscale(const void* dU_k, const void* Y_k, const float* 
  * sbp_backward_attention_engine (host only) reports which kernel serves a size: 1 = matrix-core kernel with one
  * workgroup per (sample, head) (bf16, d in {32, 64, 128}, the kept tokens of one head fit LDS: n_k <= 256 at
  * d = 64), 2 = matrix-core kernel tiled over chunks of 128 tokens (bf16, d in {32, 64, 128}, any n_k),
- * 0 = plain kernel (fp32, d = 16).
+ * 0 = fp32 tensors (fp32 matrix cores at d in {32, 64, 128}) and d = 16 (plain kernel).
  */
 int32_t sbp_backward_attention_engine(int32_t n_k, int32_t d, int32_t dtype);
 int32_t sbp_backward_attention(const void* qkv_k, const void* A_k, const void* dA_k, const float* lse_k,

@@ -6,8 +6,8 @@
 //   dV_j  = sum_i S_ij dA_i
 //   dM_ij = S_ij (dA_i.v_j - dA_i.A_i)          the softmax row term sum_l S_il dS_il equals dA_i.A_i (A = S V)
 //   dQ_i  = scale sum_j dM_ij k_j,   dK_j = scale sum_i dM_ij q_i
-// Two kernels: an MFMA kernel for bf16 (one workgroup per sample and head, all kept tokens of the head in
-// LDS) and a plain fp32-arithmetic kernel for fp32 tensors and for sizes beyond the LDS budget.
+// Kernels: for bf16 an MFMA kernel with one workgroup per sample and head (all kept tokens of the head in LDS) and a tiled one
+// for any number of tokens; for fp32 tensors a tiled one on the fp32 matrix cores; a plain kernel for d = 16.
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -579,6 +579,179 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 3) attn_bwd_tiled_kernel(c
 }
 
 // ------------------------------------------------------------------------------------------------
+// fp32 tensors, d = 32, 64, 128: the same products on v_mfma_f32_32x32x2_f32 (fp32 operands and sums).  A workgroup owns 128
+// tokens of one (sample, head) in one of two roles, every wavefront 32 of them: as keys (dK, dV; the queries' rows of q and
+// dA stream through LDS in tiles of 32, with their lse and delta) or as queries (dQ; rows of k and v stream).  Layouts (lane
+// l, half u = l >> 5): an MFMA takes A[row l & 31][step u] and B[step u][column l & 31]; its result register v is row
+// 8 (v >> 2) + 4 u + (v & 3), column l & 31.
+//   S, dP: contraction over the head dimension; in a group of 8 dimensions half u multiplies 4 u .. 4 u + 3 (16-byte reads)
+//   dV, dK, dQ: contraction over the tile's tokens; step v takes register v of P or dS as B as it is, and A is the tile's
+//     element [row of register v][head dimension l & 31]: one 4-byte LDS read per MFMA of 64 cycles, no transpose
+// Bound: the matrix cores (fp32 rate), half of a chunk's padding included.  64 samples x 3 heads of 64, 99 kept tokens: 225 us
+// with one thread per 16 elements of a token (the plain kernels), 41 us here (18 us of MFMA time if spread evenly; 384
+// workgroups of unequal length on 256 CUs).
+// ------------------------------------------------------------------------------------------------
+typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+static constexpr int kAttnF32Tile = 32;
+
+template <int D, bool KEY>
+struct AttnF32 {
+  static constexpr int P = D + 4, CH = D / 4, R = kAttnF32Tile * CH / 256, DB = D / 32;   // LDS pitch, 16-byte pieces per row, per thread
+  float own1[D / 2], own2[D / 2];      // k, v (KEY) or q, dA of token l & 31: dimensions 8 c + 4 u .. + 3
+  float l, dl;                         // query role: lse and delta of the own token
+  f32x16_t acc1[DB], acc2[KEY ? DB : 1];
+  f32x4v_t x1[R], x2[R], x3[KEY ? R : 1];
+  float xl;
+
+  __device__ __forceinline__ void init(const float* q, const float* a, const float* g, const float* lse, long long ldq, int hd, int h,
+                                       int own, int lane) {
+    const int u = lane >> 5;
+    const float* r1 = q + own * ldq + (KEY ? hd : 0);
+    const float* r2 = KEY ? r1 + hd : g + (long long)own * hd;
+    float part = 0.f;
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) {
+      const float4 b1 = *reinterpret_cast<const float4*>(r1 + 8 * c + 4 * u), b2 = *reinterpret_cast<const float4*>(r2 + 8 * c + 4 * u);
+      own1[4 * c] = b1.x; own1[4 * c + 1] = b1.y; own1[4 * c + 2] = b1.z; own1[4 * c + 3] = b1.w;
+      own2[4 * c] = b2.x; own2[4 * c + 1] = b2.y; own2[4 * c + 2] = b2.z; own2[4 * c + 3] = b2.w;
+      if constexpr (!KEY) {
+        const float4 o = *reinterpret_cast<const float4*>(a + (long long)own * hd + 8 * c + 4 * u);
+        part = fmaf(b2.x, o.x, fmaf(b2.y, o.y, fmaf(b2.z, o.z, fmaf(b2.w, o.w, part))));
+      }
+    }
+    if constexpr (!KEY) { dl = part + __shfl_xor(part, 32); l = lse[(long long)own * h]; }
+#pragma unroll
+    for (int x = 0; x < DB; ++x)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { acc1[x][e] = 0.f; if constexpr (KEY) acc2[x][e] = 0.f; }
+  }
+  // rows t0 .. t0 + 31 of the other side into registers (past n_k: some valid row, zeroed when stored)
+  __device__ __forceinline__ void load(const float* q, const float* a, const float* g, const float* lse, long long ldq, int hd, int h,
+                                       int t0, int n_k) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int tok = min(t0 + (t + 256 * r) / CH, n_k - 1), c = 4 * ((t + 256 * r) % CH);
+      const float* row = q + tok * ldq + c;
+      x1[r] = *reinterpret_cast<const f32x4v_t*>(row + (KEY ? 0 : hd));
+      x2[r] = *reinterpret_cast<const f32x4v_t*>(KEY ? g + (long long)tok * hd + c : row + 2 * hd);
+      if constexpr (KEY) x3[r] = *reinterpret_cast<const f32x4v_t*>(a + (long long)tok * hd + c);
+    }
+    if constexpr (KEY) xl = lse[(long long)min(t0 + (t & 31), n_k - 1) * h];
+  }
+  __device__ __forceinline__ void store_tile(float* s1, float* s2, float* lse_s, float* delta_s, int t0, int n_k) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      asm volatile("" : "+v"(x1[r]), "+v"(x2[r]));         // (loaded registers stay where they are until here)
+      if constexpr (KEY) asm volatile("" : "+v"(x3[r]));
+      const int row = (t + 256 * r) / CH, ch = (t + 256 * r) % CH;
+      const bool ok = t0 + row < n_k;
+      f32x4v_t y1 = x1[r], y2 = x2[r];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { y1[e] = ok ? y1[e] : 0.f; y2[e] = ok ? y2[e] : 0.f; }
+      *reinterpret_cast<f32x4v_t*>(s1 + row * P + 4 * ch) = y1;
+      *reinterpret_cast<f32x4v_t*>(s2 + row * P + 4 * ch) = y2;
+      if constexpr (KEY) {
+        float d = fmaf(y2[0], x3[r][0], fmaf(y2[1], x3[r][1], fmaf(y2[2], x3[r][2], y2[3] * x3[r][3])));
+        d = ok ? d : 0.f;
+#pragma unroll
+        for (int m = 1; m < CH; m <<= 1) d += __shfl_xor(d, m);
+        if (ch == 0) delta_s[row] = d;
+      }
+    }
+    if (KEY && t < kAttnF32Tile) lse_s[t] = t0 + t < n_k ? xl : 0.f;
+  }
+  __device__ __forceinline__ void run(const float* s1, const float* s2, const float* lse_s, const float* delta_s, float scale, int t0,
+                                      int n_k, int lane) {
+    const int u = lane >> 5, col = lane & 31;
+    f32x16_t s, dp;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) {
+      const float4 a1 = *reinterpret_cast<const float4*>(s1 + col * P + 8 * c + 4 * u), a2 = *reinterpret_cast<const float4*>(s2 + col * P + 8 * c + 4 * u);
+      const float v1[4] = {a1.x, a1.y, a1.z, a1.w}, v2[4] = {a2.x, a2.y, a2.z, a2.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(v1[e], own1[4 * c + e], s, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x2f32(v2[e], own2[4 * c + e], dp, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int r = 8 * (v >> 2) + 4 * u + (v & 3);
+      float p = expf(scale * s[v] - (KEY ? lse_s[r] : l));
+      if (!KEY) p = t0 + r < n_k ? p : 0.f;                // (KEY: rows past n_k have lse = delta = 0 and zero rows)
+      s[v] = p;
+      dp[v] = p * (dp[v] - (KEY ? delta_s[r] : dl));
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int off = (8 * (v >> 2) + 4 * u + (v & 3)) * P + col;
+#pragma unroll
+      for (int x = 0; x < DB; ++x) {
+        acc1[x] = __builtin_amdgcn_mfma_f32_32x32x2f32(s1[off + 32 * x], dp[v], acc1[x], 0, 0, 0);          // dK^T or dQ^T
+        if constexpr (KEY) acc2[x] = __builtin_amdgcn_mfma_f32_32x32x2f32(s2[off + 32 * x], s[v], acc2[x], 0, 0, 0);   // dV^T
+      }
+    }
+  }
+  // out: row 0 of the head's columns in dqkv
+  __device__ __forceinline__ void store(float* out, long long ldq, int hd, int own, float scale, int lane) const {
+    float* o1 = out + own * ldq + (KEY ? hd : 0) + 4 * (lane >> 5);
+#pragma unroll
+    for (int x = 0; x < DB; ++x)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        *reinterpret_cast<float4*>(o1 + 32 * x + 8 * q4) =
+            make_float4(acc1[x][4 * q4] * scale, acc1[x][4 * q4 + 1] * scale, acc1[x][4 * q4 + 2] * scale, acc1[x][4 * q4 + 3] * scale);
+        if constexpr (KEY)
+          *reinterpret_cast<float4*>(o1 + hd + 32 * x + 8 * q4) = make_float4(acc2[x][4 * q4], acc2[x][4 * q4 + 1], acc2[x][4 * q4 + 2], acc2[x][4 * q4 + 3]);
+      }
+  }
+};
+
+template <int D, bool KEY>
+__device__ __forceinline__ void attn_f32_body(float* smem, const float* qkv, const float* A, const float* dA, const float* lse, int b,
+                                              int head, int chunk, int n_k, int h, float scale, float* dqkv) {
+  const int t = threadIdx.x, lane = t & 63, hd = h * D;
+  const long long row0 = (long long)b * n_k, ldq = 3LL * hd;
+  const float *q = qkv + row0 * ldq + head * D, *a = A + row0 * hd + head * D, *g = dA + row0 * hd + head * D, *ls = lse + row0 * h + head;
+  float *s1 = smem, *s2 = s1 + kAttnF32Tile * (D + 4), *lse_s = s2 + kAttnF32Tile * (D + 4), *delta_s = lse_s + kAttnF32Tile;
+  const int first = chunk * kAttnChunk + (t >> 6) * 32, own = first + (lane & 31);
+  const bool busy = first < n_k;                           // wavefronts without tokens only help with the tiles
+  AttnF32<D, KEY> f;
+  f.init(q, a, g, ls, ldq, hd, h, min(own, n_k - 1), lane);
+  f.load(q, a, g, ls, ldq, hd, h, 0, n_k);
+  int t0 = 0;
+  for (; t0 + kAttnF32Tile < n_k; t0 += kAttnF32Tile) {
+    __syncthreads();                                       // the tile before has been consumed
+    f.store_tile(s1, s2, lse_s, delta_s, t0, n_k);
+    __syncthreads();
+    f.load(q, a, g, ls, ldq, hd, h, t0 + kAttnF32Tile, n_k);
+    if (busy) f.run(s1, s2, lse_s, delta_s, scale, t0, n_k, lane);
+  }
+  __syncthreads();
+  f.store_tile(s1, s2, lse_s, delta_s, t0, n_k);
+  __syncthreads();
+  if (busy) f.run(s1, s2, lse_s, delta_s, scale, t0, n_k, lane);
+  if (own < n_k) f.store(dqkv + row0 * ldq + head * D, ldq, hd, own, scale, lane);
+}
+
+// blockIdx.x: (sample, head, chunk) in the key role, then all of them in the query role (the shorter one)
+template <int D>
+__global__ void __launch_bounds__(256, D == 128 ? 1 : 2) attn_bwd_f32_kernel(const float* __restrict__ qkv, const float* __restrict__ A,
+                                                              const float* __restrict__ dA, const float* __restrict__ lse, int n_units,
+                                                              int n_k, int h, float scale, int nchunks, float* __restrict__ dqkv) {
+  __shared__ __attribute__((aligned(16))) float smem[2 * kAttnF32Tile * (D + 4) + 2 * kAttnF32Tile];
+  const bool key = (int)blockIdx.x < n_units;
+  const int unit = key ? blockIdx.x : blockIdx.x - n_units;
+  const int chunk = unit % nchunks, bh = unit / nchunks, head = bh % h, b = bh / h;
+  if (key) attn_f32_body<D, true>(smem, qkv, A, dA, lse, b, head, chunk, n_k, h, scale, dqkv);
+  else attn_f32_body<D, false>(smem, qkv, A, dA, lse, b, head, chunk, n_k, h, scale, dqkv);
+}
+
+// ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
 static constexpr size_t kAttnMaxLds = 160 * 1024;
@@ -634,6 +807,15 @@ static void launch_attn_plain(const T* qkv, const T* A, const T* dA, const float
   }
 }
 
+template <int D>
+static void launch_attn_f32(const float* qkv, const float* A, const float* dA, const float* lse, int B, int n_k, int h, float scale,
+                            float* dqkv, hipStream_t s) {
+  const int nchunks = (int)ceil_div(n_k, kAttnChunk);
+  const long long units = (long long)B * h * nchunks;
+  SBP_LAUNCH(SBP_PROF_ATTENTION, s, (attn_bwd_f32_kernel<D>), dim3((unsigned)(2 * units)), dim3(256), 0, s, qkv, A, dA, lse, (int)units,
+             n_k, h, scale, nchunks, dqkv);
+}
+
 int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA, const float* lse, int32_t B, int32_t n_k,
                                   int32_t h, int32_t d, float scale, int32_t dtype, void* dqkv, hipStream_t s) {
   const int engine = attention_engine(n_k, d, dtype);
@@ -652,6 +834,11 @@ int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA
   } else if (dtype == SBP_BF16) {
     launch_attn_plain<uint16_t>((const uint16_t*)qkv, (const uint16_t*)A, (const uint16_t*)dA, lse, B, n_k, h, d, scale,
                                 (uint16_t*)dqkv, s);
+  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && (int64_t)B * h * ceil_div(n_k, kAttnChunk) < (1 << 30)) {
+    const float *q = (const float*)qkv, *a = (const float*)A, *g = (const float*)dA;
+    if (d == 32) launch_attn_f32<32>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
+    else if (d == 64) launch_attn_f32<64>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
+    else launch_attn_f32<128>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
   } else {
     launch_attn_plain<float>((const float*)qkv, (const float*)A, (const float*)dA, lse, B, n_k, h, d, scale, (float*)dqkv, s);
   }

@@ -149,3 +149,13 @@ def test_tiled_kernel_at_sizes_the_single_workgroup_kernel_also_serves(B, n, h, 
         assert sbp.backward_attention_engine(n_k, d, sbp.BF16) == "mfma"
         errs_w = _run(B, n, h, d, keep, "bf16", 13)
     assert max(errs_w) <= TOL_BF16, errs_w
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("n_k", [31, 64, 65, 128, 129])
+def test_f32_matrix_core_kernel_at_tile_and_chunk_edges(d, n_k):
+    # streamed tiles of 32 tokens, chunks of 128 owned per workgroup; the plain kernel stays behind the option
+    keep = _keep_sets(2, 160, n_k, 23)
+    assert max(_run(2, 160, 2, d, keep, "f32", 25)) <= TOL_F32
+    with sbp.options(attn="plain"):
+        assert max(_run(2, 160, 2, d, keep, "f32", 25)) <= TOL_F32
