@@ -393,9 +393,9 @@ int32_t sbp_backward_layerscale(const void* dU_k, const void* Y_k, const float* 
  *   d       head dimension: 16, 32, 64 or 128.   scale: usually 1/sqrt(d).
  * All pointers 16-byte aligned.  fp32 arithmetic and accumulation; in bf16 the probabilities S and dM are
  * rounded to bf16 before the second products (matrix cores), outputs rounded once.  Deterministic.
- * sbp_backward_attention_engine (host only) reports which kernel serves a size: 1 = matrix-core kernel with one
- * workgroup per (sample, head) (bf16, d in {32, 64, 128}, the kept tokens of one head fit LDS: n_k <= 256 at
- * d = 64), 2 = matrix-core kernel tiled over chunks of 128 tokens (bf16, d in {32, 64, 128}, any n_k),
+ * sbp_backward_attention_engine (host only) reports which kernels serve a size: 1 = matrix cores, the kept tokens of one
+ * head fit LDS (bf16, d in {32, 64, 128}; n_k <= 256 at d = 64): one workgroup per (sample, head) up to 64 tokens, chunks of
+ * 128 tokens above; 2 = matrix cores, beyond that size (bf16, d in {32, 64, 128}): chunks of 128 tokens, any n_k;
  * 0 = fp32 tensors (fp32 matrix cores at d in {32, 64, 128}) and d = 16 (plain kernel).
  */
 int32_t sbp_backward_attention_engine(int32_t n_k, int32_t d, int32_t dtype);

@@ -158,22 +158,61 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& c, int ks) {
   return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3]));
 }
 
-// A operand [32 head-dim rows from dcol0][16 tokens]: token rows row0 + 4u + (0..3) and row0 + 8 + 4u + (0..3)
-template <int PITCH>
-__device__ __forceinline__ bf16x8_t read_tr_tokens(const char* tile, int row0, int dcol0, int lane) {
-  const int g = lane >> 4, i = lane & 15;
-  const char* p = tile + (row0 + 4 * (g >> 1) + (i >> 2)) * PITCH + (dcol0 + 16 * (g & 1) + 4 * (i & 3)) * 2;
-  const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p));
-  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p + 8 * PITCH));
-  return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
+// Two LDS layouts of a tile of token rows, each with the lane's two kinds of operand reads:
+//   row(tile, row0, ks): 16 bytes of row row0 + (lane & 31), head dimensions 16 ks + 8 u .. + 7
+//   tr(tile, row0, x):   A operand [head dimensions 32 x .. + 31][16 tokens]: token rows row0 + 4u + (0..3) and
+//                        row0 + 8 + 4u + (0..3) (two transposing reads; row0 is a multiple of 16)
+// AttnPadded: rows of 2 D + 16 bytes, written from registers.
+template <int D>
+struct AttnPadded {
+  static constexpr int PITCH = AttnLds<D>::PITCH;
+  int foff, toff;
+  __device__ __forceinline__ explicit AttnPadded(int lane) {
+    const int g = lane >> 4, i = lane & 15;
+    foff = (lane & 31) * PITCH + 16 * (lane >> 5);
+    toff = (4 * (g >> 1) + (i >> 2)) * PITCH + (16 * (g & 1) + 4 * (i & 3)) * 2;
+  }
+  __device__ __forceinline__ bf16x8_t row(const char* tile, int row0, int ks) const {
+    return *reinterpret_cast<const bf16x8_t*>(tile + row0 * PITCH + foff + ks * 32);
+  }
+  __device__ __forceinline__ bf16x8_t tr(const char* tile, int row0, int x) const {
+    const char* p = tile + row0 * PITCH + toff + 64 * x;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p + 8 * PITCH));
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
+// AttnSwizzled: rows of 2 D bytes, 16-byte chunk c of row r at place c ^ swz(r), written by global -> LDS copies whose lanes
+// choose the chunk they fetch (the copy fixes the LDS place by lane).  8 neighbouring rows fall on distinct banks.
+template <int D>
+struct AttnSwizzled {
+  static constexpr int RB = 2 * D, CH = D / 8, KS = D / 16, DB = D / 32;
+  static __device__ __forceinline__ int swz(int r) { return D == 32 ? (r >> 1) & 3 : r & 7; }
+  int foff[KS], toff[DB];
+  __device__ __forceinline__ explicit AttnSwizzled(int lane) {
+    const int g = lane >> 4, i = lane & 15, r = lane & 31, rt = 4 * (g >> 1) + (i >> 2);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) foff[ks] = r * RB + (((2 * ks + (lane >> 5)) ^ swz(r)) << 4);
+#pragma unroll
+    for (int x = 0; x < DB; ++x) toff[x] = rt * RB + (((4 * x + 2 * (g & 1) + ((i & 3) >> 1)) ^ swz(rt)) << 4) + 8 * (i & 1);
+  }
+  __device__ __forceinline__ bf16x8_t row(const char* tile, int row0, int ks) const {
+    return *reinterpret_cast<const bf16x8_t*>(tile + row0 * RB + foff[ks]);
+  }
+  __device__ __forceinline__ bf16x8_t tr(const char* tile, int row0, int x) const {
+    const char* p = tile + row0 * RB + toff[x];
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p + 8 * RB));
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+};
 
 // The LDS image of one (sample, head): four tiles and two tables.
 template <int D>
 struct AttnTiles {
   static constexpr int PITCH = AttnLds<D>::PITCH;
   char *tq, *tk, *tv, *tg;       // q, k, v, dA
-  float *lse_s, *delta_s;        // lse * log2(e), dA.A
+  float *lse_s, *delta_s;        // lse * log2(e), -dA.A
   __device__ __forceinline__ void place(char* base, int npad) {
     tq = base;
     tk = tq + npad * PITCH;
@@ -240,7 +279,7 @@ struct AttnPieces {
 #pragma unroll
         for (int e = 0; e < 4; ++e) s += bf16_lo(gw[e]) * bf16_lo(aw[e]) + bf16_hi(gw[e]) * bf16_hi(aw[e]);
         for (int m = 1; m < CH; m <<= 1) s += __shfl_xor(s, m);
-        if (ch == 0) T.delta_s[tok] = s;
+        if (ch == 0) T.delta_s[tok] = -s;
       }
     }
   }
@@ -268,46 +307,41 @@ struct AttnKeyAcc {
       vf[ks] = *reinterpret_cast<const bf16x8_t*>(tv + foff + ks * 32);
     }
   }
-  // ... or straight from memory: k and v of token `tok` (zeros if valid is false), row pointers of the head's columns
-  __device__ __forceinline__ void keys_from_memory(const uint16_t* krow, const uint16_t* vrow, bool valid, int lane) {
-    const int u = lane >> 5;
+  // ... or straight from memory: k and v of the lane's token (row pointers of the head's columns)
+  __device__ __forceinline__ void from_memory(const uint16_t* krow, const uint16_t* vrow, int lane) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      uint4 a = make_uint4(0, 0, 0, 0), b = a;
-      if (valid) {
-        a = *reinterpret_cast<const uint4*>(krow + 16 * ks + 8 * u);
-        b = *reinterpret_cast<const uint4*>(vrow + 16 * ks + 8 * u);
-      }
-      kf[ks] = __builtin_bit_cast(bf16x8_t, a);
-      vf[ks] = __builtin_bit_cast(bf16x8_t, b);
+      kf[ks] = *reinterpret_cast<const bf16x8_t*>(krow + 16 * ks + 8 * (lane >> 5));
+      vf[ks] = *reinterpret_cast<const bf16x8_t*>(vrow + 16 * ks + 8 * (lane >> 5));
     }
   }
-  __device__ __forceinline__ void run(const char* tq, const char* tg, const float* lse_s, const float* delta_s, int nblk,
+  // dP starts from -delta (read straight into the accumulators), so that dS = P dP needs no subtraction
+  template <class L>
+  __device__ __forceinline__ void run(const L& lay, const char* tq, const char* tg, const float* lse_s, const float* delta_s, int nblk,
                                       float scale, int lane) {
-    const int u = lane >> 5, lrow = lane & 31;
-    const int foff = lrow * PITCH + 16 * u;              // 16-byte operand read of row (lane & 31), k chunk 8u
+    const int u = lane >> 5;
     const float c2 = scale * kLog2e;
     for (int ib = 0; ib < nblk; ++ib) {
       f32x16_t s, dp;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const f32x4_t d4 = *reinterpret_cast<const f32x4_t*>(delta_s + ib * 32 + 8 * q4 + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { dp[4 * q4 + e] = d4[e]; s[4 * q4 + e] = 0.f; }
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8_t qf = *reinterpret_cast<const bf16x8_t*>(tq + ib * 32 * PITCH + foff + ks * 32);
-        const bf16x8_t gf = *reinterpret_cast<const bf16x8_t*>(tg + ib * 32 * PITCH + foff + ks * 32);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[ks], s, 0, 0, 0);      // rows i, columns j
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf, vf[ks], dp, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tq, ib * 32, ks), kf[ks], s, 0, 0, 0);      // rows i, columns j
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tg, ib * 32, ks), vf[ks], dp, 0, 0, 0);
       }
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 l4 = *reinterpret_cast<const float4*>(lse_s + ib * 32 + 8 * q4 + 4 * u);
-        const float4 d4 = *reinterpret_cast<const float4*>(delta_s + ib * 32 + 8 * q4 + 4 * u);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dl[4] = {d4.x, d4.y, d4.z, d4.w};
+        const f32x4_t l4 = *reinterpret_cast<const f32x4_t*>(lse_s + ib * 32 + 8 * q4 + 4 * u);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float p = __builtin_amdgcn_exp2f(s[4 * q4 + e] * c2 - lv[e]);
+          const float p = __builtin_amdgcn_exp2f(s[4 * q4 + e] * c2 - l4[e]);
           s[4 * q4 + e] = p;
-          dp[4 * q4 + e] = p * (dp[4 * q4 + e] - dl[e]);
+          dp[4 * q4 + e] *= p;
         }
       }
 #pragma unroll
@@ -315,10 +349,8 @@ struct AttnKeyAcc {
         const bf16x8_t pf = pack8(s, ks), dsf = pack8(dp, ks);
 #pragma unroll
         for (int x = 0; x < DB; ++x) {
-          const bf16x8_t gt = read_tr_tokens<PITCH>(tg, ib * 32 + 16 * ks, 32 * x, lane);
-          const bf16x8_t qt = read_tr_tokens<PITCH>(tq, ib * 32 + 16 * ks, 32 * x, lane);
-          dv[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt, pf, dv[x], 0, 0, 0);   // rows head dim, columns j
-          dk[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt, dsf, dk[x], 0, 0, 0);
+          dv[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.tr(tg, ib * 32 + 16 * ks, x), pf, dv[x], 0, 0, 0);   // rows head dim, columns j
+          dk[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.tr(tq, ib * 32 + 16 * ks, x), dsf, dk[x], 0, 0, 0);
         }
       }
     }
@@ -352,7 +384,7 @@ struct AttnQueryAcc {
   static constexpr int PITCH = AttnLds<D>::PITCH, KS = D / 16, DB = D / 32;
   f32x16_t dq[DB];
   bf16x8_t qf[KS], gf[KS];
-  float l, dl;                   // lse * log2(e) and delta of query (lane & 31)
+  float l, ndl;                  // lse * log2(e) and -delta of query (lane & 31)
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int x = 0; x < DB; ++x)
@@ -368,59 +400,53 @@ struct AttnQueryAcc {
       gf[ks] = *reinterpret_cast<const bf16x8_t*>(tg + foff + ks * 32);
     }
     l = lse_s[row0 + (lane & 31)];
-    dl = delta_s[row0 + (lane & 31)];
+    ndl = delta_s[row0 + (lane & 31)];
   }
-  // straight from memory: q, dA, A rows of the token (head's columns) and its lse; zeros if valid is false
-  __device__ __forceinline__ void queries_from_memory(const uint16_t* qrow, const uint16_t* grow, const uint16_t* arow,
-                                                      const float* lse_tok, bool valid, int lane) {
-    const int u = lane >> 5;
+  // straight from memory: q, dA, A rows of the lane's token (head's columns) and its lse
+  __device__ __forceinline__ void from_memory(const uint16_t* qrow, const uint16_t* grow, const uint16_t* arow, const float* lse_tok, int lane) {
     float part = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      uint4 a = make_uint4(0, 0, 0, 0), b = a, c = a;
-      if (valid) {
-        a = *reinterpret_cast<const uint4*>(qrow + 16 * ks + 8 * u);
-        b = *reinterpret_cast<const uint4*>(grow + 16 * ks + 8 * u);
-        c = *reinterpret_cast<const uint4*>(arow + 16 * ks + 8 * u);
-      }
-      qf[ks] = __builtin_bit_cast(bf16x8_t, a);
+      qf[ks] = *reinterpret_cast<const bf16x8_t*>(qrow + 16 * ks + 8 * (lane >> 5));
+      const uint4 b = *reinterpret_cast<const uint4*>(grow + 16 * ks + 8 * (lane >> 5)), c = *reinterpret_cast<const uint4*>(arow + 16 * ks + 8 * (lane >> 5));
       gf[ks] = __builtin_bit_cast(bf16x8_t, b);
       const uint32_t gw[4] = {b.x, b.y, b.z, b.w}, aw[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) part += bf16_lo(gw[e]) * bf16_lo(aw[e]) + bf16_hi(gw[e]) * bf16_hi(aw[e]);
     }
-    dl = part + __shfl_xor(part, 32);          // the two halves of every 16 columns lie 32 lanes apart
-    l = valid ? *lse_tok * kLog2e : 0.f;
+    ndl = -(part + __shfl_xor(part, 32));      // the two halves of every 16 columns lie 32 lanes apart
+    l = *lse_tok * kLog2e;
   }
-  __device__ __forceinline__ void run(const char* tk, const char* tv, int nblk, float scale, int lane) {
-    const int u = lane >> 5, lrow = lane & 31;
-    const int foff = lrow * PITCH + 16 * u;
+  // keys: valid rows of the tile (rows past them count for nothing: their probabilities are zeroed)
+  template <class L>
+  __device__ __forceinline__ void run(const L& lay, const char* tk, const char* tv, int keys, float scale, int lane) {
+    int j0 = 0;
+    for (; j0 + 32 <= keys; j0 += 32) block<false>(lay, tk, tv, j0, keys, scale, lane);
+    if (j0 < keys) block<true>(lay, tk, tv, j0, keys, scale, lane);
+  }
+  template <bool TAIL, class L>
+  __device__ __forceinline__ void block(const L& lay, const char* tk, const char* tv, int j0, int keys, float scale, int lane) {
     const float c2 = scale * kLog2e;
-    for (int jb = 0; jb < nblk; ++jb) {
-      f32x16_t s, dp;
+    f32x16_t s, dp;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[e] = dp[e] = 0.f;
+    for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(tk + jb * 32 * PITCH + foff + ks * 32);
-        const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(tv + jb * 32 * PITCH + foff + ks * 32);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s, 0, 0, 0);      // rows j, columns i
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, gf[ks], dp, 0, 0, 0);
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tk, j0, ks), qf[ks], s, 0, 0, 0);      // rows j, columns i
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tv, j0, ks), gf[ks], dp, 0, 0, 0);
+    }
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float p = __builtin_amdgcn_exp2f(s[e] * c2 - l);
-        dp[e] = p * (dp[e] - dl);
-      }
+    for (int e = 0; e < 16; ++e) dp[e] = (dp[e] + ndl) * __builtin_amdgcn_exp2f(s[e] * c2 - l);
+    if constexpr (TAIL) {
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8_t dsf = pack8(dp, ks);
+      for (int e = 0; e < 16; ++e) dp[e] = j0 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) < keys ? dp[e] : 0.f;
+    }
 #pragma unroll
-        for (int x = 0; x < DB; ++x) {
-          const bf16x8_t kt = read_tr_tokens<PITCH>(tk, jb * 32 + 16 * ks, 32 * x, lane);
-          dq[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt, dsf, dq[x], 0, 0, 0);   // rows head dim, columns i
-        }
-      }
+    for (int ks = 0; ks < 2; ++ks) {
+      const bf16x8_t dsf = pack8(dp, ks);
+#pragma unroll
+      for (int x = 0; x < DB; ++x)
+        dq[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.tr(tk, j0 + 16 * ks, x), dsf, dq[x], 0, 0, 0);   // rows head dim, columns i
     }
   }
   __device__ __forceinline__ void store(uint16_t* __restrict__ out, int i, int n_k, int h, float scale, int lane) const {
@@ -446,17 +472,17 @@ __device__ __forceinline__ void attn_key_block(const AttnTiles<D>& T, int jb, in
   AttnKeyAcc<D> acc;
   acc.zero();
   acc.keys_from_lds(T.tk, T.tv, jb * 32, lane);
-  acc.run(T.tq, T.tg, T.lse_s, T.delta_s, nblk, scale, lane);
+  acc.run(AttnPadded<D>(lane), T.tq, T.tg, T.lse_s, T.delta_s, nblk, scale, lane);
   acc.store(out, jb * 32 + (lane & 31), n_k, h, scale, lane);
 }
 
 template <int D>
-__device__ __forceinline__ void attn_query_block(const AttnTiles<D>& T, int ib, int nblk, int n_k, int h, float scale,
+__device__ __forceinline__ void attn_query_block(const AttnTiles<D>& T, int ib, int n_k, int h, float scale,
                                                  uint16_t* __restrict__ out, int lane) {
   AttnQueryAcc<D> acc;
   acc.zero();
   acc.queries_from_lds(T.tq, T.tg, T.lse_s, T.delta_s, ib * 32, lane);
-  acc.run(T.tk, T.tv, nblk, scale, lane);
+  acc.run(AttnPadded<D>(lane), T.tk, T.tv, n_k, scale, lane);
   acc.store(out, ib * 32 + (lane & 31), n_k, h, scale, lane);
 }
 
@@ -482,100 +508,188 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 2) attn_bwd_mfma_kernel(co
   for (int i = t; i < npad; i += 256) T.lse_s[i] = i < n_k ? it.lse[(long long)i * h] * kLog2e : 0.f;
   __syncthreads();
   for (int jb = wave; jb < nblk; jb += 4) attn_key_block<D>(T, jb, nblk, n_k, h, scale, it.o, lane);
-  for (int ib = wave; ib < nblk; ib += 4) attn_query_block<D>(T, ib, nblk, n_k, h, scale, it.o, lane);
+  for (int ib = wave; ib < nblk; ib += 4) attn_query_block<D>(T, ib, n_k, h, scale, it.o, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
-// Tiled MFMA kernel: any number of kept tokens.  A workgroup owns a chunk of 128 tokens of one (sample, head) in one of
-// two roles: as keys (dK, dV of the chunk: every wavefront holds the k and v fragments of its 32 keys in registers and
-// the queries - rows of q and dA, lse, delta - stream through LDS in tiles of 128) or as queries (dQ of the chunk: q,
-// dA fragments, lse and delta in registers, the keys - rows of k and v - stream through LDS).  The chunk itself never
-// touches LDS, a tile is two [128][D] images (37 KB at D = 64): three workgroups per CU.  Every output element is
-// written by exactly one wavefront, sums run in token order: deterministic, no atomics.
+// Tiled MFMA kernel: any number of kept tokens.  A workgroup of 4 wavefronts owns a chunk of 128 tokens of one (sample,
+// head) in one of two roles: as keys (dK, dV; every wavefront holds the k and v fragments of its 32 keys in registers, the
+// queries - rows of q and dA, lse, -delta - stream through LDS in tiles of 64) or as queries (dQ; q, dA fragments, lse,
+// -delta in registers, rows of k and v stream).  Every output element is written by exactly one wavefront, sums run in token
+// order: deterministic, no atomics.
+// A ring of three tiles is filled by global -> LDS copies, two tiles ahead; the key role makes -delta and lse tables of 512
+// queries at a time from memory, so that its loop holds nothing but fragments and accumulators: 168 registers, three
+// workgroups per CU.  (A spilled register in the loop waits, loads being counted in order, for the copies under way: with
+// 17 of them the launch took 148 us.)  dP starts from -delta in the accumulators.  Rows past n_k are copies of the last row:
+// as queries their lse is so large that their probabilities are 0, as keys their probabilities are zeroed (peeled block).
+// The outputs leave through LDS as whole rows.  The workgroups of a (sample, head) run on one XCD, whose L2 they share
+// (spread over all eight, 8 x 12 heads of 1024 tokens moved 614 MB across the L2 boundary, now 107 MB); an XCD runs its key
+// units first, the longer kind (110 -> 102 us), at the price of a second read of small heads (27.6 instead of 26.6 us at
+// 768 heads of 99 tokens).
+// Bound: the blocks themselves keep the matrix cores 80 % busy (16 and 12 MFMAs of 33 cycles per 32 x 32 block and role,
+// vector ALU 420 cycles next to them, overlapped by the three wavefronts of a SIMD); unit starts (first tiles and tables
+// from memory) and the power limit (1.85 GHz) take the rest.  8 x 12 heads of 64, 1024 kept tokens: 153 -> 102 us.
+// Two more shapes were slower: 64 tokens per wavefront (half the LDS reads per MFMA, but 330 registers and one wavefront
+// per SIMD: accumulator moves and spills, 225 us), and the same with dK and dV as separate roles (148 us).
 // ------------------------------------------------------------------------------------------------
-static constexpr int kAttnChunk = 128;
+static constexpr int kAttnChunk = 128, kAttnTile = 64, kAttnRing = 3, kAttnTable = 512;
 
-// Rows t0 .. t0 + 127 of one (sample, head) into two LDS images of 128 rows (rows past n_k as zeros).  KEY = true:
-// the queries' side (q -> t1, dA -> t2, lse * log2 e and delta = dA.A into the tables); false: the keys' side
-// (k -> t1, v -> t2).  The loads are issued before the barrier that retires the images' previous contents.
-template <int D, bool KEY>
-__device__ __forceinline__ void attn_load_tile(const AttnItem& it, int t0, int n_k, int h, char* t1, char* t2,
-                                               float* lse_s, float* delta_s) {
-  constexpr int CH = D / 8, PITCH = AttnLds<D>::PITCH, R = kAttnChunk * CH / 256;   // 16-byte pieces per thread, tensor and tile
-  const int t = threadIdx.x;
-  const long long ldq = 3LL * h * D, lda = (long long)h * D;
-  uint4 x1[R], x2[R], x3[KEY ? R : 1];
+template <int D> struct AttnTiled {
+  static constexpr int RB = 2 * D, IMG = kAttnTile * RB, STAGE = 2 * IMG;    // bytes per row, image, tile
+  static constexpr size_t LDS = (size_t)kAttnRing * STAGE + 2 * kAttnTable * sizeof(float);
+  static_assert(4 * 2 * 32 * (RB + 16) <= kAttnRing * STAGE, "the output images fit the ring");
+};
+
+__device__ __forceinline__ float attn_dot2(uint32_t a, uint32_t b, float c) {      // two exact products added in fp32
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
+}
+
+// the streamed side: two images per tile, copied global -> LDS
+template <int D>
+struct AttnStream {
+  static constexpr int CH = D / 8, RB = 2 * D, NI = D / 32;                  // 16-byte pieces and bytes per row, copies per wavefront and image
+  const uint16_t *s1, *s2;             // q, dA or k, v
+  uint32_t off1[NI], off2[NI];         // byte offsets of the lane's pieces in a tile
+  int ld1, ld2, n_k;                   // row lengths
+  __device__ __forceinline__ AttnStream(const uint16_t* s1_, const uint16_t* s2_, int ld1_, int ld2_, int n_k_, int lane, int wave)
+      : s1(s1_), s2(s2_), ld1(ld1_), ld2(ld2_), n_k(n_k_) { offsets(kAttnTile, lane, wave); }
+  __device__ __forceinline__ void offsets(int rows, int lane, int wave) {      // rows: valid rows of the tile; others copy the last one
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int p = t + 256 * r, tok = t0 + p / CH, ch = p % CH;
-    x1[r] = x2[r] = make_uint4(0, 0, 0, 0);
-    if constexpr (KEY) x3[r] = make_uint4(0, 0, 0, 0);
-    if (tok < n_k) {
-      if constexpr (KEY) {
-        x1[r] = *reinterpret_cast<const uint4*>(it.q + tok * ldq + 8 * ch);
-        x2[r] = *reinterpret_cast<const uint4*>(it.g + tok * lda + 8 * ch);
-        x3[r] = *reinterpret_cast<const uint4*>(it.a + tok * lda + 8 * ch);
-      } else {
-        x1[r] = *reinterpret_cast<const uint4*>(it.q + tok * ldq + (long long)h * D + 8 * ch);
-        x2[r] = *reinterpret_cast<const uint4*>(it.q + tok * ldq + 2LL * h * D + 8 * ch);
+    for (int n = 0; n < NI; ++n) {
+      const int row = (wave * NI + n) * (1024 / RB) + lane / CH, c = (lane % CH) ^ AttnSwizzled<D>::swz(row);
+      off1[n] = (uint32_t)min(row, rows - 1) * (uint32_t)ld1 * 2u + 16u * c;
+      off2[n] = (uint32_t)min(row, rows - 1) * (uint32_t)ld2 * 2u + 16u * c;
+    }
+  }
+  // copies of tile s (the tiles in order) into its ring place
+  __device__ __forceinline__ void issue(int s, char* ring, int lane, int wave) {
+    char* buf = ring + (s % kAttnRing) * AttnTiled<D>::STAGE + wave * NI * 1024;
+    if ((s + 1) * kAttnTile > n_k) offsets(n_k - s * kAttnTile, lane, wave);
+    const char* b1 = reinterpret_cast<const char*>(s1 + (long long)s * kAttnTile * ld1);
+    const char* b2 = reinterpret_cast<const char*>(s2 + (long long)s * kAttnTile * ld2);
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+      async_copy16(b1 + off1[n], buf + n * 1024);
+      async_copy16(b2 + off2[n], buf + AttnTiled<D>::IMG + n * 1024);
+    }
+  }
+};
+
+// Writes an accumulated [head dim][32 tokens] block to the tokens' rows (out: row 0 of the head's columns) through LDS
+// (one 32-row image of the wavefront's own, pitch 2 D + 16 bytes): whole 2 D-byte rows instead of 8-byte pieces
+template <int D>
+__device__ __forceinline__ void attn_store_rows(char* image, const f32x16_t (&acc)[D / 32], float f, uint16_t* __restrict__ out, long long ld,
+                                                int first, int n_k, int lane) {
+  constexpr int PITCH = 2 * D + 16, LPR = D / 8;           // lanes per row
+  char* row = image + (lane & 31) * PITCH + 8 * (lane >> 5);
+#pragma unroll
+  for (int x = 0; x < D / 32; ++x)
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      *reinterpret_cast<uint2*>(row + 64 * x + 16 * q4) = make_uint2(bf16_pack(acc[x][4 * q4] * f, acc[x][4 * q4 + 1] * f),
+                                                                     bf16_pack(acc[x][4 * q4 + 2] * f, acc[x][4 * q4 + 3] * f));
+#pragma unroll
+  for (int r = 0; r < 32 * LPR / 64; ++r) {                // (a wavefront's LDS accesses complete in order)
+    const int tok = r * (64 / LPR) + lane / LPR, c = lane % LPR;
+    const uint4 v = *reinterpret_cast<const uint4*>(image + tok * PITCH + 16 * c);
+    if (first + tok < n_k) *reinterpret_cast<uint4*>(out + (first + tok) * ld + 8 * c) = v;
+  }
+}
+
+// lse * log2(e) and -delta = -dA.A of tokens t0 .. t0 + 511 (key role): four lanes per row, UNR rows in flight per lane
+template <int D, int UNR>
+__device__ __forceinline__ void attn_make_tables(const AttnItem& it, int t0, int n_k, int h, float* lse_s, float* ndl_s) {
+  const int t = threadIdx.x, n = min(kAttnTable, n_k - t0);
+  const long long lda = (long long)h * D;
+  float lv[kAttnTable / 256];
+#pragma unroll
+  for (int i = 0; i < kAttnTable / 256; ++i) lv[i] = it.lse[(long long)min(t0 + t + 256 * i, n_k - 1) * h];
+  for (int r0 = 0; r0 < n; r0 += 64 * UNR) {
+    uint4 x[UNR][D / 32], y[UNR][D / 32];
+#pragma unroll
+    for (int v = 0; v < UNR; ++v) {
+      const long long off = min(t0 + r0 + 64 * v + (t >> 2), n_k - 1) * lda + (t & 3) * (D / 4);
+#pragma unroll
+      for (int r = 0; r < D / 32; ++r) {
+        x[v][r] = *reinterpret_cast<const uint4*>(it.g + off + 8 * r);
+        y[v][r] = *reinterpret_cast<const uint4*>(it.a + off + 8 * r);
       }
     }
-  }
-  float lv = 0.f;
-  if (KEY && t < kAttnChunk && t0 + t < n_k) lv = it.lse[(long long)(t0 + t) * h] * kLog2e;
-  __syncthreads();                                        // the previous contents have been consumed
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int p = t + 256 * r, tok = p / CH, ch = p % CH;
-    *reinterpret_cast<uint4*>(t1 + tok * PITCH + ch * 16) = x1[r];
-    *reinterpret_cast<uint4*>(t2 + tok * PITCH + ch * 16) = x2[r];
-    if constexpr (KEY) {
-      const uint32_t gw[4] = {x2[r].x, x2[r].y, x2[r].z, x2[r].w}, aw[4] = {x3[r].x, x3[r].y, x3[r].z, x3[r].w};
-      float sacc = 0.f;
+    for (int v = 0; v < UNR; ++v) {
+      float d = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sacc += bf16_lo(gw[e]) * bf16_lo(aw[e]) + bf16_hi(gw[e]) * bf16_hi(aw[e]);
-      for (int m = 1; m < CH; m <<= 1) sacc += __shfl_xor(sacc, m);
-      if (ch == 0) delta_s[tok] = sacc;
+      for (int r = 0; r < D / 32; ++r)
+        d = attn_dot2(x[v][r].x, y[v][r].x, attn_dot2(x[v][r].y, y[v][r].y, attn_dot2(x[v][r].z, y[v][r].z, attn_dot2(x[v][r].w, y[v][r].w, d))));
+      d += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(d), 0xB1, 0xf, 0xf, true));   // lane ^ 1
+      d += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(d), 0x4E, 0xf, 0xf, true));   // lane ^ 2
+      if ((t & 3) == 0) ndl_s[r0 + 64 * v + (t >> 2)] = -d;
     }
   }
-  if (KEY && t < kAttnChunk) lse_s[t] = lv;
+#pragma unroll
+  for (int i = 0; i < kAttnTable / 256; ++i) lse_s[t + 256 * i] = t0 + t + 256 * i < n_k ? lv[i] * kLog2e : 1e30f;
 }
 
 template <int D, bool KEY>
 __device__ __forceinline__ void attn_tiled_body(char* smem, const AttnItem& it, int chunk, int n_k, int h, float scale) {
-  constexpr int PITCH = AttnLds<D>::PITCH;
-  char* t1 = smem;                                   // rows of q (key role) or k (query role)
-  char* t2 = t1 + kAttnChunk * PITCH;                // rows of dA or v
-  float* lse_s = reinterpret_cast<float*>(t2 + kAttnChunk * PITCH);
-  float* delta_s = lse_s + kAttnChunk;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const long long ldq = 3LL * h * D, lda = (long long)h * D;
-  const int own = chunk * kAttnChunk + wave * 32 + (lane & 31);     // this lane's token of the chunk
-  const bool own_ok = own < n_k;
-  const int own_c = min(own, n_k - 1);
+  using T = AttnTiled<D>;
+  float *lse_s = reinterpret_cast<float*>(smem + kAttnRing * T::STAGE), *ndl_s = lse_s + kAttnTable;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int first = chunk * kAttnChunk + wave * 32;         // first token of this wavefront
+  const int ns = (n_k + kAttnTile - 1) / kAttnTile, hD = h * D;
+  const bool busy = first < n_k;                            // wavefronts without tokens only help with the tiles
+  const AttnSwizzled<D> lay(lane);
+  AttnStream<D> st(KEY ? it.q : it.q + hD, KEY ? it.g : it.q + 2LL * hD, 3 * hD, KEY ? hD : 3 * hD, n_k, lane, wave);
+  st.issue(0, smem, lane, wave);
+  if (ns > 1) st.issue(1, smem, lane, wave);
   typename std::conditional<KEY, AttnKeyAcc<D>, AttnQueryAcc<D>>::type acc;
   acc.zero();
-  if constexpr (KEY) acc.keys_from_memory(it.q + own_c * ldq + (long long)h * D, it.q + own_c * ldq + 2LL * h * D, own_ok, lane);
-  else acc.queries_from_memory(it.q + own_c * ldq, it.g + own_c * lda, it.a + own_c * lda, it.lse + (long long)own_c * h, own_ok, lane);
-  const int npad = (n_k + 31) & ~31;
-  for (int t0 = 0; t0 < npad; t0 += kAttnChunk) {
-    const int rows = min(kAttnChunk, npad - t0);            // rows of this tile (a multiple of 32); rows past n_k are zeros
-    attn_load_tile<D, KEY>(it, t0, n_k, h, t1, t2, lse_s, delta_s);
-    __syncthreads();
-    if constexpr (KEY) acc.run(t1, t2, lse_s, delta_s, rows >> 5, scale, lane);
-    else acc.run(t1, t2, rows >> 5, scale, lane);
+  const long long own = min(first + (lane & 31), n_k - 1);
+  if constexpr (KEY) {
+    acc.from_memory(it.q + own * (3LL * hD) + hD, it.q + own * (3LL * hD) + 2LL * hD, lane);
+    attn_make_tables<D, 256 / D>(it, 0, n_k, h, lse_s, ndl_s);
+  } else {
+    acc.from_memory(it.q + own * (3LL * hD), it.g + own * hD, it.a + own * hD, it.lse + own * h, lane);
   }
-  acc.store(it.o, own, n_k, h, scale, lane);
+  for (int s = 0; s < ns; ++s) {
+    wait_async_copies<0>();                                 // tile s (issued two stages ago, or one: everything before this stage)
+    lds_barrier();                                          // ... everywhere; the ring place of tile s - 1 is free
+    if (KEY && s && s % (kAttnTable / kAttnTile) == 0) {
+      attn_make_tables<D, 64 / D + 1>(it, s * kAttnTile, n_k, h, lse_s, ndl_s);
+      lds_barrier();
+    }
+    if (s + 2 < ns) st.issue(s + 2, smem, lane, wave);
+    if (busy) {
+      const char* t1 = smem + (s % kAttnRing) * T::STAGE;
+      const int rows = min(kAttnTile, n_k - s * kAttnTile), q0 = (s * kAttnTile) % kAttnTable;
+      if constexpr (KEY) acc.run(lay, t1, t1 + T::IMG, lse_s + q0, ndl_s + q0, (rows + 31) >> 5, scale, lane);
+      else acc.run(lay, t1, t1 + T::IMG, rows, scale, lane);
+    }
+  }
+  lds_barrier();                                            // the tiles have been consumed: the ring becomes the wavefronts' images
+  if (busy) {
+    char* image = smem + wave * (2 * 32 * (2 * D + 16));
+    if constexpr (KEY) {
+      attn_store_rows<D>(image, acc.dk, scale, it.o + hD, 3LL * hD, first, n_k, lane);
+      attn_store_rows<D>(image + 32 * (2 * D + 16), acc.dv, 1.f, it.o + 2LL * hD, 3LL * hD, first, n_k, lane);
+    } else {
+      attn_store_rows<D>(image, acc.dq, scale, it.o, 3LL * hD, first, n_k, lane);
+    }
+  }
 }
 
 template <int D>
 __global__ void __launch_bounds__(256, D == 128 ? 1 : 3) attn_bwd_tiled_kernel(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ A,
                                                               const uint16_t* __restrict__ dA, const float* __restrict__ lse,
-                                                              int n_k, int h, float scale, int nchunks, uint16_t* __restrict__ dqkv) {
+                                                              int units, int n_k, int h, float scale, int nchunks, uint16_t* __restrict__ dqkv) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const AttnItem it = attn_item(qkv, A, dA, lse, dqkv, blockIdx.z, blockIdx.y, n_k, h, D);
-  if ((int)blockIdx.x < nchunks) attn_tiled_body<D, true>(smem, it, blockIdx.x, n_k, h, scale);
-  else attn_tiled_body<D, false>(smem, it, blockIdx.x - nchunks, n_k, h, scale);
+  // per XCD a contiguous run of (sample, head, chunk) in the key role (the longer one), then the same run in the query role
+  const int per = (units + 7) >> 3, i = blockIdx.x >> 3, unit = (blockIdx.x & 7) * per + (i < per ? i : i - per);
+  if (unit >= units) return;
+  const int bh = unit / nchunks, c = unit - bh * nchunks, b = bh / h;
+  const AttnItem it = attn_item(qkv, A, dA, lse, dqkv, b, bh - b * h, n_k, h, D);
+  if (i < per) attn_tiled_body<D, true>(smem, it, c, n_k, h, scale);
+  else attn_tiled_body<D, false>(smem, it, c, n_k, h, scale);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -592,7 +706,7 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 3) attn_bwd_tiled_kernel(c
 // workgroups of unequal length on 256 CUs).
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
-static constexpr int kAttnF32Tile = 32;
+static constexpr int kAttnF32Tile = 32, kAttnF32Chunk = 128;
 
 template <int D, bool KEY>
 struct AttnF32 {
@@ -718,7 +832,7 @@ __device__ __forceinline__ void attn_f32_body(float* smem, const float* qkv, con
   const long long row0 = (long long)b * n_k, ldq = 3LL * hd;
   const float *q = qkv + row0 * ldq + head * D, *a = A + row0 * hd + head * D, *g = dA + row0 * hd + head * D, *ls = lse + row0 * h + head;
   float *s1 = smem, *s2 = s1 + kAttnF32Tile * (D + 4), *lse_s = s2 + kAttnF32Tile * (D + 4), *delta_s = lse_s + kAttnF32Tile;
-  const int first = chunk * kAttnChunk + (t >> 6) * 32, own = first + (lane & 31);
+  const int first = chunk * kAttnF32Chunk + (t >> 6) * 32, own = first + (lane & 31);
   const bool busy = first < n_k;                           // wavefronts without tokens only help with the tiles
   AttnF32<D, KEY> f;
   f.init(q, a, g, ls, ldq, hd, h, min(own, n_k - 1), lane);
@@ -776,9 +890,7 @@ template <int D>
 static void launch_attn_mfma(const uint16_t* qkv, const uint16_t* A, const uint16_t* dA, const float* lse, int B, int n_k,
                              int h, float scale, uint16_t* dqkv, hipStream_t s) {
   const size_t image = AttnLds<D>::bytes((n_k + 31) & ~31);
-  if (image > 64 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bwd_mfma_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kAttnMaxLds);
+  allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_mfma_kernel<D>), image);
   SBP_LAUNCH(SBP_PROF_ATTENTION, s, (attn_bwd_mfma_kernel<D>), dim3(h, B), dim3(256), image, s, qkv, A, dA, lse, n_k, h, scale,
              dqkv);
 }
@@ -786,13 +898,11 @@ static void launch_attn_mfma(const uint16_t* qkv, const uint16_t* A, const uint1
 template <int D>
 static void launch_attn_tiled(const uint16_t* qkv, const uint16_t* A, const uint16_t* dA, const float* lse, int B, int n_k,
                               int h, float scale, uint16_t* dqkv, hipStream_t s) {
-  const size_t lds = (size_t)2 * kAttnChunk * AttnLds<D>::PITCH + (size_t)2 * kAttnChunk * sizeof(float);
-  if (lds > 64 * 1024)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(attn_bwd_tiled_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-  const int nchunks = (n_k + kAttnChunk - 1) / kAttnChunk;
-  SBP_LAUNCH(SBP_PROF_ATTENTION, s, (attn_bwd_tiled_kernel<D>), dim3(2 * nchunks, h, B), dim3(256), lds, s, qkv, A, dA, lse, n_k, h,
-             scale, nchunks, dqkv);
+  constexpr size_t lds = AttnTiled<D>::LDS;
+  allow_dynamic_lds(reinterpret_cast<const void*>(attn_bwd_tiled_kernel<D>), lds);
+  const int nchunks = (int)ceil_div(n_k, kAttnChunk), units = B * h * nchunks;
+  SBP_LAUNCH(SBP_PROF_ATTENTION, s, (attn_bwd_tiled_kernel<D>), dim3((unsigned)(16 * ceil_div(units, 8))), dim3(256), lds, s, qkv, A, dA,
+             lse, units, n_k, h, scale, nchunks, dqkv);
 }
 
 template <typename T>
@@ -810,7 +920,7 @@ static void launch_attn_plain(const T* qkv, const T* A, const T* dA, const float
 template <int D>
 static void launch_attn_f32(const float* qkv, const float* A, const float* dA, const float* lse, int B, int n_k, int h, float scale,
                             float* dqkv, hipStream_t s) {
-  const int nchunks = (int)ceil_div(n_k, kAttnChunk);
+  const int nchunks = (int)ceil_div(n_k, kAttnF32Chunk);
   const long long units = (long long)B * h * nchunks;
   SBP_LAUNCH(SBP_PROF_ATTENTION, s, (attn_bwd_f32_kernel<D>), dim3((unsigned)(2 * units)), dim3(256), 0, s, qkv, A, dA, lse, (int)units,
              n_k, h, scale, nchunks, dqkv);
@@ -819,10 +929,14 @@ static void launch_attn_f32(const float* qkv, const float* A, const float* dA, c
 int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA, const float* lse, int32_t B, int32_t n_k,
                                   int32_t h, int32_t d, float scale, int32_t dtype, void* dqkv, hipStream_t s) {
   const int engine = attention_engine(n_k, d, dtype);
+  // One workgroup per head where a head is at most two blocks of 32 tokens (64 x 12 heads of 64: 13.7 against 15.2 us at 50
+  // tokens, 7.8 against 10.5 at 25); from three blocks on the tiled kernel is ahead (27.6 against 30.1 us at 99, 67 against
+  // 81 at 197; d = 128: even at 99).
+  const bool tiled = engine == 2 || (n_k > 64 && options().attn_mode == 0);
   if (engine) {
     const uint16_t* q = (const uint16_t*)qkv; const uint16_t* a = (const uint16_t*)A; const uint16_t* g = (const uint16_t*)dA;
     uint16_t* o = (uint16_t*)dqkv;
-    if (engine == 2) {
+    if (tiled) {
       if (d == 32) launch_attn_tiled<32>(q, a, g, lse, B, n_k, h, scale, o, s);
       else if (d == 64) launch_attn_tiled<64>(q, a, g, lse, B, n_k, h, scale, o, s);
       else launch_attn_tiled<128>(q, a, g, lse, B, n_k, h, scale, o, s);
@@ -834,7 +948,7 @@ int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA
   } else if (dtype == SBP_BF16) {
     launch_attn_plain<uint16_t>((const uint16_t*)qkv, (const uint16_t*)A, (const uint16_t*)dA, lse, B, n_k, h, d, scale,
                                 (uint16_t*)dqkv, s);
-  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && (int64_t)B * h * ceil_div(n_k, kAttnChunk) < (1 << 30)) {
+  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && (int64_t)B * h * ceil_div(n_k, kAttnF32Chunk) < (1 << 30)) {
     const float *q = (const float*)qkv, *a = (const float*)A, *g = (const float*)dA;
     if (d == 32) launch_attn_f32<32>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
     else if (d == 64) launch_attn_f32<64>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);

@@ -159,3 +159,11 @@ def test_f32_matrix_core_kernel_at_tile_and_chunk_edges(d, n_k):
     assert max(_run(2, 160, 2, d, keep, "f32", 25)) <= TOL_F32
     with sbp.options(attn="plain"):
         assert max(_run(2, 160, 2, d, keep, "f32", 25)) <= TOL_F32
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("n_k", [64, 65, 129, 577])
+def test_bf16_dispatch_edge_and_table_refill(d, n_k):
+    # 64 tokens: the last size of the one-workgroup kernel; 65: a tile of 64 and one row; 129: a second chunk of one token;
+    # 577: the tables of queries 512 .. are made inside the loop, then one more row behind a full tile
+    assert max(_run(1, 600, 2, d, _keep_sets(1, 600, n_k, 27), "bf16", 29)) <= TOL_BF16
