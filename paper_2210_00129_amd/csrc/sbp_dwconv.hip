@@ -8,6 +8,7 @@
 // fp32 arithmetic on the vector ALUs (a depthwise conv is no dense contraction: no MFMA).
 #include <cstdlib>
 #include <mutex>
+#include <type_traits>
 
 #include "sbp_internal.h"
 
@@ -465,7 +466,7 @@ __global__ void __launch_bounds__(DW_THREADS * GROUPS) dw_both_strip_kernel(cons
 }
 
 // ------------------------------------------------------------------------------------------------
-// bf16, channel counts that are multiples of 8: LDS-tiled kernel.  A workgroup takes a tile of R rows x TS strips of 8
+// bf16, 3 x 3, channel counts that are multiples of 8: LDS-tiled kernel.  A workgroup takes a tile of R rows x TS strips of 8
 // columns and a slab of 32 channels, stages the gradient tile WITH its halo of KS - 1 rows and columns (dropped and
 // outside positions as zeros: no mask is looked at afterwards) and the X tile (no halo) in LDS once, and computes from
 // them both the dX of the tile and the tile's share of dWd and db:
@@ -723,10 +724,369 @@ __global__ void __launch_bounds__(DWF_THREADS, 2) dw_fused_kernel(const DwFusedA
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// bf16, 7 x 7, channel counts that are multiples of 8: all three outputs on the matrix cores.
+// v_mfma_f32_4x4x4_16b_bf16 is sixteen independent 4 x 4 x 4 products; block = channel, k = four neighbouring columns of one
+// row of one channel, so its operands are 8-byte pieces of the LDS lines [row][channel][column quad], and a dot2 loop
+// (32 multiply-adds per cycle and SIMD) becomes 128 per cycle of which 58 % (dX) and 77 % (dWd) are needed:
+//   dX   D[x][y] += sum_k T_i,ck[x][k] g[y - 3 + i][4 (q - 1 + ck) + k]: T holds the weights of tap row i as a band (7 tap
+//        rows x 3 column quads = 42 registers, made once per workgroup); 21 products for 4 x 4 outputs of 16 channels
+//   dWd  D[m][(e, h)] += sum_k g[r + m][4 t + k] X[y + e][4 (t + h) + k - s], two X rows and two X quads against four
+//        gradient rows: r = y - 3, y + 1 and s = 0 .. 3 reach all 49 taps (u = e - m + 6 - 4 a, v = 3 - s + 4 h) with
+//        8 accumulators of 4, kept over all tiles of the workgroup; 16 products per 4 x 4 positions
+//   db   ones x g, one product
+// Two roles of four wavefronts share a staged tile: dX (weights in registers, one gradient quad of 7 row offsets per step,
+// three outputs in flight: 7 LDS reads per 21 products) and dWd / db (4 + 1 + 2 reads and about 12 shifts per 17 products);
+// one role alone in a wavefront fits 128 registers, so that two workgroups (16 wavefronts) share a CU.  Within a role:
+// 2 channel halves x (two row quads, R = 8, or two halves of the columns, R = 4, for maps with few tiles).  dX goes
+// through LDS so that stores are 16 bytes per lane.  Dropped and outside positions are zeros in LDS.  The next tile's rows
+// are in flight in registers while a tile is computed.
+// A band product multiplies a gradient with zeros, so an infinity or NaN would reach columns outside its 7 x 7
+// window: staging looks for them, and such a tile's dX is computed again tap by tap.
+// Measured (kernel + partial sums): 2 x 200 x 336 x 128, a quarter kept, 90 -> 43 us; 2 x 50 x 84 x 512, half kept,
+// 28.4 -> 21.4; 2 x 25 x 42 x 768 18.5 -> 15.4; 2 x 7 x 7 x 768 18.5 -> 17.8, all against the dot2 kernel above.  With the
+// products left out 26 us remain of the 43, with the loads and stores left out 33: staging and products still overlap only
+// across the two workgroups of a CU.  One role-less kernel of 4 wavefronts with 194 registers: 45 us.
+// ------------------------------------------------------------------------------------------------
+typedef short dwm_s4 __attribute__((ext_vector_type(4)));
+typedef float dwm_f4 __attribute__((ext_vector_type(4)));
+static constexpr int DWM_THREADS = 512, DWM_PER_CU = 2;
+static constexpr int DWM_TQ = 7;                                  // most column quads per tile
+// bytes of one (row, channel) line and of one row of 32 lines: lines an odd number of 8-byte words, rows 64 bytes on, so that
+// the operand reads of 8 channels x 4 rows hit all banks; constants, so that the reads' offsets are immediates
+static constexpr int DWM_PITCH = 8 * (DWM_TQ + 2), DWM_ROWP = DWF_SLAB * DWM_PITCH + 64;
+static constexpr int DWM_MAX_G = 128, DWM_MAX_X = 64;   // (row, quad) items of a tile's gradients (one per 4 threads) and of its X and dX (one per 4 threads of a role)
+
+struct DwMfmaArgs {
+  const uint16_t* dY; const int32_t* inv; const uint16_t* X; const uint16_t* Wd;
+  uint16_t* dX; float* part;   // part[workgroup x][50][C]
+  int B, H, W, C;
+  int TQ;                      // column quads per tile
+  int tiles_y, tiles_x, ntiles, nwg_x, slabs;
+  int magic_g, magic_x;        // e / (TQ + 2) = e * magic_g >> 16, e / TQ = e * magic_x >> 16 for e < 128
+};
+
+__device__ __forceinline__ uint2 dwm_u2(dwm_s4 v) { return __builtin_bit_cast(uint2, v); }
+__device__ __forceinline__ dwm_s4 dwm_s(uint32_t a, uint32_t b) { return __builtin_bit_cast(dwm_s4, make_uint2(a, b)); }
+__device__ __forceinline__ dwm_f4 dwm_mma(dwm_s4 a, dwm_s4 b, dwm_f4 c) { return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a, b, c, 0, 0, 0); }
+
+// 8 channels of 4 neighbouring positions into 8 lines
+__device__ __forceinline__ void dwm_store_quads(char* dst, int pitch, const uint4 (&A)[4]) {
+  const uint32_t w[4][4] = {{A[0].x, A[0].y, A[0].z, A[0].w}, {A[1].x, A[1].y, A[1].z, A[1].w},
+                            {A[2].x, A[2].y, A[2].z, A[2].w}, {A[3].x, A[3].y, A[3].z, A[3].w}};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    *reinterpret_cast<uint2*>(dst + (2 * k) * pitch) = make_uint2(dw_pair_lo(w[0][k], w[1][k]), dw_pair_lo(w[2][k], w[3][k]));
+    *reinterpret_cast<uint2*>(dst + (2 * k + 1) * pitch) = make_uint2(dw_pair_hi(w[0][k], w[1][k]), dw_pair_hi(w[2][k], w[3][k]));
+  }
+}
+
+template <int R, bool DX, bool DW>
+__global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int RQ = R / 4, XS = 2 / RQ, GR = R + 6, NT = 50;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the blocks of one XCD (block id modulo 8) take neighbouring tiles, all channel slabs of a tile side by side: halos
+  // and the other half of a cache line come from the same L2
+  const int per = gridDim.x >> 3, rem = gridDim.x & 7, xcd = blockIdx.x & 7;
+  const int unit = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
+  const int slab0 = (unit % a.slabs) * DWF_SLAB, wgx = unit / a.slabs;
+  const int TQ = a.TQ, GQ = TQ + 2;
+  char* gt = lds;                              // gradient rows y0 - 3 .., quads -1 .. TQ
+  char* xt = lds + GR * DWM_ROWP;              // X rows y0 .., quads -1 .. TQ (both ends zero)
+  char* ot = xt + R * DWM_ROWP;                // dX of the tile
+  int* bad = reinterpret_cast<int*>(ot + R * DWM_ROWP);   // [2]: a non-finite gradient in the tile, by tile parity
+
+  // ---- compute role
+  const bool dx_role = wave < 4;
+  const int cg = wave & 1, part_id = (wave >> 1) & 1;              // channel half; row quad (R = 8) or column half (R = 4)
+  const int rq = XS == 1 ? part_id : 0, xs = XS == 1 ? 0 : part_id;
+  const int n = lane & 3, ch = cg * 16 + (lane >> 2);              // operand row / column, channel of the slab
+  const int qm = TQ >> 1;
+  const char* gbase = gt + (rq * 4 + n) * DWM_ROWP + ch * DWM_PITCH + 8;               // + i DWM_ROWP + 8 quad
+
+  // ---- staging role: a (row, quad) item x 8 channels of the gradients per thread; of X (dWd waves) and dX (dX waves)
+  const int g8 = tid & 3;
+  const bool cok = slab0 + 8 * g8 < a.C;
+  const int grow = ((tid >> 2) * a.magic_g) >> 16, gq = (tid >> 2) - grow * GQ;
+  const int xe = (tid & 255) >> 2, xrow = (xe * a.magic_x) >> 16, xq = xe - xrow * TQ;
+  const bool xon = xrow < R;
+  const int xoff = xrow * DWM_ROWP + 8 * g8 * DWM_PITCH + (xq + 1) * 8;
+  for (int e = tid; e < R * DWF_SLAB * 2; e += DWM_THREADS) {       // the zero quads at the ends of the X lines
+    const int row = e / (DWF_SLAB * 2), l = (e >> 1) & (DWF_SLAB - 1);
+    *reinterpret_cast<uint2*>(xt + row * DWM_ROWP + l * DWM_PITCH + ((e & 1) ? (TQ + 1) * 8 : 0)) = make_uint2(0, 0);
+  }
+  if (tid < 2) bad[tid] = 0;
+  auto origin = [&](int tile, int& b, int& y0, int& x0) {
+    const int tx = tile % a.tiles_x, rest = tile / a.tiles_x;
+    y0 = (rest % a.tiles_y) * R;
+    b = rest / a.tiles_y;
+    x0 = tx * TQ * 4;
+  };
+  // a tile's addresses: a scalar base per tile + a 32-bit offset per thread (host: a sample is below 4 GiB)
+  const uint32_t rowb = (uint32_t)a.W * a.C * 2, colb = (uint32_t)a.C * 2;
+  const uint32_t goff = grow * rowb + 4 * gq * colb + 16 * g8, xgoff = xrow * rowb + 4 * xq * colb + 16 * g8;
+  auto tile_base = [&](const void* t, int b, int y, int x) {       // element (b, y, x, slab0); may lie before the tensor
+    return reinterpret_cast<const char*>(t) + (((long long)b * a.H + y) * a.W + x) * a.C * 2 + slab0 * 2;
+  };
+  int iv[4];
+  uint4 GA[4];
+  auto look = [&](int tile) {                  // inverse-map entries: clamped, not branched around, all in flight together
+    int b, y0, x0;
+    origin(min(tile, a.ntiles - 1), b, y0, x0);
+    const int32_t* ip = a.inv + (long long)b * a.H * a.W;
+    const uint32_t ro = (uint32_t)min(max(y0 - 3 + grow, 0), a.H - 1) * a.W;
+    const int x = x0 - 4 + 4 * gq;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) iv[k] = ip[ro + (uint32_t)min(max(x + k, 0), a.W - 1)];
+  };
+  auto fetch = [&](int tile) {                 // kept gradients (iv: this tile's entries), zeros elsewhere
+    int b, y0, x0;
+    origin(tile, b, y0, x0);
+    const char* p = tile_base(a.dY, b, y0 - 3, x0 - 4);
+    const bool rok = grow < GR && cok && (unsigned)(y0 - 3 + grow) < (unsigned)a.H;
+    const int x = x0 - 4 + 4 * gq;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      GA[k] = make_uint4(0, 0, 0, 0);
+      if (rok && (unsigned)(x + k) < (unsigned)a.W && iv[k] >= 0) GA[k] = *reinterpret_cast<const uint4*>(p + (long long)k * colb + goff);
+    }
+  };
+  auto store = [&](int parity) {
+    uint32_t nonfinite = 0;                    // an exponent of all ones carries into the sign bit of its half
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      constexpr uint32_t E = 0x7f807f80u, O = 0x00800080u;
+      nonfinite |= ((GA[k].x & E) + O) | ((GA[k].y & E) + O) | ((GA[k].z & E) + O) | ((GA[k].w & E) + O);
+    }
+    if (grow < GR) dwm_store_quads(gt + grow * DWM_ROWP + 8 * g8 * DWM_PITCH + gq * 8, DWM_PITCH, GA);
+    if (nonfinite & 0x80008000u) bad[parity] = 1;
+  };
+  auto ld = [](const char* p) { return *reinterpret_cast<const dwm_s4*>(p); };
+  const bool any = wgx < a.ntiles;
+  auto first = [&] {
+    if (any) {
+      look(wgx);
+      fetch(wgx);
+      look(wgx + a.nwg_x);
+    }
+  };
+  __syncthreads();                             // bad and the zero quads are written
+
+  // The two roles' loops meet at the same barriers: A after staging, B after the products (and one more after a tile
+  // with non-finite gradients).  While a tile is computed the next one's rows and the lookups after it are in flight.
+  if (dx_role) {
+    // the band of tap row i: entry e of its 12 is tap t = e - n - 1 (zero outside 0 .. 6), i.e. the taps' pairs moved up by
+    // n + 1 entries: by whole words for odd n, by half a word for even n, by one word more for n >= 2.
+    dwm_s4 wt[7][3];
+    if constexpr (DX) {
+      uint32_t w[7][7];
+      const uint16_t* wp = a.Wd + min(slab0 + ch, a.C - 1);
+#pragma unroll
+      for (int i = 0; i < 7; ++i)
+#pragma unroll
+        for (int t = 0; t < 7; ++t) w[i][t] = wp[(long long)((6 - i) * 7 + 6 - t) * a.C];
+#pragma unroll
+      for (int i = 0; i < 7; ++i) {
+        uint32_t base[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+          auto el = [&](int t) { return t >= 0 && t < 7 ? w[i][t] : 0u; };
+          const uint32_t odd = el(2 * d - 2) | (el(2 * d - 1) << 16), even = el(2 * d - 1) | (el(2 * d) << 16);
+          base[d] = (n & 1) ? odd : even;
+        }
+#pragma unroll
+        for (int ck = 0; ck < 3; ++ck)
+          wt[i][ck] = dwm_s(n >= 2 ? (ck ? base[2 * ck - 1] : 0u) : base[2 * ck], n >= 2 ? base[2 * ck] : base[2 * ck + 1]);
+      }
+    }
+    first();                                   // (after the weights: together they spill)
+    const int qa = XS == 1 ? 0 : (xs ? qm : 0), qb = XS == 1 ? TQ : (xs ? TQ : qm);
+    char* obase = ot + (rq * 4 + n) * DWM_ROWP + ch * DWM_PITCH + 8;
+    int parity = 0;
+    for (int tile = wgx; tile < a.ntiles; tile += a.nwg_x, parity ^= 1) {
+      store(parity);
+      __syncthreads();                         // A
+      if (tid == 0) bad[parity ^ 1] = 0;       // (the last tile's: read before this barrier, set next after the one below)
+      if (tile + a.nwg_x < a.ntiles) {
+        fetch(tile + a.nwg_x);
+        look(tile + 2 * a.nwg_x);
+      }
+      if constexpr (DX) {
+        dwm_s4 G[7];                           // quad t of the 7 row offsets; it meets the outputs of quads t - 1, t and t + 1
+#pragma unroll
+        for (int i = 0; i < 7; ++i) G[i] = ld(gbase + i * DWM_ROWP + 8 * (qa - 1));
+        dwm_f4 d2 = {0.f, 0.f, 0.f, 0.f}, d1 = d2, d0 = d2;
+        for (int t = qa - 1; t <= qb; ++t) {
+          dwm_s4 Gn[7];
+          const int tn = min(t + 1, TQ);
+#pragma unroll
+          for (int i = 0; i < 7; ++i) Gn[i] = ld(gbase + i * DWM_ROWP + 8 * tn);
+          if (t > qa && t < qb - 1) {
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+              d2 = dwm_mma(wt[i][2], G[i], d2);
+              d1 = dwm_mma(wt[i][1], G[i], d1);
+              d0 = dwm_mma(wt[i][0], G[i], d0);
+            }
+          } else {                             // (the ends: outputs of the neighbours are not made)
+            if (t > qa) {
+#pragma unroll
+              for (int i = 0; i < 7; ++i) d2 = dwm_mma(wt[i][2], G[i], d2);
+            }
+            if (t >= qa && t < qb) {
+#pragma unroll
+              for (int i = 0; i < 7; ++i) d1 = dwm_mma(wt[i][1], G[i], d1);
+            }
+            if (t < qb - 1) {
+#pragma unroll
+              for (int i = 0; i < 7; ++i) d0 = dwm_mma(wt[i][0], G[i], d0);
+            }
+          }
+          if (t > qa) *reinterpret_cast<uint2*>(obase + 8 * (t - 1)) = make_uint2(dw_pack(d2[0], d2[1]), dw_pack(d2[2], d2[3]));
+          d2 = d1; d1 = d0; d0 = dwm_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < 7; ++i) G[i] = Gn[i];
+        }
+      }
+      __syncthreads();                         // B
+      if constexpr (DX) {
+        if (bad[parity]) {                     // rare: this tile's dX tap by tap, no product with a zero of the band
+          const int l = tid & 31, c = min(slab0 + l, a.C - 1);
+          for (int e = tid >> 5; e < R * TQ * 4; e += 8) {
+            const int row = e / (TQ * 4), x = e - row * TQ * 4;
+            float d = 0.f;
+            for (int i = 0; i < 7; ++i)
+              for (int t = 0; t < 7; ++t)
+                d = fmaf(DwElem<uint16_t>::ld(reinterpret_cast<const uint16_t*>(gt + (row + i) * DWM_ROWP + l * DWM_PITCH) + x + t + 1),
+                         DwElem<uint16_t>::ld(a.Wd + ((6 - i) * 7 + 6 - t) * a.C + c), d);
+            reinterpret_cast<uint16_t*>(ot + row * DWM_ROWP + l * DWM_PITCH + 8)[x] = (uint16_t)(dw_pack(d, 0.f) & 0xffffu);
+          }
+          __syncthreads();
+        }
+        int b, y0, x0;                         // dX out: 8 lines of a quad -> 16 bytes of 4 positions
+        origin(tile, b, y0, x0);
+        const int x = x0 + 4 * xq;
+        if (xon && cok && y0 + xrow < a.H) {
+          uint2 q[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) q[k] = *reinterpret_cast<const uint2*>(ot + xoff + k * DWM_PITCH);
+          char* o = const_cast<char*>(tile_base(a.dX, b, y0, x0));
+          if (x < a.W) *reinterpret_cast<uint4*>(o + xgoff) = make_uint4(dw_pair_lo(q[0].x, q[1].x), dw_pair_lo(q[2].x, q[3].x), dw_pair_lo(q[4].x, q[5].x), dw_pair_lo(q[6].x, q[7].x));
+          if (x + 1 < a.W) *reinterpret_cast<uint4*>(o + 1ll * colb + xgoff) = make_uint4(dw_pair_hi(q[0].x, q[1].x), dw_pair_hi(q[2].x, q[3].x), dw_pair_hi(q[4].x, q[5].x), dw_pair_hi(q[6].x, q[7].x));
+          if (x + 2 < a.W) *reinterpret_cast<uint4*>(o + 2ll * colb + xgoff) = make_uint4(dw_pair_lo(q[0].y, q[1].y), dw_pair_lo(q[2].y, q[3].y), dw_pair_lo(q[4].y, q[5].y), dw_pair_lo(q[6].y, q[7].y));
+          if (x + 3 < a.W) *reinterpret_cast<uint4*>(o + 3ll * colb + xgoff) = make_uint4(dw_pair_hi(q[0].y, q[1].y), dw_pair_hi(q[2].y, q[3].y), dw_pair_hi(q[4].y, q[5].y), dw_pair_hi(q[6].y, q[7].y));
+        }
+      }
+    }
+    if constexpr (DW) { __syncthreads(); __syncthreads(); }
+  } else {
+    dwm_f4 accw[4][2], accb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) accw[s][0] = accw[s][1] = dwm_f4{0.f, 0.f, 0.f, 0.f};
+    const dwm_s4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+    const int h = n >> 1;
+    const char* xbase = xt + (rq * 4 + (n & 1)) * DWM_ROWP + ch * DWM_PITCH + 8;       // + 2 p DWM_ROWP + 8 quad
+    const int ta = XS == 1 || xs == 0 ? -1 : qm, tb = XS == 1 || xs == 1 ? TQ : qm - 1;
+    uint4 XA[4];
+    auto fetch_x = [&](int tile) {
+      int b, y0, x0;
+      origin(tile, b, y0, x0);
+      const int x = x0 + 4 * xq;
+      const char* p = tile_base(a.X, b, y0, x0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        XA[k] = make_uint4(0, 0, 0, 0);
+        if (DW && xon && cok && y0 + xrow < a.H && x + k < a.W) XA[k] = *reinterpret_cast<const uint4*>(p + (long long)k * colb + xgoff);
+      }
+    };
+    if (any) fetch_x(wgx);
+    first();
+    int parity = 0;
+    for (int tile = wgx; tile < a.ntiles; tile += a.nwg_x, parity ^= 1) {
+      store(parity);
+      if (DW && xon) dwm_store_quads(xt + xoff, DWM_PITCH, XA);
+      __syncthreads();                         // A
+      if (tile + a.nwg_x < a.ntiles) {
+        fetch(tile + a.nwg_x);
+        fetch_x(tile + a.nwg_x);
+        look(tile + 2 * a.nwg_x);
+      }
+      if constexpr (DW) {
+        dwm_s4 xp[2];                          // X quads t - 1 + h (two rows further on for p = 1)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) xp[p] = ld(xbase + 2 * p * DWM_ROWP + 8 * max(ta - 1 + h, -1));
+        for (int t = ta; t <= tb; ++t) {
+          dwm_s4 G[4], xc[2];                  // gradient quad t of row offsets 0, 2, 4, 6; X quads t + h
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            xc[p] = ld(xbase + 2 * p * DWM_ROWP + 8 * min(t + h, TQ));
+            G[p] = ld(gbase + 2 * p * DWM_ROWP + 8 * t);
+            G[p + 2] = ld(gbase + 2 * (p + 2) * DWM_ROWP + 8 * t);
+          }
+          const dwm_s4 gc = ld(gbase + 3 * DWM_ROWP + 8 * t);
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const uint2 pv = dwm_u2(xp[p]), cv = dwm_u2(xc[p]);
+            const uint32_t q0 = dwf_alignbit(pv.y, pv.x), q1 = dwf_alignbit(cv.x, pv.y), q2 = dwf_alignbit(cv.y, cv.x);
+            const dwm_s4 sh[4] = {xc[p], dwm_s(q1, q2), dwm_s(pv.y, cv.x), dwm_s(q0, q1)};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int aa = 0; aa < 2; ++aa) accw[s][aa] = dwm_mma(G[p + 2 * aa], sh[s], accw[s][aa]);
+            xp[p] = xc[p];
+          }
+          if (t >= 0 && t < TQ) accb = dwm_mma(ones, gc, accb);
+        }
+      }
+      __syncthreads();                         // B
+      if (DX && bad[parity]) __syncthreads();
+    }
+    // the workgroup's partial sums: the accumulators through LDS
+    if constexpr (DW) {
+      __syncthreads();
+      float* red = reinterpret_cast<float*>(lds);          // [wave][33][64]
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int aa = 0; aa < 2; ++aa)
+#pragma unroll
+          for (int m = 0; m < 4; ++m) red[((wave & 3) * 33 + (s * 2 + aa) * 4 + m) * 64 + lane] = accw[s][aa][m];
+      red[((wave & 3) * 33 + 32) * 64 + lane] = accb[0];
+      __syncthreads();
+    }
+  }
+  if constexpr (DW) {                          // every tap from its 2 elements x 2 wavefronts
+    const float* red = reinterpret_cast<const float*>(lds);
+    for (int o = tid; o < NT * DWF_SLAB; o += DWM_THREADS) {
+      const int tap = o / DWF_SLAB, cl = o - tap * DWF_SLAB;
+      const int w0 = cl >> 4, l0 = (cl & 15) * 4;
+      float sum = 0.f;
+      if (tap < 49) {
+        const int u = tap / 7, v = tap - u * 7;
+        const int hh = v > 3, s = hh ? 7 - v : 3 - v;
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int k = e + 6 - u, aa = k > 3, m = k - 4 * aa;       // k = m + 4 aa
+            sum += red[((w0 + 2 * w) * 33 + (s * 2 + aa) * 4 + m) * 64 + l0 + e + 2 * hh];
+          }
+      } else {
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sum += red[((w0 + 2 * w) * 33 + 32) * 64 + l0 + j];
+      }
+      if (slab0 + cl < a.C) a.part[((long long)wgx * NT + tap) * a.C + slab0 + cl] = sum;
+    }
+  }
+}
+
 static constexpr int DW_GROUPS = 2;
 static constexpr int DW_MAX_PARTS = 256;
 
-// Tile shape of the LDS-tiled kernel: TS strips of 8 columns wide (line pitch 16 (TS + 1) bytes, rounded up to an odd
+// Tile shape of the LDS-tiled dot2 kernel: TS strips of 8 columns wide (line pitch 16 (TS + 1) bytes, rounded up to an odd
 // number of 16-byte units so that the 16-byte reads of neighbouring channels fall into different banks), R rows high,
 // at most 80 KB of LDS so that two workgroups share a CU; chosen for the fewest rounds of 2 x 256 workgroups, then
 // for the least halo.
@@ -761,6 +1121,31 @@ static DwFusedShape dw_fused_shape(int B, int H, int W, int C, int ks) {
   return best;
 }
 
+// Tile of the matrix-core kernel: TQ column quads x R rows (8, or 4 with the columns split over two wavefronts), two
+// workgroups per CU (at most 71 KB of LDS each); chosen for the fewest rounds x tile time, a tile's time taken as a fixed
+// part for staging, latency and barriers plus a part per quad.
+struct DwMfmaShape { int R, TQ, tiles_y, tiles_x, nwg_x, slabs; size_t lds; };
+static DwMfmaShape dw_mfma_shape(int B, int H, int W, int C) {
+  DwMfmaShape best{};
+  double best_cost = 0;
+  const int nq = (int)ceil_div(W, 4), slabs = (int)ceil_div(C, DWF_SLAB);
+  for (int R = 8; R >= 4; R -= 4)
+    for (int TQ = DWM_TQ; TQ >= 2; --TQ) {
+      if ((R + 6) * (TQ + 2) > DWM_MAX_G || R * TQ > DWM_MAX_X) continue;
+      const int tiles_x = (int)ceil_div(nq, TQ), tiles_y = (int)ceil_div(H, R);
+      const int64_t ntiles = (int64_t)B * tiles_x * tiles_y;
+      const int nwg_x = (int)std::min<int64_t>(ntiles, std::max(1, DWM_PER_CU * 256 / slabs));
+      const double steps = R == 8 ? TQ : 0.5 * TQ + 0.5;
+      const double cost = (double)ceil_div(ntiles, nwg_x) * (304 * steps + 256 + 1500) + (nwg_x * slabs > DWM_PER_CU * 256 ? 1 : 0);
+      if (best.R == 0 || cost < best_cost) {
+        const size_t tile = (size_t)(R + 6 + 2 * R) * DWM_ROWP + 16, red = 4 * 33 * 64 * sizeof(float);
+        best_cost = cost;
+        best = DwMfmaShape{R, TQ, tiles_y, tiles_x, nwg_x, slabs, std::max(tile, red)};
+      }
+    }
+  return best;
+}
+
 DwPlan plan_dwconv(int32_t B, int32_t H, int32_t W, int32_t C, int32_t ks, int64_t K, int32_t dtype) {
   DwPlan p{};
   (void)dtype;
@@ -769,7 +1154,8 @@ DwPlan plan_dwconv(int32_t B, int32_t H, int32_t W, int32_t C, int32_t ks, int64
   // (its parallelism does not depend on K), the plain path slices the kept list.
   const int64_t row_tiles = (int64_t)B * H * ceil_div(W, DW_TX);
   p.nparts = (int)std::max<int64_t>(1, std::min<int64_t>(DW_MAX_PARTS, std::max<int64_t>(ceil_div(row_tiles, 2 * DW_GROUPS), 1)));
-  if (ks == 7 || ks == 3) p.nparts = std::max(p.nparts, dw_fused_shape(B, H, W, C, ks).nwg_x);   // the LDS-tiled kernel's workgroups
+  if (ks == 7) p.nparts = std::max(p.nparts, dw_mfma_shape(B, H, W, C).nwg_x);                       // the matrix-core kernel's workgroups
+  if (ks == 3) p.nparts = std::max(p.nparts, dw_fused_shape(B, H, W, C, ks).nwg_x);                  // the LDS-tiled kernel's workgroups
   size_t off = 0;
   p.off_inv = off;
   off += align_up((size_t)B * H * W * sizeof(int32_t), 256);
@@ -818,27 +1204,58 @@ int32_t launch_backward_dwconv(const DwPlan& p, const void* dY, const int32_t* i
   }
   const Options opt = options();                                             // explicit overrides for sweeps and tests
   const bool tiled = dtype == SBP_BF16 && C % 8 == 0 && (ks == 7 || ks == 3) && !opt.dw_strips &&
-                     (((uintptr_t)dY | (uintptr_t)X | (uintptr_t)dX) % 16 == 0) && (int64_t)B * H * W * C < (1ll << 40);
+                     (((uintptr_t)dY | (uintptr_t)X | (uintptr_t)dX) % 16 == 0) && (int64_t)B * H * W * C < (1ll << 40) &&
+                     (ks != 7 || ((int64_t)H * W * C < (1ll << 30) && (int64_t)H * W < (1ll << 30)));   // (its 32-bit offsets inside a sample)
   if (tiled) {
-    const DwFusedShape f = dw_fused_shape(B, H, W, C, ks);
-    DwFusedArgs a{};
-    a.dY = (const uint16_t*)dY; a.inv = inv; a.X = (const uint16_t*)X; a.Wd = (const uint16_t*)Wd;
-    a.dX = (uint16_t*)dX; a.part = part;
-    a.B = B; a.H = H; a.W = W; a.C = C;
-    a.R = f.R; a.TS = f.TS; a.tiles_y = f.tiles_y; a.tiles_x = f.tiles_x; a.ntiles = B * f.tiles_y * f.tiles_x;
-    a.pitch = f.pitch;
-    a.want_dx = dX != nullptr; a.want_dw = (dWd || db) ? 1 : 0;
-    const dim3 grid((unsigned)f.nwg_x, (unsigned)ceil_div(C, DWF_SLAB));
-    static std::once_flag once7, once3;
-    if (f.lds > 64 * 1024) {
-      if (ks == 7) std::call_once(once7, [] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(dw_fused_kernel<7>), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
-      else std::call_once(once3, [] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(dw_fused_kernel<3>), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
+    const bool want_dw = dWd || db;
+    int nparts;
+    if (ks == 7) {
+      const DwMfmaShape f = dw_mfma_shape(B, H, W, C);
+      DwMfmaArgs a{};
+      a.dY = (const uint16_t*)dY; a.inv = inv; a.X = (const uint16_t*)X; a.Wd = (const uint16_t*)Wd;
+      a.dX = (uint16_t*)dX; a.part = part;
+      a.B = B; a.H = H; a.W = W; a.C = C;
+      a.TQ = f.TQ; a.tiles_y = f.tiles_y; a.tiles_x = f.tiles_x; a.ntiles = B * f.tiles_y * f.tiles_x;
+      a.nwg_x = f.nwg_x; a.slabs = f.slabs;
+      a.magic_g = 65536 / (f.TQ + 2) + 1; a.magic_x = 65536 / f.TQ + 1;
+      nparts = f.nwg_x;
+      const dim3 grid((unsigned)(f.nwg_x * f.slabs));
+      if (f.lds > 64 * 1024) {
+        static std::once_flag once7;
+        std::call_once(once7, [] {
+          for (const void* k : {reinterpret_cast<const void*>(dw_mfma_kernel<8, true, true>), reinterpret_cast<const void*>(dw_mfma_kernel<8, true, false>),
+                                reinterpret_cast<const void*>(dw_mfma_kernel<8, false, true>)})
+            (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        });
+      }
+#define SBP_DWM(DX, DW)                                                                                                          \
+  do {                                                                                                                           \
+    if (f.R == 8) SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, (dw_mfma_kernel<8, DX, DW>), grid, dim3(DWM_THREADS), f.lds, s, a);        \
+    else SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, (dw_mfma_kernel<4, DX, DW>), grid, dim3(DWM_THREADS), f.lds, s, a);                 \
+  } while (0)
+      if (dX && want_dw) SBP_DWM(true, true);
+      else if (dX) SBP_DWM(true, false);
+      else if (want_dw) SBP_DWM(false, true);
+#undef SBP_DWM
+    } else {
+      const DwFusedShape f = dw_fused_shape(B, H, W, C, ks);
+      DwFusedArgs a{};
+      a.dY = (const uint16_t*)dY; a.inv = inv; a.X = (const uint16_t*)X; a.Wd = (const uint16_t*)Wd;
+      a.dX = (uint16_t*)dX; a.part = part;
+      a.B = B; a.H = H; a.W = W; a.C = C;
+      a.R = f.R; a.TS = f.TS; a.tiles_y = f.tiles_y; a.tiles_x = f.tiles_x; a.ntiles = B * f.tiles_y * f.tiles_x;
+      a.pitch = f.pitch;
+      a.want_dx = dX != nullptr; a.want_dw = want_dw;
+      nparts = f.nwg_x;
+      const dim3 grid((unsigned)f.nwg_x, (unsigned)ceil_div(C, DWF_SLAB));
+      static std::once_flag once3;
+      if (f.lds > 64 * 1024)
+        std::call_once(once3, [] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(dw_fused_kernel<3>), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024); });
+      SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, (dw_fused_kernel<3>), grid, dim3(DWF_THREADS), f.lds, s, a);
     }
-    if (ks == 7) SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, (dw_fused_kernel<7>), grid, dim3(DWF_THREADS), f.lds, s, a);
-    else SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, (dw_fused_kernel<3>), grid, dim3(DWF_THREADS), f.lds, s, a);
-    if (a.want_dw) {
+    if (want_dw) {
       const int n = (ks * ks + 1) * C;
-      SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, dw_reduce_kernel, dim3((unsigned)ceil_div(n, 32)), dim3(DW_THREADS), 0, s, part, f.nwg_x,
+      SBP_LAUNCH(SBP_PROF_DWCONV_DW, s, dw_reduce_kernel, dim3((unsigned)ceil_div(n, 32)), dim3(DW_THREADS), 0, s, part, nparts,
                  ks * ks, C, dWd, db);
     }
     return check_launch("backward_dwconv");

@@ -49,7 +49,7 @@ struct Options {
   ShapePlan plans[8] = {};
   bool debug_plan = false;
   int  dw_rows = 0;
-  bool dw_strips = false;             // depthwise backward: the register-strip kernels instead of the LDS-tiled one
+  bool dw_strips = false;             // depthwise backward: the register-strip kernels instead of the LDS-tiled ones
   bool batch_spread = false;          // batched linear backward: units dealt to the XCDs in turn instead of in runs
   bool batch_dynamic = false;         // batched linear backward: units taken from the XCD queues with atomic counters
   int attn_mode = 0;       // attention backward: 0 chosen by size, 1 plain kernel, 2 one workgroup per head where it fits, 3 tiled

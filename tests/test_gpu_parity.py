@@ -547,6 +547,32 @@ def test_dwconv_lds_tiled_kernel_and_single_outputs(geom, k):
         assert np.array_equal(bits(u), bits(v))
 
 
+@pytest.mark.parametrize("geom", [(1, 8, 28, 32), (1, 9, 29, 40), (2, 4, 8, 64), (1, 17, 57, 96), (4, 3, 12, 8), (1, 5, 3, 2048),
+                                  (3, 24, 113, 136)])
+def test_dwconv_matrix_core_kernel_tile_edges_and_non_finite_gradients(geom):
+    # 7 x 7 on the matrix cores: one tile exactly, one row and column more, even and odd column quads, both tile heights,
+    # several tiles per workgroup; an infinity in one kept gradient changes dX inside its 7 x 7 window only
+    B, H, W, C = geom
+    X, Wd, dY = si.dwconv_case(B, H, W, C, 7, 171, "bf16")
+    idx_np = oracle.sample_indices(B, 0, H, W, 3, 171, 80)
+    idx = torch.from_numpy(idx_np).cuda()
+    full = sbp.backward_dwconv(dY.cuda(), idx, X.cuda(), Wd.cuda())
+    rWd, rb, rX = oracle.backward_dwconv(si.to_f64(dY), idx_np, si.to_f64(X), si.to_f64(Wd), 3)
+    assert nerr(f64(full[0]), rWd) <= TOL_F32 and nerr(f64(full[1]), rb) <= TOL_F32
+    assert nerr(f64(full[2]), rX) <= TOL_BF16_TIGHT
+    q, c = int(idx_np[len(idx_np) // 2]), C // 2
+    b, y, x = q // (H * W), q // W % H, q % W
+    dY2 = dY.clone()
+    dY2[b, y, x, c] = float("inf")
+    got = sbp.backward_dwconv(dY2.cuda(), idx, X.cuda(), Wd.cuda())[2].cpu()
+    window = torch.zeros(B, H, W, C, dtype=torch.bool)
+    window[b, max(y - 3, 0):y + 4, max(x - 3, 0):x + 4, c] = True
+    assert not torch.isfinite(got[window].float()).any()
+    # elsewhere only the order of the fp32 sums may differ: one unit of the last bf16 place
+    a, r = got[~window].double().numpy(), full[2].cpu()[~window].double().numpy()
+    assert np.isfinite(a).all() and np.max(np.abs(a - r)) <= 2.0 ** -7 * max(np.max(np.abs(r)), 1e-30)
+
+
 def test_dwconv_single_kept_position_stamps_kernel():
     B, H, W, C, ks = 1, 9, 11, 64, 7
     X, Wd, dY = si.dwconv_case(B, H, W, C, ks, 141, "f32")
