@@ -523,6 +523,7 @@ struct BigChoice {
   int splits, rps, n_big, rows_small, dx_bm;
   int seg_order[3];
   double fill;      // work / (CUs x finish time) of the simulated schedule
+  double cost_ns;   // its time with the reduction that follows
 };
 
 static int64_t congruent_below_host(int64_t y, int64_t t) { return (t - y + 7) >> 3; }
@@ -570,7 +571,7 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
   const int64_t slice_rows = db_slice_rows_for(K, true);
   const int64_t n_db = ceil_div(Cout, 256) * ceil_div(K, slice_rows);
   const int64_t l_db = kNsFixedHelper + slice_rows * 512 / kHelperBytesPerNs;
-  BigChoice best{M, K, Cin, Cout, 0, 0, 0, 0, 256, {0, 1, 2}, 0.0};
+  BigChoice best{M, K, Cin, Cout, 0, 0, 0, 0, 256, {0, 1, 2}, 0.0, 0.0};
   double best_cost = 0;
   auto l_dw = [](int64_t rows) { return kNsFixedDw + kNsStageDw * ceil_div(rows, big::KB); };
   static const int small_rows[] = {0, 256, 384, 512, 768, 1024, 1536};
@@ -600,7 +601,7 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
           // the reduction kernel that follows reads every split's fp32 copy of dW and writes dW
           const double cost = (double)end + 3000.0 + (double)(splits + 1) * Cout * Cin * 4.0 / kReduceBytesPerNs;
           if (best.splits == 0 || cost < best_cost) {
-            best_cost = cost;
+            best_cost = best.cost_ns = cost;
             best.splits = (int)splits; best.rps = (int)A; best.n_big = (int)nb_real; best.rows_small = (int)(ns_real ? a : 0);
             best.dx_bm = bm;
             for (int q = 0; q < 3; ++q) best.seg_order[q] = order[q];
@@ -621,7 +622,28 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
   return best;
 }
 
+// Time of one layer in the 128-tile engine with its reduction, a line through 36 shapes of 1500 to 33600 rows and 256 to 2560
+// channels (12 us + 1.55 us per GFLOP; within 15 % from 4 to 40 GFLOP): it has no large fixed parts, and is ahead of the large
+// tiles where these are few or short.  The simulated cost of the large tiles is about 1.1 times what they then take.
+// Measured, 128 tiles / large tiles: 20.6 / 25.8 us (1500 rows, 1024 x 1024), 26.5 / 33.9 (16800, 512 -> 256), 41.0 / 49.0
+// (33600, 512 -> 256), 26.3 / 29.7 (8400, 1024 -> 256), 28.2 / 28.6 (4200, 768 x 768); 37.2 / 32.9 (6336, 768 x 768),
+// 41.1 / 37.2 (4200, 512 -> 2048), 41.0 / 35.6 (8400, 768 x 768), 67.6 / 62.6 (33600, 1024 -> 256).
+static bool general_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns) {
+  return 12000.0 + 1550.0 * (4e-9 * (double)K * Cin * Cout) < 0.9 * big_cost_ns;
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general);
+
+// X_k in row groups is read by the large-tile engine only (the other one first copies it back to rows), and a layer whose
+// 128-tile splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by time.
 LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  if (flags & SBP_FLAG_XK_KMAJOR) return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
+  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true);
+  if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
+  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general) {
   LinearPlan p{};
   p.mfma = dtype == SBP_BF16 && Cin % 8 == 0 && Cout % 8 == 0;
   p.bm_w = p.bn_w = 128;
@@ -632,9 +654,12 @@ LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t 
   if (K > 0 && p.mfma) {
     const bool fits = Cout % big::KB == 0 && (uint64_t)M * (uint64_t)std::max(Cin, Cout) * 2u < (1ull << 32) &&
                       ceil_div(K, kBigMaxRowsPerSplit) <= 64;
-    // it pays where whole 256-wide tiles exist and the simulated schedule keeps the CUs reasonably busy
-    const bool pays = opt.tile_mode == 0 && Cin >= big::BT && Cout >= big::BT && K >= 1024 &&
-                      choose_big(M, K, Cin, Cout).fill >= 0.45;
+    // it pays where whole 256-wide tiles exist, the simulated schedule keeps the CUs reasonably busy and the 128 tiles are not ahead
+    bool pays = opt.tile_mode == 0 && Cin >= big::BT && Cout >= big::BT && K >= 1024;
+    if (pays) {
+      const BigChoice c = choose_big(M, K, Cin, Cout);
+      pays = c.fill >= 0.45 && !(may_prefer_general && general_engine_ahead(K, Cin, Cout, c.cost_ns));
+    }
     p.big = fits && (opt.tile_mode == 2 || pays);
   }
   bool two_sizes = false;
@@ -1204,6 +1229,13 @@ static void choose_batch(const sbp_linear_layer* L, int n, BatchLayerChoice* c) 
   overrides();
 }
 
+// A batch of little work is better off in the one launch of the 128-tile engine: the large tiles' fixed parts (row tables, first
+// stages, epilogues of 256 KB) do not shrink with it.  Batched call with its reduction, large / 128 tiles: 3.8 GFLOP
+// (256 -> 1024 -> 256, 1800 rows) 29.4 / 18.5 us, 5.9 (320, 1800 rows) 35.3 / 24.0, 11.2 (the four linears of a block of
+// 384, 1584 rows) 41.3 / 33.0, 13.2 (256, 6300 rows) 40.8 / 38.0; 15.6 (block of 320, 3168 rows) 45.7 / 46.8, 17.7 (320,
+// 5400 rows) 47.6 / 46.9, 19.9 (block of 512, 1584 rows) 45.1 / 49.3, 44.8 (block of 768) 59.4 / 85.7.
+static constexpr double kSmallBatchFlops = 14e9;
+
 BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype) {
   BatchPlan p{};
   p.n = n;
@@ -1214,6 +1246,17 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   p.fused = n >= 1 && n <= kMaxBatch;
   for (int i = 0; i < n && p.fused; ++i)
     p.fused = batch_layer_fits(L[i], dtype) && (forced || (L[i].Cin >= big::BT && L[i].Cout >= big::BT && L[i].K >= 1024));
+  if (p.fused && !forced && n >= 2) {
+    double flops = 0;
+    bool general = true;       // every layer one that launch_small_batch takes
+    for (int i = 0; i < n; ++i) {
+      const sbp_linear_layer& l = L[i];
+      flops += 4.0 * (double)l.K * l.Cin * l.Cout;
+      general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !((uintptr_t)l.dW & 15) &&
+                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags).big;
+    }
+    if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) p.fused = false;
+  }
   // layer by layer: every layer gets its own piece of the workspace.  The size returned covers both modes, so that
   // a size query made with other (e.g. differently aligned) addresses than the call still holds.
   size_t off = 0, seq_bytes = 0;

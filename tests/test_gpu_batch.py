@@ -229,6 +229,35 @@ def test_batch_of_small_layers_accumulates_and_rounds_the_weight_gradient():
     _check_against_oracle(c1, (dW1, db1, None))
 
 
+@pytest.mark.parametrize("flags", [0, sbp.FLAG_DX_COMPACT | sbp.FLAG_DY_COMPACT, sbp.FLAG_ACCUMULATE_DW, sbp.FLAG_DW_OUT_BF16])
+@pytest.mark.parametrize("geom", [(2, 0, 40, 60, 256, 320), (2, 0, 50, 33, 520, 256), (16, 1, 14, 14, 264, 1024)])
+def test_wide_layers_of_little_work_take_the_general_engine_and_agree_with_the_large_tiles(geom, flags):
+    # whole 256-wide tiles but too little work for them: alone and in a batch these run on the 128-wide tiles; exactly
+    # representable inputs, so that both engines give the same bits (a batch with an X_k in row groups keeps the large tiles)
+    B, P, H, W, Cin, Cout = geom
+    K = sbp.keep_count(B, P, H, W, 2)
+    assert K >= 1024 and sbp.backward_linear_engine(B * (P + H * W), K, Cin, Cout, sbp.BF16)[0] == "mfma"
+    ints = [_layer(B, P, H, W, Cin, Cout, 2, 151, ints=True, flags=flags), _layer(B, P, H, W, Cout // 32 * 32, 288, 2, 152, ints=True, flags=flags)]
+
+    def run(batch, **opt):
+        dev = [_to_device(c, True) for c in ints]
+        for d in dev:
+            if flags & sbp.FLAG_ACCUMULATE_DW:
+                d["dW"] = torch.full((d["W"].shape[0], d["W"].shape[1]), 2.0, device="cuda")
+                d["db"] = torch.full((d["W"].shape[0],), -1.0, device="cuda")
+        with sbp.options(**opt):
+            if batch:
+                return sbp.backward_linear_batch(dev)
+            return [sbp.backward_linear(d["dY"], d["idx"], d["X_k"], d["W"], M=d["M"], inv=d["inv"], flags=flags, dW=d.get("dW"),
+                                        db=d.get("db")) for d in dev]
+
+    ref = run(False, tile="big")
+    for got in (run(False), run(True), run(True, tile="big")):
+        for o, r in zip(got, ref):
+            for a, b in zip(o, r):
+                assert np.array_equal(bits(a), bits(b))
+
+
 def _time_batch(dev, ws, iters=12):
     for _ in range(3):
         sbp.backward_linear_batch(dev, workspace=ws)
