@@ -178,20 +178,34 @@ __device__ __forceinline__ float wave_sum(float v) {
   return ((r0 + r1) + r2) + r3;
 }
 
-// Fast path: C a multiple of 8, C <= 64 * 8 * NV.  A wavefront owns a row: lane l holds the 8-value groups
-// l, l + 64, ... of it in registers.  A block of 4 wavefronts walks the rows [r0, r1) of its slice and keeps
-// per-lane sums of dU * xhat and dU for its columns; the four wavefronts' sums are added in a fixed order
-// through LDS and written as the block's partial.
-template <typename T, int NV>
+// the same over each 16 lanes
+__device__ __forceinline__ float row16_sum(float v) {
+  v += dpp_lane<0xB1>(v);
+  v += dpp_lane<0x4E>(v);
+  v += dpp_lane<0x141>(v);
+  v += dpp_lane<0x140>(v);
+  return v;
+}
+
+// Fast path: C a multiple of 8, C <= L * 8 * NV.  L lanes own a row (64, or 16 for narrow rows, which leave most lanes of
+// a wavefront idle: 128 channels are 16 pieces of 8): lane l holds the 8-value groups l, l + L, ... of it in registers.  A
+// block of 256 / L such groups walks the rows [r0, r1) of its slice and keeps per-lane sums of dU * xhat and dU for its
+// columns; the groups' sums are added in a fixed order through LDS and written as the block's partial.
+// Bound by bytes on long maps: 33600 of 134400 rows of 128 bf16 channels with a scattered dX 30.2 us with 64 lanes per row and a
+// dropped row written by 16 of 64 lanes, 12.2 us with 16 lanes per row and the zeros side by side (51 MB: 10 us).
+template <typename T, int NV, int L>
 __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __restrict__ dU, const T* __restrict__ Xk,
                                                                   const float* __restrict__ gamma, float eps,
                                                                   const int32_t* __restrict__ idx_out, int K, int C,
                                                                   int rows_per_block, T* __restrict__ dX,
                                                                   float* __restrict__ partial, int row_blocks,
                                                                   const int32_t* __restrict__ inv, int M) {
-  extern __shared__ float red[];                       // [4][C]
+  constexpr int G = PW_THREADS / L;                    // rows in flight
+  extern __shared__ float red[];                       // [G][C]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l = threadIdx.x & (L - 1), g = threadIdx.x / L;
   const int ngroups = C / 8;
+  auto row_sum = [](float v) { return L == 64 ? wave_sum(v) : row16_sum(v); };
   if ((int)blockIdx.x >= row_blocks) {
     // The blocks behind the row blocks write +0 to the rows of dX [M, C] that are not kept (scattered output
     // only): a wavefront looks 64 rows up at once (row m is kept iff idx[inv[m]] == m) and all lanes together
@@ -207,6 +221,12 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
         dropped = !((unsigned)j < (unsigned)K && idx_out[j] == m);
       }
       unsigned long long mask = __ballot(dropped);
+      if (ngroups * PPG < 64) {                        // narrow rows: the pieces of the 64 rows side by side over the lanes
+        const uint32_t ppr = ngroups * PPG, magic = (1u << 20) / ppr + 1;        // e / ppr = e magic >> 20 for e < 64 ppr
+        for (uint32_t e = lane; e < 64 * ppr; e += 64)
+          if ((mask >> ((e * magic) >> 20)) & 1) out[(long long)base * ppr + e] = make_uint4(0, 0, 0, 0);
+        continue;
+      }
       while (mask) {
         const int b = __ffsll((long long)mask) - 1;
         mask &= mask - 1;
@@ -220,7 +240,7 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
   float gam[NV][8], sg[NV][8], sb[NV][8];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const int grp = lane + 64 * v;
+    const int grp = l + L * v;
 #pragma unroll
     for (int i = 0; i < 8; ++i) { gam[v][i] = 0.f; sg[v][i] = 0.f; sb[v][i] = 0.f; }
     if (grp < ngroups) {
@@ -230,17 +250,19 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
     }
   }
   const float invC = 1.0f / (float)C;
-  // U rows of the wavefront side by side: their loads go out together and their reduction chains interleave
-  constexpr int U = NV <= 2 ? 2 : 1;
+  // U rows of a group side by side: their loads go out together and their reduction chains interleave
+  constexpr int U = L == 64 && NV <= 2 ? 2 : 1;      // (16 lanes: four rows of a wavefront already)
   // ... and the rows of the next round are requested before this round's arithmetic starts
   typename Vec8<T>::Raw xr[U][NV], dr[U][NV];
+  int orow_next[U];
   auto request = [&](int jb) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = jb + 4 * u;
+      const int j = jb + g + G * u;
+      orow_next[u] = idx_out && j < r1 ? idx_out[j] : j;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const int grp = lane + 64 * v;
+        const int grp = l + L * v;
         if (grp < ngroups && j < r1) {
           xr[u][v] = Vec8<T>::load_raw(Xk + (long long)j * C + 8 * grp);
           dr[u][v] = Vec8<T>::load_raw(dU + (long long)j * C + 8 * grp);
@@ -251,20 +273,22 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
       }
     }
   };
-  request(r0 + wave);
-  for (int jb = r0 + wave; jb < r1; jb += 4 * U) {
+  request(r0);
+  for (int jb = r0; jb < r1; jb += G * U) {
+    int orow[U];
     float x[U][NV][8], du[U][NV][8];
     float s1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       s1[u] = 0.f;
+      orow[u] = orow_next[u];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         Vec8<T>::unpack(xr[u][v], x[u][v]);
         Vec8<T>::unpack(dr[u][v], du[u][v]);
       }
     }
-    if (jb + 4 * U < r1) request(jb + 4 * U);
+    if (jb + G * U < r1) request(jb + G * U);
     float mean[U], rstd[U], m1[U], m2[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -272,14 +296,14 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
       for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int i = 0; i < 8; ++i) s1[u] += x[u][v][i];
-      mean[u] = wave_sum(s1[u]) * invC;
+      mean[u] = row_sum(s1[u]) * invC;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float s2 = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const bool ok = lane + 64 * v < ngroups;
+        const bool ok = l + L * v < ngroups;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const float d = ok ? x[u][v][i] - mean[u] : 0.f;
@@ -287,7 +311,8 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
           s2 += d * d;
         }
       }
-      rstd[u] = rsqrtf(wave_sum(s2) * invC + eps);
+      const float r = rsqrtf(row_sum(s2) * invC + eps);
+      rstd[u] = jb + g + G * u < r1 ? r : 0.f;         // (no row: adds zeros, also with eps = 0)
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -304,23 +329,22 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
           sg[v][i] += du[u][v][i] * xh;
           sb[v][i] += du[u][v][i];
         }
-      m1[u] = wave_sum(a1) * invC;
-      m2[u] = wave_sum(a2) * invC;
+      m1[u] = row_sum(a1) * invC;
+      m2[u] = row_sum(a2) * invC;
     }
     if (dX) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int j = jb + 4 * u;
+        const int j = jb + g + G * u;
         if (j < r1) {
-          const long long orow = idx_out ? (long long)idx_out[j] : (long long)j;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
-            const int grp = lane + 64 * v;
+            const int grp = l + L * v;
             if (grp < ngroups) {
               float o[8];
 #pragma unroll
               for (int i = 0; i < 8; ++i) o[i] = (du[u][v][i] * gam[v][i] - m1[u] - x[u][v][i] * m2[u]) * rstd[u];
-              Vec8<T>::store(dX + orow * C + 8 * grp, o);
+              Vec8<T>::store(dX + (long long)orow[u] * C + 8 * grp, o);
             }
           }
         }
@@ -328,20 +352,24 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
     }
   }
   if (!partial) return;
-  // the block's partial sums: wavefronts added in the order 0, 1, 2, 3; first dgamma's, then dbeta's
+  // the block's partial sums: groups added in order; first dgamma's, then dbeta's
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const int grp = lane + 64 * v;
+      const int grp = l + L * v;
       if (grp < ngroups) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) red[wave * C + 8 * grp + i] = which == 0 ? sg[v][i] : sb[v][i];
+        for (int i = 0; i < 8; ++i) red[g * C + 8 * grp + i] = which == 0 ? sg[v][i] : sb[v][i];
       }
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < C; c += PW_THREADS)
-      partial[((long long)blockIdx.x * 2 + which) * C + c] = ((red[c] + red[C + c]) + red[2 * C + c]) + red[3 * C + c];
+    for (int c = threadIdx.x; c < C; c += PW_THREADS) {
+      float sum = red[c];
+#pragma unroll
+      for (int q = 1; q < G; ++q) sum += red[q * C + c];
+      partial[((long long)blockIdx.x * 2 + which) * C + c] = sum;
+    }
     __syncthreads();
   }
 }
@@ -437,12 +465,15 @@ __global__ void __launch_bounds__(PW_THREADS) ln_fill_zero_kernel(float* __restr
 
 static constexpr int kLnMaxBlocks = 512;
 static constexpr int kLnMaxNV = 8;                       // fast path up to C = 64 * 8 * 8 = 4096
+static constexpr int kLnNarrow = 256;                    // rows up to here: 16 lanes each (2 groups of 8 per lane)
 
 LnPlan plan_layernorm(int64_t M, int64_t K, int32_t C, int32_t, uint32_t flags) {
   LnPlan p{};
   p.fast = C % 8 == 0 && C <= 64 * 8 * kLnMaxNV;
   // a block walks at least 16 rows (four per wavefront); at most kLnMaxBlocks partial sums
   p.nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(kLnMaxBlocks, ceil_div(K, 16)));
+  // narrow rows: 16 rows at a time; whole rounds on long slices, at most twice as many blocks
+  if (p.fast && C <= kLnNarrow && K > 16 * kLnMaxBlocks) p.nblocks = (int)ceil_div(K, align_up((size_t)ceil_div(K, 2 * kLnMaxBlocks), 32));
   size_t off = 0;
   p.off_partial = off;
   off += align_up((size_t)p.nblocks * 2 * C * sizeof(float), 256);
@@ -454,14 +485,14 @@ LnPlan plan_layernorm(int64_t M, int64_t K, int32_t C, int32_t, uint32_t flags) 
   return p;
 }
 
-template <typename T, int NV>
+template <typename T, int NV, int L>
 static void launch_ln_fast(const LnPlan& p, const T* dU, const T* Xk, const float* gamma, float eps,
                            const int32_t* idx_out, int K, int C, int rpb, T* dX, float* partial, const int32_t* inv, int M,
                            hipStream_t s) {
-  const size_t lds = (size_t)4 * C * sizeof(float);   // at most 64 KB (C <= 4096)
+  const size_t lds = (size_t)(PW_THREADS / L) * C * sizeof(float);   // at most 64 KB (C <= 4096; L = 16: C <= 256)
   // scattered output: zero-fill blocks ride in the same launch
-  const int nz = (dX && idx_out && inv) ? (int)std::min<int64_t>(128, std::max<int64_t>(8, ceil_div(M, 256))) : 0;
-  SBP_LAUNCH(SBP_PROF_OTHER, s, (ln_bwd_rows_kernel<T, NV>), dim3(p.nblocks + nz), dim3(PW_THREADS), lds, s, dU, Xk, gamma, eps,
+  const int nz = (dX && idx_out && inv) ? (int)std::min<int64_t>(L == 16 ? 512 : 128, std::max<int64_t>(8, ceil_div(M, 256))) : 0;
+  SBP_LAUNCH(SBP_PROF_OTHER, s, (ln_bwd_rows_kernel<T, NV, L>), dim3(p.nblocks + nz), dim3(PW_THREADS), lds, s, dU, Xk, gamma, eps,
              idx_out, K, C, rpb, dX, partial, p.nblocks, inv, M);
 }
 
@@ -469,15 +500,18 @@ static void launch_ln_fast(const LnPlan& p, const T* dU, const T* Xk, const floa
 template <typename T>
 static bool launch_ln_t(const LnPlan& p, const T* dU, const T* Xk, const float* gamma, float eps, const int32_t* idx_out,
                         int K, int C, T* dX, float* partial, float* stats, const int32_t* inv, int M, hipStream_t s) {
-  const int rpb = (int)ceil_div(K, p.nblocks);
+  int rpb = (int)ceil_div(K, p.nblocks);
+  if (p.fast && C <= kLnNarrow && K > 16 * kLnMaxBlocks) rpb = (int)align_up((size_t)rpb, 32);
   const bool aligned = (uintptr_t)dU % 16 == 0 && (uintptr_t)Xk % 16 == 0 && (uintptr_t)dX % 16 == 0 && (uintptr_t)gamma % 16 == 0;
   if (p.fast && aligned) {
     const int nv = (int)ceil_div(C / 8, 64);
-    switch (nv) {
-      case 1: launch_ln_fast<T, 1>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
-      case 2: launch_ln_fast<T, 2>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
-      case 3: case 4: launch_ln_fast<T, 4>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
-      default: launch_ln_fast<T, 8>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
+    if (C <= 128) launch_ln_fast<T, 1, 16>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s);
+    else if (C <= kLnNarrow) launch_ln_fast<T, 2, 16>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s);
+    else switch (nv) {
+      case 1: launch_ln_fast<T, 1, 64>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
+      case 2: launch_ln_fast<T, 2, 64>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
+      case 3: case 4: launch_ln_fast<T, 4, 64>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
+      default: launch_ln_fast<T, 8, 64>(p, dU, Xk, gamma, eps, idx_out, K, C, rpb, dX, partial, inv, M, s); break;
     }
     return dX && idx_out && inv;
   } else {

@@ -100,6 +100,20 @@ def test_backward_layernorm_row_counts(K):
     _check_ln(M=300, K=K, C=64, dtype="bf16", seed=40 + K)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("C", [8, 120, 128, 136, 256, 264])
+@pytest.mark.parametrize("M,K", [(40, 17), (8300, 8192), (12345, 8193)])
+def test_backward_layernorm_narrow_rows(M, K, C, dtype):
+    # up to 256 channels 16 lanes own a row (1 or 2 groups of 8 per lane) and dropped rows are zeroed side by side; beyond
+    # 8192 rows the slices are whole rounds, the last ones partly or wholly empty
+    _check_ln(M=M, K=K, C=C, dtype=dtype, seed=C + K, inv_mode="garbage")
+
+
+def test_backward_layernorm_rows_beyond_a_slice_add_nothing_at_eps_zero():
+    _check_ln(M=60, K=33, C=128, dtype="f32", seed=5, eps=0.0)
+    _check_ln(M=60, K=33, C=512, dtype="f32", seed=6, eps=0.0)
+
+
 @pytest.mark.parametrize("inv_mode", [None, "sampler", "garbage"])
 @pytest.mark.parametrize("flags", [0, sbp.FLAG_DX_COMPACT])
 def test_backward_layernorm_inverse_map_and_compact_output(flags, inv_mode):
