@@ -599,6 +599,7 @@ __device__ __forceinline__ void attn_store_rows(char* image, const f32x16_t (&ac
 // lse * log2(e) and -delta = -dA.A of tokens t0 .. t0 + 511 (key role): four lanes per row, UNR rows in flight per lane
 template <int D, int UNR>
 __device__ __forceinline__ void attn_make_tables(const AttnItem& it, int t0, int n_k, int h, float* lse_s, float* ndl_s) {
+  static_assert(kAttnTable % (64 * UNR) == 0, "whole rounds: every row that is written lies in the table");
   const int t = threadIdx.x, n = min(kAttnTable, n_k - t0);
   const long long lda = (long long)h * D;
   float lv[kAttnTable / 256];
@@ -655,7 +656,7 @@ __device__ __forceinline__ void attn_tiled_body(char* smem, const AttnItem& it, 
     wait_async_copies<0>();                                 // tile s (issued two stages ago, or one: everything before this stage)
     lds_barrier();                                          // ... everywhere; the ring place of tile s - 1 is free
     if (KEY && s && s % (kAttnTable / kAttnTile) == 0) {
-      attn_make_tables<D, 64 / D + 1>(it, s * kAttnTile, n_k, h, lse_s, ndl_s);
+      attn_make_tables<D, D == 128 ? 1 : 2>(it, s * kAttnTile, n_k, h, lse_s, ndl_s);
       lds_barrier();
     }
     if (s + 2 < ns) st.issue(s + 2, smem, lane, wave);

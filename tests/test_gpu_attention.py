@@ -167,3 +167,9 @@ def test_bf16_dispatch_edge_and_table_refill(d, n_k):
     # 64 tokens: the last size of the one-workgroup kernel; 65: a tile of 64 and one row; 129: a second chunk of one token;
     # 577: the tables of queries 512 .. are made inside the loop, then one more row behind a full tile
     assert max(_run(1, 600, 2, d, _keep_sets(1, 600, n_k, 27), "bf16", 29)) <= TOL_BF16
+
+
+@pytest.mark.parametrize("n_k", [896, 897, 1024, 1100])
+def test_bf16_table_refills_of_short_heads(n_k):
+    # d = 32, tables of 512 queries refilled inside the loop: 384 queries in the second table, one more, a full one, a third
+    assert max(_run(1, 1100, 2, 32, _keep_sets(1, 1100, n_k, 31), "bf16", 33)) <= TOL_BF16
