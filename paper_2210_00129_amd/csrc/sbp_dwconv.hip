@@ -823,9 +823,10 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
     b = rest / a.tiles_y;
     x0 = tx * TQ * 4;
   };
-  // a tile's addresses: a scalar base per tile + a 32-bit offset per thread (host: a sample is below 4 GiB)
-  const uint32_t rowb = (uint32_t)a.W * a.C * 2, colb = (uint32_t)a.C * 2;
-  const uint32_t goff = grow * rowb + 4 * gq * colb + 16 * g8, xgoff = xrow * rowb + 4 * xq * colb + 16 * g8;
+  // a tile's addresses: a scalar base per tile + an offset per thread.  The offset counts from row y0 - 3, so it spans more
+  // rows than a low map has, and is kept in 64 bits (no more registers: 128, 5 spilled, as with 32)
+  const uint64_t rowb = (uint64_t)a.W * a.C * 2, colb = (uint64_t)a.C * 2;
+  const uint64_t goff = grow * rowb + 4 * gq * colb + 16 * g8, xgoff = xrow * rowb + 4 * xq * colb + 16 * g8;
   auto tile_base = [&](const void* t, int b, int y, int x) {       // element (b, y, x, slab0); may lie before the tensor
     return reinterpret_cast<const char*>(t) + (((long long)b * a.H + y) * a.W + x) * a.C * 2 + slab0 * 2;
   };
@@ -849,7 +850,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       GA[k] = make_uint4(0, 0, 0, 0);
-      if (rok && (unsigned)(x + k) < (unsigned)a.W && iv[k] >= 0) GA[k] = *reinterpret_cast<const uint4*>(p + (long long)k * colb + goff);
+      if (rok && (unsigned)(x + k) < (unsigned)a.W && iv[k] >= 0) GA[k] = *reinterpret_cast<const uint4*>(p + k * colb + goff);
     }
   };
   auto store = [&](int parity) {
@@ -959,7 +960,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
             for (int i = 0; i < 7; ++i)
               for (int t = 0; t < 7; ++t)
                 d = fmaf(DwElem<uint16_t>::ld(reinterpret_cast<const uint16_t*>(gt + (row + i) * DWM_ROWP + l * DWM_PITCH) + x + t + 1),
-                         DwElem<uint16_t>::ld(a.Wd + ((6 - i) * 7 + 6 - t) * a.C + c), d);
+                         DwElem<uint16_t>::ld(a.Wd + (long long)((6 - i) * 7 + 6 - t) * a.C + c), d);
             reinterpret_cast<uint16_t*>(ot + row * DWM_ROWP + l * DWM_PITCH + 8)[x] = (uint16_t)(dw_pack(d, 0.f) & 0xffffu);
           }
           __syncthreads();
@@ -973,9 +974,9 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
           for (int k = 0; k < 8; ++k) q[k] = *reinterpret_cast<const uint2*>(ot + xoff + k * DWM_PITCH);
           char* o = const_cast<char*>(tile_base(a.dX, b, y0, x0));
           if (x < a.W) *reinterpret_cast<uint4*>(o + xgoff) = make_uint4(dw_pair_lo(q[0].x, q[1].x), dw_pair_lo(q[2].x, q[3].x), dw_pair_lo(q[4].x, q[5].x), dw_pair_lo(q[6].x, q[7].x));
-          if (x + 1 < a.W) *reinterpret_cast<uint4*>(o + 1ll * colb + xgoff) = make_uint4(dw_pair_hi(q[0].x, q[1].x), dw_pair_hi(q[2].x, q[3].x), dw_pair_hi(q[4].x, q[5].x), dw_pair_hi(q[6].x, q[7].x));
-          if (x + 2 < a.W) *reinterpret_cast<uint4*>(o + 2ll * colb + xgoff) = make_uint4(dw_pair_lo(q[0].y, q[1].y), dw_pair_lo(q[2].y, q[3].y), dw_pair_lo(q[4].y, q[5].y), dw_pair_lo(q[6].y, q[7].y));
-          if (x + 3 < a.W) *reinterpret_cast<uint4*>(o + 3ll * colb + xgoff) = make_uint4(dw_pair_hi(q[0].y, q[1].y), dw_pair_hi(q[2].y, q[3].y), dw_pair_hi(q[4].y, q[5].y), dw_pair_hi(q[6].y, q[7].y));
+          if (x + 1 < a.W) *reinterpret_cast<uint4*>(o + 1 * colb + xgoff) = make_uint4(dw_pair_hi(q[0].x, q[1].x), dw_pair_hi(q[2].x, q[3].x), dw_pair_hi(q[4].x, q[5].x), dw_pair_hi(q[6].x, q[7].x));
+          if (x + 2 < a.W) *reinterpret_cast<uint4*>(o + 2 * colb + xgoff) = make_uint4(dw_pair_lo(q[0].y, q[1].y), dw_pair_lo(q[2].y, q[3].y), dw_pair_lo(q[4].y, q[5].y), dw_pair_lo(q[6].y, q[7].y));
+          if (x + 3 < a.W) *reinterpret_cast<uint4*>(o + 3 * colb + xgoff) = make_uint4(dw_pair_hi(q[0].y, q[1].y), dw_pair_hi(q[2].y, q[3].y), dw_pair_hi(q[4].y, q[5].y), dw_pair_hi(q[6].y, q[7].y));
         }
       }
     }
@@ -997,7 +998,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         XA[k] = make_uint4(0, 0, 0, 0);
-        if (DW && xon && cok && y0 + xrow < a.H && x + k < a.W) XA[k] = *reinterpret_cast<const uint4*>(p + (long long)k * colb + xgoff);
+        if (DW && xon && cok && y0 + xrow < a.H && x + k < a.W) XA[k] = *reinterpret_cast<const uint4*>(p + k * colb + xgoff);
       }
     };
     if (any) fetch_x(wgx);
@@ -1204,8 +1205,7 @@ int32_t launch_backward_dwconv(const DwPlan& p, const void* dY, const int32_t* i
   }
   const Options opt = options();                                             // explicit overrides for sweeps and tests
   const bool tiled = dtype == SBP_BF16 && C % 8 == 0 && (ks == 7 || ks == 3) && !opt.dw_strips &&
-                     (((uintptr_t)dY | (uintptr_t)X | (uintptr_t)dX) % 16 == 0) && (int64_t)B * H * W * C < (1ll << 40) &&
-                     (ks != 7 || ((int64_t)H * W * C < (1ll << 30) && (int64_t)H * W < (1ll << 30)));   // (its 32-bit offsets inside a sample)
+                     (((uintptr_t)dY | (uintptr_t)X | (uintptr_t)dX) % 16 == 0) && (int64_t)B * H * W * C < (1ll << 40);
   if (tiled) {
     const bool want_dw = dWd || db;
     int nparts;

@@ -573,6 +573,35 @@ def test_dwconv_matrix_core_kernel_tile_edges_and_non_finite_gradients(geom):
     assert np.isfinite(a).all() and np.max(np.abs(a - r)) <= 2.0 ** -7 * max(np.max(np.abs(r)), 1e-30)
 
 
+@pytest.mark.parametrize("H,W,C", [(1, 800000, 1024), (2, 300000, 768), (1100, 1000, 1024)])
+def test_dwconv_samples_and_rows_beyond_32_bit_offsets(H, W, C):
+    # a 7 x 7 tile reads its gradients from row y - 3 on: with rows of 1.6 GB the kept rows of a one-row map lie more than 4 GiB
+    # behind that; and a sample of 2^30 elements and more.  A few kept positions, compared window by window in 64 bits
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X, dY = (torch.randn(1, H, W, C, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    Wd = torch.randn(7, 7, C, generator=g, device="cuda").mul_(0.1).bfloat16()
+    pos = [(y, x) for y in sorted({0, H // 2, H - 1}) for x in (0, 5, W // 3, W // 2, W // 2 + 1, W - 4, W - 1)]
+    idx = torch.tensor([y * W + x for y, x in pos], dtype=torch.int32, device="cuda")
+    dWd, db, dX = sbp.backward_dwconv(dY, idx, X, Wd)
+    rW, rX = torch.zeros(7, 7, C, dtype=torch.float64, device="cuda"), {}
+    for y, x in pos:
+        q = dY[0, y, x].double()
+        for u in range(7):
+            for v in range(7):
+                a, b = y + u - 3, x + v - 3
+                if 0 <= a < H and 0 <= b < W:
+                    rW[u, v] += q * X[0, a, b].double()
+                    rX[a, b] = rX.get((a, b), 0) + q * Wd[u, v].double()
+    rb = sum(dY[0, y, x].double() for y, x in pos)
+    assert nerr(f64(dWd), f64(rW)) <= TOL_F32 and nerr(f64(db), f64(rb)) <= TOL_F32
+    want = torch.stack(list(rX.values()))
+    got = torch.stack([dX[0, a, b] for a, b in rX])
+    assert nerr(f64(got), f64(want)) <= TOL_BF16_TIGHT
+    touched = torch.zeros(H, W, dtype=torch.bool, device="cuda")
+    touched[tuple(torch.tensor(list(rX), device="cuda").t())] = True
+    assert not dX[0].view(torch.int16).ne(0).any(dim=-1)[~touched].any()
+
+
 def test_dwconv_single_kept_position_stamps_kernel():
     B, H, W, C, ks = 1, 9, 11, 64, 7
     X, Wd, dY = si.dwconv_case(B, H, W, C, ks, 141, "f32")
