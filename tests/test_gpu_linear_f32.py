@@ -1,6 +1,6 @@
 """The fp32 matrix-core kernel of the linear backward (fp32 tensors, odd channel counts, unaligned tensors) at the edges of
-its tiles, stages (64 each) and splits, against the oracle.  Bounds: fp32 sums of at most 22000 exact or singly
-rounded products stay below 1e-5 of max |result|; dX of bf16 tensors is rounded once (gpu_util)."""
+its tiles, stages (64 each) and splits, against the oracle.  Bounds: fp32 sums of exact or singly rounded products, in chains
+of at most 256 rows, stay below 1e-5 of max |result|; dX of bf16 tensors is rounded once (gpu_util)."""
 import numpy as np
 import pytest
 import torch
@@ -75,3 +75,24 @@ def test_unaligned_bf16_tensors_of_a_large_layer():
     rW, rb, rX = oracle.backward_linear(si.to_f64(dY), idx_np, si.to_f64(X)[idx_np], si.to_f64(W), M)
     assert nerr(f64(dW), rW) <= TOL_F32 and nerr(f64(db), rb) <= TOL_F32 and nerr(f64(dX), rX) <= TOL_BF16_TIGHT
     assert np.all(bits(dX)[np.setdiff1d(np.arange(M), idx_np)] == 0)
+
+
+@pytest.mark.parametrize("K,Cin,Cout,dtype", [(9000, 2048, 2048, "f32"), (16384, 768, 772, "f32"), (12000, 1023, 2049, "f32"),
+                                              (30000, 1021, 1031, "bf16"), (12000, 1028, 2052, "bf16")])
+def test_long_splits_are_summed_in_short_chains(K, Cin, Cout, dtype):
+    # splits of 2000 to 9000 rows, one of them written directly.  A running sum of n zero-mean products ends up off by
+    # u sqrt(n / 6) of its size (u = 2^-24: n additions, each off by up to half a unit of the last place of a partial sum that
+    # grows as sqrt(i)); chains of 256 rows added in a compensated sum, then up to 64 splits: n = 256 + 64
+    g = torch.Generator(device="cuda").manual_seed(7)
+    X, dY = (torch.randn(K, c, generator=g, device="cuda").to(si.torch_dtype(dtype)) for c in (Cin, Cout))
+    W = torch.randn(Cout, Cin, generator=g, device="cuda").to(si.torch_dtype(dtype))
+    idx = torch.randperm(K, generator=g, device="cuda").int()
+    engine, splits = sbp.backward_linear_engine(K, K, Cin, Cout, sbp.F32 if dtype == "f32" else sbp.BF16)
+    assert engine == "plain" and K // splits > 2000
+    dW, db, _ = sbp.backward_linear(dY, idx, X, W, want=("dW", "db"))
+    alone = sbp.backward_linear(dY, idx, X, W, want=("db",))[1]
+    G = dY.double()[idx.long()]
+    rW, rb = torch.matmul(G.t().contiguous(), X.double()), G.sum(0)
+    bound = 2.0 ** -24 * (320 / 6) ** 0.5
+    for got, want in ((dW, rW), (db, rb), (alone, rb)):
+        assert ((got.double() - want).norm() / want.norm()).item() <= bound
