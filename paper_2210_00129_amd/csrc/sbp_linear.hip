@@ -82,8 +82,8 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
   const int wpb = blockDim.x >> 6;                             // wavefronts per block
   const int gw = blk * wpb + (threadIdx.x >> 6);
   uint4* out = reinterpret_cast<uint4*>(a.dX);
-  for (int base = gw * 64; base < a.M; base += a.n_zero * wpb * 64) {
-    const int m = base + lane;
+  for (long long base = gw * 64; base < a.M; base += a.n_zero * wpb * 64) {   // (64 bits: M may be the largest int)
+    const long long m = base + lane;
     bool dropped = false;
     if (m < a.M) {
       const int j = a.inv[m];
@@ -93,7 +93,7 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
-      uint4* row = out + (long long)(base + b) * ppr;
+      uint4* row = out + (base + b) * ppr;
       for (int p = lane; p < ppr; p += 64) row[p] = make_uint4(0, 0, 0, 0);
     }
   }

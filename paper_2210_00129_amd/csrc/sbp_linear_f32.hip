@@ -385,8 +385,8 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
   T* dX = static_cast<T*>(a.dX);                            // ---- zero fill: a wavefront looks 64 rows up at once
   constexpr int V = VEC ? 4 : 1;
   const int pieces = a.Cin / V;
-  for (int base = (wg * 4 + wave) * 64; base < a.M; base += a.n_zero * 256) {
-    const int m = base + lane;
+  for (long long base = (wg * 4 + wave) * 64; base < a.M; base += a.n_zero * 256) {   // (64 bits: M may be the largest int)
+    const long long m = base + lane;
     bool dropped = false;
     if (m < a.M) {
       const int j = a.inv[m];
@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
-      T* row = dX + (long long)(base + b) * a.Cin;
+      T* row = dX + (base + b) * a.Cin;
       for (int p = lane; p < pieces; p += 64) {
         if constexpr (VEC) F32Quad<T, true>::zero(row + p * V);
         else row[p] = (T)0;

@@ -213,8 +213,8 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
     constexpr int PPG = 8 * sizeof(T) / 16;            // 16-byte pieces per group of 8 values
     const int nz = gridDim.x - row_blocks, gw = ((int)blockIdx.x - row_blocks) * 4 + wave;
     uint4* out = reinterpret_cast<uint4*>(dX);
-    for (int base = gw * 64; base < M; base += nz * 4 * 64) {
-      const int m = base + lane;
+    for (long long base = gw * 64; base < M; base += nz * 4 * 64) {   // (64 bits: M may be the largest int)
+      const long long m = base + lane;
       bool dropped = false;
       if (m < M) {
         const int j = inv[m];
@@ -224,13 +224,13 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
       if (ngroups * PPG < 64) {                        // narrow rows: the pieces of the 64 rows side by side over the lanes
         const uint32_t ppr = ngroups * PPG, magic = (1u << 20) / ppr + 1;        // e / ppr = e magic >> 20 for e < 64 ppr
         for (uint32_t e = lane; e < 64 * ppr; e += 64)
-          if ((mask >> ((e * magic) >> 20)) & 1) out[(long long)base * ppr + e] = make_uint4(0, 0, 0, 0);
+          if ((mask >> ((e * magic) >> 20)) & 1) out[base * ppr + e] = make_uint4(0, 0, 0, 0);
         continue;
       }
       while (mask) {
         const int b = __ffsll((long long)mask) - 1;
         mask &= mask - 1;
-        uint4* row = out + (long long)(base + b) * (ngroups * PPG);
+        uint4* row = out + (base + b) * (ngroups * PPG);
         for (int q = lane; q < ngroups * PPG; q += 64) row[q] = make_uint4(0, 0, 0, 0);
       }
     }

@@ -602,6 +602,33 @@ def test_dwconv_samples_and_rows_beyond_32_bit_offsets(H, W, C):
     assert not dX[0].view(torch.int16).ne(0).any(dim=-1)[~touched].any()
 
 
+@pytest.mark.parametrize("call", ["linear_odd", "linear", "layernorm"])
+def test_dropped_rows_of_the_largest_row_count(call):
+    # row ids are int32, so M may be 2^31 - 1: the zero fill of the dropped rows has to step past that and stop
+    M, C = 2 ** 31 - 1, 1 if call == "linear_odd" else 8
+    if torch.cuda.get_device_properties(0).total_memory < 70 * 2 ** 30:
+        pytest.skip("a map of 2^31 rows and its inverse map")
+    kept = [0, 1, 63, 64, 12345678, M - 65537, M - 257, M - 2, M - 1]
+    idx = torch.tensor(kept, dtype=torch.int32, device="cuda")
+    inv = torch.full((M,), -1, dtype=torch.int32, device="cuda")
+    inv[idx.long()] = torch.arange(len(kept), dtype=torch.int32, device="cuda")
+    dX = torch.full((M, C), 7.0, dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a, b = (torch.randn(len(kept), C, generator=g, device="cuda").bfloat16() for _ in range(2))
+    if call == "layernorm":
+        gamma = torch.ones(C, device="cuda")
+        sbp.backward_layernorm(a, b, gamma, 1e-6, idx, M, inv=inv, dX=dX, want=("dX",))
+        want = sbp.backward_layernorm(a, b, gamma, 1e-6, idx, M, flags=sbp.FLAG_DX_COMPACT, want=("dX",))[2]
+    else:
+        W = torch.randn(C, C, generator=g, device="cuda").bfloat16()
+        sbp.backward_linear(a, idx, b, W, M=M, inv=inv, flags=sbp.FLAG_DY_COMPACT, want=("dX",), dX=dX)
+        want = sbp.backward_linear(a, idx, b, W, M=M, flags=sbp.FLAG_DY_COMPACT | sbp.FLAG_DX_COMPACT, want=("dX",))[2]
+    assert np.array_equal(bits(dX[idx.long()]), bits(want))
+    dX[idx.long()] = 0
+    words = dX.view(torch.int16).view(-1)
+    assert not any(int(part.count_nonzero()) for part in words.split(2 ** 30))
+
+
 def test_dwconv_single_kept_position_stamps_kernel():
     B, H, W, C, ks = 1, 9, 11, 64, 7
     X, Wd, dY = si.dwconv_case(B, H, W, C, ks, 141, "f32")
