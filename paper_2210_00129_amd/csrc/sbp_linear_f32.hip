@@ -34,6 +34,7 @@ struct F32Args {
   const void* Xk; const void* W; void* dX;
   float* part; float* dbp;             // [splits][Cout][Cin], [splits][Cout] (dW and db themselves with one split)
   int K, M, Cin, Cout, rows_per_split, splits;
+  int chain;                           // rows of a chain of the dW sums (a power of two, at least a stage)
   int n_dx, n_dw, n_db, n_zero;        // workgroups of every kind; in the grid dW and dX units (dx_first: dX units first), column
                                        // sums, zero fill
   int dx_first;
@@ -214,13 +215,15 @@ __device__ __forceinline__ void f32_multiply(const float* smem, int wm, int wn, 
   }
 }
 
-// Sums of more than F32_CHAIN kept rows are taken in chains of that length, and the chains added with the rounding error of
-// every addition carried along (Kahan): the error of a dW element stays that of one chain however long the split is.  2-norm
-// against 64 bits, one running sum / chains: 5.1e-7 / 2.9e-7 at 6336 rows of 768 x 768 (splits of 832), 1.4e-6 / 2.9e-7 at
-// 12608 rows of 768 x 3072 (6336), 1.6e-6 / 2.9e-7 at 65536 of 768 x 768 (8192); times the same within 1.5 %.
-static constexpr int F32_CHAIN = 4 * F32_KB;
+// Sums over many kept rows are taken in chains that are added up apart, so that the error of a dW element stays about that of one
+// chain however long the split is.  FOLD 0: a split of at most 256 rows, one chain; 1: up to 16384 rows, chains of 256 or, from
+// 2048 rows on, 128; 2: longer ones, chains of 256 added with the rounding error of every addition carried along (Kahan), which
+// takes 16 registers more and would cost thin layers, whose few units wait for their own latencies, 8 % (24.1 -> 26.0 us at 33600
+// rows of 60 x 64; 23.2 with plain additions).  2-norm against 64 bits, one running sum / in chains: 5.1e-7 / 2.9e-7 at 6336 rows
+// of 768 x 768 (splits of 832), 1.4e-6 / 2.4e-7 at 12608 of 768 x 3072 (6336), 1.6e-6 / 2.6e-7 at 65536 of 768 x 768 (8192).
+static constexpr int F32_ONE_CHAIN = 256, F32_PLAIN_FOLD = 16384;
 
-__device__ __forceinline__ void f32_fold(float& chain, float& total, float& err) {
+__device__ __forceinline__ void f32_kahan(float& chain, float& total, float& err) {
   const float y = chain - err, t = total + y;
   err = (t - total) - y;
   total = t;
@@ -228,23 +231,24 @@ __device__ __forceinline__ void f32_fold(float& chain, float& total, float& err)
 }
 
 // Stage loop: registers -> LDS -> MFMA (addresses are clamped, so the loads ahead need no bounds check).  CS: operand A
-// also sums its columns.  FOLD: in chains.
-template <bool CS, bool FOLD, class LA, class LB>
-__device__ __forceinline__ void f32_stage_loop(float* smem, LA& la, LB& lb, int k0, int kend, int wm, int wn, f32x16_t& acc) {
+// also sums its columns.
+template <bool CS, int FOLD, class LA, class LB>
+__device__ __forceinline__ void f32_stage_loop(float* smem, LA& la, LB& lb, int k0, int kend, int chain, int wm, int wn, f32x16_t& acc) {
   const int lane = threadIdx.x & 63;
   float tot[16], err[16];
   float4* ctot = reinterpret_cast<float4*>(smem + 2 * F32_TILE_WORDS) + threadIdx.x;   // (the column sums' chains in LDS: registers are short)
-  if constexpr (FOLD) {
+  if constexpr (FOLD != 0) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) tot[v] = err[v] = 0.f;
     if constexpr (CS) *ctot = make_float4(0, 0, 0, 0);
   }
   auto fold = [&] {
-    if constexpr (FOLD) {
+    if constexpr (FOLD != 0) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         float a = acc[v];
-        f32_fold(a, tot[v], err[v]);
+        if (FOLD == 2) f32_kahan(a, tot[v], err[v]);
+        else { tot[v] += a; a = 0.f; }
         acc[v] = a;
       }
       if constexpr (CS) {
@@ -264,14 +268,14 @@ __device__ __forceinline__ void f32_stage_loop(float* smem, LA& la, LB& lb, int 
     __syncthreads();
     la.load(kb + F32_KB); lb.load(kb + F32_KB);
     f32_multiply(smem, wm, wn, lane, acc);
-    if (((kb - k0) & (F32_CHAIN - F32_KB)) == F32_CHAIN - F32_KB) fold();
+    if (FOLD != 0 && ((kb - k0 + F32_KB) & (chain - 1)) == 0) fold();
   }
   __syncthreads();
   la.template store<true, CS>(smem, kb);
   lb.template store<true, false>(smem + F32_TILE_WORDS, kb);
   __syncthreads();
   f32_multiply(smem, wm, wn, lane, acc);
-  if constexpr (FOLD) {
+  if constexpr (FOLD != 0) {
     fold();
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = tot[v];
@@ -280,25 +284,25 @@ __device__ __forceinline__ void f32_stage_loop(float* smem, LA& la, LB& lb, int 
 }
 
 // dW tile over the kept rows [j0, j1): with sums, smem[64 * step lane + column] holds partial column sums afterwards
-template <typename T, bool VEC, bool GATHER, bool FOLD>
+template <typename T, bool VEC, bool GATHER, int FOLD>
 __device__ __forceinline__ void f32_dw(const F32Args& a, float* smem, int m0, int n0, int j0, int j1, int wm, int wn, bool sums,
                                        f32x16_t& acc) {
   F32SlowLoader<T, VEC, GATHER> la;
   F32SlowLoader<T, VEC, false> lb;
   la.init(static_cast<const T*>(a.dY), a.idx_in, a.Cout, m0, a.Cout, j0, j1);
   lb.init(static_cast<const T*>(a.Xk), nullptr, a.Cin, n0, a.Cin, j0, j1);
-  if (!sums) { f32_stage_loop<false, FOLD>(smem, la, lb, j0, j1, wm, wn, acc); return; }
-  f32_stage_loop<true, FOLD>(smem, la, lb, j0, j1, wm, wn, acc);
+  if (!sums) { f32_stage_loop<false, FOLD>(smem, la, lb, j0, j1, a.chain, wm, wn, acc); return; }
+  f32_stage_loop<true, FOLD>(smem, la, lb, j0, j1, a.chain, wm, wn, acc);
   __syncthreads();
   *reinterpret_cast<float4*>(smem + (threadIdx.x >> 4) * F32_BT + (threadIdx.x & 15) * 4) = make_float4(la.sum[0], la.sum[1], la.sum[2], la.sum[3]);
   __syncthreads();
 }
 
-// One workgroup's unit.  VEC: channel counts and addresses allow 4-element pieces.  FOLD: the dW splits are longer than one
-// chain (the sums of the chains take 32 registers more; single elements, whose addresses take the most, are then faster with
-// three workgroups per CU than spilling with four: 243 / 287 us at 6336 rows of 769 x 771 in bf16).
-template <typename T, bool VEC, bool FOLD>
-__global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_kernel(const F32Args a) {
+// One workgroup's unit.  VEC: channel counts and addresses allow 4-element pieces.  FOLD: as above, for the dW
+// splits.  Single elements, whose addresses take the most registers, are faster with three workgroups per CU than spilling with
+// four (240 / 260 us at 6336 rows of 769 x 771 in bf16).
+template <typename T, bool VEC, int FOLD>
+__global__ void __launch_bounds__(NTHREADS, VEC ? 4 : 3) linear_f32_kernel(const F32Args a) {
   __shared__ __attribute__((aligned(16))) float smem[2 * F32_TILE_WORDS + (FOLD ? 4 * NTHREADS : 0)];
   constexpr int BT = F32_BT;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -350,7 +354,7 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
     F32SlowLoader<T, VEC, false> lb;
     la.init(dY, a.idx_in, a.Cout, m0, a.K, a.Cout);
     lb.init(static_cast<const T*>(a.W), nullptr, a.Cin, n0, a.Cin, 0, a.Cout);
-    f32_stage_loop<false, false>(smem, la, lb, 0, a.Cout, wm, wn, acc);
+    f32_stage_loop<false, 0>(smem, la, lb, 0, a.Cout, 0, wm, wn, acc);
     int* ids = reinterpret_cast<int*>(smem);
     __syncthreads();
     if (t < BT) { const int j = min(m0 + t, a.K - 1); ids[t] = a.idx_out ? a.idx_out[j] : j; }
@@ -369,11 +373,11 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
     const int j0 = split * a.rows_per_split, j1 = min(a.K, j0 + a.rows_per_split);
     float s = 0.f, err = 0.f;
     if (c < a.Cout) {
-      for (int jc = j0; jc < j1; jc += F32_CHAIN) {
+      for (int jc = j0; jc < j1; jc += F32_ONE_CHAIN) {
         float q = 0.f;
 #pragma unroll 4
-        for (int j = jc + wave; j < min(j1, jc + F32_CHAIN); j += 4) q += f32_load(dY + (long long)(a.idx_in ? a.idx_in[j] : j) * a.Cout + c);
-        f32_fold(q, s, err);
+        for (int j = jc + wave; j < min(j1, jc + F32_ONE_CHAIN); j += 4) q += f32_load(dY + (long long)(a.idx_in ? a.idx_in[j] : j) * a.Cout + c);
+        f32_kahan(q, s, err);
       }
     }
     smem[t] = s;
@@ -393,10 +397,11 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
       dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == m);
     }
     unsigned long long mask = __ballot(dropped);
+    T* rows = dX + base * a.Cin;
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
-      T* row = dX + (base + b) * a.Cin;
+      T* row = rows + (long long)b * a.Cin;
       for (int p = lane; p < pieces; p += 64) {
         if constexpr (VEC) F32Quad<T, true>::zero(row + p * V);
         else row[p] = (T)0;
@@ -416,6 +421,11 @@ void plan_linear_f32(int64_t K, int32_t Cin, int32_t Cout, int* splits, int* row
   *splits = (int)ceil_div(K, *rows_per_split);
 }
 
+template <typename T, bool VEC>
+static auto f32_kernel(int fold) {
+  return fold == 0 ? linear_f32_kernel<T, VEC, 0> : (fold == 1 ? linear_f32_kernel<T, VEC, 1> : linear_f32_kernel<T, VEC, 2>);
+}
+
 void launch_linear_f32(int splits, int rows_per_split, const void* dY, const int32_t* idx_in, const int32_t* idx_out,
                        const int32_t* idx, const int32_t* inv, const void* Xk, const void* W, int64_t M, int64_t K, int32_t Cin,
                        int32_t Cout, int32_t dtype, bool want_dw, float* part, float* dbp, void* dX, hipStream_t s) {
@@ -433,11 +443,10 @@ void launch_linear_f32(int splits, int rows_per_split, const void* dY, const int
   if (grid == 0) return;
   const uintptr_t addr = (uintptr_t)dY | (uintptr_t)(want_dw ? Xk : nullptr) | (uintptr_t)(dX ? W : nullptr) | (uintptr_t)dX;
   const bool f32 = dtype == SBP_F32, vec = Cin % 4 == 0 && Cout % 4 == 0 && addr % (f32 ? 16 : 8) == 0;
-  const bool fold = want_dw && rows_per_split > F32_CHAIN;
-  auto kernel = fold ? (f32 ? (vec ? linear_f32_kernel<float, true, true> : linear_f32_kernel<float, false, true>)
-                            : (vec ? linear_f32_kernel<uint16_t, true, true> : linear_f32_kernel<uint16_t, false, true>))
-                     : (f32 ? (vec ? linear_f32_kernel<float, true, false> : linear_f32_kernel<float, false, false>)
-                            : (vec ? linear_f32_kernel<uint16_t, true, false> : linear_f32_kernel<uint16_t, false, false>));
+  a.chain = rows_per_split > 2048 && rows_per_split <= F32_PLAIN_FOLD ? 128 : 256;
+  const int fold = !want_dw || rows_per_split <= F32_ONE_CHAIN ? 0 : (rows_per_split <= F32_PLAIN_FOLD ? 1 : 2);
+  auto kernel = f32 ? (vec ? f32_kernel<float, true>(fold) : f32_kernel<float, false>(fold))
+                    : (vec ? f32_kernel<uint16_t, true>(fold) : f32_kernel<uint16_t, false>(fold));
   SBP_LAUNCH(SBP_PROF_DW_GEMM, s, kernel, dim3(grid), dim3(NTHREADS), 0, s, a);
 }
 

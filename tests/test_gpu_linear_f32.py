@@ -78,11 +78,14 @@ def test_unaligned_bf16_tensors_of_a_large_layer():
 
 
 @pytest.mark.parametrize("K,Cin,Cout,dtype", [(9000, 2048, 2048, "f32"), (16384, 768, 772, "f32"), (12000, 1023, 2049, "f32"),
-                                              (30000, 1021, 1031, "bf16"), (12000, 1028, 2052, "bf16")])
+                                              (30000, 1021, 1031, "bf16"), (12000, 1028, 2052, "bf16"),
+                                              (20000, 2048, 2052, "f32"), (20000, 2049, 2051, "f32"), (20000, 2052, 2052, "bf16"),
+                                              (20000, 2049, 2049, "bf16")])
 def test_long_splits_are_summed_in_short_chains(K, Cin, Cout, dtype):
-    # splits of 2000 to 9000 rows, one of them written directly.  A running sum of n zero-mean products ends up off by
+    # splits of 2000 to 20000 rows, single ones written directly.  A running sum of n zero-mean products ends up off by
     # u sqrt(n / 6) of its size (u = 2^-24: n additions, each off by up to half a unit of the last place of a partial sum that
-    # grows as sqrt(i)); chains of 256 rows added in a compensated sum, then up to 64 splits: n = 256 + 64
+    # grows as sqrt(i)); chains of at most 256 rows, at most 128 of them or in a compensated sum, then
+    # up to 64 splits: n = 256 + 64
     g = torch.Generator(device="cuda").manual_seed(7)
     X, dY = (torch.randn(K, c, generator=g, device="cuda").to(si.torch_dtype(dtype)) for c in (Cin, Cout))
     W = torch.randn(Cout, Cin, generator=g, device="cuda").to(si.torch_dtype(dtype))
