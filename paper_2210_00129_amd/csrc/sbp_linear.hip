@@ -90,10 +90,11 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
       dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == m);
     }
     unsigned long long mask = __ballot(dropped);
+    uint4* rows = out + base * ppr;
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;
-      uint4* row = out + (base + b) * ppr;
+      uint4* row = rows + (long long)b * ppr;
       for (int p = lane; p < ppr; p += 64) row[p] = make_uint4(0, 0, 0, 0);
     }
   }

@@ -299,10 +299,11 @@ __device__ __forceinline__ void f32_dw(const F32Args& a, float* smem, int m0, in
 }
 
 // One workgroup's unit.  VEC: channel counts and addresses allow 4-element pieces.  FOLD: as above, for the dW
-// splits.  Single elements, whose addresses take the most registers, are faster with three workgroups per CU than spilling with
-// four (240 / 260 us at 6336 rows of 769 x 771 in bf16).
+// splits.  Single elements, whose addresses take the most registers, are then faster with three workgroups per CU than spilling
+// with four (240 / 287 us at 6336 rows of 769 x 771 in bf16), but not without the chains' sums (69 / 64 us for the dX alone of
+// 100000 rows of 65 x 67).
 template <typename T, bool VEC, int FOLD>
-__global__ void __launch_bounds__(NTHREADS, VEC ? 4 : 3) linear_f32_kernel(const F32Args a) {
+__global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_kernel(const F32Args a) {
   __shared__ __attribute__((aligned(16))) float smem[2 * F32_TILE_WORDS + (FOLD ? 4 * NTHREADS : 0)];
   constexpr int BT = F32_BT;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -398,6 +399,15 @@ __global__ void __launch_bounds__(NTHREADS, VEC ? 4 : 3) linear_f32_kernel(const
     }
     unsigned long long mask = __ballot(dropped);
     T* rows = dX + base * a.Cin;
+    if (pieces < 64 && pieces <= __popcll(mask)) {           // narrow rows: the pieces of the 64 rows side by side over the lanes
+      const uint32_t magic = (1u << 20) / pieces + 1;       // e / pieces = e magic >> 20 for e < 64 pieces
+      for (uint32_t e = lane; e < 64u * pieces; e += 64)
+        if ((mask >> ((e * magic) >> 20)) & 1) {
+          if constexpr (VEC) F32Quad<T, true>::zero(rows + e * V);
+          else rows[e] = (T)0;
+        }
+      continue;
+    }
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;

@@ -221,16 +221,19 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
         dropped = !((unsigned)j < (unsigned)K && idx_out[j] == m);
       }
       unsigned long long mask = __ballot(dropped);
-      if (ngroups * PPG < 64) {                        // narrow rows: the pieces of the 64 rows side by side over the lanes
+      uint4* rows = out + base * (ngroups * PPG);
+      // narrow rows: the pieces of the 64 rows side by side over the lanes, in one step per piece of a row, where a row at a
+      // time would take more (384 channels, half dropped: 6.4 row at a time, 7.0 us side by side; 128 channels: 30 / 12 us)
+      if (ngroups * PPG < 64 && ngroups * PPG <= __popcll(mask)) {
         const uint32_t ppr = ngroups * PPG, magic = (1u << 20) / ppr + 1;        // e / ppr = e magic >> 20 for e < 64 ppr
         for (uint32_t e = lane; e < 64 * ppr; e += 64)
-          if ((mask >> ((e * magic) >> 20)) & 1) out[base * ppr + e] = make_uint4(0, 0, 0, 0);
+          if ((mask >> ((e * magic) >> 20)) & 1) rows[e] = make_uint4(0, 0, 0, 0);
         continue;
       }
       while (mask) {
         const int b = __ffsll((long long)mask) - 1;
         mask &= mask - 1;
-        uint4* row = out + (base + b) * (ngroups * PPG);
+        uint4* row = rows + b * (ngroups * PPG);
         for (int q = lane; q < ngroups * PPG; q += 64) row[q] = make_uint4(0, 0, 0, 0);
       }
     }
