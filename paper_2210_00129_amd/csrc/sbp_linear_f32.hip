@@ -193,7 +193,9 @@ static constexpr int F32_TILE_WORDS = F32_BT * F32_PITCH + F32_BT;
 
 // one stage out of LDS; the operands of a group are read while the group before is multiplied (and not earlier: left
 // alone, the compiler reads the whole stage first and spills)
-__device__ __forceinline__ void f32_multiply(const float* smem, int wm, int wn, int lane, f32x16_t& acc) {
+// (PART: only the first groups of 8 steps, for the last stage of a contraction, which may be all there is)
+template <bool PART = false>
+__device__ __forceinline__ void f32_multiply(const float* smem, int wm, int wn, int lane, f32x16_t& acc, int groups = F32_KB / 8) {
   const float* pa = smem + f32_place(wm + (lane & 31), lane >> 5);
   const float* pb = smem + F32_TILE_WORDS + f32_place(wn + (lane & 31), lane >> 5);
   float4 a[2], b[2];
@@ -201,6 +203,7 @@ __device__ __forceinline__ void f32_multiply(const float* smem, int wm, int wn, 
   b[0] = *reinterpret_cast<const float4*>(pb);
 #pragma unroll
   for (int g = 0; g < F32_KB / 8; ++g) {
+    if (PART && g >= groups) break;
     if (g + 1 < F32_KB / 8) {
       a[(g + 1) & 1] = *reinterpret_cast<const float4*>(pa + 8 * (g + 1));
       b[(g + 1) & 1] = *reinterpret_cast<const float4*>(pb + 8 * (g + 1));
@@ -274,7 +277,7 @@ __device__ __forceinline__ void f32_stage_loop(float* smem, LA& la, LB& lb, int 
   la.template store<true, CS>(smem, kb);
   lb.template store<true, false>(smem + F32_TILE_WORDS, kb);
   __syncthreads();
-  f32_multiply(smem, wm, wn, lane, acc);
+  f32_multiply<true>(smem, wm, wn, lane, acc, (kend - kb + 7) >> 3);
   if constexpr (FOLD != 0) {
     fold();
 #pragma unroll
