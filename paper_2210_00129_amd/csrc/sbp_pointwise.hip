@@ -203,7 +203,11 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
   constexpr int G = PW_THREADS / L;                    // rows in flight
   extern __shared__ float red[];                       // [G][C]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l = threadIdx.x & (L - 1), g = threadIdx.x / L;
+  // Wide rows fill the registers: there every wavefront walks its own rows (uniform addresses, no row to mask) and looks an output
+  // row up when it stores it; narrower ones walk in step with the lookups ahead (in step / own rows: 160 / 114 us at 6336 rows of
+  // 4096 fp32 channels, 30.9 / 26.7 at 6336 of 2048 bf16 channels; 16.3 / 17.2 at 6336 of 1024 fp32 channels, dX alone).
+  constexpr bool OWN = NV >= 4;
+  const int l = threadIdx.x & (L - 1), g = OWN ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x / L;
   const int ngroups = C / 8;
   auto row_sum = [](float v) { return L == 64 ? wave_sum(v) : row16_sum(v); };
   if ((int)blockIdx.x >= row_blocks) {
@@ -261,8 +265,8 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
   auto request = [&](int jb) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = jb + g + G * u;
-      orow_next[u] = idx_out && j < r1 ? idx_out[j] : j;
+      const int j = jb + (OWN ? 0 : g) + G * u;
+      if (!OWN) orow_next[u] = idx_out && j < r1 ? idx_out[j] : j;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int grp = l + L * v;
@@ -276,15 +280,16 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
       }
     }
   };
-  request(r0);
-  for (int jb = r0; jb < r1; jb += G * U) {
+  const int first = OWN ? r0 + g : r0;
+  request(first);
+  for (int jb = first; jb < r1; jb += G * U) {
     int orow[U];
     float x[U][NV][8], du[U][NV][8];
     float s1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       s1[u] = 0.f;
-      orow[u] = orow_next[u];
+      if (!OWN) orow[u] = orow_next[u];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         Vec8<T>::unpack(xr[u][v], x[u][v]);
@@ -315,7 +320,7 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
         }
       }
       const float r = rsqrtf(row_sum(s2) * invC + eps);
-      rstd[u] = jb + g + G * u < r1 ? r : 0.f;         // (no row: adds zeros, also with eps = 0)
+      rstd[u] = OWN || jb + g + G * u < r1 ? r : 0.f;   // (no row: adds zeros, also with eps = 0)
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -338,8 +343,9 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
     if (dX) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int j = jb + g + G * u;
+        const int j = jb + (OWN ? 0 : g) + G * u;
         if (j < r1) {
+          if (OWN) orow[u] = idx_out ? idx_out[j] : j;
 #pragma unroll
           for (int v = 0; v < NV; ++v) {
             const int grp = l + L * v;

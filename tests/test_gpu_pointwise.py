@@ -109,6 +109,15 @@ def test_backward_layernorm_narrow_rows(M, K, C, dtype):
     _check_ln(M=M, K=K, C=C, dtype=dtype, seed=C + K, inv_mode="garbage")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("C", [1024, 1032, 2056, 4096])
+@pytest.mark.parametrize("M,K", [(5, 1), (40, 17), (700, 333)])
+def test_backward_layernorm_wide_rows(M, K, C, dtype):
+    # from 1032 channels on every wavefront walks its own rows: fewer rows than wavefronts, one past whole rounds, ragged slices
+    _check_ln(M=M, K=K, C=C, dtype=dtype, seed=C + K, inv_mode="garbage")
+    _check_ln(M=M, K=K, C=C, dtype=dtype, seed=C + K, eps=0.0)
+
+
 def test_backward_layernorm_rows_beyond_a_slice_add_nothing_at_eps_zero():
     _check_ln(M=60, K=33, C=128, dtype="f32", seed=5, eps=0.0)
     _check_ln(M=60, K=33, C=512, dtype="f32", seed=6, eps=0.0)
