@@ -933,8 +933,10 @@ int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA
   // One workgroup per head where a head is at most two blocks of 32 tokens (64 x 12 heads of 64: 13.7 against 15.2 us at 50
   // tokens, 7.8 against 10.5 at 25); from three blocks on the tiled kernel is ahead (27.6 against 30.1 us at 99, 67 against
   // 81 at 197; d = 128: even at 99).
-  const bool tiled = engine == 2 || (n_k > 64 && options().attn_mode == 0);
-  if (engine) {
+  // (a grid of the tiled and fp32 kernels, two workgroups of 256 threads per chunk, stays below 2^32 threads)
+  const bool grid_fits = (int64_t)B * h * ceil_div(n_k, kAttnChunk) < (1 << 23) - 8;
+  const bool tiled = engine && grid_fits && (engine == 2 || (n_k > 64 && options().attn_mode == 0));
+  if (engine == 1 || tiled) {
     const uint16_t* q = (const uint16_t*)qkv; const uint16_t* a = (const uint16_t*)A; const uint16_t* g = (const uint16_t*)dA;
     uint16_t* o = (uint16_t*)dqkv;
     if (tiled) {
@@ -949,7 +951,7 @@ int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA
   } else if (dtype == SBP_BF16) {
     launch_attn_plain<uint16_t>((const uint16_t*)qkv, (const uint16_t*)A, (const uint16_t*)dA, lse, B, n_k, h, d, scale,
                                 (uint16_t*)dqkv, s);
-  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && (int64_t)B * h * ceil_div(n_k, kAttnF32Chunk) < (1 << 30)) {
+  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && grid_fits) {
     const float *q = (const float*)qkv, *a = (const float*)A, *g = (const float*)dA;
     if (d == 32) launch_attn_f32<32>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
     else if (d == 64) launch_attn_f32<64>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);

@@ -173,3 +173,32 @@ def test_bf16_dispatch_edge_and_table_refill(d, n_k):
 def test_bf16_table_refills_of_short_heads(n_k):
     # d = 32, tables of 512 queries refilled inside the loop: 384 queries in the second table, one more, a full one, a third
     assert max(_run(1, 1100, 2, 32, _keep_sets(1, 1100, n_k, 31), "bf16", 33)) <= TOL_BF16
+
+
+def test_f32_more_heads_than_one_grid_of_the_matrix_core_kernel_holds():
+    # two workgroups of 256 threads per head: 2^23 heads would be a grid of 2^32 threads, from there on the plain kernel runs
+    B, h, d, n_k = 65535, 129, 32, 3
+    g = torch.Generator(device="cuda").manual_seed(3)
+    qkv = torch.randn(B * n_k, 3 * h * d, generator=g, device="cuda")
+    dA = torch.randn(B * n_k, h * d, generator=g, device="cuda")
+    A = torch.zeros_like(dA)
+    lse = torch.zeros(B * n_k, h, device="cuda")
+    some = [(0, 0), (0, h - 1), (B // 2, 64), (B - 1, 0), (B - 1, h - 1)]
+    want = []
+    for b, head in some:
+        rows, c = slice(b * n_k, (b + 1) * n_k), slice(head * d, (head + 1) * d)
+        q, k, v = (qkv[rows, i * h * d + head * d:i * h * d + (head + 1) * d].double() for i in range(3))
+        s = torch.matmul(q, k.t().contiguous()) * d ** -0.5
+        lse[rows, head] = torch.logsumexp(s, -1).float()
+        P = torch.softmax(s, -1)
+        A[rows, c] = torch.matmul(P, v).float()
+        G = dA[rows, c].double()
+        dS = P * (torch.matmul(G, v.t().contiguous()) - (G * A[rows, c].double()).sum(-1, keepdim=True))
+        want.append([torch.matmul(dS, k) * d ** -0.5, torch.matmul(dS.t().contiguous(), q) * d ** -0.5, torch.matmul(P.t().contiguous(), G)])
+    out = torch.full_like(qkv, float("nan"))
+    sbp.backward_attention(qkv, A, dA, lse, B, h, d, d ** -0.5, out=out)
+    for (b, head), w in zip(some, want):
+        for i in range(3):
+            got = out[b * n_k:(b + 1) * n_k, i * h * d + head * d:i * h * d + (head + 1) * d]
+            assert nerr(f64(got), f64(w[i])) <= TOL_F32
+    assert not torch.isnan(out).any()
