@@ -393,10 +393,10 @@ int32_t sbp_backward_layerscale(const void* dU_k, const void* Y_k, const float* 
  *   d       head dimension: 16, 32, 64 or 128.   scale: usually 1/sqrt(d).
  * All pointers 16-byte aligned.  fp32 arithmetic and accumulation; in bf16 the probabilities S and dM are
  * rounded to bf16 before the second products (matrix cores), outputs rounded once.  Deterministic.
- * sbp_backward_attention_engine (host only) reports which kernels serve a size: 1 = matrix cores, the kept tokens of one
- * head fit LDS (bf16, d in {32, 64, 128}; n_k <= 256 at d = 64): one workgroup per (sample, head) up to 64 tokens, chunks of
- * 128 tokens above; 2 = matrix cores, beyond that size (bf16, d in {32, 64, 128}): chunks of 128 tokens, any n_k;
- * 0 = fp32 tensors (fp32 matrix cores at d in {32, 64, 128}) and d = 16 (plain kernel).
+ * sbp_backward_attention_engine (host only) reports which kernel serves a size: 1 = matrix cores, one workgroup per (sample,
+ * head) (bf16, d in {32, 64, 128}, n_k <= 64); 2 = matrix cores, chunks of 128 tokens (bf16, any more tokens); 3 = fp32 matrix
+ * cores (fp32 tensors, d in {32, 64, 128}); 0 = plain kernel (d = 16).  Calls of more than 2^23 chunks of 128 tokens over all
+ * samples and heads take 1 where a head fits LDS, else 0.
  */
 int32_t sbp_backward_attention_engine(int32_t n_k, int32_t d, int32_t dtype);
 int32_t sbp_backward_attention(const void* qkv_k, const void* A_k, const void* dA_k, const float* lse_k,

@@ -876,16 +876,24 @@ static size_t attn_lds_bytes(int n_k, int d) {
   return d == 32 ? AttnLds<32>::bytes(npad) : d == 64 ? AttnLds<64>::bytes(npad) : AttnLds<128>::bytes(npad);
 }
 
-// 2: tiled MFMA kernel, 1: MFMA kernel with one workgroup per (sample, head), 0: plain kernel
-int attention_engine(int32_t n_k, int32_t d, int32_t dtype) {
-  if (dtype != SBP_BF16) return 0;
-  if (d != 32 && d != 64 && d != 128) return 0;
-  const Options opt = options();
-  if (opt.attn_mode == 1) return 0;                         // explicit overrides (sbp_set_option "attn" = "plain" | "whole" | "tiled")
-  if (opt.attn_mode == 3) return 2;
+// Which kernel runs; decided here alone.  1: one workgroup per (sample, head), 2: tiled, 3: fp32 matrix cores, 0: plain.
+// bf16: one workgroup per head where a head is at most two blocks of 32 tokens (64 x 12 heads of 64, one workgroup / tiled: 12.3 /
+// 14.0 us at 49 tokens, 7.2 / 10.6 at 25; of 32: 8.6 / 9.9 and 5.2 / 7.8; of 128: 39.9 / 44.3 and 22.9 / 31.9); from three blocks on
+// the tiled kernel is ahead (64 x 6 heads: of 64 11.1 / 10.6 at 65 and 16.3 / 14.1 at 99; of 32 8.5 / 8.0 and 11.5 / 9.9; of 128
+// 32.4 / 27.5 and 44.2 / 39.1).
+static int attention_kernel(int64_t heads, int32_t n_k, int32_t d, int32_t dtype) {
+  const int mode = options().attn_mode;                     // explicit overrides (sbp_set_option "attn" = "plain" | "whole" | "tiled")
+  if ((d != 32 && d != 64 && d != 128) || mode == 1) return 0;
+  // (a grid of the tiled and fp32 kernels, two workgroups of 256 threads per chunk, stays below 2^32 threads)
+  const bool grid_fits = heads * ceil_div(n_k, kAttnChunk) < (1 << 23) - 8;
+  if (dtype != SBP_BF16) return grid_fits ? 3 : 0;
   const bool fits = attn_lds_bytes(n_k, d) <= kAttnMaxLds;
-  return fits ? 1 : 2;
+  if (mode == 0 ? n_k > 64 : (mode == 3 || !fits)) {
+    if (grid_fits) return 2;
+  }
+  return fits ? 1 : 0;
 }
+int attention_engine(int32_t n_k, int32_t d, int32_t dtype) { return attention_kernel(4096, n_k, d, dtype); }
 
 template <int D>
 static void launch_attn_mfma(const uint16_t* qkv, const uint16_t* A, const uint16_t* dA, const float* lse, int B, int n_k,
@@ -929,17 +937,11 @@ static void launch_attn_f32(const float* qkv, const float* A, const float* dA, c
 
 int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA, const float* lse, int32_t B, int32_t n_k,
                                   int32_t h, int32_t d, float scale, int32_t dtype, void* dqkv, hipStream_t s) {
-  const int engine = attention_engine(n_k, d, dtype);
-  // One workgroup per head where a head is at most two blocks of 32 tokens (64 x 12 heads of 64: 13.7 against 15.2 us at 50
-  // tokens, 7.8 against 10.5 at 25); from three blocks on the tiled kernel is ahead (27.6 against 30.1 us at 99, 67 against
-  // 81 at 197; d = 128: even at 99).
-  // (a grid of the tiled and fp32 kernels, two workgroups of 256 threads per chunk, stays below 2^32 threads)
-  const bool grid_fits = (int64_t)B * h * ceil_div(n_k, kAttnChunk) < (1 << 23) - 8;
-  const bool tiled = engine && grid_fits && (engine == 2 || (n_k > 64 && options().attn_mode == 0));
-  if (engine == 1 || tiled) {
+  const int kernel = attention_kernel((int64_t)B * h, n_k, d, dtype);
+  if (kernel == 1 || kernel == 2) {
     const uint16_t* q = (const uint16_t*)qkv; const uint16_t* a = (const uint16_t*)A; const uint16_t* g = (const uint16_t*)dA;
     uint16_t* o = (uint16_t*)dqkv;
-    if (tiled) {
+    if (kernel == 2) {
       if (d == 32) launch_attn_tiled<32>(q, a, g, lse, B, n_k, h, scale, o, s);
       else if (d == 64) launch_attn_tiled<64>(q, a, g, lse, B, n_k, h, scale, o, s);
       else launch_attn_tiled<128>(q, a, g, lse, B, n_k, h, scale, o, s);
@@ -948,14 +950,14 @@ int32_t launch_backward_attention(const void* qkv, const void* A, const void* dA
       else if (d == 64) launch_attn_mfma<64>(q, a, g, lse, B, n_k, h, scale, o, s);
       else launch_attn_mfma<128>(q, a, g, lse, B, n_k, h, scale, o, s);
     }
-  } else if (dtype == SBP_BF16) {
-    launch_attn_plain<uint16_t>((const uint16_t*)qkv, (const uint16_t*)A, (const uint16_t*)dA, lse, B, n_k, h, d, scale,
-                                (uint16_t*)dqkv, s);
-  } else if ((d == 32 || d == 64 || d == 128) && options().attn_mode != 1 && grid_fits) {
+  } else if (kernel == 3) {
     const float *q = (const float*)qkv, *a = (const float*)A, *g = (const float*)dA;
     if (d == 32) launch_attn_f32<32>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
     else if (d == 64) launch_attn_f32<64>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
     else launch_attn_f32<128>(q, a, g, lse, B, n_k, h, scale, (float*)dqkv, s);
+  } else if (dtype == SBP_BF16) {
+    launch_attn_plain<uint16_t>((const uint16_t*)qkv, (const uint16_t*)A, (const uint16_t*)dA, lse, B, n_k, h, d, scale,
+                                (uint16_t*)dqkv, s);
   } else {
     launch_attn_plain<float>((const float*)qkv, (const float*)A, (const float*)dA, lse, B, n_k, h, d, scale, (float*)dqkv, s);
   }

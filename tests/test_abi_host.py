@@ -242,10 +242,15 @@ def test_backward_attention_argument_errors_and_engine():
     assert call(n_k=0, q=None, a=None, g=None, l=None, o=None) == 0          # nothing kept: nothing to do
     assert call(q=None) == -1 and call(l=None) == -1 and call(o=None) == -1
     assert call(a=ctypes.c_void_p(260)) == -2                                # alignment
-    assert L.sbp_backward_attention_engine(99, 64, 1) == 1                   # bf16: matrix-core kernel
-    assert L.sbp_backward_attention_engine(256, 64, 1) == 1 and L.sbp_backward_attention_engine(257, 64, 1) == 2   # beyond one LDS image: tiled
-    assert L.sbp_backward_attention_engine(128, 128, 1) == 1 and L.sbp_backward_attention_engine(129, 128, 1) == 2
-    assert L.sbp_backward_attention_engine(99, 64, 0) == 0 and L.sbp_backward_attention_engine(99, 16, 1) == 0
+    for d in (32, 64, 128):                                                  # bf16: one workgroup per head up to 64 tokens, then tiled
+        assert [L.sbp_backward_attention_engine(n, d, 1) for n in (1, 64, 65, 256, 257, 4096)] == [1, 1, 2, 2, 2, 2]
+    assert L.sbp_backward_attention_engine(99, 64, 0) == 3                   # fp32 matrix cores
+    assert L.sbp_backward_attention_engine(99, 16, 0) == 0 and L.sbp_backward_attention_engine(99, 16, 1) == 0
+    for name, bf16, f32 in ((b"plain", [0, 0, 0], 0), (b"whole", [1, 1, 2], 3), (b"tiled", [2, 2, 2], 3)):   # explicit overrides
+        assert L.sbp_set_option(b"attn", name) == 0
+        assert [L.sbp_backward_attention_engine(n, 64, 1) for n in (25, 256, 257)] == bf16
+        assert L.sbp_backward_attention_engine(99, 64, 0) == f32
+    assert L.sbp_set_option(b"attn", None) == 0
     assert L.sbp_backward_attention_engine(99, 48, 1) == -1
 
 

@@ -47,8 +47,8 @@ CASES = [  # B, n, h, d, n_k
     (2, 50, 2, 64, 1),        # a single kept token
     (2, 70, 2, 64, 32),       # exactly one block
     (1, 70, 1, 64, 33),
-    (1, 300, 1, 64, 256),     # the largest size of the matrix-core kernel at d = 64
-    (1, 300, 1, 64, 257),     # one more: tiled over chunks of 128 tokens (three chunks, the last with one token)
+    (1, 300, 1, 64, 256),     # two full chunks (the most that one workgroup per head could hold at d = 64)
+    (1, 300, 1, 64, 257),     # one more: three chunks, the last with one token
     (1, 600, 2, 64, 512),     # four full chunks
     (1, 1100, 1, 64, 1024),
     (1, 400, 1, 32, 390),
@@ -68,11 +68,11 @@ def test_attention_backward_matches_oracle(B, n, h, d, n_k, dtype):
 
 
 def test_engine_choice():
-    assert sbp.backward_attention_engine(99, 64, sbp.BF16) == "mfma"
-    assert sbp.backward_attention_engine(256, 64, sbp.BF16) == "mfma"
+    assert sbp.backward_attention_engine(64, 64, sbp.BF16) == "mfma"
+    assert sbp.backward_attention_engine(99, 64, sbp.BF16) == "mfma_tiled"
     assert sbp.backward_attention_engine(257, 64, sbp.BF16) == "mfma_tiled"
     assert sbp.backward_attention_engine(4096, 128, sbp.BF16) == "mfma_tiled"
-    assert sbp.backward_attention_engine(99, 64, sbp.F32) == "plain"
+    assert sbp.backward_attention_engine(99, 64, sbp.F32) == "mfma_f32"
     assert sbp.backward_attention_engine(99, 16, sbp.BF16) == "plain"
 
 
@@ -80,7 +80,7 @@ def test_plain_kernel_on_bf16_matches_oracle():
     with sbp.options(attn="plain"):
         assert sbp.backward_attention_engine(99, 64, sbp.BF16) == "plain"
         errs = _run(2, 197, 3, 64, _keep_sets(2, 197, 99, 7), "bf16", 9)
-    assert sbp.backward_attention_engine(99, 64, sbp.BF16) == "mfma"
+    assert sbp.backward_attention_engine(99, 64, sbp.BF16) == "mfma_tiled"
     assert max(errs) <= TOL_BF16, errs
 
 
