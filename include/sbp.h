@@ -395,7 +395,8 @@ int32_t sbp_backward_layerscale(const void* dU_k, const void* Y_k, const float* 
  * rounded to bf16 before the second products (matrix cores), outputs rounded once.  Deterministic.
  * sbp_backward_attention_engine (host only) reports which kernel serves a size: 1 = matrix cores, one workgroup per (sample,
  * head) (bf16, d in {32, 64, 128}, n_k <= 64); 2 = matrix cores, chunks of 128 tokens (bf16, any more tokens); 3 = fp32 matrix
- * cores (fp32 tensors, d in {32, 64, 128}); 0 = plain kernel (d = 16).  Calls of more than 2^23 chunks of 128 tokens over all
+ * cores (fp32 tensors, d in {32, 64, 128}); 0 = plain kernel (d = 16; fp32 heads of up to 2, 4, 16 tokens at d = 32, 64, 128 -
+ * of up to 1, 2, 4 in calls of fewer than 256 heads over all samples, which the report does not know).  Calls of more than 2^23 chunks of 128 tokens over all
  * samples and heads take 1 where a head fits LDS, else 0.
  */
 int32_t sbp_backward_attention_engine(int32_t n_k, int32_t d, int32_t dtype);

@@ -8,6 +8,7 @@
 //   dQ_i  = scale sum_j dM_ij k_j,   dK_j = scale sum_i dM_ij q_i
 // Kernels: for bf16 an MFMA kernel with one workgroup per sample and head (all kept tokens of the head in LDS) and a tiled one
 // for any number of tokens; for fp32 tensors a tiled one on the fp32 matrix cores; a plain kernel for d = 16.
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -881,12 +882,19 @@ static size_t attn_lds_bytes(int n_k, int d) {
 // 14.0 us at 49 tokens, 7.2 / 10.6 at 25; of 32: 8.6 / 9.9 and 5.2 / 7.8; of 128: 39.9 / 44.3 and 22.9 / 31.9); from three blocks on
 // the tiled kernel is ahead (64 x 6 heads: of 64 11.1 / 10.6 at 65 and 16.3 / 14.1 at 99; of 32 8.5 / 8.0 and 11.5 / 9.9; of 128
 // 32.4 / 27.5 and 44.2 / 39.1).
+// fp32: the matrix-core kernel computes blocks of 32 tokens whatever their number, so the plain one is ahead for heads of a few
+// tokens, for the more the wider the head (plain / matrix cores, 1024 x 8 heads: of 32 61 / 76 us at 2 tokens and 97 / 76 at 4; of 64
+// 185 / 236 at 4 and 256 / 236 at 6; of 128 652 / 743 at 16 and 802 / 762 at 20) and for fewer where a few heads leave the chip to
+// latencies (4 x 4 heads: of 32 5.1 / 5.4 at 1 and 6.1 / 5.5 at 2; of 64 7.6 / 8.1 at 2 and 10.2 / 8.1 at 4; of 128 11.7 / 13.4 at 4
+// and 15.0 / 13.4 at 6).
+static int few_tokens_f32(int64_t heads, int32_t d) { return heads < 256 ? d / 32 : std::max(2, d * d / 1024); }
+
 static int attention_kernel(int64_t heads, int32_t n_k, int32_t d, int32_t dtype) {
   const int mode = options().attn_mode;                     // explicit overrides (sbp_set_option "attn" = "plain" | "whole" | "tiled")
   if ((d != 32 && d != 64 && d != 128) || mode == 1) return 0;
   // (a grid of the tiled and fp32 kernels, two workgroups of 256 threads per chunk, stays below 2^32 threads)
   const bool grid_fits = heads * ceil_div(n_k, kAttnChunk) < (1 << 23) - 8;
-  if (dtype != SBP_BF16) return grid_fits ? 3 : 0;
+  if (dtype != SBP_BF16) return grid_fits && (mode != 0 || n_k > few_tokens_f32(heads, d)) ? 3 : 0;
   const bool fits = attn_lds_bytes(n_k, d) <= kAttnMaxLds;
   if (mode == 0 ? n_k > 64 : (mode == 3 || !fits)) {
     if (grid_fits) return 2;

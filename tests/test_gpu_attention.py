@@ -202,3 +202,13 @@ def test_f32_more_heads_than_one_grid_of_the_matrix_core_kernel_holds():
             got = out[b * n_k:(b + 1) * n_k, i * h * d + head * d:i * h * d + (head + 1) * d]
             assert nerr(f64(got), f64(w[i])) <= TOL_F32
     assert not torch.isnan(out).any()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,h", [(2, 2), (40, 8)])
+@pytest.mark.parametrize("n_k", [1, 2, 3, 4, 5, 16, 17])
+def test_f32_heads_of_a_few_tokens(B, h, d, n_k):
+    # the plain kernel up to 2, 4, 16 tokens (1, 2, 4 where there are few heads), the matrix cores beyond: the same gradients
+    assert max(_run(B, 20, h, d, _keep_sets(B, 20, n_k, 35), "f32", 37)) <= TOL_F32
+    few = {32: 2, 64: 4, 128: 16}[d]
+    assert sbp.backward_attention_engine(n_k, d, sbp.F32) == ("plain" if n_k <= few else "mfma_f32")
