@@ -23,7 +23,6 @@ GRID_PER_CELL, GRID_SHARED, RANDOM_MASK, TEMPORAL = 0, 1, 2, 3
 FLAG_DY_COMPACT, FLAG_DX_COMPACT, FLAG_ACCUMULATE_DW, FLAG_DW_OUT_BF16, FLAG_XK_KMAJOR = 1, 2, 4, 8, 16
 LAYOUT_ROWS, LAYOUT_KMAJOR = 0, 1
 
-_raw_stream = torch._C._cuda_getCurrentRawStream
 _DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
 
 
@@ -45,8 +44,9 @@ def _dev(t, name):
 
 
 def _stream(device) -> int:
-    # (the handle alone: a Stream object made on every call cost 3 us of host time, 10 of the 40 us of a small layer's three calls)
-    return _raw_stream(device.index)
+    # (the handle alone: a Stream object made on every call cost 3 us of host time, 10 of the 40 us of a small layer's three calls;
+    # looked up here: a torch without GPU support does not have it)
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def make_desc(B, P, H, W, k, seed, stream_id, mode=GRID_PER_CELL, per_sample=True, cell=2) -> SampleDesc:

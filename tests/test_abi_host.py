@@ -3,6 +3,8 @@ bad arguments before touching the GPU (none of these calls launches a kernel).""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -26,6 +28,13 @@ def test_library_exports_every_declared_symbol():
     for n in names:
         assert hasattr(handle, n), n
     assert sorted(_lib.PROTOTYPES) == names
+
+
+def test_package_imports_with_a_torch_without_gpu_support():
+    # such a torch has no stream functions; the host-only calls need none
+    code = ("import torch\nfor n in [n for n in dir(torch._C) if n.startswith('_cuda_')]: delattr(torch._C, n)\n"
+            "import paper_2210_00129_amd as sbp\nassert sbp.keep_count(2, 0, 8, 8, 2) == 64")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=100)
 
 
 def test_status_strings():
