@@ -741,8 +741,9 @@ __global__ void __launch_bounds__(DWF_THREADS, 2) dw_fused_kernel(const DwFusedA
 // 2 channel halves x (two row quads, R = 8, or two halves of the columns, R = 4, for maps with few tiles).  dX goes
 // through LDS so that stores are 16 bytes per lane.  Dropped and outside positions are zeros in LDS.  The next tile's rows
 // are in flight in registers while a tile is computed.
-// A band product multiplies a gradient with zeros, so an infinity or NaN would reach columns outside its 7 x 7
-// window: staging looks for them, and such a tile's dX is computed again tap by tap.
+// A band product multiplies a gradient with zeros, and so do the dWd products at the edges of a tile and of the map: an
+// infinity or NaN would reach dX outside its 7 x 7 window and taps that reach outside the map.  Staging looks for them;
+// such a tile's dX is computed again tap by tap, and its share of dWd and db over the pairs there are.
 // Measured (kernel + partial sums): 2 x 200 x 336 x 128, a quarter kept, 90 -> 43 us; 2 x 50 x 84 x 512, half kept,
 // 28.4 -> 21.4; 2 x 25 x 42 x 768 18.5 -> 15.4; 2 x 7 x 7 x 768 18.5 -> 17.8, all against the dot2 kernel above.  With the
 // products left out 26 us remain of the 43, with the loads and stores left out 33: staging and products still overlap only
@@ -795,7 +796,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
   char* gt = lds;                              // gradient rows y0 - 3 .., quads -1 .. TQ
   char* xt = lds + GR * DWM_ROWP;              // X rows y0 .., quads -1 .. TQ (both ends zero)
   char* ot = xt + R * DWM_ROWP;                // dX of the tile
-  int* bad = reinterpret_cast<int*>(ot + R * DWM_ROWP);   // [2]: a non-finite gradient in the tile, by tile parity
+  int* bad = reinterpret_cast<int*>(ot + R * DWM_ROWP);   // [2]: a non-finite gradient in the tile, by tile parity; then in any tile
 
   // ---- compute role
   const bool dx_role = wave < 4;
@@ -816,13 +817,16 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
     const int row = e / (DWF_SLAB * 2), l = (e >> 1) & (DWF_SLAB - 1);
     *reinterpret_cast<uint2*>(xt + row * DWM_ROWP + l * DWM_PITCH + ((e & 1) ? (TQ + 1) * 8 : 0)) = make_uint2(0, 0);
   }
-  if (tid < 2) bad[tid] = 0;
+  if (tid < 3) bad[tid] = 0;
+  float* extra = reinterpret_cast<float*>(bad + 4);               // [50][32]: dWd and db of the tiles with non-finite gradients, if bad[2]
   auto origin = [&](int tile, int& b, int& y0, int& x0) {
     const int tx = tile % a.tiles_x, rest = tile / a.tiles_x;
     y0 = (rest % a.tiles_y) * R;
     b = rest / a.tiles_y;
     x0 = tx * TQ * 4;
   };
+  auto x0_of = [&](int tile) { return tile % a.tiles_x * TQ * 4; };
+  auto y0_of = [&](int tile) { return tile / a.tiles_x % a.tiles_y * R; };
   // a tile's addresses: a scalar base per tile + an offset per thread.  The offset counts from row y0 - 3, so it spans more
   // rows than a low map has, and is kept in 64 bits (no more registers: 128, 5 spilled, as with 32)
   const uint64_t rowb = (uint64_t)a.W * a.C * 2, colb = (uint64_t)a.C * 2;
@@ -904,6 +908,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
     first();                                   // (after the weights: together they spill)
     const int qa = XS == 1 ? 0 : (xs ? qm : 0), qb = XS == 1 ? TQ : (xs ? TQ : qm);
     char* obase = ot + (rq * 4 + n) * DWM_ROWP + ch * DWM_PITCH + 8;
+    bool any_bad = false;
     int parity = 0;
     for (int tile = wgx; tile < a.ntiles; tile += a.nwg_x, parity ^= 1) {
       store(parity);
@@ -951,9 +956,29 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
         }
       }
       __syncthreads();                         // B
-      if constexpr (DX) {
-        if (bad[parity]) {                     // rare: this tile's dX tap by tap, no product with a zero of the band
-          const int l = tid & 31, c = min(slab0 + l, a.C - 1);
+      if (bad[parity]) {                       // rare
+        const int l = tid & 31;
+        if constexpr (DW) {                    // the tile's share of dWd and db, tap by tap over the pairs there are (the other role skipped it)
+          const int rows = min(R, a.H - y0_of(tile)), cols = min(4 * TQ, a.W - x0_of(tile));
+#pragma unroll 1
+          for (int tap = tid >> 5; tap < NT; tap += 8) {
+            const int u = tap / 7, v = tap - u * 7;          // (tap 49: the column sums)
+            const char* gl = gt + (tap < 49 ? 6 - u : 3) * DWM_ROWP + l * DWM_PITCH + 2 * (tap < 49 ? 7 - v : 4);
+            const char* xl = xt + l * DWM_PITCH + 8;
+            float sum = any_bad ? extra[tap * DWF_SLAB + l] : 0.f;
+#pragma unroll 1
+            for (int row = 0; row < rows; ++row, gl += DWM_ROWP, xl += DWM_ROWP)
+#pragma unroll 1
+              for (int x = 0; x < cols; ++x)
+                sum = fmaf(DwElem<uint16_t>::ld(reinterpret_cast<const uint16_t*>(gl) + x),
+                           tap < 49 ? DwElem<uint16_t>::ld(reinterpret_cast<const uint16_t*>(xl) + x) : 1.f, sum);
+            extra[tap * DWF_SLAB + l] = sum;
+          }
+          any_bad = true;
+          if (tid == 0) bad[2] = 1;
+        }
+        if constexpr (DX) {                    // its dX tap by tap, no product with a zero of the band
+          const int c = min(slab0 + l, a.C - 1);
           for (int e = tid >> 5; e < R * TQ * 4; e += 8) {
             const int row = e / (TQ * 4), x = e - row * TQ * 4;
             float d = 0.f;
@@ -963,8 +988,10 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
                          DwElem<uint16_t>::ld(a.Wd + (long long)((6 - i) * 7 + 6 - t) * a.C + c), d);
             reinterpret_cast<uint16_t*>(ot + row * DWM_ROWP + l * DWM_PITCH + 8)[x] = (uint16_t)(dw_pack(d, 0.f) & 0xffffu);
           }
-          __syncthreads();
         }
+        __syncthreads();
+      }
+      if constexpr (DX) {
         int b, y0, x0;                         // dX out: 8 lines of a quad -> 16 bytes of 4 positions
         origin(tile, b, y0, x0);
         const int x = x0 + 4 * xq;
@@ -1008,12 +1035,13 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
       store(parity);
       if (DW && xon) dwm_store_quads(xt + xoff, DWM_PITCH, XA);
       __syncthreads();                         // A
+      const int tile_bad = bad[parity];
       if (tile + a.nwg_x < a.ntiles) {
         fetch(tile + a.nwg_x);
         fetch_x(tile + a.nwg_x);
         look(tile + 2 * a.nwg_x);
       }
-      if constexpr (DW) {
+      if (DW && !tile_bad) {
         dwm_s4 xp[2];                          // X quads t - 1 + h (two rows further on for p = 1)
 #pragma unroll
         for (int p = 0; p < 2; ++p) xp[p] = ld(xbase + 2 * p * DWM_ROWP + 8 * max(ta - 1 + h, -1));
@@ -1041,7 +1069,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
         }
       }
       __syncthreads();                         // B
-      if (DX && bad[parity]) __syncthreads();
+      if (tile_bad) __syncthreads();
     }
     // the workgroup's partial sums: the accumulators through LDS
     if constexpr (DW) {
@@ -1059,6 +1087,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
   }
   if constexpr (DW) {                          // every tap from its 2 elements x 2 wavefronts
     const float* red = reinterpret_cast<const float*>(lds);
+    const int any_bad = bad[2];
     for (int o = tid; o < NT * DWF_SLAB; o += DWM_THREADS) {
       const int tap = o / DWF_SLAB, cl = o - tap * DWF_SLAB;
       const int w0 = cl >> 4, l0 = (cl & 15) * 4;
@@ -1079,6 +1108,7 @@ __global__ void __launch_bounds__(DWM_THREADS, 4) dw_mfma_kernel(const DwMfmaArg
 #pragma unroll
           for (int j = 0; j < 4; ++j) sum += red[((w0 + 2 * w) * 33 + 32) * 64 + l0 + j];
       }
+      if (any_bad) sum += extra[o];
       if (slab0 + cl < a.C) a.part[((long long)wgx * NT + tap) * a.C + slab0 + cl] = sum;
     }
   }
@@ -1123,7 +1153,7 @@ static DwFusedShape dw_fused_shape(int B, int H, int W, int C, int ks) {
 }
 
 // Tile of the matrix-core kernel: TQ column quads x R rows (8, or 4 with the columns split over two wavefronts), two
-// workgroups per CU (at most 71 KB of LDS each); chosen for the fewest rounds x tile time, a tile's time taken as a fixed
+// workgroups per CU (at most 77 KB of LDS each); chosen for the fewest rounds x tile time, a tile's time taken as a fixed
 // part for staging, latency and barriers plus a part per quad.
 struct DwMfmaShape { int R, TQ, tiles_y, tiles_x, nwg_x, slabs; size_t lds; };
 static DwMfmaShape dw_mfma_shape(int B, int H, int W, int C) {
@@ -1139,7 +1169,7 @@ static DwMfmaShape dw_mfma_shape(int B, int H, int W, int C) {
       const double steps = R == 8 ? TQ : 0.5 * TQ + 0.5;
       const double cost = (double)ceil_div(ntiles, nwg_x) * (304 * steps + 256 + 1500) + (nwg_x * slabs > DWM_PER_CU * 256 ? 1 : 0);
       if (best.R == 0 || cost < best_cost) {
-        const size_t tile = (size_t)(R + 6 + 2 * R) * DWM_ROWP + 16, red = 4 * 33 * 64 * sizeof(float);
+        const size_t tile = (size_t)(R + 6 + 2 * R) * DWM_ROWP + 16 + 50 * DWF_SLAB * sizeof(float), red = 4 * 33 * 64 * sizeof(float);
         best_cost = cost;
         best = DwMfmaShape{R, TQ, tiles_y, tiles_x, nwg_x, slabs, std::max(tile, red)};
       }

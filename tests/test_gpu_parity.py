@@ -629,6 +629,33 @@ def test_dropped_rows_of_the_largest_row_count(call):
     assert not any(int(part.count_nonzero()) for part in words.split(2 ** 30))
 
 
+@pytest.mark.parametrize("geom", [(1, 8, 28, 32), (1, 9, 29, 40), (2, 4, 8, 64), (1, 17, 57, 96), (1, 5, 3, 2048), (2, 13, 61, 40)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_dwconv_non_finite_gradients_reach_the_taps_they_meet(geom, value):
+    # corners, edges, the inside and both sides of a tile boundary: the tap (u, v) of the channel is non-finite exactly where
+    # the gradient's position has an X at (u - 3, v - 3) inside the map; the other channels and the other taps keep their values
+    B, H, W, C = geom
+    X, Wd, dY = si.dwconv_case(B, H, W, C, 7, 173, "bf16")
+    X = torch.where(X == 0, torch.ones_like(X), X)
+    idx = torch.arange(B * H * W, dtype=torch.int32, device="cuda")
+    clean = [f64(t) for t in sbp.backward_dwconv(dY.cuda(), idx, X.cuda(), Wd.cuda(), want=("dWd", "db"))[:2]]
+    for i, (y, x) in enumerate({(0, 0), (0, W - 1), (H - 1, 0), (H - 1, W - 1), (H // 2, W // 2), (min(3, H - 1), min(27, W - 1)),
+                                (min(4, H - 1), min(28, W - 1)), (min(8, H - 1), 0)}):
+        c = (5 * i) % C
+        bad = dY.clone()
+        bad[B - 1, y, x, c] = value
+        for want in (("dWd", "db", "dX"), ("dWd", "db")):
+            dWd, db, _ = (None if t is None else f64(t) for t in sbp.backward_dwconv(bad.cuda(), idx, X.cuda(), Wd.cuda(), want=want))
+            meets = np.array([[0 <= y + u - 3 < H and 0 <= x + v - 3 < W for v in range(7)] for u in range(7)])
+            assert np.array_equal(~np.isfinite(dWd[:, :, c]), meets) and not np.isfinite(db[c])
+            keep = np.arange(C) != c
+            assert nerr(dWd[:, :, keep], clean[0][:, :, keep]) <= TOL_F32 and nerr(db[keep], clean[1][keep]) <= TOL_F32
+            zeroed = dY.clone()
+            zeroed[B - 1, y, x, c] = 0
+            rest = f64(sbp.backward_dwconv(zeroed.cuda(), idx, X.cuda(), Wd.cuda(), want=("dWd",))[0])[:, :, c]
+            assert np.max(np.abs((dWd[:, :, c] - rest)[~meets]), initial=0.0) <= TOL_F32 * np.max(np.abs(rest))
+
+
 def test_dwconv_single_kept_position_stamps_kernel():
     B, H, W, C, ks = 1, 9, 11, 64, 7
     X, Wd, dY = si.dwconv_case(B, H, W, C, ks, 141, "f32")
