@@ -1155,7 +1155,13 @@ static DwFusedShape dw_fused_shape(int B, int H, int W, int C, int ks) {
 // Tile of the matrix-core kernel: TQ column quads x R rows (8, or 4 with the columns split over two wavefronts), two
 // workgroups per CU (at most 77 KB of LDS each); chosen for the fewest rounds x tile time, a tile's time taken as a fixed
 // part for staging, latency and barriers plus a part per quad.
-struct DwMfmaShape { int R, TQ, tiles_y, tiles_x, nwg_x, slabs; size_t lds; };
+// A workgroup keeps running sums of dWd over all its tiles.  Where one round of workgroups would walk more than DWM_CHAIN tiles
+// each, dWd is made by as many rounds as it takes: 2-norm against 64 bits, one round / now / the 256 workgroups of the dot2 kernel,
+// 2.2e-7 / 1.4e-7 / 1.4e-7 at 4 x 200 x 336 x 384 (29 tiles; 193 -> 225 us), 1.7e-7 / 1.1e-7 / 1.1e-7 at 2 x 100 x 168 x 2048 (20 tiles;
+// 142 -> 152 us); with 8 tiles 1.2e-7 / 1.1e-7 (2 x 100 x 168 x 768).  Adding the sums up in memory of their own every 4 tiles
+// instead took 262 us for the first, and slowed every launch.
+static constexpr int DWM_CHAIN = 8;
+struct DwMfmaShape { int R, TQ, tiles_y, tiles_x, nwg_x, nwg_dw, slabs; size_t lds; };
 static DwMfmaShape dw_mfma_shape(int B, int H, int W, int C) {
   DwMfmaShape best{};
   double best_cost = 0;
@@ -1171,7 +1177,8 @@ static DwMfmaShape dw_mfma_shape(int B, int H, int W, int C) {
       if (best.R == 0 || cost < best_cost) {
         const size_t tile = (size_t)(R + 6 + 2 * R) * DWM_ROWP + 16 + 50 * DWF_SLAB * sizeof(float), red = 4 * 33 * 64 * sizeof(float);
         best_cost = cost;
-        best = DwMfmaShape{R, TQ, tiles_y, tiles_x, nwg_x, slabs, std::max(tile, red)};
+        const int nwg_dw = (int)std::min<int64_t>(ntiles, (int64_t)nwg_x * ceil_div(ceil_div(ntiles, nwg_x), DWM_CHAIN));
+        best = DwMfmaShape{R, TQ, tiles_y, tiles_x, nwg_x, nwg_dw, slabs, std::max(tile, red)};
       }
     }
   return best;
@@ -1185,7 +1192,7 @@ DwPlan plan_dwconv(int32_t B, int32_t H, int32_t W, int32_t C, int32_t ks, int64
   // (its parallelism does not depend on K), the plain path slices the kept list.
   const int64_t row_tiles = (int64_t)B * H * ceil_div(W, DW_TX);
   p.nparts = (int)std::max<int64_t>(1, std::min<int64_t>(DW_MAX_PARTS, std::max<int64_t>(ceil_div(row_tiles, 2 * DW_GROUPS), 1)));
-  if (ks == 7) p.nparts = std::max(p.nparts, dw_mfma_shape(B, H, W, C).nwg_x);                       // the matrix-core kernel's workgroups
+  if (ks == 7) p.nparts = std::max(p.nparts, dw_mfma_shape(B, H, W, C).nwg_dw);                      // the matrix-core kernel's workgroups
   if (ks == 3) p.nparts = std::max(p.nparts, dw_fused_shape(B, H, W, C, ks).nwg_x);                  // the LDS-tiled kernel's workgroups
   size_t off = 0;
   p.off_inv = off;
@@ -1246,10 +1253,10 @@ int32_t launch_backward_dwconv(const DwPlan& p, const void* dY, const int32_t* i
       a.dX = (uint16_t*)dX; a.part = part;
       a.B = B; a.H = H; a.W = W; a.C = C;
       a.TQ = f.TQ; a.tiles_y = f.tiles_y; a.tiles_x = f.tiles_x; a.ntiles = B * f.tiles_y * f.tiles_x;
-      a.nwg_x = f.nwg_x; a.slabs = f.slabs;
+      a.nwg_x = want_dw ? f.nwg_dw : f.nwg_x; a.slabs = f.slabs;
       a.magic_g = 65536 / (f.TQ + 2) + 1; a.magic_x = 65536 / f.TQ + 1;
-      nparts = f.nwg_x;
-      const dim3 grid((unsigned)(f.nwg_x * f.slabs));
+      nparts = a.nwg_x;
+      const dim3 grid((unsigned)(a.nwg_x * f.slabs));
       if (f.lds > 64 * 1024) {
         static std::once_flag once7;
         std::call_once(once7, [] {

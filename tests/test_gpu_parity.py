@@ -656,6 +656,27 @@ def test_dwconv_non_finite_gradients_reach_the_taps_they_meet(geom, value):
             assert np.max(np.abs((dWd[:, :, c] - rest)[~meets]), initial=0.0) <= TOL_F32 * np.max(np.abs(rest))
 
 
+@pytest.mark.parametrize("geom", [(2, 100, 168, 2048), (4, 200, 336, 384)])
+def test_dwconv_sums_of_many_channels_are_as_exact_as_of_few(geom):
+    # with many channels a round of workgroups walks 20 or 29 tiles each, with 32 channels 1 or 3.  Running sums of at most 8
+    # tiles of 16 additions against 1 tile, then up to 256 partial sums: the error grows by at most sqrt((8 16 + 256) / (16 + 256))
+    B, H, W, C = geom
+    g = torch.Generator(device="cuda").manual_seed(9)
+    X, dY = (torch.randn(B, H, W, C, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    idx = torch.arange(0, B * H * W, 2, dtype=torch.int32, device="cuda")
+    err = []
+    x32, d32 = X[..., :32].contiguous(), dY[..., :32].contiguous()
+    kept = torch.zeros(B * H * W, 1, dtype=torch.float64, device="cuda")
+    kept[idx.long()] = 1
+    G = (d32.double().view(-1, 32) * kept).view(B, H, W, 32)
+    P = torch.nn.functional.pad(x32.double(), (0, 0, 3, 3, 3, 3))
+    ref = torch.stack([(G * P[:, u:u + H, v:v + W]).sum((0, 1, 2)) for u in range(7) for v in range(7)]).view(7, 7, 32)
+    for x, d in ((X, dY), (x32, d32)):
+        dWd = sbp.backward_dwconv(d, idx, x, torch.zeros(7, 7, x.shape[-1], dtype=torch.bfloat16, device="cuda"), want=("dWd",))[0]
+        err.append((dWd[..., :32].double() - ref).norm().item())
+    assert err[0] <= 1.2 * err[1]
+
+
 def test_dwconv_single_kept_position_stamps_kernel():
     B, H, W, C, ks = 1, 9, 11, 64, 7
     X, Wd, dY = si.dwconv_case(B, H, W, C, ks, 141, "f32")
