@@ -171,7 +171,7 @@ size_t sbp_backward_linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t 
 
 /*
  * Host only.  Which kernels sbp_backward_linear runs for these sizes (a report for logs and
- * benchmarks; the results do not depend on it): SBP_ENGINE_PLAIN (fp32 matrix cores: fp32 tensors, or
+ * benchmarks; for a call that wants dX and dW; the results do not depend on it): SBP_ENGINE_PLAIN (fp32 matrix cores: fp32 tensors, or
  * channel counts that are not multiples of 8), SBP_ENGINE_MFMA (128 x 128 tiles), SBP_ENGINE_MFMA_LARGE (256-wide tiles, one
  * workgroup per CU); -1 on invalid sizes.  If split_count is not NULL it receives the number of
  * fp32 partial sums of dW that the reduction adds.

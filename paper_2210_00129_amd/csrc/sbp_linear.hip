@@ -629,22 +629,43 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
 // Measured, 128 tiles / large tiles: 20.6 / 25.8 us (1500 rows, 1024 x 1024), 26.5 / 33.9 (16800, 512 -> 256), 41.0 / 49.0
 // (33600, 512 -> 256), 26.3 / 29.7 (8400, 1024 -> 256), 28.2 / 28.6 (4200, 768 x 768); 37.2 / 32.9 (6336, 768 x 768),
 // 41.1 / 37.2 (4200, 512 -> 2048), 41.0 / 35.6 (8400, 768 x 768), 67.6 / 62.6 (33600, 1024 -> 256).
-static bool general_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns) {
+// Layers that whole 256-wide tiles cover keep them where a dX tile is long (Cout) or the tiles are many: nothing is padded there,
+// and the large tiles take 0.7 to 0.85 of their simulated cost.  Of the 271 shapes of 1024 to 67200 rows that the estimate sends to
+// the 128 tiles these 42 are on average faster with the large ones, e.g. 128 tiles / large: 48.7 / 41.4 us (2100 rows, 1024 -> 3072),
+// 35.0 / 30.9 (4200, 512 -> 1536), 38.3 / 35.1 (1500, 2048 -> 1536); the others are 0.98 to 1.9 times as fast with the 128 tiles.
+// dX alone: where its tiles are long and not many (34.9 / 28.6, 19.6 / 16.9, but 20.9 / 23.1 for the third); dW alone: nowhere.
+static bool whole_tiles_ahead(int32_t Cin, int32_t Cout, int want) {
+  if (Cin % big::BT || Cout % big::BT || !(want & kWantDx)) return false;
+  if (want & kWantDw) return Cout >= 1536 || (int64_t)Cin * Cout >= 1536 * 1024;
+  return Cout >= 1536 && Cin <= 1536;
+}
+static bool general_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns, int want) {
+  if (whole_tiles_ahead(Cin, Cout, want)) return false;
   return 12000.0 + 1550.0 * (4e-9 * (double)K * Cin * Cout) < 0.9 * big_cost_ns;
 }
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general);
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general, int want);
 
 // X_k in row groups is read by the large-tile engine only (the other one first copies it back to rows), and a layer whose
 // 128-tile splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by time.
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  if (flags & SBP_FLAG_XK_KMAJOR) return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
-  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true);
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, int want) {
+  if (flags & SBP_FLAG_XK_KMAJOR) return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false, want);
+  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true, want);
   if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
-  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
+  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false, want);
 }
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general) {
+// whatever outputs a call wants
+size_t linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  size_t bytes = plan_linear(M, K, Cin, Cout, dtype, flags, kWantDx | kWantDw).bytes;
+  if (dtype == SBP_BF16 && Cin % big::BT == 0 && Cout % big::BT == 0) {      // (the layers whose engine depends on it)
+    bytes = std::max(bytes, plan_linear(M, K, Cin, Cout, dtype, flags, kWantDx).bytes);
+    bytes = std::max(bytes, plan_linear(M, K, Cin, Cout, dtype, flags, kWantDw).bytes);
+  }
+  return bytes;
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general, int want) {
   LinearPlan p{};
   p.mfma = dtype == SBP_BF16 && Cin % 8 == 0 && Cout % 8 == 0;
   p.bm_w = p.bn_w = 128;
@@ -659,7 +680,7 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
     bool pays = opt.tile_mode == 0 && Cin >= big::BT && Cout >= big::BT && K >= 1024;
     if (pays) {
       const BigChoice c = choose_big(M, K, Cin, Cout);
-      pays = c.fill >= 0.45 && !(may_prefer_general && general_engine_ahead(K, Cin, Cout, c.cost_ns));
+      pays = c.fill >= 0.45 && !(may_prefer_general && general_engine_ahead(K, Cin, Cout, c.cost_ns, want));
     }
     p.big = fits && (opt.tile_mode == 2 || pays);
   }
@@ -1254,7 +1275,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
       const sbp_linear_layer& l = L[i];
       flops += 4.0 * (double)l.K * l.Cin * l.Cout;
       general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !((uintptr_t)l.dW & 15) &&
-                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags).big;
+                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, 0).big;
     }
     if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) p.fused = false;
   }
@@ -1263,7 +1284,9 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   size_t off = 0, seq_bytes = 0;
   for (int i = 0; i < n; ++i) {
     if (!p.fused) p.lay[i].off = seq_bytes;
-    seq_bytes += align_up(plan_linear(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags).bytes, 256);
+    // (the layer may run in one launch with the others or by itself)
+    seq_bytes += align_up(std::max(plan_linear(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags, 0).bytes,
+                                   linear_workspace(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags)), 256);
   }
   p.bytes = seq_bytes;
   if (!p.fused) return p;
@@ -1320,7 +1343,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
   LinearPlan lp[kMaxBatch];
   for (int i = 0; i < p.n; ++i) {
     const sbp_linear_layer& l = L[i];
-    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
+    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, 0);
     if (!lp[i].mfma || lp[i].big || lp[i].bm_w != 128 || lp[i].nw_w != 4 || lp[i].kb != 64 || l.K < 1) return false;
     if (l.flags & SBP_FLAG_XK_KMAJOR) return false;
     if (!l.dW && !l.db && !l.dX) return false;
@@ -1412,7 +1435,7 @@ int32_t launch_backward_linear_batch(const BatchPlan& p, const sbp_linear_layer*
     for (int i = 0; i < p.n; ++i) {
       const sbp_linear_layer& l = L[i];
       if (!l.dW && !l.db && !l.dX) continue;
-      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
+      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, linear_want(l.dW, l.db, l.dX));
       const int32_t st = launch_backward_linear(lp, l.dY, l.idx, l.inv, l.X_k, l.W, l.M, l.K, l.Cin, l.Cout, dtype, l.dW,
                                                 l.db, l.dX, wsb + p.lay[i].off, l.flags, s);
       if (st != SBP_OK) return st;

@@ -237,6 +237,17 @@ def test_rowwise_steps_argument_errors():
     assert ln(dg=None, db=None, dX=None) == 0
 
 
+def test_linear_engine_of_layers_of_little_work():
+    # 128-wide tiles where the large ones pad; whole 256-wide tiles stay with the large ones where dX tiles are long or tiles many
+    L = _lib.lib()
+    def engine(K, Cin, Cout):
+        return L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, None)
+    for K, Cin, Cout in ((2100, 640, 1536), (4200, 320, 3072), (8400, 1024, 256), (3000, 768, 768), (33600, 512, 256)):
+        assert engine(K, Cin, Cout) == 1, (K, Cin, Cout)
+    for K, Cin, Cout in ((2100, 1024, 3072), (4200, 512, 1536), (1500, 2048, 1536), (1024, 2048, 2048), (4200, 256, 3072)):
+        assert engine(K, Cin, Cout) == 2, (K, Cin, Cout)
+
+
 def test_backward_attention_argument_errors_and_engine():
     L = _lib.lib()
     p = ctypes.c_void_p(256)     # never dereferenced: validation comes first and enqueues nothing
