@@ -135,15 +135,18 @@ void timeline_target(unsigned long long** buf, int* capacity_records) {
 
 void allow_dynamic_lds(const void* kernel, size_t lds) {
   if (lds <= 64 * 1024) return;
+  struct Grant { int device; const void* kernel; size_t lds; };
   static std::mutex m;
-  static std::vector<std::pair<const void*, size_t>> granted;      // a handful of kernels
+  static std::vector<Grant> granted;                               // a handful of kernels per device
+  int device = 0;
+  (void)hipGetDevice(&device);
   std::lock_guard<std::mutex> lock(m);
   for (auto& g : granted)
-    if (g.first == kernel) {
-      if (lds > g.second && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) g.second = lds;
+    if (g.device == device && g.kernel == kernel) {
+      if (lds > g.lds && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) g.lds = lds;
       return;
     }
-  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) granted.emplace_back(kernel, lds);
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) granted.push_back({device, kernel, lds});
 }
 
 static int32_t validate_desc(const sbp_sample_desc* d) {
