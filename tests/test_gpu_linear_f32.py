@@ -43,7 +43,7 @@ def test_more_units_than_fit_at_once(K, Cin, Cout):
 
 
 @pytest.mark.parametrize("want", [("db",), ("dX",), ("dW",), ("dW", "db"), ("db", "dX")])
-@pytest.mark.parametrize("K", [100, 2000])                   # one split (dW and db written directly) and several
+@pytest.mark.parametrize("K", [100, 2000, 20000])            # one split (dW and db written directly) and several; 64 slices of db alone
 def test_single_outputs_and_accumulation(want, K):
     M, Cin, Cout = K + 50, 72, 200
     X, W, dY = si.linear_case(M, Cin, Cout, 13, "f32")
