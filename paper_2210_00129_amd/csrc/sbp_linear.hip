@@ -82,15 +82,15 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
   const int wpb = blockDim.x >> 6;                             // wavefronts per block
   const int gw = blk * wpb + (threadIdx.x >> 6);
   uint4* out = reinterpret_cast<uint4*>(a.dX);
-  for (long long base = gw * 64; base < a.M; base += a.n_zero * wpb * 64) {   // (64 bits: M may be the largest int)
-    const long long m = base + lane;
+  for (uint32_t base = gw * 64; base < (uint32_t)a.M; base += a.n_zero * wpb * 64) {   // (unsigned: M may be the largest int)
+    const uint32_t m = base + lane;
     bool dropped = false;
-    if (m < a.M) {
+    if (m < (uint32_t)a.M) {
       const int j = a.inv[m];
-      dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == m);
+      dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == (int)m);
     }
     unsigned long long mask = __ballot(dropped);
-    uint4* rows = out + base * ppr;
+    uint4* rows = out + (long long)base * ppr;
     while (mask) {
       const int b = __ffsll((long long)mask) - 1;
       mask &= mask - 1;

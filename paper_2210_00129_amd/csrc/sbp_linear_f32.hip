@@ -393,15 +393,15 @@ __global__ void __launch_bounds__(NTHREADS, FOLD && !VEC ? 3 : 4) linear_f32_ker
   T* dX = static_cast<T*>(a.dX);                            // ---- zero fill: a wavefront looks 64 rows up at once
   constexpr int V = VEC ? 4 : 1;
   const int pieces = a.Cin / V;
-  for (long long base = (wg * 4 + wave) * 64; base < a.M; base += a.n_zero * 256) {   // (64 bits: M may be the largest int)
-    const long long m = base + lane;
+  for (uint32_t base = (wg * 4 + wave) * 64; base < (uint32_t)a.M; base += a.n_zero * 256) {   // (unsigned: M may be the largest int)
+    const uint32_t m = base + lane;
     bool dropped = false;
-    if (m < a.M) {
+    if (m < (uint32_t)a.M) {
       const int j = a.inv[m];
-      dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == m);
+      dropped = !((unsigned)j < (unsigned)a.K && a.idx[j] == (int)m);
     }
     unsigned long long mask = __ballot(dropped);
-    T* rows = dX + base * a.Cin;
+    T* rows = dX + (long long)base * a.Cin;
     if (pieces < 64 && pieces <= __popcll(mask)) {           // narrow rows: the pieces of the 64 rows side by side over the lanes
       const uint32_t magic = (1u << 20) / pieces + 1;       // e / pieces = e magic >> 20 for e < 64 pieces
       for (uint32_t e = lane; e < 64u * pieces; e += 64)

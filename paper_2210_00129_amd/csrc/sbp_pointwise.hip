@@ -217,15 +217,15 @@ __global__ void __launch_bounds__(PW_THREADS) ln_bwd_rows_kernel(const T* __rest
     constexpr int PPG = 8 * sizeof(T) / 16;            // 16-byte pieces per group of 8 values
     const int nz = gridDim.x - row_blocks, gw = ((int)blockIdx.x - row_blocks) * 4 + wave;
     uint4* out = reinterpret_cast<uint4*>(dX);
-    for (long long base = gw * 64; base < M; base += nz * 4 * 64) {   // (64 bits: M may be the largest int)
-      const long long m = base + lane;
+    for (uint32_t base = gw * 64; base < (uint32_t)M; base += nz * 4 * 64) {   // (unsigned: M may be the largest int)
+      const uint32_t m = base + lane;
       bool dropped = false;
-      if (m < M) {
+      if (m < (uint32_t)M) {
         const int j = inv[m];
-        dropped = !((unsigned)j < (unsigned)K && idx_out[j] == m);
+        dropped = !((unsigned)j < (unsigned)K && idx_out[j] == (int)m);
       }
       unsigned long long mask = __ballot(dropped);
-      uint4* rows = out + base * (ngroups * PPG);
+      uint4* rows = out + (long long)base * (ngroups * PPG);
       // narrow rows: the pieces of the 64 rows side by side over the lanes, in one step per piece of a row, where a row at a
       // time would take more (384 channels, half dropped: 6.4 row at a time, 7.0 us side by side; 128 channels: 30 / 12 us)
       if (ngroups * PPG < 64 && ngroups * PPG <= __popcll(mask)) {
