@@ -885,7 +885,7 @@ def main():
         achieved = fl / avg_ms / 1e9
         # which kernel the library runs for these layers (one fused launch per layer on the bf16 path)
         engines = sorted({sbp.backward_linear_engine(job.M, K_r, s.Cin, s.Cout, job.code)[0] for s in wl.linears})
-        kname = {"mfma_large": "linear_big_kernel", "mfma": "linear_bwd_kernel", "plain": "plain_dw_kernel"}
+        kname = {"mfma_large": "linear_big_kernel", "mfma": "linear_bwd_kernel", "plain": "linear_f32_kernel"}
         kernel = " / ".join(kname[e] for e in engines) + (" (dW + dX tiles, zero fill, db sums: one launch per layer)" if fused else "")
         if job.batched and engines == ["mfma_large"]:
             kernel = f"linear_multi_kernel (dX tiles, dW units, zero fill, db sums of the {len(wl.linears)} layers of a block: one launch per block)"

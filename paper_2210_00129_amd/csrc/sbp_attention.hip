@@ -518,18 +518,20 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 2) attn_bwd_mfma_kernel(co
 // queries - rows of q and dA, lse, -delta - stream through LDS in tiles of 64) or as queries (dQ; q, dA fragments, lse,
 // -delta in registers, rows of k and v stream).  Every output element is written by exactly one wavefront, sums run in token
 // order: deterministic, no atomics.
-// A ring of three tiles is filled by global -> LDS copies, two tiles ahead; the key role makes -delta and lse tables of 512
-// queries at a time from memory, so that its loop holds nothing but fragments and accumulators: 168 registers, three
+// A ring of three tiles is filled by global -> LDS copies that are issued two tiles ahead, but every stage begins by waiting for
+// all copies under way, so that a tile has the products of one other tile to arrive in.  The key role makes -delta and lse tables
+// of 512 queries at a time from memory, so that its loop holds nothing but fragments and accumulators: 168 registers, three
 // workgroups per CU.  (A spilled register in the loop waits, loads being counted in order, for the copies under way: with
 // 17 of them the launch took 148 us.)  dP starts from -delta in the accumulators.  Rows past n_k are copies of the last row:
 // as queries their lse is so large that their probabilities are 0, as keys their probabilities are zeroed (peeled block).
 // The outputs leave through LDS as whole rows.  The workgroups of a (sample, head) run on one XCD, whose L2 they share
-// (spread over all eight, 8 x 12 heads of 1024 tokens moved 614 MB across the L2 boundary, now 107 MB); an XCD runs its key
-// units first, the longer kind (110 -> 102 us), at the price of a second read of small heads (27.6 instead of 26.6 us at
-// 768 heads of 99 tokens).
-// Bound: the blocks themselves keep the matrix cores 80 % busy (16 and 12 MFMAs of 33 cycles per 32 x 32 block and role,
-// vector ALU 420 cycles next to them, overlapped by the three wavefronts of a SIMD); unit starts (first tiles and tables
-// from memory) and the power limit (1.85 GHz) take the rest.  8 x 12 heads of 64, 1024 kept tokens: 153 -> 102 us.
+// (8 x 12 heads of 1024 tokens, counters: 289 MB read and 41 written across the L2 boundary by the kernel before, spread over all
+// eight; now 60 and 38); an XCD runs its key units first, the longer kind (110 -> 102 us), at the price of a second read of small
+// heads (27.6 instead of 26.6 us at 768 heads of 99 tokens).
+// Bound, by counters: the matrix cores are busy 46 % of the cycles of a CU (36 % before), the LDS 55 %, of which 44 % are bank
+// conflicts of the transposing reads, and the softmax arithmetic between the products takes most of the rest; unit starts (first
+// tiles and tables from memory) and the power limit (1.85 GHz) add to it.  8 x 12 heads of 64, 1024 kept tokens, a call:
+// 134 -> 101 us.
 // Two more shapes were slower: 64 tokens per wavefront (half the LDS reads per MFMA, but 330 registers and one wavefront
 // per SIMD: accumulator moves and spills, 225 us), and the same with dK and dV as separate roles (148 us).
 // ------------------------------------------------------------------------------------------------
@@ -654,7 +656,7 @@ __device__ __forceinline__ void attn_tiled_body(char* smem, const AttnItem& it, 
     acc.from_memory(it.q + own * (3LL * hD), it.g + own * hD, it.a + own * hD, it.lse + own * h, lane);
   }
   for (int s = 0; s < ns; ++s) {
-    wait_async_copies<0>();                                 // tile s (issued two stages ago, or one: everything before this stage)
+    wait_async_copies<0>();                                 // tile s, and with it s + 1 (issued one stage ago)
     lds_barrier();                                          // ... everywhere; the ring place of tile s - 1 is free
     if (KEY && s && s % (kAttnTable / kAttnTile) == 0) {
       attn_make_tables<D, D == 128 ? 1 : 2>(it, s * kAttnTile, n_k, h, lse_s, ndl_s);

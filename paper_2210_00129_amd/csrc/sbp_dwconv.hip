@@ -3,9 +3,10 @@
 //   dWd[u,v,c] = sum_{(b,y,x) kept} dY[b,y,x,c] X[b,y+u-pad,x+v-pad,c]
 //   db[c]      = sum_{(b,y,x) kept} dY[b,y,x,c]
 //   dX[b,y,x,c]= sum_{u,v} [(b,y-u+pad,x-v+pad) kept] dY[b,y-u+pad,x-v+pad,c] Wd[u,v,c]
-// Channels-last: a wavefront's lanes are adjacent channels, so "is this neighbour kept" is the same
-// for the whole wavefront and dropped taps are skipped by a scalar branch.  bf16 or fp32 storage,
-// fp32 arithmetic on the vector ALUs (a depthwise conv is no dense contraction: no MFMA).
+// Channels-last, bf16 or fp32 storage, fp32 sums.  bf16 with channel counts that are multiples of 8: 7 x 7 on the matrix cores
+// (dw_mfma_kernel: sixteen channels side by side), 3 x 3 by an LDS-tiled kernel on the dot-product instructions
+// (dw_fused_kernel).  Other even channel counts: register-strip kernels, whose lanes are adjacent channels, so that "is this
+// neighbour kept" is the same for the whole wavefront.  Everything else: one thread per output.
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
@@ -744,10 +745,11 @@ __global__ void __launch_bounds__(DWF_THREADS, 2) dw_fused_kernel(const DwFusedA
 // A band product multiplies a gradient with zeros, and so do the dWd products at the edges of a tile and of the map: an
 // infinity or NaN would reach dX outside its 7 x 7 window and taps that reach outside the map.  Staging looks for them;
 // such a tile's dX is computed again tap by tap, and its share of dWd and db over the pairs there are.
-// Measured (kernel + partial sums): 2 x 200 x 336 x 128, a quarter kept, 90 -> 43 us; 2 x 50 x 84 x 512, half kept,
-// 28.4 -> 21.4; 2 x 25 x 42 x 768 18.5 -> 15.4; 2 x 7 x 7 x 768 18.5 -> 17.8, all against the dot2 kernel above.  With the
-// products left out 26 us remain of the 43, with the loads and stores left out 33: staging and products still overlap only
-// across the two workgroups of a CU.  One role-less kernel of 4 wavefronts with 194 registers: 45 us.
+// Measured (kernel + partial sums, half kept, against the 7 x 7 instance of the dot2 kernel above that this one replaced):
+// 2 x 200 x 336 x 128 86 -> 41 us; 2 x 50 x 84 x 512 26.8 -> 20.9; 2 x 25 x 42 x 768 16.6 -> 15.1; 2 x 7 x 7 x 768 10.1 -> 9.3.
+// Counters on the first: matrix cores busy 31 % of the cycles of a CU (22 % on the second), LDS 37 %, a third of that bank
+// conflicts; with the products left out 60 % of the time remains, with the loads and stores left out 77 %: staging and products
+// overlap only across the two workgroups of a CU.  One role-less kernel of 4 wavefronts with 194 registers: 45 us.
 // ------------------------------------------------------------------------------------------------
 typedef short dwm_s4 __attribute__((ext_vector_type(4)));
 typedef float dwm_f4 __attribute__((ext_vector_type(4)));

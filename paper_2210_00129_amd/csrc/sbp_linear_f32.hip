@@ -11,15 +11,14 @@
 // each other's barriers (128 x 128 tiles, two per CU, were no faster on large layers and worse on small ones).  Both
 // operands lie in LDS as [row or column][64 contraction steps] and are read 16 bytes at a time; operands whose contraction
 // index is the slow axis in memory (dY and X_k in dW, W in dX) are loaded in blocks of 4 steps x 4 columns per thread and
-// written as 4 columns x 4 steps: the transpose is a choice of registers.  Pitch 68 words plus 4 after every fourth row:
-// the 8 lanes served together fall on distinct banks, reading (8 neighbouring rows) as well as writing (rows 4 apart), and
-// every access of a lane is a fixed offset from one address.  The loop is straight-line code - the partial last stage is
+// written as 4 columns x 4 steps: the transpose is a choice of registers.  Pitch 68 words plus 4 after every fourth row,
+// so that 8 neighbouring rows (reads) and rows 4 apart (writes) start on distinct banks (counters: half of the LDS cycles are
+// conflicts all the same), and every access of a lane is a fixed offset from one address.  The loop is straight-line code - the partial last stage is
 // peeled, gathered and plain rows are different loops - because the compiler copies loaded registers where paths join, and
 // the copy waits for the load it was meant to overlap (57 -> 50 us on the layer below).  In a group of 8 contraction steps
 // lane half h multiplies steps 4 h .. 4 h + 3, on both operands alike.
-// ViT-Tiny fc1 (6336 kept rows, 192 -> 768, with the reduction): 600 us with one thread per output on the vector ALU, 50 us
-// here; 20000 rows, 512 -> 512: 205 us = 102 TFLOP/s, of which 182 us remain without the loads (registers alone reach
-// 148 TFLOP/s: 142 us); the rest is the units' starts and ends.
+// ViT-Tiny fc1 (6336 kept rows, 192 -> 768, with the reduction): 600 us with one thread per output on the vector ALU, 52 us
+// here; 20000 rows, 512 -> 512: 198 us = 106 TFLOP/s, with the matrix cores busy 74 % of the cycles of a CU (70 % on fc1).
 #include <algorithm>
 
 #include "sbp_internal.h"
