@@ -523,7 +523,8 @@ def test_dwconv_one_launch_two_launches_and_single_outputs_agree(geom):
                                   (1, 1, 1, 8, 7), (2, 19, 9, 264, 7)])
 @pytest.mark.parametrize("k", [1, 2, 4])
 def test_dwconv_lds_tiled_kernel_and_single_outputs(geom, k):
-    # the LDS-tiled kernel (bf16, channel counts that are multiples of 8): ragged tiles in rows, columns and channel
+    # the LDS-tiled kernels (bf16, channel counts that are multiples of 8; 7 x 7 on the matrix cores, 3 x 3 on dot
+    # products): ragged tiles in rows, columns and channel
     # slabs, maps smaller than a tile, every keep ratio; a caller that wants only dX or only the weight gradient gets
     # the same values bit for bit
     B, H, W, C, ks = geom
