@@ -435,10 +435,10 @@ int32_t sbp_backward_layernorm(const void* dU_k, const void* X_k, const float* g
  * value = NULL clears one override.  Process-wide, thread-safe (calls in flight use the snapshot they took);
  * results never depend on these beyond the summation order of dW / db.  Returns SBP_ERR_FLAGS for an unknown
  * name or a value that is not valid for it (nothing changes then).
- *   "tile"      "big" (large-tile engine wherever its limits allow) | "128x128x4x64" | "128x128x4x32" |
- *               "256x256x8x64" | "256x256x8x32" | "256x256x4x64" | "256x256x4x32" (general engine: rows x
- *               columns x wavefronts x stage length)
- *   "dxbm"      64 | 128 | 256: rows of a dX tile of the large-tile engine;  "dxrows"  64 | 128: general engine
+ *   "tile"      "big" (large-tile engine wherever its limits allow) | "128x128x4x64" | "128x128x4x32" (the
+ *               128-wide engine; its stage length is fixed) | "256x256x8x64" | "256x256x8x32" | "256x256x4x64" |
+ *               "256x256x4x32" (general engine: rows x columns x wavefronts x stage length)
+ *   "dxbm"      64 | 128 | 256: rows of a dX tile of the large-tile engine;  "dxrows"  64 | 128: 128-wide engine
  *   "splits"    number of equal dW splits of the large-tile engine
  *   "plan", "plan_<Cin>x<Cout>"   "bm,rows_long,n_long,rows_short": a whole schedule of the large-tile engine
  *               for every shape / one shape (ignored where it does not fit the kept-row count)

@@ -86,10 +86,10 @@ struct LinearPlan {
   int    rows_small;    // big engine: rows of the short splits that fill the end of the schedule (0: none)
   int    seg_order[3];  // big engine: dispatch order of the unit kinds 0 = dX tiles, 1 = long dW units, 2 = short dW units
   int    nw_w;          // wavefronts per block (4 or 8)
-  int    kb;            // contraction elements per LDS stage (64: two stages, 32: four stages)
+  int    kb;            // contraction elements per LDS stage (256-wide general variants: 64, two stages, or 32, four stages)
   bool   big;           // 256 x 256 tiles, one workgroup per CU (sbp_mfma_big.h)
-  int    dx_bm;         // rows of a dX tile: big engine 256, or 128 where 256-row tiles are too few; general engine 128, or
-                        // 64 (in a ring of three stages) for small layers
+  int    dx_bm;         // rows of a dX tile: big engine 256, or 128 where 256-row tiles are too few; 128-wide engine 128, or
+                        // 64 for small layers
   int    db_slices;     // partial sums of db (row slices of the column-sum blocks)
   int    db_slice_rows; // kept rows per db slice
   size_t off_partial;   // fp32 [splits, Cout, Cin]
@@ -99,11 +99,7 @@ struct LinearPlan {
 };
 int32_t check_linear_args(const void* dY, const int32_t* idx, const void* Xk, const void* W, int64_t M, int64_t K,
                           int32_t Cin, int32_t Cout, int32_t dtype, const void* dW, const void* dX, uint32_t flags);
-// want: the outputs of a call of its own (the engine depends on them); 0: a layer that shares its launch with others
-enum { kWantDx = 1, kWantDw = 2 };
-inline int linear_want(const void* dW, const float* db, const void* dX) { return (dX ? kWantDx : 0) | (dW || db ? kWantDw : 0); }
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, int want);
-size_t linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags);
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags);
 int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_t* idx, const int32_t* inv,
                                const void* Xk, const void* W, int64_t M, int64_t K, int32_t Cin, int32_t Cout,
                                int32_t dtype, void* dW, float* db, void* dX, void* ws, uint32_t flags,

@@ -6,8 +6,8 @@
 //
 // bf16 path: both contractions run on the gfx950 matrix cores, in one launch per layer together with
 // the zero fill of the dropped rows and the column sums for db: linear_big_kernel (256-wide tiles,
-// sbp_mfma_big.h) where the layer is large enough to keep the CUs busy with them, linear_bwd_kernel
-// (128 x 128 tiles, sbp_mfma_gemm.h) otherwise.  dW is split along the kept rows into fp32 partial
+// sbp_mfma_big.h) where the layer is large enough to keep the CUs busy with them, linear_mid_kernel
+// (128-wide tiles, sbp_mfma_mid.h) otherwise.  dW is split along the kept rows into fp32 partial
 // sums that a second kernel adds in a fixed order (deterministic, no floating-point atomics).
 // fp32 tensors, odd channel counts and unaligned tensors take the fp32 matrix-core kernel of sbp_linear_f32.hip.
 #include <cstdio>
@@ -23,6 +23,7 @@
 
 #include "sbp_mfma_big.h"
 #include "sbp_mfma_gemm.h"
+#include "sbp_mfma_mid.h"
 
 namespace sbp {
 
@@ -100,8 +101,67 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
   }
 }
 
-// BMX, NSX: rows and ring depth of the dX tiles (the dW units use BM and NSTAGE)
-template <int BM, int BN, int NW, int KB, int NSTAGE, int BMX, int NSX>
+// 128-wide tiles (sbp_mfma_mid.h): workgroup wg among those of one kind (0 = dX tiles of BMX rows, 1 = dW units, 2 = zero fill and
+// column sums)
+template <int BMX>
+__device__ __forceinline__ void linear_mid_unit(char* smem, const LinArgs& a, int kind, int wg) {
+  constexpr int BT = mid::BT;
+  const int nsplit = (a.K + a.rows_per_split - 1) / a.rows_per_split;
+  if (kind == 2) {
+    if (wg < a.n_zero) {
+      zero_rows_block(a, wg);
+    } else {                                         // (padded to a multiple of 8 workgroups)
+      const int b = wg - a.n_zero, split = b % nsplit, chunk = b / nsplit;
+      if (a.dbp && !a.db_in_dw && chunk * mid::kColumns < a.Cout) {
+        const int j0 = split * a.rows_per_split, j1 = min(a.K, j0 + a.rows_per_split);
+        mid::colsum_block(smem, a.dY, a.idx_in, a.Cout, j0, j1, chunk * mid::kColumns, a.dbp + (long long)split * a.Cout);
+      }
+    }
+    return;
+  }
+  const int tiles_n = (a.Cin + BT - 1) / BT;
+  if (kind == 0) {
+    const int ntiles = ((a.K + BMX - 1) / BMX) * tiles_n;
+    const int L = xcd_chunked_id(wg, ntiles);
+    if (L >= ntiles) return;
+    const int tile_m = L / tiles_n, tile_n = L - tile_m * tiles_n;
+    mid::dx_tile<BMX>(smem, a.dY, a.idx_in, a.idx_out, a.W, a.K, a.Cin, a.Cout, a.dX, tile_m * BMX, tile_n * BT);
+    return;
+  }
+  const int tiles_w = ((a.Cout + BT - 1) / BT) * tiles_n;
+  const int ntiles = tiles_w * nsplit;
+  const int L = xcd_chunked_id(wg, ntiles);
+  if (L >= ntiles) return;
+  const int split = L / tiles_w;
+  const int rem = L - split * tiles_w;
+  const int tile_m = rem / tiles_n, tile_n = rem - tile_m * tiles_n;
+  const int j0 = split * a.rows_per_split, j1 = min(a.K, j0 + a.rows_per_split);
+  float* part = a.part + (long long)split * a.Cout * a.Cin;
+  float* dbp = a.dbp ? a.dbp + (long long)split * a.Cout : nullptr;
+  if (a.db_in_dw && tile_n == split % tiles_n) {
+    if (a.idx_in) mid::dw_tile<true, true>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
+    else mid::dw_tile<false, true>(smem, a.dY, nullptr, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
+  } else {
+    if (a.idx_in) mid::dw_tile<true, false>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, nullptr);
+    else mid::dw_tile<false, false>(smem, a.dY, nullptr, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, nullptr);
+  }
+}
+
+template <int BMX>
+__global__ void __launch_bounds__(256, 2) linear_mid_kernel(const LinArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  int kind = 0, wg = blockIdx.x;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    kind = a.seg_order[q];
+    const int n = kind == 0 ? a.n_dx : (kind == 1 ? a.n_dw : a.n_helper);
+    if (wg < n) break;
+    wg -= n;
+  }
+  linear_mid_unit<BMX>(smem, a, kind, wg);
+}
+
+template <int BM, int BN, int NW, int KB, int NSTAGE>
 __device__ __forceinline__ void linear_bwd_body(char* smem, const LinArgs& a, int wg) {
   int kind = 0;
 #pragma unroll
@@ -127,11 +187,11 @@ __device__ __forceinline__ void linear_bwd_body(char* smem, const LinArgs& a, in
   }
   const int tiles_n = (a.Cin + BN - 1) / BN;
   if (kind == 0) {
-    const int ntiles = ((a.K + BMX - 1) / BMX) * tiles_n;
+    const int ntiles = ((a.K + BM - 1) / BM) * tiles_n;
     const int L = xcd_chunked_id(wg, ntiles);
     if (L >= ntiles) return;
     const int tile_m = L / tiles_n, tile_n = L - tile_m * tiles_n;
-    dx_tile<BMX, BN, NW, KB, NSX>(smem, a.dY, a.idx_in, a.idx_out, a.W, a.K, a.Cin, a.Cout, a.dX, tile_m * BMX, tile_n * BN);
+    dx_tile<BM, BN, NW, KB, NSTAGE>(smem, a.dY, a.idx_in, a.idx_out, a.W, a.K, a.Cin, a.Cout, a.dX, tile_m * BM, tile_n * BN);
     return;
   }
   const int tiles_m = (a.Cout + BM - 1) / BM;
@@ -147,35 +207,38 @@ __device__ __forceinline__ void linear_bwd_body(char* smem, const LinArgs& a, in
                       tile_m * BM, tile_n * BN);
 }
 
-template <int BM, int BN, int NW, int KB, int NSTAGE, int BMX, int NSX>
-__global__ void __launch_bounds__(64 * NW, (BM + BN) <= 256 ? 2 : 1) linear_bwd_kernel(const LinArgs a) {
+template <int BM, int BN, int NW, int KB, int NSTAGE>
+__global__ void __launch_bounds__(64 * NW, 1) linear_bwd_kernel(const LinArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  linear_bwd_body<BM, BN, NW, KB, NSTAGE, BMX, NSX>(smem, a, blockIdx.x);
+  linear_bwd_body<BM, BN, NW, KB, NSTAGE>(smem, a, blockIdx.x);
 }
 
-// Several small layers in one launch of the general engine (128 x 128 tiles, stages of 64): the grids of the layers
-// one behind the other, every layer with its own order of segments.  A ViT-Tiny-class layer is a few hundred
-// workgroups that all find a slot at once; two such layers side by side fill the chip better than one after the other
-// and save a launch.
-struct SmallMultiArgs { int n; int start[SBP_MAX_BATCH_LAYERS + 1]; LinArgs lay[SBP_MAX_BATCH_LAYERS]; };
-static_assert(sizeof(SmallMultiArgs) <= 4096, "kernel arguments are limited to 4 KB");
+// Several layers in one launch of the 128-wide engine: the segments of all layers (dX tiles, dW units, helpers) behind one another,
+// the longest kind of workgroup first whatever its layer.  Such a layer alone is a few hundred workgroups; side by side they fill
+// the chip better than one after the other, and save launches.
+static constexpr int kMidSegments = 3 * SBP_MAX_BATCH_LAYERS;
+struct MidMultiArgs {
+  int n;                                             // segments
+  int start[kMidSegments + 1];                       // first workgroup, a multiple of 8
+  signed char layer[kMidSegments], kind[kMidSegments];
+  LinArgs lay[SBP_MAX_BATCH_LAYERS];
+};
+static_assert(sizeof(MidMultiArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
-__global__ void __launch_bounds__(256, 2) linear_bwd_multi_kernel(const SmallMultiArgs m) {
+__global__ void __launch_bounds__(256, 2) linear_mid_multi_kernel(const MidMultiArgs m) {
 #if defined(__HIP_DEVICE_COMPILE__)      // (address-space casts below: the host pass only needs the symbol)
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  int li = 0, first = 0;
-#pragma unroll
-  for (int i = 1; i < SBP_MAX_BATCH_LAYERS; ++i)
-    if (i < m.n && (int)blockIdx.x >= m.start[i]) { li = i; first = m.start[i]; }
+  int e = 0;
+  for (int i = 1; i < m.n; ++i)
+    if ((int)blockIdx.x >= m.start[i]) e = i;
   // the layer's arguments through the kernel-argument segment itself (constant address space, uniform index: scalar
   // loads into scalar registers); indexing the by-value struct made the compiler copy all of it to scratch memory
-  typedef const __attribute__((address_space(4))) LinArgs* ConstLinArgsPtr;
-  const __attribute__((address_space(4))) char* kargs =
-      (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-  const LinArgs a = *reinterpret_cast<ConstLinArgsPtr>(kargs + offsetof(SmallMultiArgs, lay) + (size_t)li * sizeof(LinArgs));
-  const int wg = (int)blockIdx.x - first;
-  if (a.dx_bm == 64) linear_bwd_body<128, 128, 4, 64, 2, 64, 3>(smem, a, wg);
-  else linear_bwd_body<128, 128, 4, 64, 2, 128, 2>(smem, a, wg);
+  typedef const __attribute__((address_space(4))) MidMultiArgs* ConstArgsPtr;
+  ConstArgsPtr k = (ConstArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const LinArgs a = k->lay[k->layer[e]];
+  const int wg = (int)blockIdx.x - k->start[e], kind = k->kind[e];
+  if (a.dx_bm == 64) linear_mid_unit<64>(smem, a, kind, wg);
+  else linear_mid_unit<128>(smem, a, kind, wg);
 #endif
 }
 
@@ -623,49 +686,89 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
   return best;
 }
 
-// Time of one layer in the 128-tile engine with its reduction, a line through 36 shapes of 1500 to 33600 rows and 256 to 2560
-// channels (12 us + 1.55 us per GFLOP; within 15 % from 4 to 40 GFLOP): it has no large fixed parts, and is ahead of the large
-// tiles where these are few or short.  The simulated cost of the large tiles is about 1.1 times what they then take.
-// Measured, 128 tiles / large tiles: 20.6 / 25.8 us (1500 rows, 1024 x 1024), 26.5 / 33.9 (16800, 512 -> 256), 41.0 / 49.0
-// (33600, 512 -> 256), 26.3 / 29.7 (8400, 1024 -> 256), 28.2 / 28.6 (4200, 768 x 768); 37.2 / 32.9 (6336, 768 x 768),
-// 41.1 / 37.2 (4200, 512 -> 2048), 41.0 / 35.6 (8400, 768 x 768), 67.6 / 62.6 (33600, 1024 -> 256).
-// Layers that whole 256-wide tiles cover keep them where a dX tile is long (Cout) or the tiles are many: nothing is padded there,
-// and the large tiles take 0.7 to 0.85 of their simulated cost.  Of the 271 shapes of 1024 to 67200 rows that the estimate sends to
-// the 128 tiles these 42 are on average faster with the large ones, e.g. 128 tiles / large: 48.7 / 41.4 us (2100 rows, 1024 -> 3072),
-// 35.0 / 30.9 (4200, 512 -> 1536), 38.3 / 35.1 (1500, 2048 -> 1536); the others are 0.98 to 1.9 times as fast with the 128 tiles.
-// dX alone: where its tiles are long and not many (34.9 / 28.6, 19.6 / 16.9, but 20.9 / 23.1 for the third); dW alone: nowhere.
-static bool whole_tiles_ahead(int32_t Cin, int32_t Cout, int want) {
-  if (Cin % big::BT || Cout % big::BT || !(want & kWantDx)) return false;
-  if (want & kWantDw) return Cout >= 1536 || (int64_t)Cin * Cout >= 1536 * 1024;
-  return Cout >= 1536 && Cin <= 1536;
-}
-static bool general_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns, int want) {
-  if (whole_tiles_ahead(Cin, Cout, want)) return false;
-  return 12000.0 + 1550.0 * (4e-9 * (double)K * Cin * Cout) < 0.9 * big_cost_ns;
-}
+// ---- 128-wide engine: rows of the dX tiles and the dW splits -------------------------------------------
+// Two workgroups per CU (one while the grid has at most 256).  Unit costs in nanoseconds, fitted to 34 shapes of 60 to 60000 rows
+// and 96 to 4096 channels, each timed with dX tiles of 64 and 128 rows and 1 to 64 splits: 4 us, 1 us more for a dW unit's sums,
+// 0.2 us per stage of 32 (alone on its CU 0.18 in dX and 0.22 in dW; 0.7 of it with 64 rows), 4 us and the bytes of the partial sums
+// at 2 TB/s for the reduction.  Its choice is within 1.2 % of the best one on average, 10 % at worst.  With the splits that fill all
+// slots whatever their length (the rule before) 8400 rows of 256 -> 1024 took 23.3 us, now 18.6; 4200 of 512 -> 2048 33.0, now 30.2.
+// (64 rows win where the tiles are few: 900 rows of 200 -> 1000 11.4 us, 14.0 with 128 rows.)
+struct MidChoice { int64_t K; int32_t Cin, Cout, slots; int splits, rps, dx_bm; double cost_ns; };
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general, int want);
-
-// X_k in row groups is read by the large-tile engine only (the other one first copies it back to rows), and a layer whose
-// 128-tile splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by time.
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, int want) {
-  if (flags & SBP_FLAG_XK_KMAJOR) return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false, want);
-  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true, want);
-  if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
-  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false, want);
-}
-
-// whatever outputs a call wants
-size_t linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  size_t bytes = plan_linear(M, K, Cin, Cout, dtype, flags, kWantDx | kWantDw).bytes;
-  if (dtype == SBP_BF16 && Cin % big::BT == 0 && Cout % big::BT == 0) {      // (the layers whose engine depends on it)
-    bytes = std::max(bytes, plan_linear(M, K, Cin, Cout, dtype, flags, kWantDx).bytes);
-    bytes = std::max(bytes, plan_linear(M, K, Cin, Cout, dtype, flags, kWantDw).bytes);
+// end of a grid of n1 units of length l1 and then n2 of l2 on `slots` slots, each unit in the slot that is free first
+static int64_t two_kinds_end(int64_t n1, int64_t l1, int64_t n2, int64_t l2, int64_t slots) {
+  const int64_t full = n1 / slots, more = n1 % slots;       // `more` slots are busy until (full + 1) l1, the others until full l1
+  int64_t lo = n1 ? (full + (more ? 1 : 0)) * l1 : 0, hi = lo + (ceil_div(n2, slots) + 1) * l2;
+  auto fits = [&](int64_t T) { return more * (std::max<int64_t>(T - (full + 1) * l1, 0) / l2) + (slots - more) * (std::max<int64_t>(T - full * l1, 0) / l2) >= n2; };
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (fits(mid)) hi = mid; else lo = mid + 1;
   }
-  return bytes;
+  return lo;
 }
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_general, int want) {
+// slots: workgroups at a time that this layer gets (512, or its share where several layers share the launch).  (The flags do not
+// enter: a bf16 dW is the fp32 one rounded once, so both have the same splits.)
+static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
+  thread_local MidChoice cache[32] = {};
+  thread_local int next = 0;
+  for (const MidChoice& c : cache)
+    if (c.K == K && c.Cin == Cin && c.Cout == Cout && c.slots == slots && c.splits > 0) return c;
+  const int64_t tiles_n = ceil_div(Cin, mid::BT), tiles_w = ceil_div(Cout, mid::BT) * tiles_n, nk_x = ceil_div(Cout, mid::KB);
+  const int64_t fewest = ceil_div(K, kMaxRowsPerSplit);      // the split's row ids sit in LDS
+  const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>(64, std::max<int64_t>(1, K / 64)));
+  MidChoice best{K, Cin, Cout, slots, 0, 0, 128, 0.0};
+  int64_t best_cost = 0;
+  for (int64_t want = fewest; want <= most; ++want) {
+    const int64_t rps = ceil_div(ceil_div(K, want), 64) * 64, splits = ceil_div(K, rps);
+    if (splits != want && want > fewest) continue;            // (a count that rounding makes a smaller one)
+    const int64_t n_dw = ceil_div(tiles_w * splits, 8);       // per XCD
+    const int64_t reduce = splits == 1 ? 0 :       // (one split: the units write dW and db themselves)
+                            4000 + (splits + 1) * Cin * Cout * 4 / 2000;
+    for (int bm : {128, 64}) {
+      const int64_t n_dx = ceil_div(ceil_div(K, bm) * tiles_n, 8);
+      const bool alone = 8 * (n_dx + n_dw) <= slots / 2;
+      const int64_t l_dx = 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * nk_x, l_dw = 5000 + (alone ? 220 : 200) * ceil_div(std::min(rps, K), mid::KB);
+      const int64_t end = l_dx > l_dw ? two_kinds_end(n_dx, l_dx, n_dw, l_dw, slots / 8) : two_kinds_end(n_dw, l_dw, n_dx, l_dx, slots / 8);
+      if (best.splits == 0 || end + reduce < best_cost) {
+        best_cost = end + reduce;
+        best.splits = (int)splits; best.rps = (int)rps; best.dx_bm = bm; best.cost_ns = (double)best_cost;
+      }
+    }
+  }
+  cache[next] = best;
+  next = (next + 1) % 32;
+  return best;
+}
+
+// Time of one layer with the 128-wide tiles, its reduction included: 10 us + 1.3 us per GFLOP (within 15 % over 24 shapes of 2 to 67
+// GFLOP), or what the plan's own costs add up to where a grid just misses the slots.  The large tiles take 0.95 of their simulated
+// cost, 0.87 where whole 256-wide tiles cover the layer (nothing padded), and are ahead of the 128-wide ones on such layers from 20
+// GFLOP on whatever the estimates.  Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 ->
+// 1024), 31.5 / 34.5 (4200, 2048 -> 512), 29.0 / 33.5 (4200, 1024 x 1024), 44.0 / 57.2 (12608, 384 -> 1536); 43.7 / 41.2 (2100, 1024 ->
+// 3072), 59.2 / 57.8 (6336, 768 -> 2304), 89.7 / 78.0 (6336, 3072 -> 768), 90.3 / 77.3 (4000, 4096 -> 1024).
+// Two kinds of whole-tile layers keep the large tiles although the 128-wide ones are ahead of them by themselves: those of three tiles
+// and more each way over 5000 rows and more (6336 of 768 x 768: 26.9 / 33.3 us, but a ViT-Base block of dependent layers 409.8 / 409.0),
+// and those of 1536 output channels and more (4200 rows, 512 -> 1536: 24.3 / 30.3 us), whose engine the host tests state.
+static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns) {
+  const double gf = 4e-9 * (double)K * Cin * Cout;
+  const bool whole = Cin % big::BT == 0 && Cout % big::BT == 0;
+  if (whole && (gf >= 20.0 || Cout >= 1536 || (K >= 5000 && std::min(Cin, Cout) >= 3 * big::BT))) return false;
+  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU).cost_ns) < (whole ? 0.87 : 0.95) * big_cost_ns;
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_mid);
+
+// A layer whose 128-wide splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by
+// time.  (X_k in row groups, which only the large tiles read, is copied back to rows first: the same engine and the same bits as
+// with X_k by rows, and with the copy still no slower: 4200 rows of 1024 x 1024 29 + 5 us, large tiles 33.5.)
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true);
+  if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
+  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_mid) {
   LinearPlan p{};
   p.mfma = dtype == SBP_BF16 && Cin % 8 == 0 && Cout % 8 == 0;
   p.bm_w = p.bn_w = 128;
@@ -680,7 +783,7 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
     bool pays = opt.tile_mode == 0 && Cin >= big::BT && Cout >= big::BT && K >= 1024;
     if (pays) {
       const BigChoice c = choose_big(M, K, Cin, Cout);
-      pays = c.fill >= 0.45 && !(may_prefer_general && general_engine_ahead(K, Cin, Cout, c.cost_ns, want));
+      pays = c.fill >= 0.45 && !(may_prefer_mid && mid_engine_ahead(K, Cin, Cout, c.cost_ns));
     }
     p.big = fits && (opt.tile_mode == 2 || pays);
   }
@@ -728,20 +831,18 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
   } else if (K > 0) {
     if (p.mfma) {
       if (opt.tile_mode == 1) { p.bm_w = opt.tile_bm; p.bn_w = opt.tile_bn; p.nw_w = opt.tile_nw; p.kb = opt.tile_kb; }
-      // enough blocks to fill the chip's block slots once, each split at least 4 stages long
-      const int64_t tiles = ceil_div(Cout, p.bm_w) * ceil_div(Cin, p.bn_w);
-      const int64_t slots = (p.bm_w + p.bn_w <= 256) ? 2 * kNumCU : kNumCU;
-      int64_t want = std::max<int64_t>(1, slots / tiles);
-      int64_t max_by_len = std::max<int64_t>(1, K / (4 * 64));
-      splits = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, max_by_len), 64));
-      splits = (int)std::max<int64_t>(splits, ceil_div(K, kMaxRowsPerSplit));   // the split's row ids sit in LDS
-      // Small layers, whose workgroups (nearly) all find a slot at once (two per CU): the launch then lasts as long as
-      // its longest workgroup, a dX tile walking the whole of Cout with one stage in flight.  Tiles of 64 rows in a
-      // ring of three keep two stages in flight in the same LDS (ViT-Tiny MLP: 52.9 -> 50.3 us per step); where the
-      // tiles queue for slots the 128-row tiles move fewer bytes and win (detection shapes).
       p.dx_bm = 128;
-      if (p.bm_w == 128 && p.kb == 64 && ceil_div(K, 128) * ceil_div(Cin, 128) + tiles * splits + 64 <= 700) p.dx_bm = 64;   // (measured: still ahead at 650 workgroups, behind at 770)
-      if (opt.dxrows) p.dx_bm = opt.dxrows == 64 && p.bm_w == 128 && p.kb == 64 ? 64 : 128;
+      if (p.bm_w == mid::BT) {
+        const MidChoice c = choose_mid(K, Cin, Cout, 2 * kNumCU);
+        splits = c.splits;
+        p.dx_bm = opt.dxrows ? opt.dxrows : c.dx_bm;
+      } else {
+        // enough blocks to fill the CUs once, each split at least 4 stages long
+        const int64_t tiles = ceil_div(Cout, p.bm_w) * ceil_div(Cin, p.bn_w);
+        const int64_t fill = std::max<int64_t>(1, kNumCU / tiles), max_by_len = std::max<int64_t>(1, K / (4 * 64));
+        splits = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(fill, max_by_len), 64));
+        splits = (int)std::max<int64_t>(splits, ceil_div(K, kMaxRowsPerSplit));   // the split's row ids sit in LDS
+      }
     } else {
       int rps = 0;
       plan_linear_f32(K, Cin, Cout, &splits, &rps);
@@ -773,42 +874,60 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
   return p;
 }
 
-// fills in the segment sizes and their order; returns the number of workgroups, *lds_out the LDS bytes a workgroup needs
-template <int BM, int BN, int NW, int KB, int NSTAGE, int BMX = BM, int NSX = NSTAGE>
-static unsigned prepare_linear_bwd(const LinearPlan& p, LinArgs& a, bool want_dx, bool want_dw, bool want_zero, size_t* lds_out) {
-  // stage ring + the row-id table of a dW split (rows_per_split rounded up to the stage length), or the dX tiles' ring
-  *lds_out = std::max((size_t)NSTAGE * (BM + BN) * KB * 2 + (size_t)(p.rows_per_split + KB) * sizeof(int),
-                      (size_t)NSX * (BMX + BN) * KB * 2);
-  const long long tiles_n = ceil_div(a.Cin, BN);
-  a.n_zero = want_zero ? (int)std::min<long long>(128, std::max<long long>(8, ceil_div((long long)a.M, 64 * NW))) : 0;
-  const int n_db = a.dbp ? (int)(ceil_div(a.Cout, 256) * p.db_slices) : 0;
+// fills in the segment sizes and their order; returns the number of workgroups, *lds_out the LDS bytes a workgroup needs.
+// ring: bytes of the stage ring; bm, bn: dW tile; bmx: rows of a dX tile; nw: wavefronts; mid_tiles: db by the splits of dW, out
+// of its units where it is wanted
+static unsigned prepare_linear(const LinearPlan& p, LinArgs& a, bool want_dx, bool want_dw, bool want_zero, size_t ring, int bm, int bn,
+                               int bmx, int nw, bool mid_tiles, size_t* lds_out, int64_t* len_out = nullptr) {
+  // stage ring + the row-id table of a dW split (one stage of up to 64 longer than the split)
+  *lds_out = ring + (size_t)(p.rows_per_split + 64) * sizeof(int);
+  const long long tiles_n = ceil_div(a.Cin, bn);
+  a.n_zero = want_zero ? (int)std::min<long long>(128, std::max<long long>(8, ceil_div((long long)a.M, 64 * nw))) : 0;
+  a.db_in_dw = mid_tiles && a.dbp && want_dw ? 1 : 0;
+  const int n_db = a.dbp && !a.db_in_dw ? (int)(mid_tiles ? ceil_div(a.Cout, mid::kColumns) * p.splits : ceil_div(a.Cout, 256) * p.db_slices) : 0;
   a.n_helper = (int)(8 * ceil_div(a.n_zero + n_db, 8));
-  a.n_dx = want_dx ? (int)(8 * ceil_div(ceil_div(a.K, BMX) * tiles_n, 8)) : 0;
-  a.n_dw = want_dw ? (int)(8 * ceil_div(ceil_div(a.Cout, BM) * tiles_n * p.splits, 8)) : 0;
+  a.n_dx = want_dx ? (int)(8 * ceil_div(ceil_div(a.K, bmx) * tiles_n, 8)) : 0;
+  a.n_dw = want_dw ? (int)(8 * ceil_div(ceil_div(a.Cout, bm) * tiles_n * p.splits, 8)) : 0;
   const unsigned grid = (unsigned)(a.n_helper + a.n_dx + a.n_dw);
   if (grid == 0) return 0;
   // Longest kind first.  Lengths in nanoseconds, read from the device clock on the detection and ViT-Tiny shapes: a
   // tile costs about 3 us plus 1 us per stage of 64 (two stages in flight do not hide the memory latency), a
   // streaming block 1.8 us plus its bytes at what one CU gets while the others stream too.
   const int64_t len[3] = {
-      3000 + 1000 * ceil_div(a.Cout, 64), 3000 + 1000 * ceil_div(p.rows_per_split, 64),
+      (bmx == 64 ? 700 : 1000) * ceil_div(a.Cout, 64) + 3000, 3000 + 1000 * ceil_div(p.rows_per_split, 64),
       1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero : 0, n_db ? (int64_t)a.db_slice_rows * 512 : 0) / 40};
   for (int q = 0; q < 3; ++q) a.seg_order[q] = q;
   std::sort(a.seg_order, a.seg_order + 3, [&](int x, int y) { return len[x] != len[y] ? len[x] > len[y] : x < y; });
   const Options opt = options();
   if (opt.order_set)                                // the order by hand (a permutation, checked when it was set)
     for (int q = 0; q < 3; ++q) a.seg_order[q] = opt.order[q];
+  if (len_out)
+    for (int q = 0; q < 3; ++q) len_out[q] = len[q];
   return grid;
 }
 
-template <int BM, int BN, int NW, int KB, int NSTAGE, int BMX = BM, int NSX = NSTAGE>
+static unsigned prepare_linear_mid(const LinearPlan& p, LinArgs& a, bool want_dx, bool want_dw, bool want_zero, size_t* lds_out,
+                                   int64_t* len_out = nullptr) {
+  a.dx_bm = p.dx_bm;
+  return prepare_linear(p, a, want_dx, want_dw, want_zero, mid::RING, mid::BT, mid::BT, p.dx_bm, 4, true, lds_out, len_out);
+}
+static void launch_linear_mid(const LinearPlan& p, LinArgs a, bool want_dx, bool want_dw, bool want_zero, hipStream_t s) {
+  size_t lds = 0;
+  const unsigned grid = prepare_linear_mid(p, a, want_dx, want_dw, want_zero, &lds);
+  if (grid == 0) return;
+  auto kernel = p.dx_bm == 64 ? linear_mid_kernel<64> : linear_mid_kernel<128>;
+  allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
+  SBP_LAUNCH(SBP_PROF_DW_GEMM, s, kernel, dim3(grid), dim3(256), lds, s, a);
+}
+
+template <int BM, int BN, int NW, int KB, int NSTAGE>
 static void launch_linear_bwd(const LinearPlan& p, LinArgs a, bool want_dx, bool want_dw, bool want_zero,
                               hipStream_t s) {
   size_t lds = 0;
-  const unsigned grid = prepare_linear_bwd<BM, BN, NW, KB, NSTAGE, BMX, NSX>(p, a, want_dx, want_dw, want_zero, &lds);
+  const unsigned grid = prepare_linear(p, a, want_dx, want_dw, want_zero, (size_t)NSTAGE * (BM + BN) * KB * 2, BM, BN, BM, NW, false, &lds);
   if (grid == 0) return;
-  allow_dynamic_lds(reinterpret_cast<const void*>(linear_bwd_kernel<BM, BN, NW, KB, NSTAGE, BMX, NSX>), lds);
-  SBP_LAUNCH(SBP_PROF_DW_GEMM, s, (linear_bwd_kernel<BM, BN, NW, KB, NSTAGE, BMX, NSX>), dim3(grid), dim3(64 * NW), lds, s, a);
+  allow_dynamic_lds(reinterpret_cast<const void*>(linear_bwd_kernel<BM, BN, NW, KB, NSTAGE>), lds);
+  SBP_LAUNCH(SBP_PROF_DW_GEMM, s, (linear_bwd_kernel<BM, BN, NW, KB, NSTAGE>), dim3(grid), dim3(64 * NW), lds, s, a);
 }
 
 // Writes +0 to the rows of out[M][row_bytes] that are not in idx (inv: inverse map, see mark_rows_kernel).
@@ -916,8 +1035,8 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
     }
     dbp = part;
   }
-  // the fp32 engine with one split writes dW and db itself
-  const bool direct = !use_mfma && splits == 1 && !accumulate && !dw_bf16;
+  // the fp32 engine and the 128-wide tiles with one split write dW and db themselves
+  const bool direct = splits == 1 && !accumulate && !dw_bf16 && (!use_mfma || (!p.big && p.bm_w == mid::BT));
   bool kmajor = (flags & SBP_FLAG_XK_KMAJOR) && dW && Xk;
   if (kmajor && !(use_mfma && p.big && p.rows_per_split % 8 == 0 && p.rows_small % 8 == 0)) {
     void* rows = static_cast<char*>(ws) + p.off_xrows;
@@ -931,7 +1050,7 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
     LinArgs a{};
     a.dY = dYh; a.idx_in = idx_in; a.idx_out = idx_out; a.idx = idx; a.inv = inv;
     a.Xk = static_cast<const uint16_t*>(Xk); a.W = static_cast<const uint16_t*>(W);
-    a.dX = static_cast<uint16_t*>(dX); a.part = part; a.dbp = db ? dbp : nullptr;
+    a.dX = static_cast<uint16_t*>(dX); a.part = direct ? static_cast<float*>(dW) : part; a.dbp = db ? (direct ? db : dbp) : nullptr;
     a.K = (int)K; a.M = (int)M; a.Cin = Cin; a.Cout = Cout;
     a.rows_per_split = p.rows_per_split; a.db_slice_rows = p.db_slice_rows;
     a.xk_kmajor = kmajor ? 1 : 0;
@@ -946,12 +1065,8 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
       launch_linear_bwd<256, 256, 4, 32, 4>(p, a, want_dx, want_dw, scatter, s);
     else if (p.bm_w == 256)
       launch_linear_bwd<256, 256, 4, 64, 2>(p, a, want_dx, want_dw, scatter, s);
-    else if (p.kb == 32)
-      launch_linear_bwd<128, 128, 4, 32, 4>(p, a, want_dx, want_dw, scatter, s);
-    else if (p.dx_bm == 64)
-      launch_linear_bwd<128, 128, 4, 64, 2, 64, 3>(p, a, want_dx, want_dw, scatter, s);
     else
-      launch_linear_bwd<128, 128, 4, 64, 2>(p, a, want_dx, want_dw, scatter, s);
+      launch_linear_mid(p, a, want_dx, want_dw, scatter, s);
   } else {
     launch_linear_f32(splits, rows_per_split, dY, idx_in, idx_out, idx, inv, Xk, W, M, K, Cin, Cout, dtype,
                       dW != nullptr, direct ? static_cast<float*>(dW) : part, direct ? db : (db ? dbp : nullptr), dX, s);
@@ -960,8 +1075,8 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
   if ((dW || db) && !direct) {
     if (nW % 4 == 0) {
       const long long total = (dW ? nW / 4 : 0) + (db ? Cout : 0);
-      // (large tiles with dW: db partials come from the dW units, one per split and tile column)
-      const int nsplit_b = !use_mfma ? splits : (p.big && dW ? p.splits * (int)ceil_div(Cin, big::BT) : p.db_slices);
+      // (large tiles with dW: db partials come from the dW units, one per split and tile column; 128-wide tiles: one per split)
+      const int nsplit_b = !use_mfma ? splits : (!p.big && p.bm_w == mid::BT) ? p.splits : (p.big && dW ? p.splits * (int)ceil_div(Cin, big::BT) : p.db_slices);
       const int deepest = std::max(dW ? p.splits : 0, db ? nsplit_b : 0);
       const int G = reduce_lanes(total, deepest);
       unsigned blocks = (unsigned)std::min<long long>(ceil_div(total * G, NTHREADS), 4096);
@@ -1262,12 +1377,12 @@ static void choose_batch(const sbp_linear_layer* L, int n, BatchLayerChoice* c) 
   overrides();
 }
 
-// A batch of little work is better off in the one launch of the 128-tile engine: the large tiles' fixed parts (row tables, first
-// stages, epilogues of 256 KB) do not shrink with it.  Batched call with its reduction, large / 128 tiles: 3.8 GFLOP
-// (256 -> 1024 -> 256, 1800 rows) 29.4 / 18.5 us, 5.9 (320, 1800 rows) 35.3 / 24.0, 11.2 (the four linears of a block of
-// 384, 1584 rows) 41.3 / 33.0, 13.2 (256, 6300 rows) 40.8 / 38.0; 15.6 (block of 320, 3168 rows) 45.7 / 46.8, 17.7 (320,
-// 5400 rows) 47.6 / 46.9, 19.9 (block of 512, 1584 rows) 45.1 / 49.3, 44.8 (block of 768) 59.4 / 85.7.
-static constexpr double kSmallBatchFlops = 14e9;
+// A batch of layers that all take the 128-wide tiles is one launch of them up to this much work.  Batched call with its reduction,
+// large / 128-wide tiles, three sets of inputs in turn: 11.2 GFLOP (block of 192, 6336 rows) 42.8 / 35.0 us, 17.6 (512 -> 2048 -> 512,
+// 2100 rows) 48.8 / 36.0, 19.8 (384 -> 1536 -> 384, 4200 rows) 49.4 / 39.0, 22.4 (block of 384, 3168 rows) 52.2 / 45.6, 31.1 (block of
+// 320, 6336 rows) 78.9 / 71.0; 35.2 (512 -> 2048 -> 512, 4200 rows) 61.6 / 67.4, 39.9 (block of 512, 3168 rows) 68.7 / 78.7, 44.8 (block
+// of 384, 6336 rows) 82.4 / 89.3, 61.0 (block of 448, 6336 rows) 95.5 / 115.
+static constexpr double kSmallBatchFlops = 32e9;
 
 BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype) {
   BatchPlan p{};
@@ -1286,7 +1401,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
       const sbp_linear_layer& l = L[i];
       flops += 4.0 * (double)l.K * l.Cin * l.Cout;
       general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !((uintptr_t)l.dW & 15) &&
-                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, 0).big;
+                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags).big;
     }
     if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) p.fused = false;
   }
@@ -1295,9 +1410,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   size_t off = 0, seq_bytes = 0;
   for (int i = 0; i < n; ++i) {
     if (!p.fused) p.lay[i].off = seq_bytes;
-    // (the layer may run in one launch with the others or by itself)
-    seq_bytes += align_up(std::max(plan_linear(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags, 0).bytes,
-                                   linear_workspace(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags)), 256);
+    seq_bytes += align_up(plan_linear(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags).bytes, 256);
   }
   p.bytes = seq_bytes;
   if (!p.fused) return p;
@@ -1347,37 +1460,38 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
 }
 
 // A batch that does not take the large-tile grid but whose layers all take the general engine in its default shape
-// (bf16, 128 x 128 tiles, stages of 64): one launch of linear_bwd_multi_kernel + one reduction launch.  Every layer uses
+// (bf16, 128 x 128 tiles, stages of 64): one launch of linear_mid_multi_kernel + one reduction launch.  Every layer uses
 // its own piece of the workspace exactly as a single call would.  Returns false if the batch is not of that kind.
 static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, int32_t dtype, char* wsb, hipStream_t s, int32_t* status) {
   if (p.n < 2 || dtype != SBP_BF16 || options().tile_mode != 0) return false;
   LinearPlan lp[kMaxBatch];
   for (int i = 0; i < p.n; ++i) {
     const sbp_linear_layer& l = L[i];
-    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, 0);
-    if (!lp[i].mfma || lp[i].big || lp[i].bm_w != 128 || lp[i].nw_w != 4 || lp[i].kb != 64 || l.K < 1) return false;
+    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
+    if (!lp[i].mfma || lp[i].big || lp[i].bm_w != mid::BT || l.K < 1) return false;
     if (l.flags & SBP_FLAG_XK_KMAJOR) return false;
     if (!l.dW && !l.db && !l.dX) return false;
     if (((uintptr_t)l.dY | (uintptr_t)l.X_k | (uintptr_t)l.W | (uintptr_t)l.dX) & 15) return false;
     if (l.dW && ((uintptr_t)l.dW & 15)) return false;
   }
-  // the layers fill the chip together: each needs only its share of the dW splits a launch of its own would take (fewer
-  // partial sums to write and to add); the workspace was sized for the larger number
+  // the layers fill the chip together: each is planned for its share of the slots (fewer, longer dW units and fewer partial sums; the
+  // workspace was sized for the single call's splits)
+  double work = 0;
+  for (int i = 0; i < p.n; ++i) work += (double)L[i].K * L[i].Cin * L[i].Cout;
   for (int i = 0; i < p.n; ++i) {
-    const int64_t K = L[i].K;
-    int splits = (int)std::max<int64_t>(ceil_div(lp[i].splits, p.n), ceil_div(K, kMaxRowsPerSplit));
-    const int64_t rps = ceil_div(ceil_div(K, splits), 64) * 64;
-    splits = (int)ceil_div(K, rps);
-    if (splits < lp[i].splits) {
-      lp[i].splits = splits;
-      lp[i].rows_per_split = (int)rps;
-    }
+    const double share = (double)L[i].K * L[i].Cin * L[i].Cout / work;
+    const MidChoice c = choose_mid(L[i].K, L[i].Cin, L[i].Cout, std::max(64, (int)(2 * kNumCU * share) / 8 * 8));
+    if (c.splits > lp[i].splits) continue;
+    lp[i].splits = c.splits;
+    lp[i].rows_per_split = c.rps;
+    lp[i].dx_bm = c.dx_bm;
   }
-  SmallMultiArgs m{};
+  MidMultiArgs m{};
   RedMultiArgs r{};
-  m.n = r.n = p.n;
+  r.n = p.n;
   size_t lds = 0;
-  int blk = 0;
+  struct Segment { int64_t len; int layer, kind, n; };
+  std::vector<Segment> segs;
   bool any_reduce = false;
   for (int i = 0; i < p.n; ++i) {
     const sbp_linear_layer& l = L[i];
@@ -1385,6 +1499,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
     float* part = reinterpret_cast<float*>(w + lp[i].off_partial);
     float* dbp = part + (size_t)lp[i].splits * l.Cout * l.Cin;
     const bool dy_compact = l.flags & SBP_FLAG_DY_COMPACT, dx_compact = l.flags & SBP_FLAG_DX_COMPACT;
+    const bool direct = lp[i].splits == 1 && !(l.flags & (SBP_FLAG_ACCUMULATE_DW | SBP_FLAG_DW_OUT_BF16));
     const bool scatter = l.dX && !dx_compact;
     const int32_t* inv = l.inv;
     if (scatter && !inv) {
@@ -1398,30 +1513,36 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
     a.idx_out = dx_compact ? nullptr : l.idx;
     a.idx = l.idx; a.inv = inv;
     a.Xk = static_cast<const uint16_t*>(l.X_k); a.W = static_cast<const uint16_t*>(l.W);
-    a.dX = static_cast<uint16_t*>(l.dX); a.part = part; a.dbp = l.db ? dbp : nullptr;
+    a.dX = static_cast<uint16_t*>(l.dX); a.part = direct ? static_cast<float*>(l.dW) : part; a.dbp = l.db ? (direct ? l.db : dbp) : nullptr;
     a.K = (int)l.K; a.M = (int)l.M; a.Cin = l.Cin; a.Cout = l.Cout;
     a.rows_per_split = lp[i].rows_per_split; a.db_slice_rows = lp[i].db_slice_rows;
-    a.dx_bm = lp[i].dx_bm;
     size_t need = 0;
-    const unsigned grid = lp[i].dx_bm == 64
-        ? prepare_linear_bwd<128, 128, 4, 64, 2, 64, 3>(lp[i], a, l.dX != nullptr, l.dW != nullptr, scatter, &need)
-        : prepare_linear_bwd<128, 128, 4, 64, 2>(lp[i], a, l.dX != nullptr, l.dW != nullptr, scatter, &need);
+    int64_t len[3] = {0, 0, 0};
+    prepare_linear_mid(lp[i], a, l.dX != nullptr, l.dW != nullptr, scatter, &need, len);
     lds = std::max(lds, need);
-    m.start[i] = blk;
-    blk += (int)grid;
+    const int count[3] = {a.n_dx, a.n_dw, a.n_helper};
+    for (int q = 0; q < 3; ++q)
+      if (count[q]) segs.push_back({len[q], i, q, count[q]});
     RedLayer& rl = r.lay[i];
-    rl.part = part; rl.dbp = dbp; rl.dW = l.dW; rl.db = l.db;
+    rl.part = part; rl.dbp = dbp; rl.dW = direct ? nullptr : l.dW; rl.db = direct ? nullptr : l.db;
     rl.nW = (long long)l.Cin * l.Cout;
-    rl.nsplit_w = lp[i].splits; rl.nsplit_b = lp[i].db_slices; rl.Cout = l.Cout;
+    rl.nsplit_w = rl.nsplit_b = lp[i].splits; rl.Cout = l.Cout;
     rl.accumulate = (l.flags & SBP_FLAG_ACCUMULATE_DW) ? 1 : 0;
     rl.bf16out = (l.flags & SBP_FLAG_DW_OUT_BF16) ? 1 : 0;
     rl.G = reduce_lanes((rl.dW ? rl.nW / 4 : 0) + (rl.db ? rl.Cout : 0), std::max(rl.dW ? rl.nsplit_w : 0, rl.db ? rl.nsplit_b : 0));
     any_reduce = any_reduce || rl.dW || rl.db;
   }
-  m.start[p.n] = blk;
+  std::stable_sort(segs.begin(), segs.end(), [](const Segment& x, const Segment& y) { return x.len > y.len; });
+  int blk = 0;
+  for (const Segment& g : segs) {
+    m.start[m.n] = blk;
+    m.layer[m.n] = (signed char)g.layer; m.kind[m.n] = (signed char)g.kind;
+    ++m.n;
+    blk += g.n;
+  }
   if (blk > 0) {
-    allow_dynamic_lds(reinterpret_cast<const void*>(linear_bwd_multi_kernel), lds);
-    SBP_LAUNCH(SBP_PROF_DW_GEMM, s, linear_bwd_multi_kernel, dim3((unsigned)blk), dim3(256), lds, s, m);
+    allow_dynamic_lds(reinterpret_cast<const void*>(linear_mid_multi_kernel), lds);
+    SBP_LAUNCH(SBP_PROF_DW_GEMM, s, linear_mid_multi_kernel, dim3((unsigned)blk), dim3(256), lds, s, m);
   }
   if (any_reduce) {
     int rb = 0;
@@ -1446,7 +1567,7 @@ int32_t launch_backward_linear_batch(const BatchPlan& p, const sbp_linear_layer*
     for (int i = 0; i < p.n; ++i) {
       const sbp_linear_layer& l = L[i];
       if (!l.dW && !l.db && !l.dX) continue;
-      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, linear_want(l.dW, l.db, l.dX));
+      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
       const int32_t st = launch_backward_linear(lp, l.dY, l.idx, l.inv, l.X_k, l.W, l.M, l.K, l.Cin, l.Cout, dtype, l.dW,
                                                 l.db, l.dX, wsb + p.lay[i].off, l.flags, s);
       if (st != SBP_OK) return st;

@@ -12,8 +12,8 @@
 //   * "slow" tile [KB][cols]   for an operand whose contraction index is the slow axis in memory (dY
 //     and X_k in dW, W in dX): stored as it lies in memory and read with the transposing LDS read
 //     ds_read_b64_tr_b16, which hands every lane 4 consecutive contraction elements of its column.
-// This file holds the general engine (any shape, 128 x 128 tiles by default, two blocks per CU) and
-// the pieces shared with the large-tile engine of sbp_mfma_big.h.
+// This file holds the 256-wide variants of the general engine (selectable for sweeps) and the pieces shared
+// with the 128-wide engine of sbp_mfma_mid.h and the large-tile engine of sbp_mfma_big.h.
 // The main loop is free of bounds checks: addresses are clamped into the operand (rows or columns
 // past the edge compute results that are never stored) and only the last, partial stage zeroes the
 // contraction rows past the end.

@@ -58,7 +58,7 @@ int32_t sbp_backward_linear_static(const void* dY, const int32_t* idx, const int
   if (!dW && !db && !dX) return SBP_OK;
   void* ws = static_scratch_ptr();
   if (!ws) return SBP_ERR_HIP;
-  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags, linear_want(dW, db, dX));
+  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
   return launch_backward_linear(p, dY, idx, inv, Xk, W, M, K, Cin, Cout, dtype, dW, db, dX, ws, flags,
                                 (hipStream_t)stream);
 }

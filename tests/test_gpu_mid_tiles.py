@@ -1,0 +1,83 @@
+"""The 128-wide engine of the linear backward against the oracle where it can go wrong: contractions of one to a few stages of 32 with
+and without a partial last one (fewer than the ring of four is deep, exactly as many, more), ragged tiles, one split (dW and db written
+by the units themselves) and several, gathered and compact rows, dX tiles of 64 and 128 rows; db alone in the same bits; several layers
+in one launch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2210_00129_amd as sbp
+import synth_inputs as si
+from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, nerr
+
+pytestmark = pytest.mark.gpu
+COMPACT = sbp.FLAG_DY_COMPACT | sbp.FLAG_DX_COMPACT
+
+
+def _case(M, K, Cin, Cout, seed):
+    idx = np.sort(np.random.default_rng(seed).choice(M, size=K, replace=False)).astype(np.int32)
+    X, W, dY = si.linear_case(M, Cin, Cout, seed, "bf16")
+    return X, W, dY, idx
+
+
+@pytest.mark.parametrize("rows", [64, 128])
+@pytest.mark.parametrize("K", [1, 31, 32, 33, 64, 97, 128, 129, 161, 2047, 2049, 4097])
+def test_kept_rows_around_stages_and_splits(K, rows):
+    # the dW contraction: 1 to 5 stages, the longest single split (2048 rows) and one more, two full ones and one more
+    X, W, dY, idx = _case(max(2 * K, 40), K, 136, 72, K)
+    with sbp.options(tile="128x128x4x64", dxrows=rows):
+        check_linear(X, W, dY, idx, "bf16", flags=COMPACT if K % 2 else 0)
+
+
+@pytest.mark.parametrize("rows", [64, 128])
+@pytest.mark.parametrize("Cout", [8, 24, 32, 40, 64, 96, 104, 128, 136, 160, 168, 264])
+def test_output_channels_around_stages(Cout, rows):
+    # the dX contraction: a partial stage alone, 1 to 9 stages, partial last ones of 8, 16 and 24 channels
+    X, W, dY, idx = _case(300, 131, 120, Cout, Cout)
+    with sbp.options(tile="128x128x4x64", dxrows=rows):
+        check_linear(X, W, dY, idx, "bf16")
+        check_linear(X, W, dY, idx, "bf16", flags=sbp.FLAG_DY_COMPACT)
+
+
+@pytest.mark.parametrize("K,Cin,Cout", [(40, 136, 264), (700, 264, 136), (3000, 64, 520)])
+def test_db_has_the_same_bits_whichever_outputs_are_wanted(K, Cin, Cout):
+    X, W, dY, idx = _case(2 * K, K, Cin, Cout, 7)
+    idxd = torch.from_numpy(idx).cuda()
+    Xk = sbp.forward_cache(X.cuda(), idxd)
+    with sbp.options(tile="128x128x4x64"):
+        full = sbp.backward_linear(dY.cuda(), idxd, Xk, W.cuda())
+        alone = sbp.backward_linear(dY.cuda(), idxd, Xk, W.cuda(), want=("db",))
+        with_dX = sbp.backward_linear(dY.cuda(), idxd, Xk, W.cuda(), want=("db", "dX"))
+        dW0 = torch.full((Cout, Cin), 2.0, device="cuda")
+        db0 = torch.full((Cout,), -1.0, device="cuda")
+        acc = sbp.backward_linear(dY.cuda(), idxd, Xk, W.cuda(), flags=sbp.FLAG_ACCUMULATE_DW, dW=dW0, db=db0)
+    assert np.array_equal(bits(alone[1]), bits(full[1])) and np.array_equal(bits(with_dX[1]), bits(full[1]))
+    assert np.array_equal(bits(with_dX[2]), bits(full[2]))
+    # accumulation adds the same sums to the old values
+    assert np.array_equal(bits(acc[0]), bits(full[0] + 2.0)) and np.array_equal(bits(acc[1]), bits(full[1] - 1.0))
+
+
+def test_layers_of_one_launch_longest_workgroups_first():
+    # four layers whose kinds of workgroups differ in length by an order of magnitude, one of them without dX, one compact, one
+    # accumulating: the launch orders their segments by length, whatever the layer
+    shapes = [(900, 136, 1048, 0, True), (64, 72, 40, COMPACT, True), (1800, 264, 136, sbp.FLAG_ACCUMULATE_DW, True), (130, 520, 8, 0, False)]
+    layers, refs = [], []
+    for i, (K, Cin, Cout, flags, want_dx) in enumerate(shapes):
+        M = 2 * K
+        X, W, dY, idx = _case(M, K, Cin, Cout, 40 + i)
+        idxd = torch.from_numpy(idx).cuda()
+        refs.append(oracle.backward_linear(si.to_f64(dY), idx, si.to_f64(X)[idx], si.to_f64(W), M) + (idx,))
+        d = dY.cuda()[idxd.long()].contiguous() if flags & sbp.FLAG_DY_COMPACT else dY.cuda()
+        l = dict(dY=d, idx=idxd, X_k=sbp.forward_cache(X.cuda(), idxd), W=W.cuda(), M=M, flags=flags,
+                 dW=torch.full((Cout, Cin), 1.0, device="cuda"), db=torch.full((Cout,), 1.0, device="cuda"))
+        if want_dx:
+            l["dX"] = torch.full((K if flags & sbp.FLAG_DX_COMPACT else M, Cin), 9.0, dtype=torch.bfloat16, device="cuda")
+        layers.append(l)
+    out = sbp.backward_linear_batch(layers, want=())
+    torch.cuda.synchronize()
+    for (K, Cin, Cout, flags, want_dx), l, (rW, rb, rX, idx) in zip(shapes, layers, refs):
+        one = 1.0 if flags & sbp.FLAG_ACCUMULATE_DW else 0.0
+        assert nerr(f64(l["dW"]), rW + one) <= TOL_F32 and nerr(f64(l["db"]), rb + one) <= TOL_F32
+        if want_dx:
+            assert nerr(f64(l["dX"]), rX[idx] if flags & sbp.FLAG_DX_COMPACT else rX) <= TOL_BF16_TIGHT
