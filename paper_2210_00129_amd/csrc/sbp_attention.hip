@@ -184,26 +184,36 @@ struct AttnPadded {
   }
 };
 // AttnSwizzled: rows of 2 D bytes, 16-byte chunk c of row r at place c ^ swz(r), written by global -> LDS copies whose lanes
-// choose the chunk they fetch (the copy fixes the LDS place by lane).  8 neighbouring rows fall on distinct banks.
+// choose the chunk they fetch (the copy fixes the LDS place by lane; a copy fills 1 KB, 512 / D rows).  Both kinds of reads meet
+// all 64 banks once: a transposing read's half wavefront takes 64 bytes of each of 4 neighbouring rows, so these rows differ in
+// the bits of the place above the chunks it takes (bit 2; D = 128: bits 2 and 3), and the 16-byte reads of 16 neighbouring rows
+// fall on different places because the copies within 16 rows lie 16 bytes further apart than their 1 KB.  (With c ^ (r & 7) and no
+// gaps rows r and r + 2 exchanged places within the same 64 bytes: every transposing read took two turns, D = 128 four.)
 template <int D>
 struct AttnSwizzled {
   static constexpr int RB = 2 * D, CH = D / 8, KS = D / 16, DB = D / 32;
-  static __device__ __forceinline__ int swz(int r) { return D == 32 ? (r >> 1) & 3 : r & 7; }
+  static constexpr int RPC = 512 / D, COPY = D == 32 ? 1024 : 1040, G16 = (16 / RPC - 1) * COPY + 1024;   // rows of a copy, pitch of the copies, bytes of 16 rows
+  static __device__ __forceinline__ int swz(int r) {
+    return D == 32 ? (r >> 1) & 3 : D == 64 ? (r & 2) << 1 | (r & 4) >> 1 : (r & 3) << 2;
+  }
+  static __device__ __forceinline__ int place(int r) { return (r >> 4) * G16 + ((r & 15) / RPC) * COPY + (r % RPC) * RB; }
   int foff[KS], toff[DB];
   __device__ __forceinline__ explicit AttnSwizzled(int lane) {
     const int g = lane >> 4, i = lane & 15, r = lane & 31, rt = 4 * (g >> 1) + (i >> 2);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) foff[ks] = r * RB + (((2 * ks + (lane >> 5)) ^ swz(r)) << 4);
+    for (int ks = 0; ks < KS; ++ks) foff[ks] = place(r) + (((2 * ks + (lane >> 5)) ^ swz(r)) << 4);
 #pragma unroll
-    for (int x = 0; x < DB; ++x) toff[x] = rt * RB + (((4 * x + 2 * (g & 1) + ((i & 3) >> 1)) ^ swz(rt)) << 4) + 8 * (i & 1);
+    for (int x = 0; x < DB; ++x) toff[x] = place(rt) + (((4 * x + 2 * (g & 1) + ((i & 3) >> 1)) ^ swz(rt)) << 4) + 8 * (i & 1);
   }
+  // row0: a multiple of 32
   __device__ __forceinline__ bf16x8_t row(const char* tile, int row0, int ks) const {
-    return *reinterpret_cast<const bf16x8_t*>(tile + row0 * RB + foff[ks]);
+    return *reinterpret_cast<const bf16x8_t*>(tile + (row0 >> 4) * G16 + foff[ks]);
   }
+  // row0: a multiple of 16; rows 8 further on lie 8 / RPC copies further on, with the same swz
   __device__ __forceinline__ bf16x8_t tr(const char* tile, int row0, int x) const {
-    const char* p = tile + row0 * RB + toff[x];
+    const char* p = tile + (row0 >> 4) * G16 + toff[x];
     const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p));
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p + 8 * RB));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((SBP_LDS s16x4_t*)(p + (D == 32 ? 8 * RB : 8 / RPC * COPY)));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   }
 };
@@ -385,7 +395,8 @@ struct AttnQueryAcc {
   static constexpr int PITCH = AttnLds<D>::PITCH, KS = D / 16, DB = D / 32;
   f32x16_t dq[DB];
   bf16x8_t qf[KS], gf[KS];
-  float l, ndl;                  // lse * log2(e) and -delta of query (lane & 31)
+  float l;                       // lse * log2(e) of query (lane & 31)
+  f32x16_t nd;                   // -delta of that query in every register: dP starts from it
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int x = 0; x < DB; ++x)
@@ -401,7 +412,14 @@ struct AttnQueryAcc {
       gf[ks] = *reinterpret_cast<const bf16x8_t*>(tg + foff + ks * 32);
     }
     l = lse_s[row0 + (lane & 31)];
-    ndl = delta_s[row0 + (lane & 31)];
+    start(delta_s[row0 + (lane & 31)]);
+  }
+  __device__ __forceinline__ void start(float ndl) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      nd[e] = ndl;
+      asm("" : "+v"(nd[e]));                   // (16 registers for good: as one value it would be copied 16 times per block)
+    }
   }
   // straight from memory: q, dA, A rows of the lane's token (head's columns) and its lse
   __device__ __forceinline__ void from_memory(const uint16_t* qrow, const uint16_t* grow, const uint16_t* arow, const float* lse_tok, int lane) {
@@ -415,7 +433,7 @@ struct AttnQueryAcc {
 #pragma unroll
       for (int e = 0; e < 4; ++e) part += bf16_lo(gw[e]) * bf16_lo(aw[e]) + bf16_hi(gw[e]) * bf16_hi(aw[e]);
     }
-    ndl = -(part + __shfl_xor(part, 32));      // the two halves of every 16 columns lie 32 lanes apart
+    start(-(part + __shfl_xor(part, 32)));     // the two halves of every 16 columns lie 32 lanes apart
     l = *lse_tok * kLog2e;
   }
   // keys: valid rows of the tile (rows past them count for nothing: their probabilities are zeroed)
@@ -430,14 +448,14 @@ struct AttnQueryAcc {
     const float c2 = scale * kLog2e;
     f32x16_t s, dp;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+    for (int e = 0; e < 16; ++e) s[e] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tk, j0, ks), qf[ks], s, 0, 0, 0);      // rows j, columns i
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tv, j0, ks), gf[ks], dp, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lay.row(tv, j0, ks), gf[ks], ks ? dp : nd, 0, 0, 0);
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) dp[e] = (dp[e] + ndl) * __builtin_amdgcn_exp2f(s[e] * c2 - l);
+    for (int e = 0; e < 16; ++e) dp[e] *= __builtin_amdgcn_exp2f(s[e] * c2 - l);
     if constexpr (TAIL) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) dp[e] = j0 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) < keys ? dp[e] : 0.f;
@@ -528,17 +546,20 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 2) attn_bwd_mfma_kernel(co
 // (8 x 12 heads of 1024 tokens, counters: 289 MB read and 41 written across the L2 boundary by the kernel before, spread over all
 // eight; now 60 and 38); an XCD runs its key units first, the longer kind (110 -> 102 us), at the price of a second read of small
 // heads (27.6 instead of 26.6 us at 768 heads of 99 tokens).
-// Bound, by counters: the matrix cores are busy 46 % of the cycles of a CU (36 % before), the LDS 55 %, of which 44 % are bank
-// conflicts of the transposing reads, and the softmax arithmetic between the products takes most of the rest; unit starts (first
+// Bound, by counters: the matrix cores are busy 47 % of the cycles of a CU, the LDS 45 % (55 % with the conflicts of the layout
+// before, AttnSwizzled), and the softmax arithmetic between the products takes most of the rest; unit starts (first
 // tiles and tables from memory) and the power limit (1.85 GHz) add to it.  8 x 12 heads of 64, 1024 kept tokens, a call:
-// 134 -> 101 us.
+// 134 -> 101 us with the ring, 99.6 with dP of the query role started from -delta and the layout without conflicts; 8 x 12 heads of
+// 32 62.9 -> 60.4 us; 8 x 8 heads of 128, whose transposing reads took four turns, 184 -> 163 us.  Both blocks of a tile unrolled
+// (constant LDS addresses): 35 to 77 spills with three workgroups per CU, 114 us with two.  s_setprio around the products: 98.1 us, but
+// 58.8 instead of 54.9 us at 64 x 12 heads of 197 tokens.
 // Two more shapes were slower: 64 tokens per wavefront (half the LDS reads per MFMA, but 330 registers and one wavefront
 // per SIMD: accumulator moves and spills, 225 us), and the same with dK and dV as separate roles (148 us).
 // ------------------------------------------------------------------------------------------------
 static constexpr int kAttnChunk = 128, kAttnTile = 64, kAttnRing = 3, kAttnTable = 512;
 
 template <int D> struct AttnTiled {
-  static constexpr int RB = 2 * D, IMG = kAttnTile * RB, STAGE = 2 * IMG;    // bytes per row, image, tile
+  static constexpr int RB = 2 * D, IMG = kAttnTile / 16 * AttnSwizzled<D>::G16, STAGE = 2 * IMG;    // bytes per row, image, tile
   static constexpr size_t LDS = (size_t)kAttnRing * STAGE + 2 * kAttnTable * sizeof(float);
   static_assert(4 * 2 * 32 * (RB + 16) <= kAttnRing * STAGE, "the output images fit the ring");
 };
@@ -566,14 +587,14 @@ struct AttnStream {
   }
   // copies of tile s (the tiles in order) into its ring place
   __device__ __forceinline__ void issue(int s, char* ring, int lane, int wave) {
-    char* buf = ring + (s % kAttnRing) * AttnTiled<D>::STAGE + wave * NI * 1024;
+    char* buf = ring + (s % kAttnRing) * AttnTiled<D>::STAGE + wave * AttnSwizzled<D>::G16;    // (a wavefront copies 16 rows)
     if ((s + 1) * kAttnTile > n_k) offsets(n_k - s * kAttnTile, lane, wave);
     const char* b1 = reinterpret_cast<const char*>(s1 + (long long)s * kAttnTile * ld1);
     const char* b2 = reinterpret_cast<const char*>(s2 + (long long)s * kAttnTile * ld2);
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
-      async_copy16(b1 + off1[n], buf + n * 1024);
-      async_copy16(b2 + off2[n], buf + AttnTiled<D>::IMG + n * 1024);
+      async_copy16(b1 + off1[n], buf + n * AttnSwizzled<D>::COPY);
+      async_copy16(b2 + off2[n], buf + AttnTiled<D>::IMG + n * AttnSwizzled<D>::COPY);
     }
   }
 };
