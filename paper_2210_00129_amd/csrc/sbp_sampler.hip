@@ -124,6 +124,7 @@ struct VariantGeom {
   int tail_keep;      // temporal: kept frames of the partial last cell
   uint64_t base;
   uint64_t win_lo, win_hi;   // random mask on large maps: the n_keep-th smallest key is expected in [win_lo, win_hi)
+  int win_shift;             // (key - win_lo) >> win_shift numbers the window's kSelectBuckets buckets
   int mask_chunks;           // random mask on large maps: chunks of 64 positions whose keep bits fit the dynamic LDS (0: none)
 };
 
@@ -138,6 +139,18 @@ struct VariantGeom {
 // The ordered write-out of a large map keeps one 64-bit "below" and one "equal" mask per chunk of 64 positions in
 // LDS (one hash pass, a ballot per chunk), scans the chunk counts once, and every wavefront then writes its chunks
 // without further barriers; where the masks do not fit (mask_chunks == 0) the chunked loop of the small maps runs.
+static constexpr int kSelectBuckets = 1024, kSelectFew = 64;
+
+// Wavefront-aggregated append to the collected keys: one LDS atomic per wavefront that has any.  Returns the lane's slot.
+__device__ __forceinline__ int collect_slot(bool mine, int* count, int lane) {
+  const unsigned long long m = __ballot(mine);
+  if (!m) return 0;
+  int base = 0;
+  if (lane == __ffsll((long long)m) - 1) base = atomicAdd(count, (int)__popcll(m));
+  base = __shfl(base, __ffsll((long long)m) - 1);
+  return base + (int)__popcll(m & ((1ull << lane) - 1ull));
+}
+
 template <int NT, bool WINDOW>
 __global__ void __launch_bounds__(NT) sample_random_kernel(VariantGeom g, int32_t* __restrict__ idx,
                                                            int32_t* __restrict__ inv) {
@@ -145,7 +158,9 @@ __global__ void __launch_bounds__(NT) sample_random_kernel(VariantGeom g, int32_
   __shared__ uint64_t cand[CAP];
   __shared__ int cand_pos[CAP];                      // position of every collected key (large maps with keep bits in LDS)
   __shared__ int s_ncand, s_below;
-  __shared__ int hist[256];
+  __shared__ int hist[WINDOW ? kSelectBuckets : 256];
+  __shared__ uint64_t few[WINDOW ? kSelectFew : 1];
+  __shared__ int s_bucket, s_nfew;
   __shared__ uint64_t s_prefix;
   __shared__ int s_remaining;
   __shared__ int s_wave_lt[NWAVE], s_wave_eq[NWAVE];
@@ -172,15 +187,10 @@ __global__ void __launch_bounds__(NT) sample_random_kernel(VariantGeom g, int32_
       unsigned long long* m_eq0 = dyn0 + g.mask_chunks;
       for (int c = wave; c < g.mask_chunks; c += NWAVE) {
         const int p = 64 * c + lane;
-        bool lt = false;
-        if (p < n) {
-          const uint64_t key = absorb(hb, (uint64_t)p);
-          lt = key < g.win_lo;
-          if (!lt && key < g.win_hi) {
-            const int slot = atomicAdd(&s_ncand, 1);
-            if (slot < CAP) { cand[slot] = key; cand_pos[slot] = p; }
-          }
-        }
+        const uint64_t key = absorb(hb, (uint64_t)p);
+        const bool lt = p < n && key < g.win_lo, in = p < n && !lt && key < g.win_hi;
+        const int slot = collect_slot(in, &s_ncand, lane);
+        if (in && slot < CAP) { cand[slot] = key; cand_pos[slot] = p; }
         const unsigned long long mlt = __ballot(lt);
         if (lane == 0) { m_lt0[c] = mlt; m_eq0[c] = 0ull; }
         below += lt ? 1 : 0;
@@ -205,8 +215,60 @@ __global__ void __launch_bounds__(NT) sample_random_kernel(VariantGeom g, int32_
     windowed = ncand <= CAP && rank >= 1 && rank <= ncand;
     if (windowed) want = rank;
   }
-  if (t == 0) { s_prefix = 0; s_remaining = want; }
-  for (int pass = 0; pass < 8; ++pass) {
+  // The window holds some hundred keys, uniform in it: one histogram of kSelectBuckets buckets leaves a key or two in the wanted
+  // one, which a wavefront ranks by comparing them all.  (Eight passes of 8 bits over the keys took 8 of the 22 us of a 100 x 168
+  // map.)  Should more than kSelectFew keys share the bucket, the radix select below runs.
+  bool selected = false;
+  if (WINDOW && windowed) {
+    if (t == 0) { s_nfew = 0; s_prefix = 0; }
+    for (int i = t; i < kSelectBuckets; i += NT) hist[i] = 0;
+    __syncthreads();
+    for (int i = t; i < ncand; i += NT) atomicAdd(&hist[(int)((cand[i] - g.win_lo) >> g.win_shift)], 1);
+    __syncthreads();
+    constexpr int PER = WINDOW ? kSelectBuckets / NT : 1;      // a thread scans PER neighbouring buckets
+    int c[PER], sum = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) { c[e] = hist[t * PER + e]; sum += c[e]; }
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) s_wave_lt[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += s_wave_lt[w];
+    int excl = incl - sum;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {                            // exactly one bucket of one thread
+      if (excl < want && want <= excl + c[e]) { s_bucket = t * PER + e; s_remaining = want - excl; }
+      excl += c[e];
+    }
+    __syncthreads();
+    const int bucket = s_bucket;
+    for (int i = t; i < ncand; i += NT)
+      if ((int)((cand[i] - g.win_lo) >> g.win_shift) == bucket) {
+        const int slot = atomicAdd(&s_nfew, 1);
+        if (slot < kSelectFew) few[slot] = cand[i];
+      }
+    __syncthreads();
+    const int nfew = s_nfew, rem = s_remaining;
+    selected = nfew <= kSelectFew;
+    __syncthreads();                                           // everyone has read s_remaining
+    if (selected && wave == 0) {
+      const uint64_t key = few[min(lane, nfew - 1)];
+      int less = 0, equal = 0;
+      for (int i = 0; i < nfew; ++i) {
+        const uint64_t other = few[i];
+        less += other < key ? 1 : 0;
+        equal += other == key ? 1 : 0;
+      }
+      if (lane < nfew && less < rem && rem <= less + equal) { s_prefix = key; s_remaining = rem - less; }   // (equal keys: the same values)
+    }
+    __syncthreads();
+  }
+  if (!selected && t == 0) { s_prefix = 0; s_remaining = want; }
+  for (int pass = 0; pass < 8 && !selected; ++pass) {
     const int shift = 56 - 8 * pass;
     if (t < 256) hist[t] = 0;
     __syncthreads();
@@ -587,20 +649,22 @@ int32_t launch_sample(const sbp_sample_desc& d, int32_t* idx, int32_t* inv, hipS
         const double lo = std::max(0.0, q - half), hi = q + half;
         v.win_lo = (uint64_t)(lo * two64);
         v.win_hi = hi >= 1.0 ? ~0ull : (uint64_t)(hi * two64);
+        v.win_shift = 0;
+        while (((v.win_hi - v.win_lo) >> v.win_shift) >= (uint64_t)kSelectBuckets) ++v.win_shift;
         const Options opt = options();
         if (opt.sampler_no_window) v.win_lo = v.win_hi = 0;   // override: an empty window, i.e. the full select
-        // keep bits and chunk prefixes of the ordered write-out: 24 bytes per 64 positions, next to 50 KB of static LDS
+        // keep bits and chunk prefixes of the ordered write-out: 24 bytes per 64 positions, next to 53 KB of static LDS
         const int64_t chunks = ceil_div((int64_t)d.H * d.W, 64);
         size_t lds = (size_t)chunks * 24;
         static std::once_flag big_lds_once;             // more than 64 KB in all: granted per kernel, asked for once
         static bool big_lds_ok = false;
-        if (lds > 12 * 1024)
+        if (lds > 11 * 1024)
           std::call_once(big_lds_once, [] {
             big_lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(sample_random_kernel<1024, true>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024) == hipSuccess;
           });
         v.mask_chunks = (int)chunks;
-        if (lds > 104 * 1024 || (lds > 12 * 1024 && !big_lds_ok) || opt.sampler_no_masks) { v.mask_chunks = 0; lds = 0; }
+        if (lds > 104 * 1024 || (lds > 11 * 1024 && !big_lds_ok) || opt.sampler_no_masks) { v.mask_chunks = 0; lds = 0; }
         SBP_LAUNCH(SBP_PROF_SAMPLE, s, (sample_random_kernel<1024, true>), dim3(d.B), dim3(1024), lds, s, v, idx, inv);
       } else {
         SBP_LAUNCH(SBP_PROF_SAMPLE, s, (sample_random_kernel<256, false>), dim3(d.B), dim3(256), 0, s, v, idx, inv);
