@@ -1035,7 +1035,9 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
     }
     dbp = part;
   }
-  // the fp32 engine and the 128-wide tiles with one split write dW and db themselves
+  // one split: the units write dW themselves (large tiles: db still as one partial sum per tile column), ...
+  const bool dw_direct = splits == 1 && dW && !accumulate && !dw_bf16;
+  // ... the fp32 engine and the 128-wide tiles db too
   const bool direct = splits == 1 && !accumulate && !dw_bf16 && (!use_mfma || (!p.big && p.bm_w == mid::BT));
   bool kmajor = (flags & SBP_FLAG_XK_KMAJOR) && dW && Xk;
   if (kmajor && !(use_mfma && p.big && p.rows_per_split % 8 == 0 && p.rows_small % 8 == 0)) {
@@ -1050,7 +1052,7 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
     LinArgs a{};
     a.dY = dYh; a.idx_in = idx_in; a.idx_out = idx_out; a.idx = idx; a.inv = inv;
     a.Xk = static_cast<const uint16_t*>(Xk); a.W = static_cast<const uint16_t*>(W);
-    a.dX = static_cast<uint16_t*>(dX); a.part = direct ? static_cast<float*>(dW) : part; a.dbp = db ? (direct ? db : dbp) : nullptr;
+    a.dX = static_cast<uint16_t*>(dX); a.part = dw_direct ? static_cast<float*>(dW) : part; a.dbp = db ? (direct ? db : dbp) : nullptr;
     a.K = (int)K; a.M = (int)M; a.Cin = Cin; a.Cout = Cout;
     a.rows_per_split = p.rows_per_split; a.db_slice_rows = p.db_slice_rows;
     a.xk_kmajor = kmajor ? 1 : 0;
@@ -1072,17 +1074,18 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
                       dW != nullptr, direct ? static_cast<float*>(dW) : part, direct ? db : (db ? dbp : nullptr), dX, s);
   }
 
-  if ((dW || db) && !direct) {
+  void* const dW_sum = dw_direct ? nullptr : dW;             // what is left to add up
+  if ((dW_sum || db) && !direct) {
     if (nW % 4 == 0) {
-      const long long total = (dW ? nW / 4 : 0) + (db ? Cout : 0);
+      const long long total = (dW_sum ? nW / 4 : 0) + (db ? Cout : 0);
       // (large tiles with dW: db partials come from the dW units, one per split and tile column; 128-wide tiles: one per split)
       const int nsplit_b = !use_mfma ? splits : (!p.big && p.bm_w == mid::BT) ? p.splits : (p.big && dW ? p.splits * (int)ceil_div(Cin, big::BT) : p.db_slices);
-      const int deepest = std::max(dW ? p.splits : 0, db ? nsplit_b : 0);
+      const int deepest = std::max(dW_sum ? p.splits : 0, db ? nsplit_b : 0);
       const int G = reduce_lanes(total, deepest);
       unsigned blocks = (unsigned)std::min<long long>(ceil_div(total * G, NTHREADS), 4096);
       auto kernel = dw_bf16 ? (G == 8 ? reduce_splits_kernel<8, true> : (G == 4 ? reduce_splits_kernel<4, true> : reduce_splits_kernel<1, true>))
                             : (G == 8 ? reduce_splits_kernel<8, false> : (G == 4 ? reduce_splits_kernel<4, false> : reduce_splits_kernel<1, false>));
-      SBP_LAUNCH(SBP_PROF_REDUCE, s, kernel, dim3(blocks), dim3(NTHREADS), 0, s, part, p.splits, nW, dW, dbp, nsplit_b, Cout, db,
+      SBP_LAUNCH(SBP_PROF_REDUCE, s, kernel, dim3(blocks), dim3(NTHREADS), 0, s, part, p.splits, nW, dW_sum, dbp, nsplit_b, Cout, db,
                  accumulate);
     } else {
       const long long total = (dW ? nW : 0) + (db ? Cout : 0);
