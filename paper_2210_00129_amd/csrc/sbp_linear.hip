@@ -693,6 +693,9 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
 // at 2 TB/s for the reduction.  Its choice is within 1.2 % of the best one on average, 10 % at worst.  With the splits that fill all
 // slots whatever their length (the rule before) 8400 rows of 256 -> 1024 took 23.3 us, now 18.6; 4200 of 512 -> 2048 33.0, now 30.2.
 // (64 rows win where the tiles are few: 900 rows of 200 -> 1000 11.4 us, 14.0 with 128 rows.)
+// Layers of more than 64 MB: their rows come from memory more often than not, and a dW stage is 0.3 us then (33600 rows of 512 -> 128,
+// four sets of inputs in turn: 35.1 us with the 23 splits of 0.2 us a stage, 28.8 with 48; 40000 of 384 -> 96 31.3 and 25.0; warm 22.8
+// and 24.5 for the first).
 struct MidChoice { int64_t K; int32_t Cin, Cout, slots; int splits, rps, dx_bm; double cost_ns; };
 
 // end of a grid of n1 units of length l1 and then n2 of l2 on `slots` slots, each unit in the slot that is free first
@@ -718,6 +721,7 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
   const int64_t fewest = ceil_div(K, kMaxRowsPerSplit);      // the split's row ids sit in LDS
   const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>(64, std::max<int64_t>(1, K / 64)));
   MidChoice best{K, Cin, Cout, slots, 0, 0, 128, 0.0};
+  const bool streams = 2.0 * (double)K * (2.0 * Cin + Cout) > 64e6;
   int64_t best_cost = 0;
   for (int64_t want = fewest; want <= most; ++want) {
     const int64_t rps = ceil_div(ceil_div(K, want), 64) * 64, splits = ceil_div(K, rps);
@@ -728,7 +732,7 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
     for (int bm : {128, 64}) {
       const int64_t n_dx = ceil_div(ceil_div(K, bm) * tiles_n, 8);
       const bool alone = 8 * (n_dx + n_dw) <= slots / 2;
-      const int64_t l_dx = 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * nk_x, l_dw = 5000 + (alone ? 220 : 200) * ceil_div(std::min(rps, K), mid::KB);
+      const int64_t l_dx = 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * nk_x, l_dw = 5000 + (streams ? 300 : alone ? 220 : 200) * ceil_div(std::min(rps, K), mid::KB);
       const int64_t end = l_dx > l_dw ? two_kinds_end(n_dx, l_dx, n_dw, l_dw, slots / 8) : two_kinds_end(n_dw, l_dw, n_dx, l_dx, slots / 8);
       if (best.splits == 0 || end + reduce < best_cost) {
         best_cost = end + reduce;
@@ -744,7 +748,7 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
 // Time of one layer with the 128-wide tiles, its reduction included: 10 us + 1.3 us per GFLOP (within 15 % over 24 shapes of 2 to 67
 // GFLOP), or what the plan's own costs add up to where a grid just misses the slots.  The large tiles take 0.95 of their simulated
 // cost, 0.87 where whole 256-wide tiles cover the layer (nothing padded), and are ahead of the 128-wide ones on such layers from 20
-// GFLOP on whatever the estimates.  Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 ->
+// GFLOP on and on all from 45 GFLOP on, whatever the estimates (25680 rows of 368 -> 2528: 138 us, 165 with 128-wide tiles).  Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 ->
 // 1024), 31.5 / 34.5 (4200, 2048 -> 512), 29.0 / 33.5 (4200, 1024 x 1024), 44.0 / 57.2 (12608, 384 -> 1536); 43.7 / 41.2 (2100, 1024 ->
 // 3072), 59.2 / 57.8 (6336, 768 -> 2304), 89.7 / 78.0 (6336, 3072 -> 768), 90.3 / 77.3 (4000, 4096 -> 1024).
 // Two kinds of whole-tile layers keep the large tiles although the 128-wide ones are ahead of them by themselves: those of three tiles
@@ -753,7 +757,7 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
 static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns) {
   const double gf = 4e-9 * (double)K * Cin * Cout;
   const bool whole = Cin % big::BT == 0 && Cout % big::BT == 0;
-  if (whole && (gf >= 20.0 || Cout >= 1536 || (K >= 5000 && std::min(Cin, Cout) >= 3 * big::BT))) return false;
+  if (gf >= 45.0 || (whole && (gf >= 20.0 || Cout >= 1536 || (K >= 5000 && std::min(Cin, Cout) >= 3 * big::BT)))) return false;
   return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU).cost_ns) < (whole ? 0.87 : 0.95) * big_cost_ns;
 }
 
