@@ -43,6 +43,10 @@ def _dev(t, name):
     return t.data_ptr()
 
 
+def _native():
+    return _lib._native or _lib.native()
+
+
 def _stream(device) -> int:
     # (the handle alone: a Stream object made on every call cost 3 us of host time, 10 of the 40 us of a small layer's three calls;
     # looked up here: a torch without GPU support does not have it)
@@ -69,16 +73,12 @@ def keep_count(B, P, H, W, k, mode=GRID_PER_CELL, per_sample=True, cell=2) -> in
 def sample_indices(B, P, H, W, k, seed, stream_id, mode=GRID_PER_CELL, per_sample=True, want_inv=False,
                    device="cuda", idx_out=None, inv_out=None, cell=2):
     """Draws the keep-set on the GPU; returns (idx [K] int32, inv [B*(P+H*W)] int32 or None)."""
-    d = make_desc(B, P, H, W, k, seed, stream_id, mode, per_sample, cell)
-    K = _lib.check(_lib.lib().sbp_keep_count(d))
     dev = torch.device(device)
-    idx = idx_out if idx_out is not None else torch.empty(K, dtype=torch.int32, device=dev)
-    inv = inv_out
-    if inv is None and want_inv:
-        inv = torch.empty(B * (P + H * W), dtype=torch.int32, device=dev)
-    _lib.check(_lib.lib().sbp_sample_indices(d, _dev(idx, "idx"), idx.numel(), _dev(inv, "inv"),
-                                             _stream(idx.device)))
-    return idx, inv
+    if dev.type != "cuda" and (idx_out is None or (want_inv and inv_out is None)):
+        keep_count(B, P, H, W, k, mode, per_sample, cell)          # (sizes are checked first)
+        raise ValueError("idx must live in GPU memory")
+    return _native().sample_indices(B, P, H, W, cell, k, mode, bool(per_sample), seed, stream_id, want_inv,
+                                    -1 if dev.index is None else dev.index, idx_out, inv_out)
 
 
 def sample_indices_batch(descs, idx_list, inv_list=None):
@@ -98,14 +98,7 @@ def sample_indices_batch(descs, idx_list, inv_list=None):
 
 def forward_cache(X: torch.Tensor, idx: torch.Tensor, out=None) -> torch.Tensor:
     """X_k = X[idx] (rows), the only part of the layer input kept for the backward pass."""
-    if X.dim() != 2:
-        raise ValueError("X must be [M, C]")
-    M, C = X.shape
-    K = idx.numel()
-    Xk = out if out is not None else torch.empty((K, C), dtype=X.dtype, device=X.device)
-    _lib.check(_lib.lib().sbp_forward_cache(_dev(X, "X"), _dev(idx, "idx"), M, K, C, _dtype_code(X),
-                                            _dev(Xk, "X_k"), _stream(X.device)))
-    return Xk
+    return _native().forward_cache(X, idx, out)
 
 
 def forward_cache_batch(Xs, idxs, outs=None, layout=LAYOUT_ROWS):
@@ -143,31 +136,8 @@ def backward_linear_engine(M, K, Cin, Cout, dtype_code, flags=0):
 def backward_linear(dY, idx, X_k, W, M=None, flags=0, want=("dW", "db", "dX"), dW=None, db=None, dX=None,
                     workspace=None, inv=None):
     """SBP backward of Y = X W^T + b on the kept rows.  Returns (dW fp32 - bf16 with FLAG_DW_OUT_BF16 -, db fp32, dX)."""
-    Cout, Cin = W.shape
-    K = idx.numel() if idx is not None else dY.shape[0]
-    if M is None:
-        if flags & FLAG_DY_COMPACT:
-            raise ValueError("M is required when dY is compact")
-        M = dY.shape[0]
-    code = _dtype_code(W)
-    dev = W.device
-    if "dW" in want and dW is None:
-        dW = torch.empty((Cout, Cin), dtype=torch.bfloat16 if flags & FLAG_DW_OUT_BF16 else torch.float32, device=dev)
-    if dW is not None and dW.dtype != (torch.bfloat16 if flags & FLAG_DW_OUT_BF16 else torch.float32):
-        raise ValueError("dW must be bfloat16 with FLAG_DW_OUT_BF16 and float32 without")
-    if "db" in want and db is None:
-        db = torch.empty((Cout,), dtype=torch.float32, device=dev)
-    if "dX" in want and dX is None:
-        rows = K if (flags & FLAG_DX_COMPACT) else M
-        dX = torch.empty((rows, Cin), dtype=W.dtype, device=dev)
-    need = backward_linear_workspace(M, K, Cin, Cout, code, flags)
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    _lib.check(_lib.lib().sbp_backward_linear(
-        _dev(dY, "dY"), _dev(idx, "idx"), _dev(inv, "inv"), _dev(X_k, "X_k"), _dev(W, "W"), M, K, Cin, Cout, code,
-        _dev(dW, "dW"), _dev(db, "db"), _dev(dX, "dX"), _dev(workspace, "workspace"), workspace.numel(),
-        flags, _stream(dev)))
-    return dW, db, dX
+    return _native().backward_linear(dY, idx, X_k, W, M, flags, ("dW" in want) | ("db" in want) << 1 | ("dX" in want) << 2,
+                                     dW, db, dX, workspace, inv)
 
 
 def make_layer(dY, idx, X_k, W, M, dW=None, db=None, dX=None, flags=0, inv=None) -> LinearLayer:

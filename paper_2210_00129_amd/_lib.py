@@ -10,6 +10,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsbp.so")
+NATIVE_PATH = os.path.join(HERE, "_native.so")
 
 c_i32, c_i64, c_u32, c_u64 = ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint64
 c_vp, c_sz, c_dbl = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_double
@@ -105,3 +106,27 @@ def check(status: int) -> int:
         text = L.sbp_last_error().decode() or L.sbp_status_string(int(status)).decode()
         raise SbpError(int(status), text)
     return status
+
+
+_native = None
+
+
+def native():
+    """The native binding of the calls of every step (csrc/sbp_binding.cpp), bound to the loaded library."""
+    global _native
+    if _native is None:
+        import importlib.machinery
+        import importlib.util
+        import torch
+        L = lib()
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2210_00129_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_native", NATIVE_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_native", NATIVE_PATH, loader=loader))
+        loader.exec_module(m)
+        names = ("sbp_keep_count", "sbp_sample_indices", "sbp_forward_cache", "sbp_backward_linear_workspace", "sbp_backward_linear")
+        # (a torch without GPU support has no stream to ask for)
+        m.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names], check,
+               getattr(torch._C, "_cuda_getCurrentRawStream", None))
+        _native = m
+    return _native
