@@ -68,9 +68,9 @@ struct LinArgs {
   int n_big, rows_small, n_dw_big;     // large-tile kernel: long and short dW splits; n_dw_big of the n_dw units are long
   int seg_order[3];                   // dispatch order: large-tile kernel 0 = dX tiles, 1 = long dW, 2 = short dW units;
                                       // general kernel 0 = dX tiles, 1 = dW units, 2 = zero-fill and column-sum blocks
-  int dx_bm;                          // large-tile kernel: rows of a dX tile (256 or 128)
-  int db_in_dw;                       // large-tile kernel: the dW units also produce db, each from its share of the rows (one
-                                      // partial per split and tile column in dbp); no column-sum blocks then
+  int dx_bm;                          // rows of a dX tile (large tiles 256, 128 or 64; 128-wide tiles 128 or 64)
+  int db_in_dw;                       // the dW units also produce db, no column-sum blocks then (large tiles: each from its share of the
+                                      // rows, one partial per split and tile column; 128-wide tiles: one unit of a split)
   int xk_kmajor;                      // large-tile kernel: Xk is in the row-group layout [K / 8][Cin][8]
 };
 
@@ -748,8 +748,8 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
 // Time of one layer with the 128-wide tiles, its reduction included: 10 us + 1.3 us per GFLOP (within 15 % over 24 shapes of 2 to 67
 // GFLOP), or what the plan's own costs add up to where a grid just misses the slots.  The large tiles take 0.95 of their simulated
 // cost, 0.87 where whole 256-wide tiles cover the layer (nothing padded), and are ahead of the 128-wide ones on such layers from 20
-// GFLOP on and on all from 45 GFLOP on, whatever the estimates (25680 rows of 368 -> 2528: 138 us, 165 with 128-wide tiles).  Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 ->
-// 1024), 31.5 / 34.5 (4200, 2048 -> 512), 29.0 / 33.5 (4200, 1024 x 1024), 44.0 / 57.2 (12608, 384 -> 1536); 43.7 / 41.2 (2100, 1024 ->
+// GFLOP on and on all from 45 GFLOP on, whatever the estimates (25680 rows of 368 -> 2528: 138 us, 165 with 128-wide tiles).
+// Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 -> 1024), 31.5 / 34.5 (4200, 2048 -> 512), 29.0 / 33.5 (4200, 1024 x 1024), 44.0 / 57.2 (12608, 384 -> 1536); 43.7 / 41.2 (2100, 1024 ->
 // 3072), 59.2 / 57.8 (6336, 768 -> 2304), 89.7 / 78.0 (6336, 3072 -> 768), 90.3 / 77.3 (4000, 4096 -> 1024).
 // Two kinds of whole-tile layers keep the large tiles although the 128-wide ones are ahead of them by themselves: those of three tiles
 // and more each way over 5000 rows and more (6336 of 768 x 768: 26.9 / 33.3 us, but a ViT-Base block of dependent layers 409.8 / 409.0),
