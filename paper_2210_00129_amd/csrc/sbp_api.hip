@@ -133,8 +133,8 @@ void timeline_target(unsigned long long** buf, int* capacity_records) {
   *capacity_records = g_timeline_cap;
 }
 
-void allow_dynamic_lds(const void* kernel, size_t lds) {
-  if (lds <= 64 * 1024) return;
+bool allow_dynamic_lds(const void* kernel, size_t lds) {
+  if (lds <= 64 * 1024) return true;
   struct Grant { int device; const void* kernel; size_t lds; };
   static std::mutex m;
   static std::vector<Grant> granted;                               // a handful of kernels per device
@@ -144,9 +144,11 @@ void allow_dynamic_lds(const void* kernel, size_t lds) {
   for (auto& g : granted)
     if (g.device == device && g.kernel == kernel) {
       if (lds > g.lds && hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) g.lds = lds;
-      return;
+      return lds <= g.lds;
     }
-  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess) granted.push_back({device, kernel, lds});
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return false;
+  granted.push_back({device, kernel, lds});
+  return true;
 }
 
 static int32_t validate_desc(const sbp_sample_desc* d) {

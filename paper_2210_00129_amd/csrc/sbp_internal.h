@@ -28,8 +28,8 @@ struct ProfScope {
 // Measurement aid: where the kernels that support it write per-workgroup time stamps (NULL, 0: nowhere).
 void timeline_target(unsigned long long** buf, int* capacity_records);
 
-// Grants a kernel more than 64 KB of dynamic LDS on the current device; asked of the runtime once per device, kernel and size.
-void allow_dynamic_lds(const void* kernel, size_t lds);
+// Grants a kernel more than 64 KB of dynamic LDS on the current device; asked of the runtime once per device, kernel and size.  False: refused.
+bool allow_dynamic_lds(const void* kernel, size_t lds);
 
 #define SBP_LAUNCH(cls, stream, ...)             \
   do {                                            \

@@ -8,7 +8,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
-#include <mutex>
 
 #include "sbp_internal.h"
 
@@ -656,15 +655,10 @@ int32_t launch_sample(const sbp_sample_desc& d, int32_t* idx, int32_t* inv, hipS
         // keep bits and chunk prefixes of the ordered write-out: 24 bytes per 64 positions, next to 53 KB of static LDS
         const int64_t chunks = ceil_div((int64_t)d.H * d.W, 64);
         size_t lds = (size_t)chunks * 24;
-        static std::once_flag big_lds_once;             // more than 64 KB in all: granted per kernel, asked for once
-        static bool big_lds_ok = false;
-        if (lds > 11 * 1024)
-          std::call_once(big_lds_once, [] {
-            big_lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(sample_random_kernel<1024, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024) == hipSuccess;
-          });
+        const bool big_lds_ok = lds <= 11 * 1024 ||      // more than 64 KB in all: granted per kernel and device
+                                allow_dynamic_lds(reinterpret_cast<const void*>(sample_random_kernel<1024, true>), 104 * 1024);
         v.mask_chunks = (int)chunks;
-        if (lds > 104 * 1024 || (lds > 11 * 1024 && !big_lds_ok) || opt.sampler_no_masks) { v.mask_chunks = 0; lds = 0; }
+        if (lds > 104 * 1024 || !big_lds_ok || opt.sampler_no_masks) { v.mask_chunks = 0; lds = 0; }
         SBP_LAUNCH(SBP_PROF_SAMPLE, s, (sample_random_kernel<1024, true>), dim3(d.B), dim3(1024), lds, s, v, idx, inv);
       } else {
         SBP_LAUNCH(SBP_PROF_SAMPLE, s, (sample_random_kernel<256, false>), dim3(d.B), dim3(256), 0, s, v, idx, inv);

@@ -364,3 +364,21 @@ def test_batch_longest_single_split():
     assert all(c["idx"].size == 7936 for c in cases)
     with sbp.options(splits=1):
         _run(cases)
+
+
+@pytest.mark.parametrize("B,Cin,Cout", [(1, 264, 288), (9, 520, 264), (9, 256, 512)])
+def test_single_call_with_one_split_of_large_tiles(B, Cin, Cout):
+    # the dW units write dW themselves and the reduction launch adds the db sums of the tile columns: ragged tiles and whole ones, one
+    # stage and a few; the flags that need the sums go through the partial sums
+    c = _layer(B, 1, 14, 14, Cin, Cout, 2, 161)
+    d = _to_device(c, True)
+    args = (d["dY"], d["idx"], d["X_k"], d["W"])
+    with sbp.options(splits=1, tile="big"):
+        full = sbp.backward_linear(*args, inv=d["inv"])
+        dW_alone = sbp.backward_linear(*args, inv=d["inv"], want=("dW",))[0]
+        bf16 = sbp.backward_linear(*args, inv=d["inv"], flags=sbp.FLAG_DW_OUT_BF16)[0]
+        dW0, db0 = torch.full((Cout, Cin), 2.0, device="cuda"), torch.full((Cout,), -1.0, device="cuda")
+        sbp.backward_linear(*args, inv=d["inv"], flags=sbp.FLAG_ACCUMULATE_DW, dW=dW0, db=db0)
+    _check_against_oracle(c, full)
+    assert np.array_equal(bits(dW_alone), bits(full[0])) and np.array_equal(bits(bf16), bits(full[0].to(torch.bfloat16)))
+    assert np.array_equal(bits(dW0), bits(full[0] + 2.0)) and np.array_equal(bits(db0), bits(full[1] - 1.0))
