@@ -477,12 +477,14 @@ struct DwProb {
 #pragma unroll
     for (int f = 1; f < 4; ++f) a[f] = read_slow1(buf, a_off[f], ks);
   }
-  // rows kvalid .. 31 of the last stage: the dY tile is zeroed, so whatever X_k holds there adds nothing (XT: the rows of a
-  // partly filled group come from memory, where rows past K are stored as zeros and rows of the next split are finite
-  // values of X_k that meet zeros of dY; whole groups past the split are copies of its last group)
+  // rows kvalid .. 31 of the last stage are zeroed in both tiles (zero times an infinite value would be NaN; XT: whole groups past
+  // the split; the rows of a partly filled one come from memory, where rows past K are stored as zeros - splits are whole groups)
   __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const {
     zero_slow_tail(buf, kvalid, threadIdx.x);
     if constexpr (!XT) zero_slow_tail(buf + TILE_BYTES, kvalid, threadIdx.x);
+    else
+      for (int q = threadIdx.x + ((kvalid + 7) / 8) * BT; q < KB / 8 * BT; q += 256)       // 16-byte pieces, BT per group
+        *reinterpret_cast<uint4*>(buf + TILE_BYTES + q * 16) = make_uint4(0, 0, 0, 0);
   }
 };
 

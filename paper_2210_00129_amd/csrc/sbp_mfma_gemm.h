@@ -77,7 +77,7 @@ __device__ __forceinline__ void lds_barrier() {
 //            c ^ (m & 7); a 1 KB block is 8 physical rows.
 //   KB = 32:  64-byte rows; chunk c of row m at slot c ^ ((m >> 2) & 3); a 1 KB block is 16 rows.
 // Rows past the end are clamped to the last row (their results are never stored); in the tail stage
-// chunks past kdim re-read the last chunk (the other operand is zero there).
+// chunks past kdim re-read the last chunk and are zeroed like the other operand's rows (zero times an infinite value is NaN).
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ int prow(int m) { return (m & ~9) | ((m & 1) << 3) | ((m >> 3) & 1); }
 
@@ -121,7 +121,16 @@ struct RowTileLoader {
       async_copy16(rowp[n] + k, tile + (blk0 + n) * 1024);
     }
   }
-  __device__ __forceinline__ void zero_tail(char*, int, int) const {}
+  // zero the chunks kvalid / 8 .. of every row (kvalid is a multiple of 8)
+  __device__ __forceinline__ void zero_tail(char* tile, int kvalid, int t) const {
+    constexpr int CPR = KB / 8;                         // 16-byte pieces per row
+#pragma unroll
+    for (int i = 0; i < ROWS * CPR / (64 * NW); ++i) {
+      const int q = t + 64 * NW * i, row = q / CPR;     // physical row; prow is its own inverse
+      const int c = (q % CPR) ^ (KB == 64 ? prow(row) & 7 : (row >> 2) & 3);
+      if (8 * c >= kvalid) *reinterpret_cast<uint4*>(tile + q * 16) = make_uint4(0, 0, 0, 0);
+    }
+  }
 };
 
 // per-lane byte offset of the operand fragment rows wbase + 32 f + (lane & 31) in a row tile

@@ -204,7 +204,7 @@ struct DxProb {
   __device__ __forceinline__ void extra(const bf16x8_t&) {}
   __device__ __forceinline__ void prefetch(int) {}
   __device__ __forceinline__ void issue(char* buf, int kvalid) {
-    const int back = kvalid < KB ? max(kchunk - (kvalid - 8), 0) : 0;              // chunks past the end: the last one (W is zero there)
+    const int back = kvalid < KB ? max(kchunk - (kvalid - 8), 0) : 0;              // chunks past the end: the last one (zeroed, zero_tail)
 #pragma unroll
     for (int n = 0; n < FM; ++n) {
       async_copy16(pa[n] - 2 * back, buf + (FM * wave + n) * 1024);
@@ -217,7 +217,15 @@ struct DxProb {
 #pragma unroll
     for (int f = 0; f < FM; ++f) a[f] = *reinterpret_cast<const bf16x8_t*>(buf + a_off[ks] + f * (32 * KB * 2));
   }
-  __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const { SlowCopy::zero_tail(buf + A_BYTES, kvalid); }
+  // both operands past the end: zero times an infinite gradient would be NaN
+  __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const {
+    SlowCopy::zero_tail(buf + A_BYTES, kvalid);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int q = threadIdx.x + 256 * i, m = q >> 2;  // 16-byte piece; 4 pieces per row, chunk c in place c ^ ((m >> 2) & 3)
+      if (8 * ((q & 3) ^ ((m >> 2) & 3)) >= kvalid) *reinterpret_cast<uint4*>(buf + q * 16) = make_uint4(0, 0, 0, 0);
+    }
+  }
 };
 
 // BMX kept rows (128 or 64) x 128 input channels

@@ -81,3 +81,43 @@ def test_layers_of_one_launch_longest_workgroups_first():
         assert nerr(f64(l["dW"]), rW + one) <= TOL_F32 and nerr(f64(l["db"]), rb + one) <= TOL_F32
         if want_dx:
             assert nerr(f64(l["dX"]), rX[idx] if flags & sbp.FLAG_DX_COMPACT else rX) <= TOL_BF16_TIGHT
+
+
+@pytest.mark.parametrize("opts", [dict(dxrows=64, tile="128x128x4x64"), dict(dxrows=128, tile="128x128x4x64"), dict(tile="256x256x8x64"),
+                                  dict(tile="256x256x4x32")])
+@pytest.mark.parametrize("Cout", [8, 40, 72, 120, 200])
+def test_infinite_gradients_in_the_last_partial_stage(Cout, opts):
+    # dX of a row with an infinite gradient is infinite where its weight is not zero, never NaN: the last, partial stage of the
+    # contraction over Cout holds copies of the row's last 8 channels, which must count for nothing
+    X, W, dY, idx = _case(300, 131, 120, Cout, Cout + 1)
+    rows = torch.from_numpy(idx[::7]).long()
+    dY[rows, Cout - 1 - (rows % 8)] = float("inf")
+    W[W == 0] = 0.01
+    idxd = torch.from_numpy(idx).cuda()
+    with sbp.options(**opts):
+        dX = sbp.backward_linear(dY.cuda(), idxd, None, W.cuda(), want=("dX",))[2]
+    got = dX.cpu().double()[torch.from_numpy(idx).long()]
+    ref = dY.double()[torch.from_numpy(idx).long()] @ W.double()
+    assert torch.isinf(ref).any() and not torch.isnan(ref).any()
+    fin = torch.isfinite(ref)
+    assert torch.equal(got[~fin], ref[~fin])
+    assert nerr(got[fin].numpy(), ref[fin].numpy()) <= TOL_BF16_TIGHT
+
+
+@pytest.mark.parametrize("K", [33, 40, 41, 57, 1001])
+@pytest.mark.parametrize("tile", ["128x128x4x64", "big"])
+def test_infinite_cached_values_in_the_last_row_group(K, tile):
+    # the same for dW with X_k in row groups: whole groups past the last row hold copies of the last group
+    X, W, dY, idx = _case(2 * K, K, 136, 96, K)
+    last = int(idx[-1])
+    X[last, 5] = float("inf")
+    dY[last][dY[last] == 0] = 0.5
+    idxd = torch.from_numpy(idx).cuda()
+    (Xt,) = sbp.forward_cache_batch([X.cuda()], [idxd], layout=sbp.LAYOUT_KMAJOR)
+    with sbp.options(tile=tile):
+        dW = sbp.backward_linear(dY.cuda(), idxd, Xt, W.cuda(), flags=sbp.FLAG_XK_KMAJOR, want=("dW",))[0].cpu().double()
+    rows = torch.from_numpy(idx).long()
+    ref = dY.double()[rows].T @ X.double()[rows]
+    fin = torch.isfinite(ref)
+    assert torch.equal(dW[~fin], ref[~fin]) and not fin[:, 5].any() and fin[:, 6:].all()
+    assert nerr(dW[fin].numpy(), ref[fin].numpy()) <= TOL_F32
