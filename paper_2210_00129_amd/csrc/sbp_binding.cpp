@@ -9,6 +9,7 @@
 #include <ATen/ATen.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 
 #include "sbp.h"
 
@@ -60,7 +61,10 @@ struct WithoutGil {
   ~WithoutGil() { PyEval_RestoreThread(state); }
 };
 
+// as torch.empty: a process that has not used the GPU yet gets torch.cuda's initialization (and with it the fork check), a child
+// forked from one that has gets torch's error
 at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, c10::Device device) {
+  if (device.is_cuda()) torch::utils::device_lazy_init(at::kCUDA);
   WithoutGil no_gil;
   return at::empty(sizes, at::TensorOptions().dtype(type).device(device));
 }

@@ -37,3 +37,16 @@ def test_sizes_of_a_draw_are_checked_first():
         sbp.sample_indices(2, 0, 4, 4, 2, 1, 1, device="cpu")
     with pytest.raises(ValueError, match="GPU memory"):
         sbp.sample_indices(2, 0, 4, 4, 2, 2**64 - 1, -1, idx_out=torch.zeros(16, dtype=torch.int32))
+
+
+def test_first_allocation_on_a_gpu_initializes_torch(monkeypatch):
+    # what torch.empty does before it allocates: without it the fork check is missing (here the check's own error, as in a child
+    # forked from a process that has used the GPU)
+    if torch.cuda.is_initialized():
+        pytest.skip("this process has used the GPU")
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+    monkeypatch.setattr(torch.cuda, "_lazy_init", refuse)
+    with pytest.raises(RuntimeError, match="forked subprocess"):
+        sbp.sample_indices(2, 0, 4, 4, 2, 1, 1)
