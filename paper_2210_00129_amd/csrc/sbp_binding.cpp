@@ -7,6 +7,7 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/utils/device_lazy_init.h>
@@ -52,7 +53,8 @@ void* dev(const at::Tensor* t, const char* name) {
 int32_t dtype_code(const at::Tensor& t) {
   if (t.scalar_type() == at::kFloat) return SBP_F32;
   if (t.scalar_type() == at::kBFloat16) return SBP_BF16;
-  fail(PyExc_TypeError, "unsupported dtype %s; use float32 or bfloat16", c10::toString(t.scalar_type()));
+  PyErr_Format(PyExc_TypeError, "unsupported dtype %S; use float32 or bfloat16", reinterpret_cast<PyObject*>(torch::getTHPDtype(t.scalar_type())));
+  throw PyFail{};
 }
 
 // Other Python threads run while memory is allocated or work is enqueued (either may block).
@@ -104,8 +106,8 @@ int64_t integer(PyObject* o, bool whole = false) {                   // whole: n
   return v;
 }
 int32_t integer32(PyObject* o) { return (int32_t)integer(o); }       // (as a C int field takes it: the low 32 bits)
-uint64_t bits64(PyObject* o) {
-  PyObject* n = PyNumber_Long(o);
+uint64_t bits64(PyObject* o, bool whole = false) {
+  PyObject* n = whole ? PyNumber_Index(o) : PyNumber_Long(o);
   if (!n) throw PyFail{};
   const unsigned long long v = PyLong_AsUnsignedLongLongMask(n);
   Py_DECREF(n);
@@ -170,7 +172,9 @@ PyObject* sample_indices(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor *idx_out = tensor(a[12], "idx"), *inv_out = tensor(a[13], "inv");
     at::Tensor idx, inv;
     if (!idx_out) idx = empty({K}, at::kInt, device);
-    if (!inv_out && PyObject_IsTrue(a[10]) == 1) inv = empty({(int64_t)d.B * (d.P + (int64_t)d.H * d.W)}, at::kInt, device);
+    const int want_inv = PyObject_IsTrue(a[10]);
+    if (want_inv < 0) throw PyFail{};
+    if (!inv_out && want_inv) inv = empty({(int64_t)d.B * (d.P + (int64_t)d.H * d.W)}, at::kInt, device);
     const at::Tensor& i = idx_out ? *idx_out : idx;
     void* const ip = dev(&i, "idx");
     void* const vp = dev(inv_out ? inv_out : (inv.defined() ? &inv : nullptr), "inv");
@@ -213,7 +217,7 @@ PyObject* backward_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor *dW = tensor(a[7], "dW"), *db = tensor(a[8], "db"), *dX = tensor(a[9], "dX"), *ws = tensor(a[10], "workspace"), *inv = tensor(a[11], "inv");
     if (W.dim() != 2) fail(PyExc_ValueError, "%s", "W must be [Cout, Cin]");
     const int64_t Cout = W.size(0), Cin = W.size(1);
-    const uint32_t flags = (uint32_t)bits64(a[5]), want = (uint32_t)integer(a[6]);
+    const uint32_t flags = (uint32_t)bits64(a[5], true), want = (uint32_t)integer(a[6]);
     if (!idx && dY.dim() < 1) fail(PyExc_ValueError, "%s", "dY must be [rows, Cout]");
     const int64_t K = idx ? idx->numel() : dY.size(0);
     int64_t M;

@@ -50,3 +50,17 @@ def test_first_allocation_on_a_gpu_initializes_torch(monkeypatch):
     monkeypatch.setattr(torch.cuda, "_lazy_init", refuse)
     with pytest.raises(RuntimeError, match="forked subprocess"):
         sbp.sample_indices(2, 0, 4, 4, 2, 1, 1)
+
+
+def test_flags_are_whole_numbers_and_dtypes_are_named_as_torch_names_them():
+    W, dY, idx = torch.zeros(8, 4), torch.zeros(6, 8), torch.zeros(3, dtype=torch.int32)
+    with pytest.raises(TypeError):
+        sbp.backward_linear(dY, idx, dY, W, flags=1.5)
+    with pytest.raises(TypeError, match=r"unsupported dtype torch\.float64; use float32 or bfloat16"):
+        sbp.backward_linear(dY, idx, dY, W.double())
+
+    class Neither:
+        def __bool__(self):
+            raise KeyError("neither")
+    with pytest.raises(KeyError):
+        sbp.sample_indices(2, 0, 4, 4, 2, 1, 1, want_inv=Neither(), idx_out=torch.zeros(16, dtype=torch.int32))
