@@ -263,8 +263,8 @@ int32_t sbp_backward_linear_batch(const sbp_linear_layer* layers, int32_t n, int
  * belongs to the library (one per GPU, held from the library's first use on that GPU until the process ends;
  * its address is looked up once per device, on the first call with that device current).  The call allocates
  * and frees nothing.  Sizes that need more scratch than that (sbp_backward_linear_workspace(...) >
- * SBP_STATIC_SCRATCH_BYTES) are refused with SBP_ERR_CAPACITY before anything is enqueued; every layer of the
- * ViT / ConvNeXt workloads this library is measured on fits.  All calls on one GPU share the array: two calls
+ * SBP_STATIC_SCRATCH_BYTES, unless the 128-wide engine does with less than the one chosen by time) are refused with
+ * SBP_ERR_CAPACITY before anything is enqueued; every layer of the ViT / ConvNeXt workloads this library is measured on fits.  All calls on one GPU share the array: two calls
  * that may overlap in time on that GPU (different streams, or graph branches) race; calls on one stream are
  * ordered and safe.  Nothing in the array has to be cleared between calls (every element read was written by
  * the same call first).  sbp_static_scratch_bytes() returns SBP_STATIC_SCRATCH_BYTES (host only).

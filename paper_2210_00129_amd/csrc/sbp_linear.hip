@@ -696,7 +696,7 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
 // Layers of more than 64 MB: their rows come from memory more often than not, and a dW stage is 0.3 us then (33600 rows of 512 -> 128,
 // four sets of inputs in turn: 35.1 us with the 23 splits of 0.2 us a stage, 28.8 with 48; 40000 of 384 -> 96 31.3 and 25.0; warm 22.8
 // and 24.5 for the first).
-struct MidChoice { int64_t K; int32_t Cin, Cout, slots; int splits, rps, dx_bm; double cost_ns; };
+struct MidChoice { int64_t K; int32_t Cin, Cout, slots, cap; int splits, rps, dx_bm; double cost_ns; };
 
 // end of a grid of n1 units of length l1 and then n2 of l2 on `slots` slots, each unit in the slot that is free first
 static int64_t two_kinds_end(int64_t n1, int64_t l1, int64_t n2, int64_t l2, int64_t slots) {
@@ -710,17 +710,18 @@ static int64_t two_kinds_end(int64_t n1, int64_t l1, int64_t n2, int64_t l2, int
   return lo;
 }
 
-// slots: workgroups at a time that this layer gets (512, or its share where several layers share the launch).  (The flags do not
-// enter: a bf16 dW is the fp32 one rounded once, so both have the same splits.)
-static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
+// slots: workgroups at a time that this layer gets (512, or its share where several layers share the launch); cap: most splits whose
+// partial sums there is room for (more only where the longest legal splits are more).  (The flags do not enter: a bf16 dW is the
+// fp32 one rounded once, so both have the same splits.)
+static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int cap) {
   thread_local MidChoice cache[32] = {};
   thread_local int next = 0;
   for (const MidChoice& c : cache)
-    if (c.K == K && c.Cin == Cin && c.Cout == Cout && c.slots == slots && c.splits > 0) return c;
+    if (c.K == K && c.Cin == Cin && c.Cout == Cout && c.slots == slots && c.cap == cap && c.splits > 0) return c;
   const int64_t tiles_n = ceil_div(Cin, mid::BT), tiles_w = ceil_div(Cout, mid::BT) * tiles_n, nk_x = ceil_div(Cout, mid::KB);
   const int64_t fewest = ceil_div(K, kMaxRowsPerSplit);      // the split's row ids sit in LDS
-  const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>(64, std::max<int64_t>(1, K / 64)));
-  MidChoice best{K, Cin, Cout, slots, 0, 0, 128, 0.0};
+  const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>({64, cap, std::max<int64_t>(1, K / 64)}));
+  MidChoice best{K, Cin, Cout, slots, cap, 0, 0, 128, 0.0};
   const bool streams = 2.0 * (double)K * (2.0 * Cin + Cout) > 64e6;
   int64_t best_cost = 0;
   for (int64_t want = fewest; want <= most; ++want) {
@@ -754,25 +755,47 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots) {
 // Two kinds of whole-tile layers keep the large tiles although the 128-wide ones are ahead of them by themselves: those of three tiles
 // and more each way over 5000 rows and more (6336 of 768 x 768: 26.9 / 33.3 us, but a ViT-Base block of dependent layers 409.8 / 409.0),
 // and those of 1536 output channels and more (4200 rows, 512 -> 1536: 24.3 / 30.3 us), whose engine the host tests state.
-static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, double big_cost_ns) {
+static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, int cap, double big_cost_ns) {
   const double gf = 4e-9 * (double)K * Cin * Cout;
   const bool whole = Cin % big::BT == 0 && Cout % big::BT == 0;
   if (gf >= 45.0 || (whole && (gf >= 20.0 || Cout >= 1536 || (K >= 5000 && std::min(Cin, Cout) >= 3 * big::BT)))) return false;
-  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU).cost_ns) < (whole ? 0.87 : 0.95) * big_cost_ns;
+  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU, cap).cost_ns) < (whole ? 0.87 : 0.95) * big_cost_ns;
 }
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_mid);
+// The parts of the workspace that do not depend on the splits: the inverse map of a scattered dX, and X_k copied back to rows for the
+// engines that do not read row groups.
+static size_t inv_bytes(int64_t M, uint32_t flags) { return flags & SBP_FLAG_DX_COMPACT ? 0 : align_up((size_t)M * sizeof(int32_t), 256); }
+static size_t xrows_bytes(int64_t K, int32_t Cin, uint32_t flags) { return flags & SBP_FLAG_XK_KMAJOR ? align_up((size_t)K * Cin * 2, 256) : 0; }
+
+// Splits of the 128-wide engine whose partial sums fit the static scratch buffer with the rest of the workspace: a layer that fits
+// with few splits is not refused there for the sake of a better schedule.
+static int mid_split_cap(int64_t M, int64_t K, int32_t Cin, int32_t Cout, uint32_t flags) {
+  const int64_t room = (int64_t)SBP_STATIC_SCRATCH_BYTES - 256 - (int64_t)(inv_bytes(M, flags) + xrows_bytes(K, Cin, flags));
+  return (int)std::min<int64_t>(64, std::max<int64_t>(1, room / ((int64_t)sizeof(float) * Cout * (Cin + 1))));
+}
+
+enum class EngineRule { by_time, large, mid };      // large: wherever they pay and 128-wide ones may be faster
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, EngineRule rule);
 
 // A layer whose 128-wide splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by
 // time.  (X_k in row groups, which only the large tiles read, is copied back to rows first: the same engine and the same bits as
 // with X_k by rows, and with the copy still no slower: 4200 rows of 1024 x 1024 29 + 5 us, large tiles 33.5.)
 LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, true);
+  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::by_time);
   if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
-  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, false);
+  return plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::large);
 }
 
-static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool may_prefer_mid) {
+// The plan of a call that has no more than the static scratch buffer: where the faster large tiles need more (1794 rows of 7816 -> 864,
+// two splits of 27 MB), the 128-wide ones with fewer splits.
+LinearPlan plan_linear_static(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
+  if (!p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES || options().tile_mode == 2) return p;
+  const LinearPlan q = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::mid);
+  return q.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES ? q : p;
+}
+
+static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, EngineRule rule) {
   LinearPlan p{};
   p.mfma = dtype == SBP_BF16 && Cin % 8 == 0 && Cout % 8 == 0;
   p.bm_w = p.bn_w = 128;
@@ -785,9 +808,10 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
                       ceil_div(K, kBigMaxRowsPerSplit) <= 64;
     // it pays where whole 256-wide tiles exist, the simulated schedule keeps the CUs reasonably busy and the 128 tiles are not ahead
     bool pays = opt.tile_mode == 0 && Cin >= big::BT && Cout >= big::BT && K >= 1024;
+    if (rule == EngineRule::mid) pays = false;
     if (pays) {
       const BigChoice c = choose_big(M, K, Cin, Cout);
-      pays = c.fill >= 0.45 && !(may_prefer_mid && mid_engine_ahead(K, Cin, Cout, c.cost_ns));
+      pays = c.fill >= 0.45 && !(rule == EngineRule::by_time && mid_engine_ahead(K, Cin, Cout, mid_split_cap(M, K, Cin, Cout, flags), c.cost_ns));
     }
     p.big = fits && (opt.tile_mode == 2 || pays);
   }
@@ -837,7 +861,7 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
       if (opt.tile_mode == 1) { p.bm_w = opt.tile_bm; p.bn_w = opt.tile_bn; p.nw_w = opt.tile_nw; p.kb = opt.tile_kb; }
       p.dx_bm = 128;
       if (p.bm_w == mid::BT) {
-        const MidChoice c = choose_mid(K, Cin, Cout, 2 * kNumCU);
+        const MidChoice c = choose_mid(K, Cin, Cout, 2 * kNumCU, mid_split_cap(M, K, Cin, Cout, flags));
         splits = c.splits;
         p.dx_bm = opt.dxrows ? opt.dxrows : c.dx_bm;
       } else {
@@ -866,14 +890,15 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
   size_t off = 0;
   p.off_partial = off;
   p.db_slice_rows = db_slice_rows_for(K, p.big);
-  p.db_slices = p.mfma ? (int)std::max<int64_t>(1, ceil_div(K, p.db_slice_rows)) : splits;
-  // db partials: one per slice of the column-sum blocks, or (large tiles, db out of the dW units) per split and tile column
+  p.db_slices = p.mfma && p.bm_w != mid::BT ? (int)std::max<int64_t>(1, ceil_div(K, p.db_slice_rows)) : splits;
+  // db partials: one per slice of the column-sum blocks (128-wide tiles: per split), or (large tiles, db out of the dW units) per split
+  // and tile column
   const int64_t db_parts = std::max<int64_t>(p.db_slices, (int64_t)splits * (p.big ? ceil_div(Cin, big::BT) : 1));
   off += align_up(((size_t)splits * Cout * Cin + (size_t)db_parts * Cout) * sizeof(float), 256);
   p.off_inv = off;
-  if (!(flags & SBP_FLAG_DX_COMPACT)) off += align_up((size_t)M * sizeof(int32_t), 256);
-  p.off_xrows = off;      // X_k copied back to rows, for the engines that do not read the row-group layout
-  if (flags & SBP_FLAG_XK_KMAJOR) off += align_up((size_t)K * Cin * 2, 256);
+  off += inv_bytes(M, flags);
+  p.off_xrows = off;
+  off += xrows_bytes(K, Cin, flags);
   p.bytes = off;
   return p;
 }
@@ -1487,8 +1512,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
   for (int i = 0; i < p.n; ++i) work += (double)L[i].K * L[i].Cin * L[i].Cout;
   for (int i = 0; i < p.n; ++i) {
     const double share = (double)L[i].K * L[i].Cin * L[i].Cout / work;
-    const MidChoice c = choose_mid(L[i].K, L[i].Cin, L[i].Cout, std::max(64, (int)(2 * kNumCU * share) / 8 * 8));
-    if (c.splits > lp[i].splits) continue;
+    const MidChoice c = choose_mid(L[i].K, L[i].Cin, L[i].Cout, std::max(64, (int)(2 * kNumCU * share) / 8 * 8), lp[i].splits);
     lp[i].splits = c.splits;
     lp[i].rows_per_split = c.rps;
     lp[i].dx_bm = c.dx_bm;

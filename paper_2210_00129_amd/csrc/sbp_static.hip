@@ -51,14 +51,14 @@ int32_t sbp_backward_linear_static(const void* dY, const int32_t* idx, const int
   // the host-side checks of sbp_backward_linear, then the size limit, then (first HIP call) the scratch address
   int32_t st = check_linear_args(dY, idx, Xk, W, M, K, Cin, Cout, dtype, dW, dX, flags);
   if (st != SBP_OK) return st;
-  const size_t need = sbp_backward_linear_workspace(M, K, Cin, Cout, dtype, flags);
+  const LinearPlan p = plan_linear_static(M, K, Cin, Cout, dtype, flags);
+  const size_t need = p.bytes;
   if (need > (size_t)SBP_STATIC_SCRATCH_BYTES)
     return fail(SBP_ERR_CAPACITY, "these sizes need %zu bytes of scratch, the static buffer holds %zu: use sbp_backward_linear "
                 "with a workspace of the caller's", need, (size_t)SBP_STATIC_SCRATCH_BYTES);
   if (!dW && !db && !dX) return SBP_OK;
   void* ws = static_scratch_ptr();
   if (!ws) return SBP_ERR_HIP;
-  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
   return launch_backward_linear(p, dY, idx, inv, Xk, W, M, K, Cin, Cout, dtype, dW, db, dX, ws, flags,
                                 (hipStream_t)stream);
 }

@@ -248,6 +248,20 @@ def test_linear_engine_of_layers_of_little_work():
         assert engine(K, Cin, Cout) == 2, (K, Cin, Cout)
 
 
+def test_layers_that_fit_the_static_scratch_with_few_splits_are_not_refused():
+    # the 128-wide engine's schedule would like more splits (9 to 60) than the 48 MB hold the partial sums of
+    L = _lib.lib()
+    for K, Cin, Cout in ((15641, 1928, 792), (64798, 112, 3032), (21539, 264, 4040), (7994, 440, 6216), (103063, 56, 3664),
+                         (7087, 560, 4744), (106700, 2624, 88), (90198, 512, 528)):
+        for flags in (0, 2, 8):
+            assert 0 < L.sbp_backward_linear_workspace(2 * K, K, Cin, Cout, 1, flags) <= L.sbp_static_scratch_bytes(), (K, Cin, Cout)
+    assert L.sbp_backward_linear_workspace(65536, 65536, 4096, 4096, 1, 0) > L.sbp_static_scratch_bytes()
+    # large tiles by time, with two splits of 27 MB: the static call runs the other engine (nothing asked for: nothing enqueued)
+    p = ctypes.c_void_p(4096)
+    assert L.sbp_backward_linear_static(p, p, None, p, p, 3588, 1794, 7816, 864, 1, None, None, None, 0, None) == 0
+    assert L.sbp_backward_linear_static(p, p, None, p, p, 65536, 65536, 4096, 4096, 1, None, None, None, 0, None) == -5
+
+
 def test_backward_attention_argument_errors_and_engine():
     L = _lib.lib()
     p = ctypes.c_void_p(256)     # never dereferenced: validation comes first and enqueues nothing
