@@ -199,8 +199,8 @@ int32_t sbp_backward_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Co
  *                       and -1 for every dropped row, i.e. what sbp_sample_indices writes.
  *   X_k    device, in,  [K, Cin] rows cached by sbp_forward_cache (may be NULL if dW is NULL); with
  *                       SBP_FLAG_XK_KMAJOR in the row-group layout written by sbp_forward_cache_batch (bf16, Cin % 8
- *                       == 0 and a 16-byte aligned X_k, else SBP_ERR_FLAGS): the large-tile engine reads it as it
- *                       is, every other engine first copies it back to rows in the workspace
+ *                       == 0 and a 16-byte aligned X_k, else SBP_ERR_FLAGS): the matrix-core engines of 128- and
+ *                       256-wide tiles read it as it is, the others first copy it back to rows in the workspace
  *   W      device, in,  [Cout, Cin]                       (may be NULL if dX is NULL)
  *   dW, db, dX   device, out; each may be NULL to skip that output.  dW is fp32, or bf16 with
  *                SBP_FLAG_DW_OUT_BF16 (the same fp32 sum, rounded to nearest even once; together with

@@ -102,8 +102,8 @@ __device__ __forceinline__ void zero_rows_block(const LinArgs& a, int blk) {
 }
 
 // 128-wide tiles (sbp_mfma_mid.h): workgroup wg among those of one kind (0 = dX tiles of BMX rows, 1 = dW units, 2 = zero fill and
-// column sums)
-template <int BMX>
+// column sums).  GROUPS: X_k may lie in row groups.
+template <int BMX, bool GROUPS>
 __device__ __forceinline__ void linear_mid_unit(char* smem, const LinArgs& a, int kind, int wg) {
   constexpr int BT = mid::BT;
   const int nsplit = (a.K + a.rows_per_split - 1) / a.rows_per_split;
@@ -138,16 +138,24 @@ __device__ __forceinline__ void linear_mid_unit(char* smem, const LinArgs& a, in
   const int j0 = split * a.rows_per_split, j1 = min(a.K, j0 + a.rows_per_split);
   float* part = a.part + (long long)split * a.Cout * a.Cin;
   float* dbp = a.dbp ? a.dbp + (long long)split * a.Cout : nullptr;
+  auto dw = [&](auto gather, auto db) {
+    constexpr bool G = decltype(gather)::value, D = decltype(db)::value;
+    if constexpr (GROUPS)
+      if (a.xk_kmajor) return mid::dw_tile<G, D, true>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
+    mid::dw_tile<G, D, false>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
   if (a.db_in_dw && tile_n == split % tiles_n) {
-    if (a.idx_in) mid::dw_tile<true, true>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
-    else mid::dw_tile<false, true>(smem, a.dY, nullptr, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, dbp);
+    if (a.idx_in) dw(yes{}, yes{});
+    else dw(no{}, yes{});
   } else {
-    if (a.idx_in) mid::dw_tile<true, false>(smem, a.dY, a.idx_in, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, nullptr);
-    else mid::dw_tile<false, false>(smem, a.dY, nullptr, a.Xk, a.Cin, a.Cout, j0, j1, part, tile_m * BT, tile_n * BT, nullptr);
+    if (a.idx_in) dw(yes{}, no{});
+    else dw(no{}, no{});
   }
 }
 
-template <int BMX>
+template <int BMX, bool GROUPS>
 __global__ void __launch_bounds__(256, 2) linear_mid_kernel(const LinArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int kind = 0, wg = blockIdx.x;
@@ -158,7 +166,7 @@ __global__ void __launch_bounds__(256, 2) linear_mid_kernel(const LinArgs a) {
     if (wg < n) break;
     wg -= n;
   }
-  linear_mid_unit<BMX>(smem, a, kind, wg);
+  linear_mid_unit<BMX, GROUPS>(smem, a, kind, wg);
 }
 
 template <int BM, int BN, int NW, int KB, int NSTAGE>
@@ -237,8 +245,8 @@ __global__ void __launch_bounds__(256, 2) linear_mid_multi_kernel(const MidMulti
   ConstArgsPtr k = (ConstArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const LinArgs a = k->lay[k->layer[e]];
   const int wg = (int)blockIdx.x - k->start[e], kind = k->kind[e];
-  if (a.dx_bm == 64) linear_mid_unit<64>(smem, a, kind, wg);
-  else linear_mid_unit<128>(smem, a, kind, wg);
+  if (a.dx_bm == 64) linear_mid_unit<64, false>(smem, a, kind, wg);
+  else linear_mid_unit<128, false>(smem, a, kind, wg);
 #endif
 }
 
@@ -778,8 +786,7 @@ enum class EngineRule { by_time, large, mid };      // large: wherever they pay 
 static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, EngineRule rule);
 
 // A layer whose 128-wide splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by
-// time.  (X_k in row groups, which only the large tiles read, is copied back to rows first: the same engine and the same bits as
-// with X_k by rows, and with the copy still no slower: 4200 rows of 1024 x 1024 29 + 5 us, large tiles 33.5.)
+// time.  (X_k in row groups is read as it is by both: the same engine and the same bits as with X_k by rows.)
 LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
   const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::by_time);
   if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
@@ -944,7 +951,8 @@ static void launch_linear_mid(const LinearPlan& p, LinArgs a, bool want_dx, bool
   size_t lds = 0;
   const unsigned grid = prepare_linear_mid(p, a, want_dx, want_dw, want_zero, &lds);
   if (grid == 0) return;
-  auto kernel = p.dx_bm == 64 ? linear_mid_kernel<64> : linear_mid_kernel<128>;
+  auto kernel = a.xk_kmajor ? (p.dx_bm == 64 ? linear_mid_kernel<64, true> : linear_mid_kernel<128, true>)
+                            : (p.dx_bm == 64 ? linear_mid_kernel<64, false> : linear_mid_kernel<128, false>);
   allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
   SBP_LAUNCH(SBP_PROF_DW_GEMM, s, kernel, dim3(grid), dim3(256), lds, s, a);
 }
@@ -1069,7 +1077,7 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
   // ... the fp32 engine and the 128-wide tiles db too
   const bool direct = splits == 1 && !accumulate && !dw_bf16 && (!use_mfma || (!p.big && p.bm_w == mid::BT));
   bool kmajor = (flags & SBP_FLAG_XK_KMAJOR) && dW && Xk;
-  if (kmajor && !(use_mfma && p.big && p.rows_per_split % 8 == 0 && p.rows_small % 8 == 0)) {
+  if (kmajor && !(use_mfma && (p.big || p.bm_w == mid::BT) && p.rows_per_split % 8 == 0 && p.rows_small % 8 == 0)) {
     void* rows = static_cast<char*>(ws) + p.off_xrows;
     const int32_t st = launch_kmajor_to_rows(Xk, K, Cin, rows, s);
     if (st != SBP_OK) return st;

@@ -19,6 +19,8 @@
 #ifndef SBP_MFMA_MID_H_
 #define SBP_MFMA_MID_H_
 
+#include <type_traits>
+
 #include "sbp_mfma_gemm.h"
 
 namespace sbp {
@@ -193,6 +195,30 @@ struct SlowCopy {
   }
 };
 
+// X_k in groups of 8 rows, [row group][channel][8 rows]: a stage is 4 groups x 128 pieces of 16 bytes, copied as they lie (a
+// wavefront copies one group), and a fragment is one 16-byte LDS read per lane instead of two transposing reads.
+struct GroupCopy {
+  const char* p[2];       // this lane's piece of columns 0 .. 63 and 64 .. 127 in the next stage
+  size_t ld, step;        // bytes of a group, of a stage
+  __device__ __forceinline__ void init(const void* src, int Cin, int col0, int lane, int wave) {
+    ld = (size_t)Cin * 16; step = KB / 8 * ld;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) p[n] = static_cast<const char*>(src) + (size_t)wave * ld + (size_t)min(col0 + 64 * n + lane, Cin - 1) * 16;
+  }
+  __device__ __forceinline__ void issue(char* tile, int kvalid, int wave) {
+    const size_t back = kvalid < KB ? (size_t)max(wave - ((kvalid - 1) >> 3), 0) * ld : 0;      // groups past the end: the last one
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      async_copy16(p[n] - back, tile + (2 * wave + n) * 1024);
+      p[n] += step;
+    }
+  }
+  // whole groups past the end (rows past the last one of its group are stored as zeros)
+  static __device__ __forceinline__ void zero_tail(char* tile, int kvalid) {
+    for (int q = threadIdx.x + ((kvalid + 7) >> 3) * BT; q < KB / 8 * BT; q += 256) *reinterpret_cast<uint4*>(tile + q * 16) = make_uint4(0, 0, 0, 0);
+  }
+};
+
 // ---- dX = dY_k W -------------------------------------------------------------------------------------------------------
 template <int FM_>
 struct DxProb {
@@ -284,12 +310,14 @@ __device__ __forceinline__ void dx_tile(char* smem, const uint16_t* __restrict__
 
 // ---- dW partial = dY_k[j0:j1]^T X_k[j0:j1] -----------------------------------------------------------------------------
 // The two wavefronts that own the same 64 rows of the tile (and hold the same dY fragments) take them in opposite order, so that
-// "the column sums of fragment 0" is every row's sum once.
-template <bool GATHER, bool DB>
+// "the column sums of fragment 0" is every row's sum once.  XT: X_k lies in row groups (j0 is a whole number of them); the same
+// products in the same order.
+template <bool GATHER, bool DB, bool XT>
 struct DwProb {
   static constexpr bool SWAP = false;
-  static constexpr int FM = 2, CPS = 4, NREAD = 8, NPRE = GATHER ? 1 : 0, CHAIN = 10, STAGE = 2 * TILE;       // (the two row ids are one read)
-  SlowCopy ca, cb;
+  static constexpr int FM = 2, CPS = 4, NREAD = XT ? 6 : 8, NPRE = GATHER ? 1 : 0, CHAIN = 10, STAGE = 2 * TILE;       // (the two row ids are one read)
+  SlowCopy ca;
+  std::conditional_t<XT, GroupCopy, SlowCopy> cb;
   const char* dY;
   const int* rows;                 // LDS table: row of dY of kept row j0 + i, whole stages
   int rid[2];
@@ -323,28 +351,34 @@ struct DwProb {
     cb.issue(buf + TILE, kvalid, wave);
   }
   __device__ __forceinline__ void read(const char* buf, int ks, bf16x8_t (&a)[2], bf16x8_t (&b)[2]) const {
-    read_slow_frags<BT, 2>(buf + TILE, b_off, ks, b);
+    if constexpr (XT) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f) b[f] = *reinterpret_cast<const bf16x8_t*>(buf + TILE + b_off[f] + ks * (2 * BT * 16));
+    } else {
+      read_slow_frags<BT, 2>(buf + TILE, b_off, ks, b);
+    }
     read_slow_frags<BT, 2>(buf, a_off, ks, a);
   }
   __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const {
     SlowCopy::zero_tail(buf, kvalid);
-    SlowCopy::zero_tail(buf + TILE, kvalid);
+    decltype(cb)::zero_tail(buf + TILE, kvalid);
   }
 };
 
 // dbp (DB): the column sums of the tile's dY panel over [j0, j1)
-template <bool GATHER, bool DB>
+template <bool GATHER, bool DB, bool XT>
 __device__ __forceinline__ void dw_tile(char* smem, const uint16_t* __restrict__ dY, const int32_t* __restrict__ idx,
                                         const uint16_t* __restrict__ Xk, int Cin, int Cout, int j0, int j1,
                                         float* __restrict__ part, int m0, int n0, float* __restrict__ dbp) {
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), flip = wave & 1;
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
   const int nrows = j1 - j0, nk = (nrows + KB - 1) / KB;
-  DwProb<GATHER, DB> pb;
+  DwProb<GATHER, DB, XT> pb;
   pb.wave = wave;
   pb.dY = reinterpret_cast<const char*>(dY);
   pb.ca.init(GATHER ? dY : dY + (size_t)j0 * Cout, (size_t)Cout * 2, m0, Cout, lane, wave);
-  pb.cb.init(Xk + (size_t)j0 * Cin, (size_t)Cin * 2, n0, Cin, lane, wave);
+  if constexpr (XT) pb.cb.init(Xk + (size_t)j0 * Cin, Cin, n0, lane, wave);
+  else pb.cb.init(Xk + (size_t)j0 * Cin, (size_t)Cin * 2, n0, Cin, lane, wave);
   pb.rows = nullptr;
   if constexpr (GATHER) {
     int* rows = reinterpret_cast<int*>(smem + RING);
@@ -360,7 +394,12 @@ __device__ __forceinline__ void dw_tile(char* smem, const uint16_t* __restrict__
     pb.a_off[0] = flip ? off[1] : off[0];
     pb.a_off[1] = flip ? off[0] : off[1];
   }
-  slow_tile_lane_offs<BT, 2>(wn, lane, pb.b_off);
+  if constexpr (XT) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) pb.b_off[f] = ((lane >> 5) * BT + wn + 32 * f + (lane & 31)) * 16;
+  } else {
+    slow_tile_lane_offs<BT, 2>(wn, lane, pb.b_off);
+  }
   f32x16_t acc[2][2];
   zero_acc<2, 2>(acc);
   ring_loop(smem, pb, nk, nrows - (nk - 1) * KB, acc);

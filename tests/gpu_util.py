@@ -34,6 +34,18 @@ def bits(t):
     return t.view(torch.int16 if t.dtype == torch.bfloat16 else torch.int32).numpy()
 
 
+def launches(call):
+    """Kernel launches of a call by class (the classes of sbp_profile_read)."""
+    torch.cuda.synchronize()
+    sbp.profile_read()
+    sbp.profile_enable(True)
+    try:
+        call()
+    finally:
+        sbp.profile_enable(False)
+    return {name: n for name, (_, n) in sbp.profile_read().items()}
+
+
 def check_linear(X, W, dY, idx_np, dtype, flags=0, check_cache=True, inv_mode=None):
     """Runs cache + backward on the GPU and the oracle; returns the three normalised errors."""
     M = X.shape[0]

@@ -9,7 +9,7 @@ import torch
 import oracle
 import paper_2210_00129_amd as sbp
 import synth_inputs as si
-from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, f64, nerr
+from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, f64, launches, nerr
 
 pytestmark = pytest.mark.gpu
 KM = sbp.FLAG_XK_KMAJOR
@@ -93,6 +93,24 @@ def test_linear_backward_reads_row_groups(shape, opts):
     assert nerr(f64(grp[2]), rX) <= TOL_BF16_TIGHT
     for a, b in zip(rows, grp):                     # same products, same order of every sum
         assert np.array_equal(bits(a), bits(b))
+
+
+@pytest.mark.parametrize("K,Cin,Cout,flags", [(1, 8, 8, 0), (7, 136, 72, 0), (8, 120, 264, 2), (31, 264, 40, 1), (33, 128, 128, 3), (97, 72, 136, 0),
+                                              (129, 200, 200, 8), (2047, 136, 72, 0), (2049, 264, 72, 1), (4100, 128, 264, 3)])
+def test_mid_tiles_read_row_groups_as_they_are(K, Cin, Cout, flags):
+    # stages of 32 with and without a partial last group, ragged columns, one split and several, gathered and compact gradients: the
+    # bits of the call on rows, without a launch that copies them back
+    M = 2 * K + 3
+    X, Wt, dY = si.linear_case(M, Cin, Cout, K, "bf16")
+    idx = np.sort(np.random.default_rng(K).choice(M, size=K, replace=False)).astype(np.int32)
+    rows, grp = _both_layouts(M, X, Wt, dY, idx, flags=flags, opts=dict(tile="128x128x4x64"))
+    for a, b in zip(rows, grp):
+        assert np.array_equal(bits(a), bits(b))
+    idxd = torch.from_numpy(idx).cuda()
+    (Xt,) = sbp.forward_cache_batch([X.cuda()], [idxd], layout=sbp.LAYOUT_KMAJOR)
+    with sbp.options(tile="128x128x4x64"):
+        n = launches(lambda: sbp.backward_linear(dY.cuda(), idxd, Xt, Wt.cuda(), flags=KM, want=("dW",)))
+    assert n["dw_gemm"] == 1 and n["gather"] == n["other"] == 0
 
 
 @pytest.mark.parametrize("flags", [sbp.FLAG_DY_COMPACT, sbp.FLAG_DY_COMPACT | sbp.FLAG_DX_COMPACT, sbp.FLAG_DW_OUT_BF16])
