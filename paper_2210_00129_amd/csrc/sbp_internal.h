@@ -82,6 +82,7 @@ struct LinearPlan {
   int    bm_w, bn_w;    // tile of both contractions (rows x columns)
   int    splits;        // split-K factor of the dW contraction
   int    rows_per_split;// kept rows per split (multiple of the k-step)
+  int    splits_f32, rows_f32;   // the same for the fp32 engine, where a bf16 plan's call has unaligned tensors
   int    n_big;         // big engine: the first n_big splits have rows_per_split rows, the others rows_small
   int    rows_small;    // big engine: rows of the short splits that fill the end of the schedule (0: none)
   int    seg_order[3];  // big engine: dispatch order of the unit kinds 0 = dX tiles, 1 = long dW units, 2 = short dW units

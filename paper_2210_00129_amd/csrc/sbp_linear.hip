@@ -901,7 +901,23 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
   // db partials: one per slice of the column-sum blocks (128-wide tiles: per split), or (large tiles, db out of the dW units) per split
   // and tile column
   const int64_t db_parts = std::max<int64_t>(p.db_slices, (int64_t)splits * (p.big ? ceil_div(Cin, big::BT) : 1));
-  off += align_up(((size_t)splits * Cout * Cin + (size_t)db_parts * Cout) * sizeof(float), 256);
+  size_t sums = ((size_t)splits * Cout * Cin + (size_t)db_parts * Cout) * sizeof(float);
+  // The fp32 engine's splits where a call's tensors are not 16-byte aligned: its units are smaller than the 128-wide ones, whose one to
+  // three long splits left it few (900 rows of 200 -> 1000, dW alone, 35.8 us instead of 17.5): 512 tiles of 128 x 128 in all, at least
+  // 256 rows each, as many as the static scratch buffer holds.  (The fp32 tensors' rule, plan_linear_f32: that layer 43.6 us instead
+  // of 38.2 with all outputs, 400 rows of 1024 x 1024 52.3 instead of 41.9.)
+  p.splits_f32 = splits;
+  p.rows_f32 = p.rows_per_split;
+  if (p.mfma && !p.big && K > 0) {
+    const int64_t one = ((int64_t)Cin + 1) * Cout * (int64_t)sizeof(float);
+    const int64_t room = std::max<int64_t>(sums, (int64_t)SBP_STATIC_SCRATCH_BYTES - 256 - (int64_t)(inv_bytes(M, flags) + xrows_bytes(K, Cin, flags)));
+    const int64_t fill = 2 * kNumCU / (ceil_div(Cout, 128) * ceil_div(Cin, 128));
+    const int64_t n = std::max<int64_t>(1, std::min<int64_t>({64, fill, K / 256, room / one}));
+    p.rows_f32 = (int)(ceil_div(ceil_div(K, n), 64) * 64);
+    p.splits_f32 = (int)ceil_div(K, p.rows_f32);
+    sums = std::max(sums, (size_t)(p.splits_f32 * one));
+  }
+  off += align_up(sums, 256);
   p.off_inv = off;
   off += inv_bytes(M, flags);
   p.off_xrows = off;
@@ -1064,6 +1080,11 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
   // db alone in the fp32 engine: a reading of dY, cut into slices of at least 256 rows (16384 rows of 768 channels: 8 slices, the
   // splits of dW, 175 us; 64 slices 29 us) as far as the partial sums that dW would take hold theirs
   int splits = p.splits, rows_per_split = p.rows_per_split;
+  if (!use_mfma && p.mfma) {
+    splits = p.splits_f32;
+    rows_per_split = p.rows_f32;
+    dbp = part + (size_t)splits * Cout * Cin;
+  }
   if (!use_mfma && db && !dW) {
     const int64_t n = std::min<int64_t>(std::min<int64_t>(64, ceil_div(K, 256)), (int64_t)p.splits * Cin + 1);
     if (n > splits) {
@@ -1117,12 +1138,12 @@ int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_
       const long long total = (dW_sum ? nW / 4 : 0) + (db ? Cout : 0);
       // (large tiles with dW: db partials come from the dW units, one per split and tile column; 128-wide tiles: one per split)
       const int nsplit_b = !use_mfma ? splits : (!p.big && p.bm_w == mid::BT) ? p.splits : (p.big && dW ? p.splits * (int)ceil_div(Cin, big::BT) : p.db_slices);
-      const int deepest = std::max(dW_sum ? p.splits : 0, db ? nsplit_b : 0);
+      const int deepest = std::max(dW_sum ? splits : 0, db ? nsplit_b : 0);
       const int G = reduce_lanes(total, deepest);
       unsigned blocks = (unsigned)std::min<long long>(ceil_div(total * G, NTHREADS), 4096);
       auto kernel = dw_bf16 ? (G == 8 ? reduce_splits_kernel<8, true> : (G == 4 ? reduce_splits_kernel<4, true> : reduce_splits_kernel<1, true>))
                             : (G == 8 ? reduce_splits_kernel<8, false> : (G == 4 ? reduce_splits_kernel<4, false> : reduce_splits_kernel<1, false>));
-      SBP_LAUNCH(SBP_PROF_REDUCE, s, kernel, dim3(blocks), dim3(NTHREADS), 0, s, part, p.splits, nW, dW_sum, dbp, nsplit_b, Cout, db,
+      SBP_LAUNCH(SBP_PROF_REDUCE, s, kernel, dim3(blocks), dim3(NTHREADS), 0, s, part, splits, nW, dW_sum, dbp, nsplit_b, Cout, db,
                  accumulate);
     } else {
       const long long total = (dW ? nW : 0) + (db ? Cout : 0);

@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2210_00129_amd as sbp
 import synth_inputs as si
-from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, nerr
+from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, launches, nerr
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +99,27 @@ def test_long_splits_are_summed_in_short_chains(K, Cin, Cout, dtype):
     bound = 2.0 ** -24 * (320 / 6) ** 0.5
     for got, want in ((dW, rW), (db, rb), (alone, rb)):
         assert ((got.double() - want).norm() / want.norm()).item() <= bound
+
+
+@pytest.mark.parametrize("K,Cin,Cout", [(900, 200, 1000), (2100, 640, 264), (16800, 136, 256), (130, 72, 40)])
+@pytest.mark.parametrize("off", ["dY", "X_k", "W"])
+def test_unaligned_bf16_tensors_have_splits_of_their_own(K, Cin, Cout, off):
+    # a tensor one element off 16 bytes sends a bf16 layer to the fp32 engine, whose units are smaller than those of the bf16 ones: it
+    # cuts dW by a rule of its own (several splits from 512 rows on where the layer is small), in the workspace of the bf16 plan
+    M = K + 40
+    X, W, dY = si.linear_case(M, Cin, Cout, 17, "bf16")
+    idx_np = _rows(M, K)
+
+    def put(t, name):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        view = flat[1:] if name == off else flat[:-1]
+        return view.view(t.shape).copy_(t)
+    idx = torch.from_numpy(idx_np).cuda()
+    dYd, Xk, Wd = put(dY, "dY"), put(X[torch.from_numpy(idx_np).long()], "X_k"), put(W, "W")
+    ref = oracle.backward_linear(si.to_f64(dY), idx_np, si.to_f64(X)[idx_np], si.to_f64(W), M)
+    for flags in (0, sbp.FLAG_DW_OUT_BF16):
+        dW, db, dX = sbp.backward_linear(dYd, idx, Xk, Wd, flags=flags)
+        assert nerr(f64(dW), ref[0]) <= (TOL_BF16_TIGHT if flags else TOL_F32) and nerr(f64(db), ref[1]) <= TOL_F32
+        assert nerr(f64(dX), ref[2]) <= TOL_BF16_TIGHT
+    n = launches(lambda: sbp.backward_linear(dYd, idx, Xk, Wd, want=("dW",)))
+    assert n["dw_gemm"] == 1 and n["reduce"] == (1 if K > 256 else 0)
