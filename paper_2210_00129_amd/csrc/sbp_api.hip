@@ -1,5 +1,6 @@
 // C ABI of libsbp: host-side validation, then kernel launches.  Every argument check runs
 // before the first HIP call so that error paths need no device.
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -32,6 +33,8 @@ int32_t check_launch(const char* what) {
 // ---- explicit overrides -------------------------------------------------------------------------
 static std::mutex g_opt_mutex;
 static Options g_opt;
+static std::atomic<uint64_t> g_opt_generation{1};
+uint64_t options_generation() { return g_opt_generation.load(std::memory_order_acquire); }
 Options options() {
   std::lock_guard<std::mutex> lock(g_opt_mutex);
   return g_opt;
@@ -551,12 +554,14 @@ int32_t sbp_set_option(const char* name, const char* value) {
   std::lock_guard<std::mutex> lock(g_opt_mutex);
   if (!name) {                 // back to the defaults
     g_opt = Options{};
+    g_opt_generation.fetch_add(1, std::memory_order_release);
     return SBP_OK;
   }
   Options o = g_opt;
   if (!apply_option(o, name, value))
     return fail(SBP_ERR_FLAGS, "unknown option or invalid value: %s = %s", name, value ? value : "(unset)");
   g_opt = o;
+  g_opt_generation.fetch_add(1, std::memory_order_release);
   return SBP_OK;
 }
 

@@ -56,6 +56,7 @@ struct Options {
   bool dw_separate = false, sampler_no_window = false, sampler_no_masks = false, patch_wide = false;
 };
 Options options();                    // a snapshot (taken under a lock; safe against a concurrent sbp_set_option)
+uint64_t options_generation();        // counts the changes from 1 on
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

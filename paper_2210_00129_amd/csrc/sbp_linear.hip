@@ -602,20 +602,37 @@ static int64_t congruent_below_host(int64_t y, int64_t t) { return (t - y + 7) >
 
 // finish time of the grid: segments {count, unit length} in grid order
 static int64_t simulate_grid(const int64_t* n, const int64_t* l, int nseg) {
-  int64_t end = 0;
+  constexpr int CUS = kNumCU / kNumXCD, MAXSEG = 5;
+  int64_t seen[kNumXCD][MAXSEG], end = 0;
   for (int x = 0; x < kNumXCD; ++x) {
-    std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> cu;
-    for (int i = 0; i < kNumCU / kNumXCD; ++i) cu.push(0);
     int64_t start = 0;
     for (int q = 0; q < nseg; ++q) {
-      const int64_t mine = congruent_below_host(x, start + n[q]) - congruent_below_host(x, start);
-      for (int64_t i = 0; i < mine; ++i) {
-        const int64_t t = cu.top() + l[q];
-        cu.pop();
-        cu.push(t);
-        end = std::max(end, t);
-      }
+      seen[x][q] = congruent_below_host(x, start + n[q]) - congruent_below_host(x, start);
       start += n[q];
+    }
+    bool again = false;                               // (an XCD with the unit counts of an earlier one ends when that one does)
+    for (int y = 0; y < x && !again; ++y) again = std::equal(seen[x], seen[x] + nseg, seen[y]);
+    if (again) continue;
+    int64_t cu[CUS] = {};                             // when each CU is free, a heap (earliest first)
+    for (int q = 0; q < nseg; ++q) {
+      int64_t mine = seen[x][q];
+      if (mine > 2 * CUS) {                           // all units that end by T, as long as there are that many, are certain
+        int64_t T = mine * l[q];
+        for (int64_t t : cu) T += t;
+        T /= CUS;
+        auto fit = [&] { int64_t c = 0; for (int64_t t : cu) c += std::max<int64_t>(T - t, 0) / l[q]; return c; };
+        int64_t c = fit();
+        while (c > mine) { T -= l[q]; c = fit(); }
+        for (int64_t& t : cu) { t += std::max<int64_t>(T - t, 0) / l[q] * l[q]; end = std::max(end, t); }
+        mine -= c;
+        std::make_heap(cu, cu + CUS, std::greater<int64_t>());
+      }
+      for (int64_t i = 0; i < mine; ++i) {
+        std::pop_heap(cu, cu + CUS, std::greater<int64_t>());
+        cu[CUS - 1] += l[q];
+        end = std::max(end, cu[CUS - 1]);
+        std::push_heap(cu, cu + CUS, std::greater<int64_t>());
+      }
     }
   }
   return end;
@@ -668,10 +685,17 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
           std::sort(order, order + 3, [&](int x, int y) { return kl[x] > kl[y]; });   // longest kind first
           const int64_t n[5] = {kn[order[0]], kn[order[1]], kn[order[2]], n_zero, n_db};
           const int64_t l[5] = {kl[order[0]], kl[order[1]], kl[order[2]], l_zero, l_db};
-          const int64_t end = simulate_grid(n, l, 5);
           const int64_t splits = nb_real + ns_real;
           // the reduction kernel that follows reads every split's fp32 copy of dW and writes dW
-          const double cost = (double)end + 3000.0 + (double)(splits + 1) * Cout * Cin * 4.0 / kReduceBytesPerNs;
+          const double reduce = 3000.0 + (double)(splits + 1) * Cout * Cin * 4.0 / kReduceBytesPerNs;
+          // no grid ends before its longest unit or an even share of all units: most schedules need no simulation (a first call on a
+          // new size took up to 50 ms of host time, 9 on average over 1024 to 65536 rows)
+          int64_t least = 0, all = 0;
+          for (int q = 0; q < 5; ++q)
+            if (n[q] > 0) { least = std::max(least, l[q]); all += n[q] * l[q]; }
+          if (best.splits > 0 && (double)std::max(least, all / kNumCU) + reduce >= best_cost) continue;
+          const int64_t end = simulate_grid(n, l, 5);
+          const double cost = (double)end + reduce;
           if (best.splits == 0 || cost < best_cost) {
             best_cost = best.cost_ns = cost;
             best.splits = (int)splits; best.rps = (int)A; best.n_big = (int)nb_real; best.rows_small = (int)(ns_real ? a : 0);
@@ -787,10 +811,31 @@ static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t 
 
 // A layer whose 128-wide splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by
 // time.  (X_k in row groups is read as it is by both: the same engine and the same bits as with X_k by rows.)
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+static LinearPlan make_plan(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
   const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::by_time);
   if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
   return plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::large);
+}
+
+// The plans of the last sizes, per thread: 256 of them in sets of 4 by a hash of the size (a call asks for its plan twice or more, and
+// a network with many layer shapes or maps of changing size for all of them in turn).  New overrides make them stale.
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  struct Entry { uint64_t generation; int64_t M, K; int32_t Cin, Cout, dtype; uint32_t flags; LinearPlan p; };
+  constexpr int SETS = 64, WAYS = 4;
+  thread_local std::vector<Entry> cache;
+  thread_local unsigned char next[SETS] = {};
+  if (cache.empty()) cache.resize(SETS * WAYS);
+  const uint64_t gen = options_generation();         // (read first: a plan made under later overrides is stored as stale)
+  uint64_t h = 0;
+  for (uint64_t v : {(uint64_t)M, (uint64_t)K, (uint64_t)Cin, (uint64_t)Cout, (uint64_t)dtype, (uint64_t)flags}) h = (h ^ v) * 0x9e3779b97f4a7c15ull;
+  const int set = (int)(h >> 58);
+  Entry* e = &cache[set * WAYS];
+  for (int w = 0; w < WAYS; ++w)
+    if (e[w].generation == gen && e[w].M == M && e[w].K == K && e[w].Cin == Cin && e[w].Cout == Cout && e[w].dtype == dtype && e[w].flags == flags)
+      return e[w].p;
+  Entry& into = e[next[set]++ % WAYS];
+  into = Entry{gen, M, K, Cin, Cout, dtype, flags, make_plan(M, K, Cin, Cout, dtype, flags)};
+  return into.p;
 }
 
 // The plan of a call that has no more than the static scratch buffer: where the faster large tiles need more (1794 rows of 7816 -> 864,

@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+import time
 
 import pytest
 
@@ -260,6 +261,21 @@ def test_layers_that_fit_the_static_scratch_with_few_splits_are_not_refused():
     p = ctypes.c_void_p(4096)
     assert L.sbp_backward_linear_static(p, p, None, p, p, 3588, 1794, 7816, 864, 1, None, None, None, 0, None) == 0
     assert L.sbp_backward_linear_static(p, p, None, p, p, 65536, 65536, 4096, 4096, 1, None, None, None, 0, None) == -5
+
+
+def test_plans_of_new_sizes_cost_little_host_time_and_follow_the_overrides():
+    # 60 sizes that no call has had: 0.07 ms each (9 ms before schedules were ruled out by a bound on their length)
+    L = _lib.lib()
+    sizes = [(1024 + 977 * i, 256 + 8 * (i % 50), 256 + 32 * (i % 60)) for i in range(60)]
+    t0 = time.thread_time()
+    first = [L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, None) for K, Cin, Cout in sizes]
+    assert time.thread_time() - t0 < 60 * 1.5e-3
+    assert L.sbp_set_option(b"tile", b"big") == 0
+    assert all(L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, None) == 2 for K, Cin, Cout in sizes)
+    assert L.sbp_set_option(b"tile", b"128x128x4x64") == 0
+    assert all(L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, None) == 1 for K, Cin, Cout in sizes)
+    assert L.sbp_set_option(b"tile", None) == 0
+    assert [L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, None) for K, Cin, Cout in sizes] == first
 
 
 def test_backward_attention_argument_errors_and_engine():
