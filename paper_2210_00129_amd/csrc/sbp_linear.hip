@@ -111,10 +111,13 @@ __device__ __forceinline__ void linear_mid_unit(char* smem, const LinArgs& a, in
     if (wg < a.n_zero) {
       zero_rows_block(a, wg);
     } else {                                         // (padded to a multiple of 8 workgroups)
-      const int b = wg - a.n_zero, split = b % nsplit, chunk = b / nsplit;
-      if (a.dbp && !a.db_in_dw && chunk * mid::kColumns < a.Cout) {
+      const int chunks = (a.Cout + mid::kColumns - 1) / mid::kColumns;
+      const int b = xcd_chunked_id(wg - a.n_zero, chunks * nsplit), split = b / chunks, c0 = (b - split * chunks) * mid::kColumns;
+      if (a.dbp && !a.db_in_dw && split < nsplit) {
         const int j0 = split * a.rows_per_split, j1 = min(a.K, j0 + a.rows_per_split);
-        mid::colsum_block(smem, a.dY, a.idx_in, a.Cout, j0, j1, chunk * mid::kColumns, a.dbp + (long long)split * a.Cout);
+        float* dbp = a.dbp + (long long)split * a.Cout;
+        if ((uint64_t)(unsigned)a.M * (2u * (unsigned)a.Cout) < (1ull << 32)) mid::colsum_block<false>(smem, a.dY, a.idx_in, a.Cout, j0, j1, c0, dbp);
+        else mid::colsum_block<true>(smem, a.dY, a.idx_in, a.Cout, j0, j1, c0, dbp);
       }
     }
     return;
@@ -981,7 +984,7 @@ static unsigned prepare_linear(const LinearPlan& p, LinArgs& a, bool want_dx, bo
   const long long tiles_n = ceil_div(a.Cin, bn);
   a.n_zero = want_zero ? (int)std::min<long long>(128, std::max<long long>(8, ceil_div((long long)a.M, 64 * nw))) : 0;
   a.db_in_dw = mid_tiles && a.dbp && want_dw ? 1 : 0;
-  const int n_db = a.dbp && !a.db_in_dw ? (int)(mid_tiles ? ceil_div(a.Cout, mid::kColumns) * p.splits : ceil_div(a.Cout, 256) * p.db_slices) : 0;
+  const int n_db = a.dbp && !a.db_in_dw ? (int)(mid_tiles ? 8 * ceil_div(ceil_div(a.Cout, mid::kColumns) * p.splits, 8) : ceil_div(a.Cout, 256) * p.db_slices) : 0;
   a.n_helper = (int)(8 * ceil_div(a.n_zero + n_db, 8));
   a.n_dx = want_dx ? (int)(8 * ceil_div(ceil_div(a.K, bmx) * tiles_n, 8)) : 0;
   a.n_dw = want_dw ? (int)(8 * ceil_div(ceil_div(a.Cout, bm) * tiles_n * p.splits, 8)) : 0;

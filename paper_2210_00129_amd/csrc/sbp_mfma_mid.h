@@ -437,36 +437,56 @@ __device__ __forceinline__ void dw_tile(char* smem, const uint16_t* __restrict__
 }
 
 // db alone: the column sums of one split, 64 channels from c0 on, in the chains of dw_tile (the same bits whichever outputs are
-// wanted).  Thread (x = t & 31, y = t >> 5) owns 2 channels and rows 2 y, 2 y + 1 of every 16: word y & 3 of half y >> 2.
+// wanted).  Thread (x = t & 31, y = t >> 5) owns 2 channels and rows 2 y, 2 y + 1 of every 16: word y & 3 of half y >> 2.  These
+// are few workgroups of long chains, so what bounds them is the instructions of a step and the loads in flight: the rows' offsets are
+// staged in LDS as they are added to the base (WIDE: tensors of 4 GB and more, row ids), and U steps are loaded at a time with no
+// shorter loop behind them, which would wait for every row.  db alone, a call, with a loop over 64-bit addresses / now (operands from
+// memory): 900 rows of 1000 channels 6.5 / 5.1 us (9.3 / 6.5), 8400 of 256 9.3 / 7.2 (12.5 / 8.3), 16800 of 1024 14.4 / 9.8 (17.8 / 12.5),
+// 33600 of 256 12.7 / 9.3 (17.0 / 11.4), 60000 of 288 16.9 / 12.5 (17.4 / 13.3).
 static constexpr int kColumns = 64;
+template <bool WIDE>
 __device__ __forceinline__ void colsum_block(char* smem, const uint16_t* __restrict__ dY, const int32_t* __restrict__ idx, int Cout,
                                              int j0, int j1, int c0, float* __restrict__ dbp) {
-  constexpr int CHUNK = 1024;                                 // row ids staged at a time, a multiple of 16
-  float(*red)[kColumns] = reinterpret_cast<float(*)[kColumns]>(smem);
-  int* ids = reinterpret_cast<int*>(smem + sizeof(float) * 8 * kColumns);
-  const int x = threadIdx.x & 31, y = threadIdx.x >> 5, col = c0 + 2 * x;
+  constexpr int U = 16;
+  const int t = threadIdx.x, x = t & 31, y = t >> 5, n = j1 - j0, steps = (n + 15) / 16;
+  uint32_t* rows = reinterpret_cast<uint32_t*>(smem);         // whole batches of U steps, the last row repeated past the end
+  for (int i = t; i < (steps + U - 1) / U * U * 16; i += 256) {
+    const int j = min(j0 + i, j1 - 1);
+    rows[i] = (uint32_t)(idx ? idx[j] : j) * (WIDE ? 1u : 2u * (uint32_t)Cout);
+  }
+  __syncthreads();
+  const char* src = reinterpret_cast<const char*>(dY);
+  const uint32_t colb = 2u * (uint32_t)min(c0 + 2 * x, Cout - 2);
   const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3f803f80u);
   float s0 = 0.f, s1 = 0.f;
-  for (int b0 = j0; b0 < j1; b0 += CHUNK) {
-    const int n = min(CHUNK, j1 - b0);
-    for (int i = threadIdx.x; i < n; i += 256) ids[i] = idx ? idx[b0 + i] : b0 + i;
-    __syncthreads();
-    if (col < Cout) {
-#pragma unroll 16
-      for (int j = 2 * y; j < n; j += 16) {
-        const unsigned a = *reinterpret_cast<const unsigned*>(dY + (long long)ids[j] * Cout + col);
-        unsigned b = *reinterpret_cast<const unsigned*>(dY + (long long)ids[min(j + 1, n - 1)] * Cout + col);
-        if (j + 1 >= n) b = 0u;
-        s0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (a & 0xffffu) | (b << 16)), ones, s0, false);
-        s1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (a >> 16) | (b & 0xffff0000u)), ones, s1, false);
-      }
+  auto batch = [&](int q0, auto last) {
+    unsigned a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint2 r = *reinterpret_cast<const uint2*>(rows + 16 * (q0 + u) + 2 * y);
+      const size_t ra = WIDE ? (size_t)r.x * (2u * (uint32_t)Cout) + colb : (size_t)(r.x + colb), rb = WIDE ? (size_t)r.y * (2u * (uint32_t)Cout) + colb : (size_t)(r.y + colb);
+      a[u] = *reinterpret_cast<const unsigned*>(src + ra);
+      b[u] = *reinterpret_cast<const unsigned*>(src + rb);
     }
-    __syncthreads();
-  }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (decltype(last)::value) {
+        const int j = 16 * (q0 + u) + 2 * y;
+        if (j >= n) a[u] = 0u;
+        if (j + 1 >= n) b[u] = 0u;
+      }
+      s0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (a[u] & 0xffffu) | (b[u] << 16)), ones, s0, false);
+      s1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (a[u] >> 16) | (b[u] & 0xffff0000u)), ones, s1, false);
+    }
+  };
+  int q0 = 0;
+  for (; 16 * (q0 + U) <= n; q0 += U) batch(q0, std::false_type{});
+  if (q0 < steps) batch(q0, std::true_type{});
+  __syncthreads();
+  float(*red)[kColumns] = reinterpret_cast<float(*)[kColumns]>(smem);
   red[y][2 * x] = s0;
   red[y][2 * x + 1] = s1;
   __syncthreads();
-  const int t = threadIdx.x;
   if (t < kColumns && c0 + t < Cout)
     dbp[c0 + t] = ((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + ((red[4][t] + red[5][t]) + (red[6][t] + red[7][t]));
 }

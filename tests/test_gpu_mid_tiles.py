@@ -58,6 +58,33 @@ def test_db_has_the_same_bits_whichever_outputs_are_wanted(K, Cin, Cout):
     assert np.array_equal(bits(acc[0]), bits(full[0] + 2.0)) and np.array_equal(bits(acc[1]), bits(full[1] - 1.0))
 
 
+@pytest.mark.parametrize("K", [1, 2, 15, 16, 17, 255, 256, 257, 271, 512, 2047, 2048, 2049, 4500])
+@pytest.mark.parametrize("Cout,flags", [(8, 0), (72, sbp.FLAG_DY_COMPACT), (136, 0)])
+def test_db_alone_around_steps_and_batches(K, Cout, flags):
+    # the column-sum blocks load 16 steps of 16 rows at a time: part of a step, one short of a batch, a whole one, one more row
+    X, W, dY, idx = _case(2 * K, K, 40, Cout, K)
+    idxd = torch.from_numpy(idx).cuda()
+    d = dY.cuda()[idxd.long()].contiguous() if flags else dY.cuda()
+    args = (d, idxd, sbp.forward_cache(X.cuda(), idxd), W.cuda())
+    with sbp.options(tile="128x128x4x64"):
+        full = sbp.backward_linear(*args, M=2 * K, flags=flags)
+        for want in (("db",), ("db", "dX")):
+            assert np.array_equal(bits(sbp.backward_linear(*args, M=2 * K, flags=flags, want=want)[1]), bits(full[1]))
+    assert nerr(f64(full[1]), si.to_f64(dY)[idx].sum(0)) <= TOL_F32
+
+
+def test_db_alone_of_a_gradient_beyond_4_GB():
+    # row offsets that need more than 32 bits
+    M, Cout, K = 2_200_000, 1000, 300
+    dY = torch.empty((M, Cout), dtype=torch.bfloat16, device="cuda")
+    idx = np.sort(np.random.default_rng(5).choice(M - 1, size=K - 1, replace=False)).astype(np.int32)
+    idxd = torch.from_numpy(np.append(idx, M - 1).astype(np.int32)).cuda()
+    rows = torch.randn((K, Cout)).to(torch.bfloat16)
+    dY[idxd.long()] = rows.cuda()
+    db = sbp.backward_linear(dY, idxd, None, torch.empty((Cout, 8), dtype=torch.bfloat16, device="cuda"), want=("db",))[1]
+    assert nerr(f64(db), si.to_f64(rows).sum(0)) <= TOL_F32
+
+
 def test_layers_of_one_launch_longest_workgroups_first():
     # four layers whose kinds of workgroups differ in length by an order of magnitude, one of them without dX, one compact, one
     # accumulating: the launch orders their segments by length, whatever the layer
