@@ -306,13 +306,13 @@ extern "C" {
 size_t sbp_backward_linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype,
                                      uint32_t flags) {
   if (validate_linear(M, K, Cin, Cout, dtype, flags) != SBP_OK) return 0;
-  return plan_linear(M, K, Cin, Cout, dtype, flags).bytes;
+  return linear_workspace(M, K, Cin, Cout, dtype, flags);
 }
 
 int32_t sbp_backward_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags,
                                    int32_t* split_count) {
   if (validate_linear(M, K, Cin, Cout, dtype, flags) != SBP_OK) return -1;
-  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
+  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags, true);
   if (split_count) *split_count = p.splits;
   return !p.mfma ? SBP_ENGINE_PLAIN : (p.big ? SBP_ENGINE_MFMA_LARGE : SBP_ENGINE_MFMA);
 }
@@ -323,14 +323,14 @@ int32_t sbp_backward_linear(const void* dY, const int32_t* idx, const int32_t* i
                             void* dX, void* ws, size_t ws_bytes, uint32_t flags, void* stream) {
   int32_t st = check_linear_args(dY, idx, Xk, W, M, K, Cin, Cout, dtype, dW, dX, flags);
   if (st != SBP_OK) return st;
-  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
-  const size_t need = p.bytes;
+  const size_t need = linear_workspace(M, K, Cin, Cout, dtype, flags);
   if (need) {
     if (!ws) return fail(SBP_ERR_WORKSPACE, "workspace is NULL, %zu bytes needed", need);
     if (ws_bytes < need) return fail(SBP_ERR_WORKSPACE, "workspace %zu bytes < %zu needed", ws_bytes, need);
     if ((uintptr_t)ws % 256) return fail(SBP_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   }
   if (!dW && !db && !dX) return SBP_OK;
+  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags, takes_dx_plan(K, Cout, dW, dX));
   return launch_backward_linear(p, dY, idx, inv, Xk, W, M, K, Cin, Cout, dtype, dW, db, dX, ws, flags,
                                 (hipStream_t)stream);
 }

@@ -101,8 +101,14 @@ struct LinearPlan {
 };
 int32_t check_linear_args(const void* dY, const int32_t* idx, const void* Xk, const void* W, int64_t M, int64_t K,
                           int32_t Cin, int32_t Cout, int32_t dtype, const void* dW, const void* dX, uint32_t flags);
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags);
-LinearPlan plan_linear_static(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags);
+// A size has two plans: for calls that want dX, and for those that do not (see mid_without_dx).  The first one also serves db alone of
+// much dY (24 MB and more), whose column sums the large tiles' wider blocks read faster (12672 rows of 1536 channels 10.7 us, with
+// 128-wide tiles 12.5; 6336 of 3072 10.8 and 11.6; but 8400 of 256 9.1 and 7.2, 2100 of 3072 9.2 and 7.9), and a layer that shares its
+// launch with others.
+inline bool takes_dx_plan(int64_t K, int32_t Cout, const void* dW, const void* dX) { return dX || (!dW && 2 * K * Cout >= 24000000); }
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool want_dx);
+LinearPlan plan_linear_static(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool want_dx);
+size_t linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags);   // whatever a call wants
 int32_t launch_backward_linear(const LinearPlan& p, const void* dY, const int32_t* idx, const int32_t* inv,
                                const void* Xk, const void* W, int64_t M, int64_t K, int32_t Cin, int32_t Cout,
                                int32_t dtype, void* dW, float* db, void* dX, void* ws, uint32_t flags,

@@ -809,21 +809,29 @@ static int mid_split_cap(int64_t M, int64_t K, int32_t Cin, int32_t Cout, uint32
   return (int)std::min<int64_t>(64, std::max<int64_t>(1, room / ((int64_t)sizeof(float) * Cout * (Cin + 1))));
 }
 
-enum class EngineRule { by_time, large, mid };      // large: wherever they pay and 128-wide ones may be faster
+enum class EngineRule { by_time, large, mid };      // large: also where the 128-wide tiles are faster
 static LinearPlan plan_linear_engine(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, EngineRule rule);
+
+// Without dX (dW and db, or one of them) the 128-wide tiles are ahead up to far larger layers, as no long dX tile keeps their grid
+// open: 35 layers of 2 to 96 GFLOP, 128-wide / large: 19.5 / 33.2 us (1584 rows, 768 -> 2304), 22.0 / 39.8 (4200, 256 -> 3072), 39.2 / 57.0
+// (6336, 768 -> 2304), 52.8 / 69.8 (4096, 2048 x 2048), 80.0 / 115.7 (25680, 368 -> 2528), operands from memory 24.6 / 34.5, 26.9 / 41.7,
+// 43.3 / 56.6, 56.0 / 71.4, 97.2 / 115.1; 83.8 / 68.4 for 134 GFLOP (2000, 4096 x 4096).
+static bool mid_without_dx(int64_t K, int32_t Cin, int32_t Cout) { return 4e-9 * (double)K * Cin * Cout < 100.0; }
 
 // A layer whose 128-wide splits would not fit the static scratch buffer keeps the large tiles: there the engine is not chosen by
 // time.  (X_k in row groups is read as it is by both: the same engine and the same bits as with X_k by rows.)
-static LinearPlan make_plan(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::by_time);
+static LinearPlan make_plan(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool want_dx) {
+  const EngineRule rule = !want_dx && mid_without_dx(K, Cin, Cout) ? EngineRule::mid : EngineRule::by_time;
+  const LinearPlan p = plan_linear_engine(M, K, Cin, Cout, dtype, flags, rule);
   if (p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES) return p;
   return plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::large);
 }
 
 // The plans of the last sizes, per thread: 256 of them in sets of 4 by a hash of the size (a call asks for its plan twice or more, and
 // a network with many layer shapes or maps of changing size for all of them in turn).  New overrides make them stale.
-LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  struct Entry { uint64_t generation; int64_t M, K; int32_t Cin, Cout, dtype; uint32_t flags; LinearPlan p; };
+struct LinearPlans { LinearPlan with_dx, without_dx; size_t bytes; };
+static LinearPlans linear_plans(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  struct Entry { uint64_t generation; int64_t M, K; int32_t Cin, Cout, dtype; uint32_t flags; LinearPlans p; };
   constexpr int SETS = 64, WAYS = 4;
   thread_local std::vector<Entry> cache;
   thread_local unsigned char next[SETS] = {};
@@ -836,15 +844,24 @@ LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t 
   for (int w = 0; w < WAYS; ++w)
     if (e[w].generation == gen && e[w].M == M && e[w].K == K && e[w].Cin == Cin && e[w].Cout == Cout && e[w].dtype == dtype && e[w].flags == flags)
       return e[w].p;
-  Entry& into = e[next[set]++ % WAYS];
-  into = Entry{gen, M, K, Cin, Cout, dtype, flags, make_plan(M, K, Cin, Cout, dtype, flags)};
-  return into.p;
+  LinearPlans p{make_plan(M, K, Cin, Cout, dtype, flags, true), make_plan(M, K, Cin, Cout, dtype, flags, false), 0};
+  p.bytes = std::max(p.with_dx.bytes, p.without_dx.bytes);
+  e[next[set]++ % WAYS] = Entry{gen, M, K, Cin, Cout, dtype, flags, p};
+  return p;
+}
+
+LinearPlan plan_linear(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool want_dx) {
+  const LinearPlans p = linear_plans(M, K, Cin, Cout, dtype, flags);
+  return want_dx ? p.with_dx : p.without_dx;
+}
+size_t linear_workspace(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
+  return linear_plans(M, K, Cin, Cout, dtype, flags).bytes;
 }
 
 // The plan of a call that has no more than the static scratch buffer: where the faster large tiles need more (1794 rows of 7816 -> 864,
 // two splits of 27 MB), the 128-wide ones with fewer splits.
-LinearPlan plan_linear_static(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags) {
-  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags);
+LinearPlan plan_linear_static(int64_t M, int64_t K, int32_t Cin, int32_t Cout, int32_t dtype, uint32_t flags, bool want_dx) {
+  const LinearPlan p = plan_linear(M, K, Cin, Cout, dtype, flags, want_dx);
   if (!p.big || p.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES || options().tile_mode == 2) return p;
   const LinearPlan q = plan_linear_engine(M, K, Cin, Cout, dtype, flags, EngineRule::mid);
   return q.bytes <= (size_t)SBP_STATIC_SCRATCH_BYTES ? q : p;
@@ -1510,7 +1527,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
       const sbp_linear_layer& l = L[i];
       flops += 4.0 * (double)l.K * l.Cin * l.Cout;
       general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !((uintptr_t)l.dW & 15) &&
-                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags).big;
+                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, true).big;
     }
     if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) p.fused = false;
   }
@@ -1519,7 +1536,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   size_t off = 0, seq_bytes = 0;
   for (int i = 0; i < n; ++i) {
     if (!p.fused) p.lay[i].off = seq_bytes;
-    seq_bytes += align_up(plan_linear(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags).bytes, 256);
+    seq_bytes += align_up(linear_workspace(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags), 256);
   }
   p.bytes = seq_bytes;
   if (!p.fused) return p;
@@ -1576,7 +1593,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
   LinearPlan lp[kMaxBatch];
   for (int i = 0; i < p.n; ++i) {
     const sbp_linear_layer& l = L[i];
-    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
+    lp[i] = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, true);
     if (!lp[i].mfma || lp[i].big || lp[i].bm_w != mid::BT || l.K < 1) return false;
     if (l.flags & SBP_FLAG_XK_KMAJOR) return false;
     if (!l.dW && !l.db && !l.dX) return false;
@@ -1675,7 +1692,7 @@ int32_t launch_backward_linear_batch(const BatchPlan& p, const sbp_linear_layer*
     for (int i = 0; i < p.n; ++i) {
       const sbp_linear_layer& l = L[i];
       if (!l.dW && !l.db && !l.dX) continue;
-      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags);
+      const LinearPlan lp = plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, takes_dx_plan(l.K, l.Cout, l.dW, l.dX));
       const int32_t st = launch_backward_linear(lp, l.dY, l.idx, l.inv, l.X_k, l.W, l.M, l.K, l.Cin, l.Cout, dtype, l.dW,
                                                 l.db, l.dX, wsb + p.lay[i].off, l.flags, s);
       if (st != SBP_OK) return st;

@@ -51,7 +51,7 @@ int32_t sbp_backward_linear_static(const void* dY, const int32_t* idx, const int
   // the host-side checks of sbp_backward_linear, then the size limit, then (first HIP call) the scratch address
   int32_t st = check_linear_args(dY, idx, Xk, W, M, K, Cin, Cout, dtype, dW, dX, flags);
   if (st != SBP_OK) return st;
-  const LinearPlan p = plan_linear_static(M, K, Cin, Cout, dtype, flags);
+  const LinearPlan p = plan_linear_static(M, K, Cin, Cout, dtype, flags, takes_dx_plan(K, Cout, dW, dX));
   const size_t need = p.bytes;
   if (need > (size_t)SBP_STATIC_SCRATCH_BYTES)
     return fail(SBP_ERR_CAPACITY, "these sizes need %zu bytes of scratch, the static buffer holds %zu: use sbp_backward_linear "

@@ -148,3 +148,23 @@ def test_infinite_cached_values_in_the_last_row_group(K, tile):
     fin = torch.isfinite(ref)
     assert torch.equal(dW[~fin], ref[~fin]) and not fin[:, 5].any() and fin[:, 6:].all()
     assert nerr(dW[fin].numpy(), ref[fin].numpy()) <= TOL_F32
+
+
+@pytest.mark.parametrize("K,Cin,Cout", [(1500, 2048, 1536), (3000, 256, 3072), (1584, 768, 2304), (2100, 1024, 3072)])
+@pytest.mark.parametrize("want", [("dW",), ("dW", "db"), ("db",)])
+def test_calls_without_dX_take_the_128_wide_tiles(K, Cin, Cout, want):
+    # layers whose full call takes (or took) the large tiles: the engines sum in different orders, so the bits tell which one ran; the
+    # workspace is the one that is asked for without knowing the wanted outputs
+    X, W, dY, idx = _case(K + 64, K, Cin, Cout, K)
+    idxd = torch.from_numpy(idx).cuda()
+    args = (dY.cuda(), idxd, sbp.forward_cache(X.cuda(), idxd), W.cuda())
+    ws = torch.empty(max(256, sbp.backward_linear_workspace(K + 64, K, Cin, Cout, sbp.BF16)), dtype=torch.uint8, device="cuda")
+    out = sbp.backward_linear(*args, want=want, workspace=ws)
+    forced = {}
+    for tile in ("128x128x4x64", "big"):
+        with sbp.options(tile=tile):
+            forced[tile] = sbp.backward_linear(*args, want=want)
+    for a, b, c in zip(out[:2], forced["128x128x4x64"], forced["big"]):
+        if a is not None:
+            assert np.array_equal(bits(a), bits(b)) and not np.array_equal(bits(a), bits(c))
+            assert nerr(f64(a), f64(c)) <= 2 * TOL_F32
