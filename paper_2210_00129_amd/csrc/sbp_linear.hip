@@ -1589,7 +1589,8 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
 // (bf16, 128 x 128 tiles, stages of 64): one launch of linear_mid_multi_kernel + one reduction launch.  Every layer uses
 // its own piece of the workspace exactly as a single call would.  Returns false if the batch is not of that kind.
 static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, int32_t dtype, char* wsb, hipStream_t s, int32_t* status) {
-  if (p.n < 2 || dtype != SBP_BF16 || options().tile_mode != 0) return false;
+  const Options opt = options();
+  if (p.n < 2 || dtype != SBP_BF16 || opt.tile_mode != 0) return false;
   LinearPlan lp[kMaxBatch];
   for (int i = 0; i < p.n; ++i) {
     const sbp_linear_layer& l = L[i];
@@ -1609,7 +1610,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
     const MidChoice c = choose_mid(L[i].K, L[i].Cin, L[i].Cout, std::max(64, (int)(2 * kNumCU * share) / 8 * 8), lp[i].splits);
     lp[i].splits = c.splits;
     lp[i].rows_per_split = c.rps;
-    lp[i].dx_bm = c.dx_bm;
+    lp[i].dx_bm = opt.dxrows ? opt.dxrows : c.dx_bm;
   }
   MidMultiArgs m{};
   RedMultiArgs r{};
@@ -1657,7 +1658,18 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
     rl.G = reduce_lanes((rl.dW ? rl.nW / 4 : 0) + (rl.db ? rl.Cout : 0), std::max(rl.dW ? rl.nsplit_w : 0, rl.db ? rl.nsplit_b : 0));
     any_reduce = any_reduce || rl.dW || rl.db;
   }
-  std::stable_sort(segs.begin(), segs.end(), [](const Segment& x, const Segment& y) { return x.len > y.len; });
+  int place[3] = {0, 0, 0};                          // the order of the kinds by hand goes before the length
+  if (opt.order_set)
+    for (int q = 0; q < 3; ++q) place[opt.order[q]] = q;
+  std::stable_sort(segs.begin(), segs.end(), [&](const Segment& x, const Segment& y) {
+    return place[x.kind] != place[y.kind] ? place[x.kind] < place[y.kind] : x.len > y.len;
+  });
+  if (opt.debug_plan) {
+    std::fprintf(stderr, "sbp batch of 128-wide tiles:");
+    for (const Segment& g : segs) std::fprintf(stderr, " L%d.k%d %d x %.1fus", g.layer, g.kind, g.n, g.len / 1e3);
+    for (int i = 0; i < p.n; ++i) std::fprintf(stderr, " [L%d: dx rows %d, %d splits]", i, lp[i].dx_bm, lp[i].splits);
+    std::fprintf(stderr, "\n");
+  }
   int blk = 0;
   for (const Segment& g : segs) {
     m.start[m.n] = blk;

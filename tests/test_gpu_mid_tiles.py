@@ -2,6 +2,8 @@
 and without a partial last one (fewer than the ring of four is deep, exactly as many, more), ragged tiles, one split (dW and db written
 by the units themselves) and several, gathered and compact rows, dX tiles of 64 and 128 rows; db alone in the same bits; several layers
 in one launch."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -9,7 +11,7 @@ import torch
 import oracle
 import paper_2210_00129_amd as sbp
 import synth_inputs as si
-from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, nerr
+from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, check_linear, f64, launches, nerr
 
 pytestmark = pytest.mark.gpu
 COMPACT = sbp.FLAG_DY_COMPACT | sbp.FLAG_DX_COMPACT
@@ -108,6 +110,42 @@ def test_layers_of_one_launch_longest_workgroups_first():
         assert nerr(f64(l["dW"]), rW + one) <= TOL_F32 and nerr(f64(l["db"]), rb + one) <= TOL_F32
         if want_dx:
             assert nerr(f64(l["dX"]), rX[idx] if flags & sbp.FLAG_DX_COMPACT else rX) <= TOL_BF16_TIGHT
+
+
+@pytest.mark.parametrize("dxrows", [None, 64, 128])
+@pytest.mark.parametrize("order", [None, "0,1,2", "2,0,1", "1,2,0"])
+def test_batch_in_one_launch_follows_the_overrides(dxrows, order, capfd):
+    # three layers, one split and several, one of them without dX: one launch, its segments by length or by the kinds' order given by
+    # hand, dX tiles as given by hand; every choice with the bits of dX and dW that the oracle bounds
+    shapes = [(500, 136, 264, True), (1800, 264, 136, True), (700, 72, 520, False)]
+    layers, refs = [], []
+    for i, (K, Cin, Cout, want_dx) in enumerate(shapes):
+        X, W, dY, idx = _case(2 * K, K, Cin, Cout, 60 + i)
+        idxd = torch.from_numpy(idx).cuda()
+        refs.append(oracle.backward_linear(si.to_f64(dY), idx, si.to_f64(X)[idx], si.to_f64(W), 2 * K))
+        layers.append(dict(dY=dY.cuda(), idx=idxd, X_k=sbp.forward_cache(X.cuda(), idxd), W=W.cuda(), M=2 * K,
+                           inv=torch.from_numpy(oracle.inverse_map(idx, 2 * K)).cuda(), dW=torch.empty((Cout, Cin), device="cuda"),
+                           db=torch.empty((Cout,), device="cuda")))
+        if want_dx:
+            layers[-1]["dX"] = torch.empty((2 * K, Cin), dtype=torch.bfloat16, device="cuda")
+    opts = {k: v for k, v in dict(dxrows=dxrows, order=order).items() if v}
+    with sbp.options(debug_plan=1, **opts):
+        n = launches(lambda: sbp.backward_linear_batch(layers, want=()))
+    assert n["dw_gemm"] == 1 and n["reduce"] == 1
+    text = [line for line in capfd.readouterr().err.splitlines() if line.startswith("sbp batch of 128-wide tiles:")][-1]
+    segments = [(int(l), int(k), float(us)) for l, k, us in re.findall(r"L(\d)\.k(\d) \d+ x ([\d.]+)us", text)]
+    assert sorted((l, k) for l, k, _ in segments) == [(0, 0), (0, 1), (0, 2), (1, 0), (1, 1), (1, 2), (2, 1)]
+    kinds = [k for _, k, _ in segments]
+    if order:
+        assert kinds == sorted(kinds, key=[int(k) for k in order.split(",")].index)
+    for (_, k0, a), (_, k1, b) in zip(segments, segments[1:]):
+        assert a >= b or (order and k0 != k1)
+    rows = [int(r) for r in re.findall(r"dx rows (\d+)", text)]
+    assert len(rows) == 3 and (not dxrows or set(rows) == {dxrows})
+    for l, (rW, rb, rX), (_, _, _, want_dx) in zip(layers, refs, shapes):
+        assert nerr(f64(l["dW"]), rW) <= TOL_F32 and nerr(f64(l["db"]), rb) <= TOL_F32
+        if want_dx:
+            assert nerr(f64(l["dX"]), rX) <= TOL_BF16_TIGHT
 
 
 @pytest.mark.parametrize("opts", [dict(dxrows=64, tile="128x128x4x64"), dict(dxrows=128, tile="128x128x4x64"), dict(tile="256x256x8x64"),
