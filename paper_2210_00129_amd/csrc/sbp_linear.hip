@@ -1304,15 +1304,16 @@ __global__ void __launch_bounds__(NTHREADS) reduce_multi_kernel(const RedMultiAr
 }
 
 // Is this layer one the multi-layer launch can take?  (bf16 on the matrix cores, the large-tile engine's limits,
-// something kept, 16-byte aligned tensors; everything else runs layer by layer.)
+// something kept; 16-byte aligned tensors; everything else runs layer by layer.)
 static bool batch_layer_fits(const sbp_linear_layer& l, int32_t dtype) {
   if (dtype != SBP_BF16 || l.K < 1) return false;
   if (l.Cin % 8 || l.Cout % big::KB) return false;
   if ((uint64_t)l.M * (uint64_t)std::max(l.Cin, l.Cout) * 2u >= (1ull << 32)) return false;
-  if (ceil_div(l.K, kBigMaxRowsPerSplit) > 64) return false;
+  return ceil_div(l.K, kBigMaxRowsPerSplit) <= 64;
+}
+static bool batch_layer_aligned(const sbp_linear_layer& l) {
   if (((uintptr_t)l.dY | (uintptr_t)l.X_k | (uintptr_t)l.W | (uintptr_t)l.dX) & 15) return false;
-  if (l.dW && (l.flags & SBP_FLAG_DW_OUT_BF16) == 0 && ((uintptr_t)l.dW & 15)) return false;
-  return true;
+  return !l.dW || (l.flags & SBP_FLAG_DW_OUT_BF16) || !((uintptr_t)l.dW & 15);
 }
 
 // Unit costs inside a batched launch, read from the per-unit time stamps of the ViT-Base block (sbp_profile_timeline) with
@@ -1517,29 +1518,30 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   // tiles to pay (narrower layers are better off with the 128-tile engine, layer by layer); override "tile" = "big"
   // takes the common grid wherever the limits allow
   const bool forced = options().tile_mode == 2;
-  p.fused = n >= 1 && n <= kMaxBatch;
-  for (int i = 0; i < n && p.fused; ++i)
-    p.fused = batch_layer_fits(L[i], dtype) && (forced || (L[i].Cin >= big::BT && L[i].Cout >= big::BT && L[i].K >= 1024));
-  if (p.fused && !forced && n >= 2) {
+  bool common = n >= 1 && n <= kMaxBatch;            // by the sizes alone: the workspace must not depend on the addresses
+  for (int i = 0; i < n && common; ++i)
+    common = batch_layer_fits(L[i], dtype) && (forced || (L[i].Cin >= big::BT && L[i].Cout >= big::BT && L[i].K >= 1024));
+  if (common && !forced && n >= 2) {
     double flops = 0;
     bool general = true;       // every layer one that launch_small_batch takes
     for (int i = 0; i < n; ++i) {
       const sbp_linear_layer& l = L[i];
       flops += 4.0 * (double)l.K * l.Cin * l.Cout;
-      general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !((uintptr_t)l.dW & 15) &&
-                !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, true).big;
+      general = general && !(l.flags & SBP_FLAG_XK_KMAJOR) && (l.dW || l.db || l.dX) && !plan_linear(l.M, l.K, l.Cin, l.Cout, dtype, l.flags, true).big;
     }
-    if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) p.fused = false;
+    if (general && options().tile_mode == 0 && flops < kSmallBatchFlops) common = false;
   }
+  p.fused = common;
+  for (int i = 0; i < n && p.fused; ++i) p.fused = batch_layer_aligned(L[i]);
   // layer by layer: every layer gets its own piece of the workspace.  The size returned covers both modes, so that
   // a size query made with other (e.g. differently aligned) addresses than the call still holds.
-  size_t off = 0, seq_bytes = 0;
+  size_t off = 0, seq_bytes = 0, seq_off[SBP_MAX_BATCH_LAYERS] = {};
   for (int i = 0; i < n; ++i) {
-    if (!p.fused) p.lay[i].off = seq_bytes;
+    p.lay[i].off = seq_off[i] = seq_bytes;
     seq_bytes += align_up(linear_workspace(L[i].M, L[i].K, L[i].Cin, L[i].Cout, dtype, L[i].flags), 256);
   }
   p.bytes = seq_bytes;
-  if (!p.fused) return p;
+  if (!common) return p;
   BatchLayerChoice c[kMaxBatch];
   choose_batch(L, n, c);
   for (int i = 0; i < n; ++i) {
@@ -1568,6 +1570,10 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
   p.off_counters = off;
   off += 256;
   p.bytes = std::max(off, seq_bytes);
+  if (!p.fused) {                                    // addresses that the common grid does not take
+    for (int i = 0; i < n; ++i) p.lay[i].off = seq_off[i];
+    return p;
+  }
   if (options().debug_plan) {
     Job jobs[kMaxJobs];
     double red = 0;
@@ -1598,8 +1604,7 @@ static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, in
     if (!lp[i].mfma || lp[i].big || lp[i].bm_w != mid::BT || l.K < 1) return false;
     if (l.flags & SBP_FLAG_XK_KMAJOR) return false;
     if (!l.dW && !l.db && !l.dX) return false;
-    if (((uintptr_t)l.dY | (uintptr_t)l.X_k | (uintptr_t)l.W | (uintptr_t)l.dX) & 15) return false;
-    if (l.dW && ((uintptr_t)l.dW & 15)) return false;
+    if (!batch_layer_aligned(l)) return false;
   }
   // the layers fill the chip together: each is planned for its share of the slots (fewer, longer dW units and fewer partial sums; the
   // workspace was sized for the single call's splits)

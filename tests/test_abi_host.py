@@ -263,6 +263,22 @@ def test_layers_that_fit_the_static_scratch_with_few_splits_are_not_refused():
     assert L.sbp_backward_linear_static(p, p, None, p, p, 65536, 65536, 4096, 4096, 1, None, None, None, 0, None) == -5
 
 
+def test_batch_workspace_does_not_depend_on_the_addresses():
+    # a query made with other (differently aligned) addresses than the call still holds
+    L = _lib.lib()
+
+    def need(shapes, off, dW_off, flags):
+        layers = (_lib.LinearLayer * len(shapes))()
+        for l, (K, Cin, Cout) in zip(layers, shapes):
+            l.dY, l.dW, l.M, l.K, l.Cin, l.Cout, l.flags = 4096 + off, 4096 + dW_off, 2 * K, K, Cin, Cout, flags
+            l.idx = l.inv = l.X_k = l.W = l.db = l.dX = 4096
+        return L.sbp_backward_linear_batch_workspace(layers, len(shapes), 1)
+    for shapes in ([(14109, 448, 1728), (14109, 1088, 1920)], [(6336, 768, 2304), (6336, 768, 768)], [(1800, 320, 1280), (1800, 1280, 320)],
+                   [(2100, 512, 2048), (2100, 2048, 512)], [(400, 72, 40), (300, 40, 72)], [(2048, 1024, 4096)]):
+        for flags in (0, 8):
+            assert len({need(shapes, off, dW_off, flags) for off in (0, 2) for dW_off in (0, 2, 4)}) == 1, (shapes, flags)
+
+
 def test_plans_of_new_sizes_cost_little_host_time_and_follow_the_overrides():
     # 60 sizes that no call has had: 0.07 ms each (9 ms before schedules were ruled out by a bound on their length)
     L = _lib.lib()

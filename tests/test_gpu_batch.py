@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2210_00129_amd as sbp
 import synth_inputs as si
-from gpu_util import TOL_BF16_TIGHT, TOL_F32, bits, f64, nerr
+from gpu_util import launches, TOL_BF16_TIGHT, TOL_F32, bits, f64, nerr
 
 pytestmark = pytest.mark.gpu
 
@@ -382,3 +382,20 @@ def test_single_call_with_one_split_of_large_tiles(B, Cin, Cout):
     _check_against_oracle(c, full)
     assert np.array_equal(bits(dW_alone), bits(full[0])) and np.array_equal(bits(bf16), bits(full[0].to(torch.bfloat16)))
     assert np.array_equal(bits(dW0), bits(full[0] + 2.0)) and np.array_equal(bits(db0), bits(full[1] - 1.0))
+
+
+@pytest.mark.parametrize("forced", [False, True])
+def test_batch_with_an_unaligned_bf16_weight_gradient_keeps_its_launch(forced):
+    # dW in bf16 goes through the partial sums, so its address does not matter to the launch, and the workspace query does not look at it
+    cases = [_layer(8, 1, 14, 14, 320, 288, 2, 171, flags=sbp.FLAG_DW_OUT_BF16), _layer(8, 1, 14, 14, 288, 320, 2, 172, flags=sbp.FLAG_DW_OUT_BF16)]
+    dev = [_to_device(c, True) for c in cases]
+    want = sbp.backward_linear_batch(dev)
+    for c, d in zip(cases, dev):
+        d["dW"] = torch.empty(c["W"].numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(c["W"].shape)
+    with sbp.options(**({"tile": "big"} if forced else {})):
+        n = launches(lambda: sbp.backward_linear_batch(dev))
+    assert n["dw_gemm"] == 1 and n["reduce"] == 1
+    for d, w in zip(dev, want):
+        if not forced:
+            assert np.array_equal(bits(d["dW"]), bits(w[0]))
+        assert nerr(f64(d["dW"]), f64(w[0])) <= 2 ** -8
