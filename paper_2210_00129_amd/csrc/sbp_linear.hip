@@ -731,6 +731,9 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
 // Layers of more than 64 MB: their rows come from memory more often than not, and a dW stage is 0.3 us then (33600 rows of 512 -> 128,
 // four sets of inputs in turn: 35.1 us with the 23 splits of 0.2 us a stage, 28.8 with 48; 40000 of 384 -> 96 31.3 and 25.0; warm 22.8
 // and 24.5 for the first).
+static int64_t mid_dx_ns(int bm, int64_t Cout, bool alone) { return 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * ceil_div(Cout, mid::KB); }
+static int64_t mid_dw_ns(int64_t rows, bool streams, bool alone) { return 5000 + (streams ? 300 : alone ? 220 : 200) * ceil_div(rows, mid::KB); }
+static bool mid_streams(int64_t K, int32_t Cin, int32_t Cout) { return 2.0 * (double)K * (2.0 * Cin + Cout) > 64e6; }
 struct MidChoice { int64_t K; int32_t Cin, Cout, slots, cap; int splits, rps, dx_bm; double cost_ns; };
 
 // end of a grid of n1 units of length l1 and then n2 of l2 on `slots` slots, each unit in the slot that is free first
@@ -753,11 +756,11 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int
   thread_local int next = 0;
   for (const MidChoice& c : cache)
     if (c.K == K && c.Cin == Cin && c.Cout == Cout && c.slots == slots && c.cap == cap && c.splits > 0) return c;
-  const int64_t tiles_n = ceil_div(Cin, mid::BT), tiles_w = ceil_div(Cout, mid::BT) * tiles_n, nk_x = ceil_div(Cout, mid::KB);
+  const int64_t tiles_n = ceil_div(Cin, mid::BT), tiles_w = ceil_div(Cout, mid::BT) * tiles_n;
   const int64_t fewest = ceil_div(K, kMaxRowsPerSplit);      // the split's row ids sit in LDS
   const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>({64, cap, std::max<int64_t>(1, K / 64)}));
   MidChoice best{K, Cin, Cout, slots, cap, 0, 0, 128, 0.0};
-  const bool streams = 2.0 * (double)K * (2.0 * Cin + Cout) > 64e6;
+  const bool streams = mid_streams(K, Cin, Cout);
   int64_t best_cost = 0;
   for (int64_t want = fewest; want <= most; ++want) {
     const int64_t rps = ceil_div(ceil_div(K, want), 64) * 64, splits = ceil_div(K, rps);
@@ -768,7 +771,7 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int
     for (int bm : {128, 64}) {
       const int64_t n_dx = ceil_div(ceil_div(K, bm) * tiles_n, 8);
       const bool alone = 8 * (n_dx + n_dw) <= slots / 2;
-      const int64_t l_dx = 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * nk_x, l_dw = 5000 + (streams ? 300 : alone ? 220 : 200) * ceil_div(std::min(rps, K), mid::KB);
+      const int64_t l_dx = mid_dx_ns(bm, Cout, alone), l_dw = mid_dw_ns(std::min(rps, K), streams, alone);
       const int64_t end = l_dx > l_dw ? two_kinds_end(n_dx, l_dx, n_dw, l_dw, slots / 8) : two_kinds_end(n_dw, l_dw, n_dx, l_dx, slots / 8);
       if (best.splits == 0 || end + reduce < best_cost) {
         best_cost = end + reduce;
@@ -1007,12 +1010,15 @@ static unsigned prepare_linear(const LinearPlan& p, LinArgs& a, bool want_dx, bo
   a.n_dw = want_dw ? (int)(8 * ceil_div(ceil_div(a.Cout, bm) * tiles_n * p.splits, 8)) : 0;
   const unsigned grid = (unsigned)(a.n_helper + a.n_dx + a.n_dw);
   if (grid == 0) return 0;
-  // Longest kind first.  Lengths in nanoseconds, read from the device clock on the detection and ViT-Tiny shapes: a
-  // tile costs about 3 us plus 1 us per stage of 64 (two stages in flight do not hide the memory latency), a
-  // streaming block 1.8 us plus its bytes at what one CU gets while the others stream too.
+  // Longest kind first.  Lengths in nanoseconds: 128-wide tiles by the planner's unit costs (without the 1 us of a dW unit's sums, stores
+  // that the next unit's start overlaps: the MLP of ViT-Tiny, dX tiles of 24 stages and dW units of 20, 33.4 us a step with the dX tiles
+  // first, 33.8 behind the units); the general engine's tile about 3 us plus 1 us per stage of 64 (read from the device clock); a
+  // streaming block 1.8 us plus its bytes at what one CU gets while the others stream.
+  const int64_t db_bytes = !n_db ? 0 : mid_tiles ? (int64_t)p.rows_per_split * 2 * mid::kColumns : (int64_t)a.db_slice_rows * 512;
   const int64_t len[3] = {
-      (bmx == 64 ? 700 : 1000) * ceil_div(a.Cout, 64) + 3000, 3000 + 1000 * ceil_div(p.rows_per_split, 64),
-      1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero : 0, n_db ? (int64_t)a.db_slice_rows * 512 : 0) / 40};
+      mid_tiles ? mid_dx_ns(bmx, a.Cout, false) : 3000 + 1000 * ceil_div(a.Cout, 64),
+      mid_tiles ? mid_dw_ns(p.rows_per_split, mid_streams(a.K, a.Cin, a.Cout), false) - 1000 : 3000 + 1000 * ceil_div(p.rows_per_split, 64),
+      1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero : 0, db_bytes) / 40};
   for (int q = 0; q < 3; ++q) a.seg_order[q] = q;
   std::sort(a.seg_order, a.seg_order + 3, [&](int x, int y) { return len[x] != len[y] ? len[x] > len[y] : x < y; });
   const Options opt = options();
