@@ -82,11 +82,10 @@ __device__ __forceinline__ void half_order() {
 // P::CHAIN (dW): the sums run in chains of that many stages, each from 0, that are added up apart - the splits are as long as the
 // schedule wants them, but one running sum over 900 rows is 1.7e-7 off 64 bits (2-norm) where sums of 320 are 1.0e-7 off.
 // P: prefetch(s) - row ids of stage s; issue(buffer, kvalid) - the copies of the next stage, kvalid < 32 in a partial last
-// one; read(buffer, step, a, b); zero_tail(buffer, kvalid); extra(a).
+// one; read(buffer, step, a, b); extra(a).
 template <class P>
 __device__ __forceinline__ void ring_loop(char* smem, P& pb, int nk, int kvalid_last, f32x16_t (&acc)[P::FM][2]) {
   constexpr int FM = P::FM, CPS = P::CPS, STAGE = P::STAGE, NM = 2 * FM;
-  const bool tail = kvalid_last < KB;
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < nk) {
@@ -95,10 +94,6 @@ __device__ __forceinline__ void ring_loop(char* smem, P& pb, int nk, int kvalid_
     }
   wait_stages<CPS>(min(NS - 2, nk - 1));
   lds_barrier();
-  if (tail && nk == 1) {
-    pb.zero_tail(smem, kvalid_last);
-    lds_barrier();
-  }
   bf16x8_t pa[FM], pbf[2], qa[FM], qb[2];
   pb.read(smem, 0, pa, pbf);
   char *cur = smem, *nxt = smem + STAGE, *dst = smem + (NS - 1) * STAGE;
@@ -148,10 +143,6 @@ __device__ __forceinline__ void ring_loop(char* smem, P& pb, int nk, int kvalid_
     if (s + 1 < nk) {
       wait_stages<CPS, NS - 3>(nk - 2 - s);          // stages s + 2 .. (at most s + NS - 2 have been issued) may be under way
       lds_barrier();
-      if (tail && s + 2 == nk) {
-        pb.zero_tail(nxt, kvalid_last);
-        lds_barrier();
-      }
       pb.read(nxt, 0, pa, pbf);
       if (more) pb.issue(dst, s + NS == nk ? kvalid_last : KB);
     }
@@ -162,6 +153,10 @@ __device__ __forceinline__ void ring_loop(char* smem, P& pb, int nk, int kvalid_
   if constexpr (P::CHAIN > 0) add_acc<FM>(acc, sum);
   lds_barrier();                                     // the ring is free
 }
+
+// What the copies of a partial last stage read past the end of an operand: zeros on both sides (zero times an infinite value is NaN).
+__device__ const uint4 zeros[1] = {};
+__device__ __forceinline__ const char* zero_line() { return reinterpret_cast<const char*>(zeros); }
 
 // ---- copies of a slow tile [32 k][128 columns]: 8 blocks of 4 rows, 2 per wavefront ---------------------------------
 struct SlowCopy {
@@ -179,18 +174,9 @@ struct SlowCopy {
   __device__ __forceinline__ void issue(char* tile, int kvalid, int wave) {
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-      const char* q = p[n];
-      if (kvalid < KB) q -= (size_t)max(kl + 4 * n - (kvalid - 1), 0) * ld;       // rows past the end: the last one
+      const char* q = kvalid < KB && kl + 4 * n >= kvalid ? zero_line() : p[n];
       async_copy16(q, tile + (2 * wave + n) * 1024);
       p[n] += step;
-    }
-  }
-  // rows kvalid .. 31 of a tile
-  static __device__ __forceinline__ void zero_tail(char* tile, int kvalid) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int q = threadIdx.x + 256 * i;             // 16-byte piece; 16 pieces per row
-      if ((q >> 4) >= kvalid) *reinterpret_cast<uint4*>(tile + q * 16) = make_uint4(0, 0, 0, 0);
     }
   }
 };
@@ -206,16 +192,12 @@ struct GroupCopy {
     for (int n = 0; n < 2; ++n) p[n] = static_cast<const char*>(src) + (size_t)wave * ld + (size_t)min(col0 + 64 * n + lane, Cin - 1) * 16;
   }
   __device__ __forceinline__ void issue(char* tile, int kvalid, int wave) {
-    const size_t back = kvalid < KB ? (size_t)max(wave - ((kvalid - 1) >> 3), 0) * ld : 0;      // groups past the end: the last one
+    const bool past = kvalid < KB && 8 * wave >= kvalid;             // (rows past the last one of its group are stored as zeros)
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-      async_copy16(p[n] - back, tile + (2 * wave + n) * 1024);
+      async_copy16(past ? zero_line() : p[n], tile + (2 * wave + n) * 1024);
       p[n] += step;
     }
-  }
-  // whole groups past the end (rows past the last one of its group are stored as zeros)
-  static __device__ __forceinline__ void zero_tail(char* tile, int kvalid) {
-    for (int q = threadIdx.x + ((kvalid + 7) >> 3) * BT; q < KB / 8 * BT; q += 256) *reinterpret_cast<uint4*>(tile + q * 16) = make_uint4(0, 0, 0, 0);
   }
 };
 
@@ -230,10 +212,9 @@ struct DxProb {
   __device__ __forceinline__ void extra(const bf16x8_t&) {}
   __device__ __forceinline__ void prefetch(int) {}
   __device__ __forceinline__ void issue(char* buf, int kvalid) {
-    const int back = kvalid < KB ? max(kchunk - (kvalid - 8), 0) : 0;              // chunks past the end: the last one (zeroed, zero_tail)
 #pragma unroll
     for (int n = 0; n < FM; ++n) {
-      async_copy16(pa[n] - 2 * back, buf + (FM * wave + n) * 1024);
+      async_copy16(kvalid < KB && kchunk >= kvalid ? zero_line() : pa[n], buf + (FM * wave + n) * 1024);
       pa[n] += KB * 2;
     }
     cb.issue(buf + A_BYTES, kvalid, wave);
@@ -242,15 +223,6 @@ struct DxProb {
     read_slow_frags<BT, 2>(buf + A_BYTES, b_off, ks, b);
 #pragma unroll
     for (int f = 0; f < FM; ++f) a[f] = *reinterpret_cast<const bf16x8_t*>(buf + a_off[ks] + f * (32 * KB * 2));
-  }
-  // both operands past the end: zero times an infinite gradient would be NaN
-  __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const {
-    SlowCopy::zero_tail(buf + A_BYTES, kvalid);
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int q = threadIdx.x + 256 * i, m = q >> 2;  // 16-byte piece; 4 pieces per row, chunk c in place c ^ ((m >> 2) & 3)
-      if (8 * ((q & 3) ^ ((m >> 2) & 3)) >= kvalid) *reinterpret_cast<uint4*>(buf + q * 16) = make_uint4(0, 0, 0, 0);
-    }
   }
 };
 
@@ -344,7 +316,9 @@ struct DwProb {
   __device__ __forceinline__ void issue(char* buf, int kvalid) {
     if constexpr (GATHER) {        // (the table repeats the last row past the end)
 #pragma unroll
-      for (int n = 0; n < 2; ++n) async_copy16(dY + (uint64_t)(uint32_t)rid[n] * (uint32_t)ca.ld + ca.colb, buf + (2 * wave + n) * 1024);
+      for (int n = 0; n < 2; ++n)
+        async_copy16(kvalid < KB && ca.kl + 4 * n >= kvalid ? zero_line() : dY + (uint64_t)(uint32_t)rid[n] * (uint32_t)ca.ld + ca.colb,
+                     buf + (2 * wave + n) * 1024);
     } else {
       ca.issue(buf, kvalid, wave);
     }
@@ -358,10 +332,6 @@ struct DwProb {
       read_slow_frags<BT, 2>(buf + TILE, b_off, ks, b);
     }
     read_slow_frags<BT, 2>(buf, a_off, ks, a);
-  }
-  __device__ __forceinline__ void zero_tail(char* buf, int kvalid) const {
-    SlowCopy::zero_tail(buf, kvalid);
-    decltype(cb)::zero_tail(buf + TILE, kvalid);
   }
 };
 
