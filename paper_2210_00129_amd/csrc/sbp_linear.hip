@@ -722,18 +722,17 @@ static BigChoice choose_big(int64_t M, int64_t K, int32_t Cin, int32_t Cout) {
 }
 
 // ---- 128-wide engine: rows of the dX tiles and the dW splits -------------------------------------------
-// Two workgroups per CU (one while the grid has at most 256).  Unit costs in nanoseconds, fitted to 34 shapes of 60 to 60000 rows
-// and 96 to 4096 channels, each timed with dX tiles of 64 and 128 rows and 1 to 64 splits: 4 us, 1 us more for a dW unit's sums,
-// 0.2 us per stage of 32 (alone on its CU 0.18 in dX and 0.22 in dW; 0.7 of it with 64 rows), 4 us and the bytes of the partial sums
-// at 2 TB/s for the reduction.  Its choice is within 1.2 % of the best one on average, 10 % at worst.  With the splits that fill all
-// slots whatever their length (the rule before) 8400 rows of 256 -> 1024 took 23.3 us, now 18.6; 4200 of 512 -> 2048 33.0, now 30.2.
+// Two workgroups per CU.  Unit costs in nanoseconds: 4 us, 1 us more for a dW unit's sums, 0.3 us per stage of 32 (0.7 of it with 64
+// rows), 5 us and the bytes of the partial sums at 2 TB/s for the reduction (4 us on the GPU; its launch is 3 us more of host time where
+// the host is the bound: 720 rows of 648 -> 128 in six splits 9.0 us instead of 10.1, but 22.1 instead of 18.6 with draw and cache from
+// Python).  A stage takes 0.2 us where the operands are in the
+// last-level cache, up to 0.5 where they come from memory and few workgroups ask for them; with 0.2 for layers up to 64 MB the long
+// single splits of small layers lost what they gained as soon as the operands were cold.  120 random layers of 32 to 75000 rows against
+// the splits that fill all slots whatever their length (the rule before), geometric mean and worst, warm 0.768 / 1.26 with 0.2 and 0.763 /
+// 1.18 with 0.3, from memory 0.854 / 1.44 and 0.836 / 1.12 (1493 rows of 1256 -> 272: 16.8 us before, 21.6, now 14.0); 0.4 for dW: 0.778, 0.849.
 // (64 rows win where the tiles are few: 900 rows of 200 -> 1000 11.4 us, 14.0 with 128 rows.)
-// Layers of more than 64 MB: their rows come from memory more often than not, and a dW stage is 0.3 us then (33600 rows of 512 -> 128,
-// four sets of inputs in turn: 35.1 us with the 23 splits of 0.2 us a stage, 28.8 with 48; 40000 of 384 -> 96 31.3 and 25.0; warm 22.8
-// and 24.5 for the first).
-static int64_t mid_dx_ns(int bm, int64_t Cout, bool alone) { return 4000 + (alone ? 18 : 20) * (bm == 64 ? 7 : 10) * ceil_div(Cout, mid::KB); }
-static int64_t mid_dw_ns(int64_t rows, bool streams, bool alone) { return 5000 + (streams ? 300 : alone ? 220 : 200) * ceil_div(rows, mid::KB); }
-static bool mid_streams(int64_t K, int32_t Cin, int32_t Cout) { return 2.0 * (double)K * (2.0 * Cin + Cout) > 64e6; }
+static int64_t mid_dx_ns(int bm, int64_t Cout) { return 4000 + (bm == 64 ? 210 : 300) * ceil_div(Cout, mid::KB); }
+static int64_t mid_dw_ns(int64_t rows) { return 5000 + 300 * ceil_div(rows, mid::KB); }
 struct MidChoice { int64_t K; int32_t Cin, Cout, slots, cap; int splits, rps, dx_bm; double cost_ns; };
 
 // end of a grid of n1 units of length l1 and then n2 of l2 on `slots` slots, each unit in the slot that is free first
@@ -760,18 +759,16 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int
   const int64_t fewest = ceil_div(K, kMaxRowsPerSplit);      // the split's row ids sit in LDS
   const int64_t most = std::max<int64_t>(fewest, std::min<int64_t>({64, cap, std::max<int64_t>(1, K / 64)}));
   MidChoice best{K, Cin, Cout, slots, cap, 0, 0, 128, 0.0};
-  const bool streams = mid_streams(K, Cin, Cout);
   int64_t best_cost = 0;
   for (int64_t want = fewest; want <= most; ++want) {
     const int64_t rps = ceil_div(ceil_div(K, want), 64) * 64, splits = ceil_div(K, rps);
     if (splits != want && want > fewest) continue;            // (a count that rounding makes a smaller one)
     const int64_t n_dw = ceil_div(tiles_w * splits, 8);       // per XCD
     const int64_t reduce = splits == 1 ? 0 :       // (one split: the units write dW and db themselves)
-                            4000 + (splits + 1) * Cin * Cout * 4 / 2000;
+                            5000 + (splits + 1) * Cin * Cout * 4 / 2000;
     for (int bm : {128, 64}) {
       const int64_t n_dx = ceil_div(ceil_div(K, bm) * tiles_n, 8);
-      const bool alone = 8 * (n_dx + n_dw) <= slots / 2;
-      const int64_t l_dx = mid_dx_ns(bm, Cout, alone), l_dw = mid_dw_ns(std::min(rps, K), streams, alone);
+      const int64_t l_dx = mid_dx_ns(bm, Cout), l_dw = mid_dw_ns(std::min(rps, K));
       const int64_t end = l_dx > l_dw ? two_kinds_end(n_dx, l_dx, n_dw, l_dw, slots / 8) : two_kinds_end(n_dw, l_dw, n_dx, l_dx, slots / 8);
       if (best.splits == 0 || end + reduce < best_cost) {
         best_cost = end + reduce;
@@ -1016,8 +1013,8 @@ static unsigned prepare_linear(const LinearPlan& p, LinArgs& a, bool want_dx, bo
   // streaming block 1.8 us plus its bytes at what one CU gets while the others stream.
   const int64_t db_bytes = !n_db ? 0 : mid_tiles ? (int64_t)p.rows_per_split * 2 * mid::kColumns : (int64_t)a.db_slice_rows * 512;
   const int64_t len[3] = {
-      mid_tiles ? mid_dx_ns(bmx, a.Cout, false) : 3000 + 1000 * ceil_div(a.Cout, 64),
-      mid_tiles ? mid_dw_ns(p.rows_per_split, mid_streams(a.K, a.Cin, a.Cout), false) - 1000 : 3000 + 1000 * ceil_div(p.rows_per_split, 64),
+      mid_tiles ? mid_dx_ns(bmx, a.Cout) : 3000 + 1000 * ceil_div(a.Cout, 64),
+      mid_tiles ? mid_dw_ns(p.rows_per_split) - 1000 : 3000 + 1000 * ceil_div(p.rows_per_split, 64),
       1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero : 0, db_bytes) / 40};
   for (int q = 0; q < 3; ++q) a.seg_order[q] = q;
   std::sort(a.seg_order, a.seg_order + 3, [&](int x, int y) { return len[x] != len[y] ? len[x] > len[y] : x < y; });

@@ -263,6 +263,19 @@ def test_layers_that_fit_the_static_scratch_with_few_splits_are_not_refused():
     assert L.sbp_backward_linear_static(p, p, None, p, p, 65536, 65536, 4096, 4096, 1, None, None, None, 0, None) == -5
 
 
+def test_dw_splits_of_small_layers():
+    # few workgroups, cold operands: one long split (47 stages of up to 0.5 us) was 21.6 us for the first, four 14.0; a reduction launch
+    # has to save more than the 3 us of host time that it costs
+    L = _lib.lib()
+
+    def splits(K, Cin, Cout):
+        n = ctypes.c_int32(0)
+        assert L.sbp_backward_linear_engine(2 * K, K, Cin, Cout, 1, 0, ctypes.byref(n)) == 1
+        return n.value
+    assert all(2 <= splits(*s) <= 8 for s in ((1493, 1256, 272), (1048, 1696, 88), (979, 1408, 128)))
+    assert all(splits(*s) == 1 for s in ((720, 648, 128), (900, 200, 1000), (400, 256, 256)))
+
+
 def test_batch_workspace_does_not_depend_on_the_addresses():
     # a query made with other (differently aligned) addresses than the call still holds
     L = _lib.lib()
