@@ -1031,7 +1031,18 @@ static unsigned prepare_linear_mid(const LinearPlan& p, LinArgs& a, bool want_dx
   a.dx_bm = p.dx_bm;
   return prepare_linear(p, a, want_dx, want_dw, want_zero, mid::RING, mid::BT, mid::BT, p.dx_bm, 4, true, lds_out, len_out);
 }
-static void launch_linear_mid(const LinearPlan& p, LinArgs a, bool want_dx, bool want_dw, bool want_zero, hipStream_t s) {
+static void launch_linear_mid(const LinearPlan& plan, LinArgs a, bool want_dx, bool want_dw, bool want_zero, hipStream_t s) {
+  LinearPlan p = plan;
+  if (want_dx && !want_dw && !options().dxrows) {     // dX without dW has the slots to itself: the plan's tile height is for both
+    // (4233 rows of 1656 -> 2160, from memory: 72 us with 64 rows, two rounds, 58 with 128).  Two tiles on a CU take 1.3 times one's time
+    // (1104 of 3200 -> 448: 450 tiles of 64 rows 15.0 us, 225 of 128 13.0; 1493 of 1448 -> 3664, 288 and 144: 41.4 and 51.6).
+    const int64_t tiles_n = ceil_div(a.Cin, mid::BT);
+    auto end = [&](int bm) {
+      const int64_t tiles = ceil_div((int64_t)a.K, bm) * tiles_n;
+      return ceil_div(tiles, 2 * kNumCU) * mid_dx_ns(bm, a.Cout) * (tiles > kNumCU ? 13 : 10);
+    };
+    p.dx_bm = end(64) < end(128) ? 64 : 128;
+  }
   size_t lds = 0;
   const unsigned grid = prepare_linear_mid(p, a, want_dx, want_dw, want_zero, &lds);
   if (grid == 0) return;
