@@ -446,7 +446,7 @@ int32_t sbp_backward_layernorm(const void* dU_k, const void* X_k, const float* g
  *   "dw_rows"   rows per strip of the depthwise kernels;  "dw_separate"  "1": dX and dWd as two launches
  *   "attn"      "plain": attention backward without the matrix cores | "whole": one workgroup per (sample, head)
  *               where its tokens fit LDS | "tiled": chunks of 128 tokens per workgroup, at any size
- *   "sampler_no_window", "sampler_no_masks", "patch_wide", "debug_plan"   "1" | "0"
+ *   "sampler_no_window", "sampler_no_masks", "sampler_one_bucket", "patch_wide", "debug_plan"   "1" | "0"
  *   "batch_spread"  "1": batched linear call deals its units to the XCDs in turn (no neighbour affinity)
  *   "batch_dynamic" "1": batched linear call fetches units through one counter per XCD instead of static queues
  *   "dw_strips"     "1": depthwise backward with the register-strip kernels instead of the LDS-tiled ones

@@ -103,6 +103,7 @@ static bool apply_option(Options& o, const char* name, const char* v) {
   }
   bool* flag = n == "debug_plan" ? &o.debug_plan : n == "dw_separate" ? &o.dw_separate
              : n == "sampler_no_window" ? &o.sampler_no_window : n == "sampler_no_masks" ? &o.sampler_no_masks
+             : n == "sampler_one_bucket" ? &o.sampler_one_bucket
              : n == "patch_wide" ? &o.patch_wide : n == "batch_dynamic" ? &o.batch_dynamic
              : n == "batch_spread" ? &o.batch_spread : n == "dw_strips" ? &o.dw_strips
              : nullptr;

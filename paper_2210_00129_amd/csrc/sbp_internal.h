@@ -53,7 +53,7 @@ struct Options {
   bool batch_spread = false;          // batched linear backward: units dealt to the XCDs in turn instead of in runs
   bool batch_dynamic = false;         // batched linear backward: units taken from the XCD queues with atomic counters
   int attn_mode = 0;       // attention backward: 0 chosen by size, 1 plain kernel, 2 one workgroup per head where it fits, 3 tiled
-  bool dw_separate = false, sampler_no_window = false, sampler_no_masks = false, patch_wide = false;
+  bool dw_separate = false, sampler_no_window = false, sampler_no_masks = false, sampler_one_bucket = false, patch_wide = false;
 };
 Options options();                    // a snapshot (taken under a lock; safe against a concurrent sbp_set_option)
 uint64_t options_generation();        // counts the changes from 1 on

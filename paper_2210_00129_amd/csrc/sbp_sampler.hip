@@ -651,6 +651,7 @@ int32_t launch_sample(const sbp_sample_desc& d, int32_t* idx, int32_t* inv, hipS
         v.win_shift = 0;
         while (((v.win_hi - v.win_lo) >> v.win_shift) >= (uint64_t)kSelectBuckets) ++v.win_shift;
         const Options opt = options();
+        if (opt.sampler_one_bucket) v.win_shift = 63;         // override: all keys of the window share a bucket, i.e. the radix select over them
         if (opt.sampler_no_window) v.win_lo = v.win_hi = 0;   // override: an empty window, i.e. the full select
         // keep bits and chunk prefixes of the ordered write-out: 24 bytes per 64 positions, next to 53 KB of static LDS
         const int64_t chunks = ceil_div((int64_t)d.H * d.W, 64);

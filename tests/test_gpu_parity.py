@@ -76,6 +76,19 @@ def test_random_mask_sampler_large_maps_window_and_full_select(window, masks):
                     assert np.array_equal(inv.cpu().numpy(), oracle.inverse_map(ref, B * (P + H * W)))
 
 
+@pytest.mark.parametrize("masks", [True, False])
+def test_random_mask_sampler_bucket_of_more_keys_than_are_ranked_by_counting(masks):
+    # all keys of the window in one bucket: some hundred of them for k < 4, beyond the 64 that one wavefront ranks, so the radix select
+    # runs over the window's keys; k = 4 leaves fewer than 64
+    B, P, H, W = 3, 1, 50, 84
+    for k in (1, 2, 3, 4):
+        ref = oracle.sample_indices_random(B, P, H, W, k, 5, 6)
+        with sbp.options(sampler_one_bucket=1, sampler_no_masks=int(not masks)):
+            idx, inv = sbp.sample_indices(B, P, H, W, k, 5, 6, mode=sbp.RANDOM_MASK, want_inv=True)
+        assert np.array_equal(idx.cpu().numpy(), ref)
+        assert np.array_equal(inv.cpu().numpy(), oracle.inverse_map(ref, B * (P + H * W)))
+
+
 @pytest.mark.parametrize("c,k", [(2, 1), (2, 2), (3, 2), (4, 1), (4, 3)])
 @pytest.mark.parametrize("geom", [(2, 1, 8, 196), (3, 0, 9, 5), (1, 0, 1, 7), (2, 2, 10, 49), (2, 0, 16, 3136)])
 def test_temporal_sampler_bit_exact(geom, c, k):
