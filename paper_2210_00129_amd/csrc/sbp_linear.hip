@@ -782,19 +782,19 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int
 }
 
 // Time of one layer with the 128-wide tiles, its reduction included: 10 us + 1.3 us per GFLOP (within 15 % over 24 shapes of 2 to 67
-// GFLOP), or what the plan's own costs add up to where a grid just misses the slots.  The large tiles take 0.95 of their simulated
-// cost, 0.87 where whole 256-wide tiles cover the layer (nothing padded), and are ahead of the 128-wide ones on such layers from 20
-// GFLOP on and on all from 45 GFLOP on, whatever the estimates (25680 rows of 368 -> 2528: 138 us, 165 with 128-wide tiles).
-// Measured, 128-wide / large: 22.6 / 32.9 us (16800 rows, 512 -> 256), 18.6 / 26.4 (8400, 256 -> 1024), 31.5 / 34.5 (4200, 2048 -> 512), 29.0 / 33.5 (4200, 1024 x 1024), 44.0 / 57.2 (12608, 384 -> 1536); 43.7 / 41.2 (2100, 1024 ->
-// 3072), 59.2 / 57.8 (6336, 768 -> 2304), 89.7 / 78.0 (6336, 3072 -> 768), 90.3 / 77.3 (4000, 4096 -> 1024).
-// Two kinds of whole-tile layers keep the large tiles although the 128-wide ones are ahead of them by themselves: those of three tiles
-// and more each way over 5000 rows and more (6336 of 768 x 768: 26.9 / 33.3 us, but a ViT-Base block of dependent layers 409.8 / 409.0),
-// and those of 1536 output channels and more (4200 rows, 512 -> 1536: 24.3 / 30.3 us), whose engine the host tests state.
+// GFLOP), or what the plan's own costs add up to where a grid just misses the slots.  They run where that is below 0.89 of the large
+// tiles' simulated cost.  100 random layers of 3 to 96 GFLOP (1024 to 34000 rows, 63 of them of whole 256-wide tiles) against the faster
+// engine of each, geometric mean: warm 1.006, operands from memory 1.004, worst 1.08.  (0.87: 1.007, 1.005, 1.15; 0.90: 1.007, 1.007,
+// 1.27; 0.95, and for whole tiles limits of 20 GFLOP, 1536 channels or 5000 rows of 768: 1.053, 1.033, 1.58.)  128-wide / large, us:
+//   6336 rows, 768 -> 768     27.1 / 32.0   from memory 32.9 / 33.9
+//   4200 rows, 512 -> 1536    25.2 / 30.8               29.3 / 31.2
+//   4200 rows, 512 -> 2048    30.0 / 36.7               33.5 / 36.7
+//   2100 rows, 1024 -> 3072   44.8 / 41.1               53.4 / 55.8
+//   3400 rows, 1680 -> 1824   68.4 / 59.5               73.3 / 60.6
+//   6336 rows, 3072 -> 768    90.4 / 78.8              100.7 / 94.0
 static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, int cap, double big_cost_ns) {
   const double gf = 4e-9 * (double)K * Cin * Cout;
-  const bool whole = Cin % big::BT == 0 && Cout % big::BT == 0;
-  if (gf >= 45.0 || (whole && (gf >= 20.0 || Cout >= 1536 || (K >= 5000 && std::min(Cin, Cout) >= 3 * big::BT)))) return false;
-  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU, cap).cost_ns) < (whole ? 0.87 : 0.95) * big_cost_ns;
+  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU, cap).cost_ns) < 0.89 * big_cost_ns;
 }
 
 // The parts of the workspace that do not depend on the splits: the inverse map of a scattered dX, and X_k copied back to rows for the
@@ -1606,7 +1606,7 @@ BatchPlan plan_linear_batch(const sbp_linear_layer* L, int32_t n, int32_t dtype)
 }
 
 // A batch that does not take the large-tile grid but whose layers all take the general engine in its default shape
-// (bf16, 128 x 128 tiles, stages of 64): one launch of linear_mid_multi_kernel + one reduction launch.  Every layer uses
+// (bf16, 128 x 128 tiles): one launch of linear_mid_multi_kernel + one reduction launch.  Every layer uses
 // its own piece of the workspace exactly as a single call would.  Returns false if the batch is not of that kind.
 static bool launch_small_batch(const BatchPlan& p, const sbp_linear_layer* L, int32_t dtype, char* wsb, hipStream_t s, int32_t* status) {
   const Options opt = options();
