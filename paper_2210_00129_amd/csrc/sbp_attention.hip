@@ -184,10 +184,12 @@ struct AttnPadded {
   }
 };
 // AttnSwizzled: rows of 2 D bytes, 16-byte chunk c of row r at place c ^ swz(r), written by global -> LDS copies whose lanes
-// choose the chunk they fetch (the copy fixes the LDS place by lane; a copy fills 1 KB, 512 / D rows).  Both kinds of reads meet
-// all 64 banks once: a transposing read's half wavefront takes 64 bytes of each of 4 neighbouring rows, so these rows differ in
-// the bits of the place above the chunks it takes (bit 2; D = 128: bits 2 and 3), and the 16-byte reads of 16 neighbouring rows
-// fall on different places because the copies within 16 rows lie 16 bytes further apart than their 1 KB.  (With c ^ (r & 7) and no
+// choose the chunk they fetch (the copy fixes the LDS place by lane; a copy fills 1 KB, 512 / D rows).  By their addresses both
+// kinds of reads meet all 64 banks once: a transposing read's half wavefront takes 64 bytes of each of 4 neighbouring rows, so these
+// rows differ in the bits of the place above the chunks it takes (bit 2; D = 128: bits 2 and 3), and the 16-byte reads of 16
+// neighbouring rows fall on different places because the copies within 16 rows lie 16 bytes further apart than their 1 KB (not for
+// D = 32, whose 16 rows are one copy: rows r and r + 8 share banks, two turns).  That holds for 16 consecutive lanes to a turn; the
+// counter still has conflicts in 31 % of the LDS cycles at D = 64, 44 before.  (With c ^ (r & 7) and no
 // gaps rows r and r + 2 exchanged places within the same 64 bytes: every transposing read took two turns, D = 128 four.)
 template <int D>
 struct AttnSwizzled {
@@ -546,10 +548,10 @@ __global__ void __launch_bounds__(256, D == 128 ? 1 : 2) attn_bwd_mfma_kernel(co
 // (8 x 12 heads of 1024 tokens, counters: 289 MB read and 41 written across the L2 boundary by the kernel before, spread over all
 // eight; now 60 and 38); an XCD runs its key units first, the longer kind (110 -> 102 us), at the price of a second read of small
 // heads (27.6 instead of 26.6 us at 768 heads of 99 tokens).
-// Bound, by counters: the matrix cores are busy 47 % of the cycles of a CU, the LDS 45 % (55 % with the conflicts of the layout
-// before, AttnSwizzled), and the softmax arithmetic between the products takes most of the rest; unit starts (first
+// Bound, by counters: the matrix cores are busy 47 % of the cycles of a CU, the LDS 46 % (55 % with the layout before,
+// AttnSwizzled; conflicts 31 and 44 % of that), and the softmax arithmetic between the products takes most of the rest; unit starts (first
 // tiles and tables from memory) and the power limit (1.85 GHz) add to it.  8 x 12 heads of 64, 1024 kept tokens, a call:
-// 134 -> 101 us with the ring, 99.6 with dP of the query role started from -delta and the layout without conflicts; 8 x 12 heads of
+// 134 -> 101 us with the ring, 99.6 with dP of the query role started from -delta and that layout; 8 x 12 heads of
 // 32 62.9 -> 60.4 us; 8 x 8 heads of 128, whose transposing reads took four turns, 184 -> 163 us.  Both blocks of a tile unrolled
 // (constant LDS addresses): 35 to 77 spills with three workgroups per CU, 114 us with two.  s_setprio around the products: 98.1 us, but
 // 58.8 instead of 54.9 us at 64 x 12 heads of 197 tokens.
