@@ -1010,12 +1010,16 @@ static unsigned prepare_linear(const LinearPlan& p, LinArgs& a, bool want_dx, bo
   // Longest kind first.  Lengths in nanoseconds: 128-wide tiles by the planner's unit costs (without the 1 us of a dW unit's sums, stores
   // that the next unit's start overlaps: the MLP of ViT-Tiny, dX tiles of 24 stages and dW units of 20, 33.4 us a step with the dX tiles
   // first, 33.8 behind the units); the general engine's tile about 3 us plus 1 us per stage of 64 (read from the device clock); a
-  // streaming block 1.8 us plus its bytes at what one CU gets while the others stream.
+  // column-sum block 1.8 us plus its bytes at what one CU gets while the others stream (40 per ns).  Zero-fill blocks cost twice that:
+  // their stores hide behind the tiles' products, but take the memory's time where they are left for the end.  At 40 they fell behind the
+  // short dX tiles of 67200 rows (of 134400) of 512 -> 128: with 128 -> 512 in one call 115.0 us, now 107.2; 33600 rows (of 134400) of
+  // 128 -> 512 alone 39.7 and 33.7.  29 maps of ConvNeXt stages at keep ratios of 1/4 to 3/4 on average 0.9 % faster in a batch and layer
+  // by layer; at 10 per ns 0.7 % and 1.4 %, but the MLP of ViT-Tiny, whose fills are small, 33.4 us a step instead of 32.8.
   const int64_t db_bytes = !n_db ? 0 : mid_tiles ? (int64_t)p.rows_per_split * 2 * mid::kColumns : (int64_t)a.db_slice_rows * 512;
   const int64_t len[3] = {
       mid_tiles ? mid_dx_ns(bmx, a.Cout) : 3000 + 1000 * ceil_div(a.Cout, 64),
       mid_tiles ? mid_dw_ns(p.rows_per_split) - 1000 : 3000 + 1000 * ceil_div(p.rows_per_split, 64),
-      1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero : 0, db_bytes) / 40};
+      1800 + std::max<int64_t>(a.n_zero ? (int64_t)(a.M - a.K) * a.Cin * 2 / a.n_zero / 20 : 0, db_bytes / 40)};
   for (int q = 0; q < 3; ++q) a.seg_order[q] = q;
   std::sort(a.seg_order, a.seg_order + 3, [&](int x, int y) { return len[x] != len[y] ? len[x] > len[y] : x < y; });
   const Options opt = options();
