@@ -792,9 +792,11 @@ static MidChoice choose_mid(int64_t K, int32_t Cin, int32_t Cout, int slots, int
 //   2100 rows, 1024 -> 3072   44.8 / 41.1               53.4 / 55.8
 //   3400 rows, 1680 -> 1824   68.4 / 59.5               73.3 / 60.6
 //   6336 rows, 3072 -> 768    90.4 / 78.8              100.7 / 94.0
+// From 45 GFLOP on always the large tiles: the 128-wide ones took 0.99 to 1.15 of their time on the 13 of the layers above that are this
+// large (1.05 to 1.25 from memory), and the estimates leave out the zero-fill (33600 of 134400 rows, 1280 -> 320: 156.4 / 144.0).
 static bool mid_engine_ahead(int64_t K, int32_t Cin, int32_t Cout, int cap, double big_cost_ns) {
   const double gf = 4e-9 * (double)K * Cin * Cout;
-  return std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU, cap).cost_ns) < 0.89 * big_cost_ns;
+  return gf < 45.0 && std::max(10000.0 + 1300.0 * gf, choose_mid(K, Cin, Cout, 2 * kNumCU, cap).cost_ns) < 0.89 * big_cost_ns;
 }
 
 // The parts of the workspace that do not depend on the splits: the inverse map of a scattered dX, and X_k copied back to rows for the
